@@ -112,9 +112,8 @@ srtm_status scratch_address(void** out) {
   return SRTM_OK;
 }
 
-const char* const kFilterKernels[] = {"k_constants", "k_fwd_reduce", "k_fwd_tiles", "k_fwd_final", "k_recover"};
-const char* const kSmoothKernels[] = {"k_constants", "k_fwd_reduce", "k_fwd_tiles",
-                                      "k_fwd_bwd",   "k_bwd_tiles",  "k_recover"};
+const char* const kFilterKernels[] = {"k_constants", "k_fwd_reduce", "k_tile_tree", "k_fold", "k_recover"};
+const char* const kSmoothKernels[] = {"k_constants", "k_fwd_reduce", "k_tile_tree", "k_fold", "k_recover"};
 
 }  // namespace
 

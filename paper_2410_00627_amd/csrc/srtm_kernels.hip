@@ -56,6 +56,9 @@ SRTM_DEV void put_global(T* p, T v) {
   *(__attribute__((address_space(1))) T*)p = v;
 }
 
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+
 // Staged copy of n scalars with the nthr threads of a workgroup: value q = ld(q) is handed to
 // st(q, value). Each thread issues up to B loads before its first store.
 template <int B, typename T, class LD, class ST>
@@ -77,52 +80,126 @@ SRTM_DEV void staged_copy(int n, int tid, int nthr, LD ld, ST st) {
 }
 
 // ============================================================================ constants
-// Cofactor (r, c) of the NX x NX row-major matrix M: (-1)^{r+c} times the determinant of M
-// without row r and column c.
-template <int NX>
-SRTM_DEV double cofactor(const double* M, int r, int c) {
-  constexpr int K = NX - 1;
-  if constexpr (K == 0) {
-    return 1.0;
-  } else {
-    double a[K][K];
-#pragma unroll
-    for (int i = 0; i < K; ++i) {
-      const int ri = i < r ? i : i + 1;
-#pragma unroll
-      for (int j = 0; j < K; ++j) a[i][j] = M[ri * NX + (j < c ? j : j + 1)];
-    }
-    double d;
-    if constexpr (K == 1) {
-      d = a[0][0];
-    } else if constexpr (K == 2) {
-      d = a[0][0] * a[1][1] - a[0][1] * a[1][0];
-    } else {
-      d = a[0][0] * (a[1][1] * a[2][2] - a[1][2] * a[2][1]) - a[0][1] * (a[1][0] * a[2][2] - a[1][2] * a[2][0]) +
-          a[0][2] * (a[1][0] * a[2][1] - a[1][1] * a[2][0]);
-    }
-    return ((r + c) & 1) ? -d : d;
-  }
+// ---------------------------------------------------------------- 4 x 4 blocks on the matrix cores
+// Up to four NX x NX problems (NX <= 4, padded with zeros to 4 x 4) per wave, one matrix entry per
+// lane: lane 16 r + 4 b + c holds entry (r, c) of block b's matrix ("block layout"), the layout in which
+// v_mfma_f64_4x4x4_4b takes its B operand and returns its result. Read as the A operand the same register is
+// the transpose, so mm4(X, Y, C) = X^T Y + C for four blocks at once, and a chain of products needs no
+// exchange between lanes as long as every product is written with the transposed or symmetric operand
+// first. A vector is held as a matrix with equal columns. One lane per problem (64 problems per wave)
+// moves more problems per cycle, but a dependent 4 x 4 combine then takes about 1 us (600 instructions of
+// 4 cycles); this form takes about 0.2 us and is meant for the short chains that everything waits for.
+SRTM_DEV double mm4(double x, double y, double c) { return __builtin_amdgcn_mfma_f64_4x4x4f64(x, y, c, 0, 0, 0); }
+
+// The value of another lane of the quad: CTRL 0xB1 swaps neighbours, 0x4E swaps pairs.
+template <int CTRL>
+SRTM_DEV double quad_swap(double x) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(x), CTRL, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(x), CTRL, 0xf, 0xf, true);
+  return __hiloint2double(hi, lo);
 }
 
-// Level chain over levels p0 .. p1-1, run by wave 0 of a workgroup (one lane per matrix entry).
-// `chain` is 19 nx^2 doubles of LDS whose first 3 nx^2 hold F, D, J of Theta(2^p0). Writes the
+// One wave's view of the block layout: this lane's place and its 64 doubles of LDS scratch.
+struct Block4 {
+  int r, b, c;
+  double* own;          // this lane's scratch entry
+  const double* base;   // its block's entries, row-major
+  double eye;
+  SRTM_DEV Block4(double* scratch) {
+    const int lane = threadIdx.x & 63;
+    r = lane >> 4;
+    b = (lane >> 2) & 3;
+    c = lane & 3;
+    base = scratch + 16 * b;
+    own = scratch + 16 * b + 4 * r + c;
+    eye = r == c ? 1.0 : 0.0;
+  }
+  // Transposed inverse of M (entry (r, c) of the result is entry (c, r) of M^{-1}): cofactors over the
+  // determinant. Cofactor (r, c) is the determinant of the rows r^1, r^2, r^3 and columns c^1, c^2, c^3 in
+  // that order: the parity of each order cancels the sign (-1)^{r+c}. ok &= the determinant is usable.
+  SRTM_DEV double inv_t(double M, bool& ok) const {
+    *own = M;
+    wave_sync();
+    double x[3][3];
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+#pragma unroll
+      for (int j = 0; j < 3; ++j) x[i][j] = sld(base + 4 * (r ^ (i + 1)) + (c ^ (j + 1)));
+    wave_sync();
+    const double cof = x[0][0] * (x[1][1] * x[2][2] - x[1][2] * x[2][1]) -
+                       x[0][1] * (x[1][0] * x[2][2] - x[1][2] * x[2][0]) +
+                       x[0][2] * (x[1][0] * x[2][1] - x[1][1] * x[2][0]);
+    double det = M * cof;  // summed along the row
+    det += quad_swap<0xB1>(det);
+    det += quad_swap<0x4E>(det);
+    const double id = rcp_nr(det);
+    ok = ok && det != 0.0 && isfinite(id);
+    return cof * id;
+  }
+  // Symmetric product X Y of a pair whose exact product is symmetric (Xt = X^T, Y symmetric): both
+  // orders of the product are transposes of each other bit by bit, so their mean is exactly symmetric.
+  SRTM_DEV static double mm_sym(double Xt, double Y) { return 0.5 * (mm4(Xt, Y, 0.0) + mm4(Y, Xt, 0.0)); }
+};
+
+// Level chain over levels p0 .. p1-1, run by wave 0 of a workgroup.
+// `chain` is chain_doubles(nx) doubles of LDS whose first 3 nx^2 hold F, D, J of Theta(2^p0). Writes the
 // level records p0 .. p1-1 and, when p1 < nlev, F, D, J of Theta(2^p1) in float64 to `hand`
 // (3 nx^2 doubles), where a continuation of the chain in a later launch picks them up.
 //   Theta(2^{p+1}) = Theta(2^p) (x) Theta(2^p) under eq. op-filter, W = (I + D J)^{-1}, and the
 // coefficients that combine the vector parts of two runs of 2^p elements:
 //   d_ij = G1 d_i + G2 eta_j + d_j,   eta_ij = G3 eta_j - G4 d_i + eta_i,
 //   G1 = F W, G2 = F W D, G3 = (W F)^T, G4 = (W F)^T J.
-// W is the adjugate of I + D J over its determinant, with one cofactor per lane (nx <= 4).
+// nx <= 4: on the matrix cores, one entry per lane and no exchange but the inverse's. nx > 4: one lane
+// per matrix entry with the operands in LDS.
+template <typename T, int NX>
+SRTM_DEV int level_chain4(double* chain, T* __restrict__ cst, const ConstLayout& lay, int p0, int p1, int nlev,
+                          double* __restrict__ hand) {
+  constexpr int NN = NX * NX;
+  static_assert(NX <= 4, "4 x 4 blocks");
+  const Block4 B(chain + 3 * NN);
+  const bool in = B.r < NX && B.c < NX;
+  const int rc = in ? B.r * NX + B.c : 0, cr = in ? B.c * NX + B.r : 0;
+  double F = in ? chain[rc] : 0.0, Ft = in ? chain[cr] : 0.0;
+  double D = in ? chain[NN + rc] : 0.0, J = in ? chain[2 * NN + rc] : 0.0;
+  bool ok = true;
+  for (int p = p0; p < p1; ++p) {
+    const double Wt = B.inv_t(mm4(D, J, B.eye), ok);  // W^T
+    const double W = mm4(Wt, B.eye, 0.0);
+    const double WF = mm4(Wt, F, 0.0);
+    const double G3 = mm4(F, Wt, 0.0);  // (W F)^T
+    const double G1 = mm4(Ft, W, 0.0);
+    const double XD = Block4::mm_sym(Wt, D);  // W D
+    const double XDF = mm4(XD, Ft, 0.0);      // W D F^T
+    const double G2 = mm4(Ft, XD, 0.0);
+    const double G4 = mm4(WF, J, 0.0);
+    const double JWF = mm4(J, WF, 0.0);
+    if (in) {  // the record, two entries per lane: rows (G1, G2) and (G3, -G4), then F, D, J
+      T* dst = cst + lay.lev + p * lay.lev_stride;
+      const double a = B.b == 0 ? G1 : B.b == 1 ? G2 : B.b == 2 ? G3 : -G4;
+      dst[lay.o_C + ((B.b >> 1) * NX + B.r) * 2 * NX + (B.b & 1) * NX + B.c] = (T)a;
+      if (B.b < 3) dst[lay.o_F + B.b * NN + rc] = (T)(B.b == 0 ? F : B.b == 1 ? D : J);
+    }
+    const double nF = mm4(Ft, WF, 0.0), nFt = mm4(WF, Ft, 0.0);
+    D = Block4::mm_sym(Ft, XDF) + D;  // F W D F^T + D
+    J = Block4::mm_sym(F, JWF) + J;   // (W F)^T J F + J
+    F = nF;
+    Ft = nFt;
+  }
+  if (p1 < nlev && in && B.b < 3) put_global(hand + B.b * NN + rc, B.b == 0 ? F : B.b == 1 ? D : J);
+  return ok ? 0 : SRTM_INFO_COMBINE_SINGULAR;
+}
+
 template <typename T, int NX>
 SRTM_DEV int level_chain(double* chain, T* __restrict__ cst, const ConstLayout& lay, int p0, int p1, int nlev,
                          double* __restrict__ hand) {
+  if constexpr (NX <= 4) {
+    return level_chain4<T, NX>(chain, cst, lay, p0, p1, nlev, hand);
+  } else {
   constexpr int NN = NX * NX;
   double* rec = chain;
   double* nrec = chain + 7 * NN;
   double* sM = chain + 14 * NN;
-  double* sCof = sM + NN;
-  double* sW = sCof + NN;
+  double* sW = sM + NN;
   double* sWF = sW + NN;
   double* sXD = sWF + NN;
   int lflag = 0;
@@ -138,25 +215,14 @@ SRTM_DEV int level_chain(double* chain, T* __restrict__ cst, const ConstLayout& 
       sM[o] = acc;
     }
     wave_sync();
-    if constexpr (NX <= 4) {
-      if (e < NN) sCof[e] = cofactor<NX>(sM, e / NX, e % NX);
-      wave_sync();
-      if (e < NN) {  // W = adj(M) / det(M), adj(M)[r][c] = C[c][r]
-        double det = 0.0;
-        for (int c = 0; c < NX; ++c) det += sM[c] * sCof[c];
-        const double id = rcp_nr(det);
-        if (e == 0 && !(det != 0.0 && isfinite(id))) lflag |= SRTM_INFO_COMBINE_SINGULAR;
-        sW[e] = sCof[(e % NX) * NX + e / NX] * id;
-      }
-    } else {  // larger states: one lane, Gaussian elimination with partial pivoting
-      if (e == 0) {
-        double Mr[NX][NX], Wr[NX][NX];
-        for (int r = 0; r < NX; ++r)
-          for (int c = 0; c < NX; ++c) Mr[r][c] = sM[r * NX + c];
-        if (!inv_small(Mr, Wr)) lflag |= SRTM_INFO_COMBINE_SINGULAR;
-        for (int r = 0; r < NX; ++r)
-          for (int c = 0; c < NX; ++c) sW[r * NX + c] = Wr[r][c];
-      }
+    // one lane, Gaussian elimination with partial pivoting
+    if (e == 0) {
+      double Mr[NX][NX], Wr[NX][NX];
+      for (int r = 0; r < NX; ++r)
+        for (int c = 0; c < NX; ++c) Mr[r][c] = sM[r * NX + c];
+      if (!inv_small(Mr, Wr)) lflag |= SRTM_INFO_COMBINE_SINGULAR;
+      for (int r = 0; r < NX; ++r)
+        for (int c = 0; c < NX; ++c) sW[r * NX + c] = Wr[r][c];
     }
     wave_sync();
     // The three products of each phase are formed by three groups of lanes with the same
@@ -200,8 +266,17 @@ SRTM_DEV int level_chain(double* chain, T* __restrict__ cst, const ConstLayout& 
       }
       nrec[(1 + part) * NN + o] = 0.5 * (t1 + t2) + rec[(1 + part) * NN + o];
     }
-    T* dst = cst + lay.lev + p * lay.lev_stride;  // the level record, as laid out in LDS
-    for (int q = e; q < 7 * NN; q += 64) dst[q] = (T)rec[q];
+    T* dst = cst + lay.lev + p * lay.lev_stride;  // the level record
+    for (int q = e; q < 7 * NN; q += 64) {
+      if (q < 4 * NN) {  // rows (G1, G2), then (G3, -G4)
+        const int r = q / (2 * NX), c = q % (2 * NX);
+        const int g = r < NX ? (c < NX ? 3 : 4) : (c < NX ? 5 : 6);
+        const double v = rec[g * NN + (r % NX) * NX + c % NX];
+        dst[q] = (T)(g == 6 ? -v : v);
+      } else {
+        dst[q] = (T)rec[q - 4 * NN];
+      }
+    }
     wave_sync();
     double* t = rec;
     rec = nrec;
@@ -211,6 +286,7 @@ SRTM_DEV int level_chain(double* chain, T* __restrict__ cst, const ConstLayout& 
     for (int q = threadIdx.x; q < 3 * NN; q += 64) put_global(hand + q, rec[q]);
   }
   return lflag;
+  }
 }
 
 // Levels 0 .. CHAIN_SPLIT-1 come from the constants kernel (the in-tile scans need the levels
@@ -221,12 +297,12 @@ SRTM_DEV int level_chain(double* chain, T* __restrict__ cst, const ConstLayout& 
 constexpr int CHAIN_SPLIT = LOG_TILE;
 static_assert(CHAIN_SPLIT >= LOG_TILE, "the tile reductions read levels below LOG_TILE");
 
-// Dynamic LDS of the tile-reduction launch: the larger of a tile reduction's slots and level
-// coefficients and a level chain's float64 scratch.
+// Dynamic LDS of the tile-reduction launch: the larger of a tile reduction's elements, tree and row
+// tables and a level chain's float64 scratch.
 template <typename T, int NX>
 constexpr size_t fwd_reduce_lds_bytes() {
-  constexpr size_t red = sizeof(T) * (size_t)(2 * NX * TILE + LOG_TILE * 4 * NX * NX);
-  constexpr size_t chn = sizeof(double) * (size_t)(19 * NX * NX);
+  constexpr size_t red = sizeof(T) * (size_t)(4 * NX * TILE + LOG_TILE * 4 * NX * NX);
+  constexpr size_t chn = sizeof(double) * (size_t)chain_doubles(NX);
   return red > chn ? red : chn;
 }
 
@@ -237,7 +313,7 @@ SRTM_DEV void chain_tail_body(T* __restrict__ cst, const double* __restrict__ ha
                               int32_t* info) {
   constexpr int NN = NX * NX;
   extern __shared__ char smraw[];
-  double* chain = reinterpret_cast<double*>(smraw);  // 19 nx^2 (fwd_reduce_lds_bytes)
+  double* chain = reinterpret_cast<double*>(smraw);  // chain_doubles(nx)
   const int tid = threadIdx.x;
   if (tid >= 64 || nlev <= CHAIN_SPLIT) return;
   __builtin_amdgcn_s_setprio(3);
@@ -274,7 +350,7 @@ SRTM_DEV void constants_body(const T* __restrict__ Fm, const T* __restrict__ Qm,
   double* W1 = Qii + (L + 1) * NN;      // (L+1) NN scratch
   double* W2 = W1 + (L + 1) * NN;       // (L+1) W2S scratch
   double* ci = W2 + (L + 1) * W2S;      // (L+1) NXY, ci[i] = c_i
-  double* chain = ci + (L + 1) * NXY;   // 19 NN: level-chain records and scratch
+  double* chain = ci + (L + 1) * NXY;   // chain_doubles(nx): level-chain records and scratch
 
   for (int e = tid; e < NN; e += nthr) {
     sA[e] = (double)Fm[e];
@@ -1423,75 +1499,54 @@ SRTM_DEV int smoother_element(const MV& M, int L, const Window<T, NX, NY>& w, bo
 }
 
 // ============================================================================ forward
-// Vector part of eq. op-filter for two runs of 2^p elements (level-p coefficients).
+// The scans use one dyadic tree over the windows 0 .. N-1 of a sequence (0-based here): node i of level
+// p is the run [i 2^p, (i+1) 2^p), and because the model is time invariant its matrices are Theta(2^p)
+// for every i. Only the vector parts (d, eta) are per run. A filter state at window k is the prior followed
+// by the runs of the set bits of k, highest first, and the information of all windows after k comes from
+// the runs of the clear bits of k below the highest bit in which k and N differ, on top of the runs of N's
+// own set bits below it (fold section). The run that bit p of k asks for is always the sibling of the
+// node that holds k at that level, (k >> p) ^ 1.
+// Levels 1 .. 7 lie within a tile (TILE windows) and are kept per tile in `utree`, node i of level p in
+// slot tree_off(p) + i, 2 nx scalars (d, eta) per slot; level-0 nodes are the window's own elements and are
+// formed again from y where they are needed. Level 8 (whole tiles) is `ftagg`, and the levels above it
+// follow each other in `ttree` (tile_level_off).
+inline __host__ __device__ constexpr int tree_off(int p) { return TILE - (TILE >> (p - 1)); }
+// First node of level LOG_TILE + q, q >= 1, among the levels above the tiles, for nf whole tiles.
+inline __host__ __device__ int64_t tile_level_off(int64_t nf, int q) {
+  int64_t o = 0;
+  for (int j = 1; j < q; ++j) o += nf >> j;
+  return o;
+}
+// Highest set bit of x > 0, and -1 for 0.
+SRTM_DEV int top_bit(int64_t x) { return x > 0 ? 63 - __clzll(x) : -1; }
+
+// Combination of the vector parts of two neighbouring runs of 2^p elements, one output row per thread
+// (rows 0 .. nx-1: d, nx .. 2nx-1: eta). Row r of a level's coefficient table is 2 nx scalars:
+//   d = d_r + G1 d_l + G2 eta_r  (G1, G2),   eta = eta_l + G3 eta_r - G4 d_l  (G3, -G4).
+// A thread that formed the whole pair instead read all 4 nx^2 coefficients for it, and those reads set the
+// time of a level (about 1 us of a wave in either precision, at nx = 4).
+template <int NX>
+constexpr int row_slots() { return 2 * NX <= 2 ? 2 : 2 * NX <= 4 ? 4 : 2 * NX <= 8 ? 8 : 16; }
+
 template <typename T, int NX>
-SRTM_DEV void level_vec_combine_g(const T* __restrict__ G, const T (&di)[NX], const T (&ei)[NX], T (&dj)[NX],
-                                  T (&ej)[NX]) {
-  constexpr int NN = NX * NX;
-  T G1[NX][NX], G2[NX][NX], G3[NX][NX], G4[NX][NX];
-  load(G1, G);
-  load(G2, G + NN);
-  load(G3, G + 2 * NN);
-  load(G4, G + 3 * NN);
-  T nd[NX], ne[NX];
+SRTM_DEV T row_combine(const T* __restrict__ co, const T* __restrict__ left, const T* __restrict__ right, int r) {
+  T acc = r < NX ? right[r] : left[r];
+  const T* a = r < NX ? left : right + NX;
+  const T* b = r < NX ? right + NX : left;
 #pragma unroll
-  for (int r = 0; r < NX; ++r) {
-    T s = dj[r], t = ei[r];
-#pragma unroll
-    for (int k = 0; k < NX; ++k) {
-      s = my_fma(G1[r][k], di[k], s);
-      s = my_fma(G2[r][k], ej[k], s);
-      t = my_fma(G3[r][k], ej[k], t);
-      t = my_fma(-G4[r][k], di[k], t);
-    }
-    nd[r] = s;
-    ne[r] = t;
+  for (int k = 0; k < NX; ++k) {
+    acc = my_fma(co[k], a[k], acc);
+    acc = my_fma(co[NX + k], b[k], acc);
   }
-#pragma unroll
-  for (int r = 0; r < NX; ++r) {
-    dj[r] = nd[r];
-    ej[r] = ne[r];
-  }
+  return acc;
 }
 
-// Vector part of eq. op-filter for two runs of 2^p elements (level-p coefficients G1..G4, which
-// follow each other in a level record).
+// Entry q of the row tables of consecutive levels (4 nx^2 scalars a level), from the level records at
+// `lev`.
 template <typename T, int NX>
-SRTM_DEV void level_vec_combine(const T* __restrict__ lev, const ConstLayout& lay, const T (&di)[NX],
-                                const T (&ei)[NX], T (&dj)[NX], T (&ej)[NX]) {
-  level_vec_combine_g<T, NX>(lev + lay.o_G1, di, ei, dj, ej);
-}
-
-// In-place up-sweep over the vector parts of the tile's elements (slots 0..TILE-1); `G` holds the
-// coefficient blocks G1..G4 of levels 0..LOG_TILE-1, 4 nx^2 scalars per level.
-template <typename T, int NX>
-SRTM_DEV void fwd_upsweep(const T* __restrict__ G, const Slots<T>& S, int tid) {
-  constexpr int NN = NX * NX;
-#pragma unroll 1
-  for (int p = 0; p < LOG_TILE; ++p) {
-    const int s = 1 << p;
-    // Pair j (slots j 2^{p+1} + s - 1 and j 2^{p+1} + 2s - 1) goes to thread j, so that the active
-    // threads fill the first waves: every active wave reads the level's coefficients from LDS,
-    // and those broadcast reads, not the arithmetic, set the time of a level.
-    if (tid < (TILE >> (p + 1))) {
-      const int dst = (tid << (p + 1)) + 2 * s - 1;
-      T di[NX], ei[NX], dj[NX], ej[NX];
-#pragma unroll
-      for (int r = 0; r < NX; ++r) {
-        di[r] = S.at(r, dst - s);
-        ei[r] = S.at(NX + r, dst - s);
-        dj[r] = S.at(r, dst);
-        ej[r] = S.at(NX + r, dst);
-      }
-      level_vec_combine_g<T, NX>(G + p * 4 * NN, di, ei, dj, ej);
-#pragma unroll
-      for (int r = 0; r < NX; ++r) {
-        S.at(r, dst) = dj[r];
-        S.at(NX + r, dst) = ej[r];
-      }
-    }
-    __syncthreads();
-  }
+SRTM_DEV T row_coefficient(const T* __restrict__ lev, const ConstLayout& lay, int q) {
+  constexpr int RT = 4 * NX * NX;
+  return gld(lev + (q / RT) * lay.lev_stride + lay.o_C + q % RT);
 }
 
 // Vector part (d, eta) of window k's filter element from its measurement yt (y_k - mu_k with
@@ -1510,23 +1565,29 @@ SRTM_DEV void fwd_element(const Model<T, NX, NY>& M, const T (&yt)[NY], const T 
   }
 }
 
-// K1: per-tile aggregate of the vector parts (d, eta) of the filter elements; the whole up-sweep
-// tree (2 nx rows of TILE slots) goes to `utree` for the per-tile forward pass.
+// K1: the dyadic tree of one tile over the vector parts (d, eta) of its windows' filter elements: levels
+// 1 .. LOG_TILE-1 to `utree`, the tile's own node to `ftagg`. One thread per node and output row
+// (row_combine), so that a level reads 4 nx scalars of coefficients per thread and is a few hundred cycles.
 template <bool INP, typename T, int NX, int NY>
 SRTM_DEV void fwd_reduce_body(const T* __restrict__ y, int64_t N, const T* __restrict__ cst, int L,
                               InputView<T> in, T* __restrict__ tagg, T* __restrict__ utree, int64_t tile) {
-  constexpr int NN = NX * NX;
+  constexpr int NN = NX * NX, R2 = 2 * NX, RS2 = row_slots<NX>();
   extern __shared__ char smraw[];
-  T* smem = reinterpret_cast<T*>(smraw);  // 2 nx TILE slots, then
-  T* sG = smem + 2 * NX * TILE;           // G1..G4 of levels 0..LOG_TILE-1 (fwd_reduce_lds_bytes)
+  T* leaf = reinterpret_cast<T*>(smraw);  // TILE elements, then the tree's TILE slots, then
+  T* tree = leaf + R2 * TILE;
+  T* sC = tree + R2 * TILE;               // the row tables of levels 0 .. LOG_TILE-1
   const Model<T, NX, NY> M{cst, make_const_layout(NX, NY, L), in};
-  const Slots<T> S{smem, TILE};
   const int tid = threadIdx.x;
   const int64_t k = tile * TILE + tid;
-  // The level coefficients were written by an earlier launch, possibly on another die: one load
-  // each, all in flight together, instead of a dependent round trip per level.
-  for (int q = tid; q < LOG_TILE * 4 * NN; q += TILE) sG[q] = gld(M.level(q / (4 * NN)) + M.lay.o_G1 + q % (4 * NN));
-  T yt[NY], zL[NX], d[NX], e[NX];
+  // The level records were written by an earlier launch, possibly on another die: one load per
+  // coefficient, all in flight together, instead of a dependent round trip per level.
+  constexpr int NC = LOG_TILE * 4 * NN, PC = (NC + TILE - 1) / TILE;
+  T cv[PC], yt[NY], zL[NX], d[NX], e[NX];
+#pragma unroll
+  for (int i = 0; i < PC; ++i) {
+    const int q = i * TILE + tid;
+    cv[i] = q < NC ? row_coefficient<T, NX>(M.level(0), M.lay, q) : T(0);
+  }
   if constexpr (INP) {  // one pass over the window's inputs; later kernels read the record
     if (k < N) {
       window_input_pass(M, y, k, L, yt, zL);
@@ -1544,24 +1605,1240 @@ SRTM_DEV void fwd_reduce_body(const T* __restrict__ y, int64_t N, const T* __res
   } else {
     window_meas<false>(M, y, k, N, yt, zL);
   }
+#pragma unroll
+  for (int i = 0; i < PC; ++i) {
+    const int q = i * TILE + tid;
+    if (q < NC) sC[q] = cv[i];
+  }
   fwd_element<INP>(M, yt, zL, d, e);
 #pragma unroll
   for (int r = 0; r < NX; ++r) {
-    S.at(r, tid) = d[r];
-    S.at(NX + r, tid) = e[r];
+    leaf[tid * R2 + r] = d[r];
+    leaf[tid * R2 + NX + r] = e[r];
   }
   __syncthreads();
-  fwd_upsweep<T, NX>(sG, S, tid);
-  T* ut = utree + tile * (2 * NX * TILE);
+  const int row = tid % RS2;
+#pragma unroll 1
+  for (int p = 1; p <= LOG_TILE; ++p) {
+    const T* src = p == 1 ? leaf : tree + tree_off(p - 1) * R2;
+    T* dst = tree + tree_off(p) * R2;
+    const int n = TILE >> p;
+    if (row < R2) {
+      T co[R2];
 #pragma unroll
-  for (int r = 0; r < 2 * NX; ++r) put_global(ut + r * TILE + tid, S.at(r, tid));
-  if (tid == TILE - 1) {
+      for (int k2 = 0; k2 < R2; ++k2) co[k2] = sC[((p - 1) * R2 + row) * R2 + k2];
+      for (int i = tid / RS2; i < n; i += TILE / RS2)
+        dst[i * R2 + row] = row_combine<T, NX>(co, src + 2 * i * R2, src + (2 * i + 1) * R2, row);
+    }
+    __syncthreads();
+  }
+  constexpr int NT = tree_off(LOG_TILE);  // slots of levels 1 .. LOG_TILE-1
+  T* ut = utree + tile * (R2 * TILE);
+  for (int q = tid; q < NT * R2; q += TILE) put_global(ut + q, tree[q]);
+  if (tid < R2) put_global(tagg + tile * R2 + tid, tree[NT * R2 + tid]);
+}
+
+// ---------------------------------------------------------------- fold: states and information
+// A filter state (m, P) followed by a run (F, d, D, eta, J) is state_combine; the information (eta, J) about
+// the state before a run, from the information after it, is
+//   W = (I + J_s D)^{-1},  eta' = F^T W (eta_s - J_s d) + eta,  J' = F^T W J_s F + J,
+// the same map with F^T for F, (J, D) for (D, J) and (eta, -d) for (d, eta). So one combine serves both, and
+// a window's bit p asks for exactly one of them: forward when the bit is set, backward when it is
+// clear. With the state (m, P) after window k and the information (eta, J) of every window after it,
+//   v = (I + J P)^{-1} (eta - J m),   W = -(I + J P)^{-1} J
+// are the smoother correction of eq. seq-smoothing-all (m^s_{k,i} = m^f_{k,i} + P^f_{k,i,l} v and
+// P^s_{k,i} = P^f_{k,i,i} + P^f_{k,i,l} W P^f_{k,i,l}^T): p(x_{k,l} | y_{1:N}) is the filter state times the
+// likelihood of the later measurements, whose information form is the (eta, J) of their filter element
+// (eq. op-filter). Unlike the smoother elements of eq. parallel-ak-smoothing, which are built from the
+// filter states and scanned after them, (eta, J) comes from the same tree as the states, so both are
+// found in one pass and no second tile-level scan follows it.
+
+// One combine in the block layout (four problems per wave): state (u, P) and run (Tt = F^T or F, Dp, Jp, vd,
+// ve), in place. u is a vector held as equal columns; P, Dp and Jp are symmetric.
+SRTM_DEV bool combine4(const Block4& B, double& u, double& P, double Tt, double Dp, double Jp, double vd, double ve) {
+  bool ok = true;
+  const double w = mm4(P, ve, u);                           // u + P ve
+  const double Wt = B.inv_t(mm4(P, Jp, B.eye), ok);         // W^T, W = (I + P Jp)^{-1}
+  const double X = Block4::mm_sym(Wt, P);                   // W P
+  u = mm4(Tt, mm4(Wt, w, 0.0), vd);
+  P = Block4::mm_sym(Tt, mm4(X, Tt, 0.0)) + Dp;
+  return ok;
+}
+
+// Scalars of a window's state or information record: the vector, then the matrix's upper triangle. The
+// records of the time-invariant path lie tile by tile and field by field within a tile, so that the
+// lanes of a wave write and read consecutive addresses: field f of window w of tile t at
+// base[t * TILE * info_stride + f * W + w], W the number of windows of that tile.
+inline __host__ __device__ constexpr int info_stride(int nx) { return nx + nx * (nx + 1) / 2; }
+SRTM_DEV int tile_windows(int64_t N, int64_t tile) {
+  const int64_t w = N - tile * TILE;
+  return (int)(w < TILE ? w : TILE);
+}
+// The information of N's own set bits below bit q, q = 0 .. top_bit(N), float64, behind the records of a
+// sequence of more than one tile (the region is sized for the larger per-window records of the
+// time-varying smoother).
+inline __host__ __device__ size_t tail_info_off(int64_t N, int nx, size_t esz) {
+  return ((size_t)N * info_stride(nx) * esz + 7) & ~size_t(7);
+}
+
+// Highest level handled one lane per window in the fold; the ones above it go four problems per wave
+// on the matrix cores (nx <= 4). A level of one lane per window costs a wave about 700 instructions whatever
+// it holds; the four problems of a wave's 16-window groups cost about 60.
+constexpr int LANE_LEVELS = 4;
+template <int NX> constexpr bool blocks4() { return NX <= 4; }
+template <int NX> constexpr int lane_levels() { return blocks4<NX>() ? LANE_LEVELS : LOG_TILE; }
+
+// LDS of the fold, in bytes from its start (level tables of nlev levels).
+template <typename T, int NX>
+struct FoldLds {
+  static constexpr int NN = NX * NX, R2 = 2 * NX, IS = info_stride(NX);
+  static constexpr int MAXT = 20;                                          // tile-level bits (N <= 2^26: 18)
+  static constexpr int NZ = LOG_TILE + 1;
+  size_t leaf, tree, lane, lev, node, tail, scratch, group, total;
+  __host__ __device__ FoldLds(int nlev) {
+    const int laneL = blocks4<NX>() ? lane_levels<NX>() : nlev;
+    size_t o = 0;
+    auto take = [&](size_t n) { const size_t at = o; o = (o + n + 15) & ~size_t(15); return at; };
+    leaf = take(sizeof(T) * R2 * TILE);
+    tree = take(sizeof(T) * R2 * TILE);
+    lane = take(sizeof(T) * (size_t)laneL * 6 * NN);                       // per level (F, D, J), (F^T, J, D)
+    lev = take(blocks4<NX>() ? sizeof(double) * 48 * (size_t)nlev : 0);    // per level F, D, J as 4 x 4 blocks
+    node = take(sizeof(T) * MAXT * R2);                                    // tile-level nodes of this tile
+    tail = take(sizeof(double) * NZ * IS * 4);                             // information of N's low bits
+    scratch = take(blocks4<NX>() ? sizeof(double) * 64 * 4 : 0);
+    group = take(blocks4<NX>() ? sizeof(double) * 4 * 4 * 40 : 0);         // states of each wave's four groups
+    total = o;
+  }
+};
+
+// Levels a sequence can have (N <= 2^26).
+constexpr int MAXLEV = 26;
+
+// Entry q of the level tables of the fold from level p0 on: F, D, J as 4 x 4 blocks, 48 entries a level.
+template <typename T, int NX>
+SRTM_DEV T block_entry(const T* __restrict__ cst, const ConstLayout& lay, int p0, int q) {
+  const int p = p0 + q / 48, e = q % 48, r = (e % 16) / 4, c = e % 4;
+  if constexpr (NX == 4) return gld(cst + lay.lev + p * lay.lev_stride + lay.o_F + e);
+  return (r < NX && c < NX) ? gld(cst + lay.lev + p * lay.lev_stride + lay.o_F + (e / 16) * NX * NX + r * NX + c) : T(0);
+}
+template <typename T, int NX>
+SRTM_DEV void stage_blocks(const T* __restrict__ cst, const ConstLayout& lay, int nlev, double* lev, int tid, int nthr) {
+  staged_copy<4, T>(nlev * 48, tid, nthr, [&](int q) { return block_entry<T, NX>(cst, lay, 0, q); },
+                    [&](int q, T v) { lev[q] = (double)v; });
+}
+
+// One lane's state / information: vector and symmetric matrix.
+template <typename T, int NX>
+struct Belief {
+  T u[NX], P[NX][NX];
+};
+
+template <typename T, int NX>
+SRTM_DEV void belief_zero(Belief<T, NX>& b) {
 #pragma unroll
-    for (int r = 0; r < 2 * NX; ++r) tagg[tile * 2 * NX + r] = S.at(r, TILE - 1);
+  for (int r = 0; r < NX; ++r) {
+    b.u[r] = T(0);
+#pragma unroll
+    for (int c = 0; c < NX; ++c) b.P[r][c] = T(0);
+  }
+}
+// From a packed record (vector, upper triangle).
+template <typename T, int NX, typename S>
+SRTM_DEV void belief_load(Belief<T, NX>& b, const S* p) {
+  int o = NX;
+#pragma unroll
+  for (int r = 0; r < NX; ++r) {
+    b.u[r] = (T)p[r];
+#pragma unroll
+    for (int c = r; c < NX; ++c) b.P[r][c] = b.P[c][r] = (T)p[o++];
   }
 }
 
-// K2 (Kogge-Stone form): tile-level forward scan in one workgroup of KS threads. Thread tau
+// One window's record (vector and symmetric matrix) from its column `col` with W windows per field.
+template <typename T, int NX, typename S>
+SRTM_DEV void record_load(T (&u)[NX], T (&P)[NX][NX], const S* __restrict__ col, int W) {
+  int o = NX;
+#pragma unroll
+  for (int r = 0; r < NX; ++r) {
+    u[r] = (T)gld(col + (int64_t)r * W);
+#pragma unroll
+    for (int c = r; c < NX; ++c) P[r][c] = P[c][r] = (T)gld(col + (int64_t)(o++) * W);
+  }
+}
+template <typename T, int NX>
+SRTM_DEV void record_store(const T (&u)[NX], const T (&P)[NX][NX], T* __restrict__ col, int W) {
+  int o = NX;
+#pragma unroll
+  for (int r = 0; r < NX; ++r) {
+    put_global(col + (int64_t)r * W, u[r]);
+#pragma unroll
+    for (int c = r; c < NX; ++c) put_global(col + (int64_t)(o++) * W, P[r][c]);
+  }
+}
+
+// One lane's combine with the run (d, e) of level tables `tab` = (F, Dp, Jp) as staged for its direction.
+template <typename T, int NX, typename S>
+SRTM_DEV bool lane_combine(Belief<T, NX>& b, const T* __restrict__ tab, const S* __restrict__ nd, bool fwd) {
+  constexpr int NN = NX * NX;
+  T F[NX][NX], D[NX][NX], J[NX][NX], d[NX], e[NX];
+  load(F, tab);
+  load(D, tab + NN);
+  load(J, tab + 2 * NN);
+#pragma unroll
+  for (int r = 0; r < NX; ++r) {
+    const T nd_d = (T)nd[r], nd_e = (T)nd[NX + r];
+    d[r] = fwd ? nd_d : nd_e;
+    e[r] = fwd ? nd_e : -nd_d;
+  }
+  return state_combine(b.u, b.P, F, d, D, e, J);
+}
+
+// Information of N's set bits below each bit (tail), low bits first, for a sequence's last windows.
+// `node(p)` is the (d, eta) of N's node of level p, 2 nx scalars in LDS; entry q of `out` (info_stride scalars
+// each) receives the information of N's set bits below bit q, q = 0 .. qmax. One wave; every block of
+// lanes (every lane, nx > 4) computes the same chain.
+template <typename T, int NX, class ND>
+SRTM_DEV bool tail_chain(const double* lev, const T* lane, double* scratch, int64_t N, int qmax, ND node, double* out) {
+  constexpr int NN = NX * NX, IS = info_stride(NX);
+  bool ok = true;
+  if constexpr (blocks4<NX>()) {
+    const Block4 B(scratch);
+    const bool in = B.r < NX && B.c < NX;
+    double u = 0.0, P = 0.0;
+    for (int q = 0; q <= qmax; ++q) {
+      if (B.b == 0 && in) {
+        if (B.c == 0) out[q * IS + B.r] = u;
+        if (B.c >= B.r) out[q * IS + NX + B.r * NX - B.r * (B.r - 1) / 2 + B.c - B.r] = P;
+      }
+      if (q < qmax && ((N >> q) & 1)) {
+        const double* lv = lev + q * 48;
+        const auto* nd = node(q);
+        const double d = B.r < NX ? (double)nd[B.r] : 0.0, e = B.r < NX ? (double)nd[NX + B.r] : 0.0;
+        if (!combine4(B, u, P, lv[4 * B.r + B.c], lv[32 + 4 * B.r + B.c], lv[16 + 4 * B.r + B.c], e, -d)) ok = false;
+      }
+    }
+  } else {
+    Belief<T, NX> b;
+    belief_zero(b);
+#pragma unroll 1
+    for (int q = 0; q <= qmax; ++q) {
+      if ((threadIdx.x & 63) == 0) {
+        int o = NX;
+#pragma unroll
+        for (int r = 0; r < NX; ++r) {
+          out[q * IS + r] = (double)b.u[r];
+#pragma unroll
+          for (int c = r; c < NX; ++c) out[q * IS + o++] = (double)b.P[r][c];
+        }
+      }
+      if (q < qmax && ((N >> q) & 1)) {
+        if (!lane_combine(b, lane + (size_t)q * 6 * NN + 3 * NN, node(q), false)) ok = false;
+      }
+    }
+  }
+  return ok;
+}
+
+// Direction tables of one lane: per level (F, D, J) for forward combines and (F^T, J, D) for backward
+// ones, 6 nx^2 scalars a level.
+template <typename T, int NX>
+SRTM_DEV void stage_lane_tables(const T* __restrict__ cst, const ConstLayout& lay, int nlev, T* out, int tid, int nthr) {
+  constexpr int NN = NX * NX;
+  staged_copy<4, T>(nlev * 6 * NN, tid, nthr,
+                    [&](int q) {
+                      const int p = q / (6 * NN), e = q % (6 * NN), m = e / NN, r = (e % NN) / NX, c = e % NX;
+                      const int off = m == 0 ? r * NX + c : m == 3 ? c * NX + r
+                                    : (m == 1 || m == 5 ? NN : 2 * NN) + r * NX + c;
+                      return gld(cst + lay.lev + p * lay.lev_stride + lay.o_F + off);
+                    },
+                    [&](int q, T v) { out[q] = v; });
+}
+
+// (d, eta) of N's level-0 node, the element of window N-1 (bit 0 of N set).
+template <bool INP, typename T, int NX, int NY>
+SRTM_DEV void last_element(const Model<T, NX, NY>& M, const T* __restrict__ y, int64_t N, T* out) {
+  T yt[NY], zL[NX], d[NX], e[NX];
+  window_meas<INP>(M, y, N - 1, N, yt, zL);
+  fwd_element<INP>(M, yt, zL, d, e);
+#pragma unroll
+  for (int r = 0; r < NX; ++r) {
+    out[r] = d[r];
+    out[NX + r] = e[r];
+  }
+}
+
+// Threads of the tile-level kernel (KS in a mixed batch), and the nodes of one level that it keeps in LDS
+// (longer levels are read back from device memory; the levels of at most this size together take less than
+// twice it).
+constexpr int TT = 512;
+template <int NX> constexpr int tt_nodes() { return NX <= 4 ? 512 : 256; }
+template <typename T, int NX>
+inline size_t tile_tree_lds_bytes(int nlev) {
+  constexpr int NN = NX * NX;
+  const size_t tab = blocks4<NX>() ? sizeof(double) * 48 * (size_t)nlev : sizeof(T) * 6 * NN * (size_t)nlev;
+  return sizeof(T) * 2 * NX * (2 * (size_t)tt_nodes<NX>()) + sizeof(T) * 4 * NN * (size_t)(nlev > LOG_TILE ? nlev - LOG_TILE : 0) +
+         tab + sizeof(T) * 2 * NX * 32 + sizeof(double) * 64 + 128;
+}
+
+// K2: the levels of the tree above the tiles, over the sequence's whole tiles (one workgroup per sequence,
+// one thread per node and output row as in the tile reductions), and, for the smoother, the information of
+// N's set bits below each bit. A sequence of one tile has no level above it and its fold finds
+// the information of N's bits by itself.
+template <bool INP, typename T, int NX, int NY>
+SRTM_DEV void tile_tree_body(const T* __restrict__ y, int64_t N, int nlev, const T* __restrict__ cst, int L,
+                             InputView<T> in, const T* __restrict__ tagg, const T* __restrict__ utree,
+                             T* __restrict__ ttree, double* __restrict__ tail, bool smoother, int32_t* info, int nthr) {
+  constexpr int NN = NX * NX, R2 = 2 * NX, RS2 = row_slots<NX>(), TT_NODES = tt_nodes<NX>();
+  const int64_t nf = N >> LOG_TILE;
+  if (N <= TILE) return;
+  extern __shared__ char smraw[];
+  T* nodes = reinterpret_cast<T*>(smraw);                                   // 2 TT_NODES nodes
+  T* sC = nodes + R2 * 2 * TT_NODES;                                        // row tables of levels LOG_TILE ..
+  T* own = sC + (nlev > LOG_TILE ? nlev - LOG_TILE : 0) * 4 * NN;           // N's nodes, by level
+  double* dbl = reinterpret_cast<double*>(((uintptr_t)(own + R2 * 32) + 15) & ~(uintptr_t)15);
+  double* scratch = dbl;                                                    // 64
+  double* lev = dbl + 64;                                                   // 4 x 4 blocks (nx <= 4) or
+  T* lane = reinterpret_cast<T*>(lev);                                      // lane tables (nx > 4)
+  const Model<T, NX, NY> M{cst, make_const_layout(NX, NY, L, nlev), in};
+  const int tid = threadIdx.x;
+  staged_copy<4, T>((nlev - LOG_TILE) * 4 * NN, tid, nthr,
+                    [&](int q) { return row_coefficient<T, NX>(M.level(LOG_TILE), M.lay, q); },
+                    [&](int q, T v) { sC[q] = v; });
+  if (smoother) {
+    if constexpr (blocks4<NX>()) stage_blocks<T, NX>(cst, M.lay, nlev, lev, tid, nthr);
+    else stage_lane_tables<T, NX>(cst, M.lay, nlev, lane, tid, nthr);
+    // N's nodes within the last tile (its bits 1 .. 7), and bit 0's window
+    const T* ut = utree + (N >> LOG_TILE) * (R2 * TILE);
+    for (int q = tid; q < (LOG_TILE - 1) * R2; q += nthr) {
+      const int p = 1 + q / R2;
+      if ((N >> p) & 1) own[p * R2 + q % R2] = gld(ut + (tree_off(p) + (((int)(N & (TILE - 1)) >> p) ^ 1)) * R2 + q % R2);
+    }
+    if (tid == nthr - 1 && (N & 1)) last_element<INP>(M, y, N, own);
+  }
+  // Up-sweep; level LOG_TILE + q has nf >> q nodes. Levels longer than the LDS buffer go through device
+  // memory (each of them waits for its stores); the others stay in LDS and are stored together at the end,
+  // so that no level waits for a store to arrive.
+  const int row = tid % RS2;
+  int q0 = 0;              // first level kept in LDS
+  while ((nf >> q0) > TT_NODES) ++q0;
+  {
+    const T* src = tagg;
+    T* dst = ttree;
+#pragma unroll 1
+    for (int q = 1; q <= q0; ++q) {
+      const int64_t nn = nf >> q;
+      __syncthreads();  // the row tables (first level), the level below
+      if (smoother && ((nf >> (q - 1)) & 1) && tid < R2) own[(LOG_TILE + q - 1) * R2 + tid] = gld(src + ((nf >> (q - 1)) - 1) * R2 + tid);
+      if (row < R2)
+        for (int64_t i = tid / RS2; i < nn; i += nthr / RS2)
+          put_global(dst + i * R2 + row, row_combine<T, NX>(sC + ((q - 1) * R2 + row) * R2, src + 2 * i * R2,
+                                                            src + (2 * i + 1) * R2, row));
+      src = dst;
+      dst += nn * R2;
+    }
+    if (q0) __syncthreads();
+    const int n = (int)(nf >> q0);
+    for (int q = tid; q < n * R2; q += nthr) nodes[q] = gld(src + q);
+    __syncthreads();
+    int at = 0;  // the level below
+#pragma unroll 1
+    for (int q = q0 + 1; (nf >> q) > 0; ++q) {
+      const int below = (int)(nf >> (q - 1)), nn = (int)(nf >> q);
+      const T* lsrc = nodes + at * R2;
+      T* ldst = nodes + (at + below) * R2;
+      if (row < R2) {
+        T co[R2];
+#pragma unroll
+        for (int k2 = 0; k2 < R2; ++k2) co[k2] = sC[((q - 1) * R2 + row) * R2 + k2];
+        for (int i = tid / RS2; i < nn; i += nthr / RS2)
+          ldst[i * R2 + row] = row_combine<T, NX>(co, lsrc + 2 * i * R2, lsrc + (2 * i + 1) * R2, row);
+      }
+      at += below;
+      __syncthreads();
+    }
+    for (int q = tid; q < (at + 1 - n) * R2; q += nthr) put_global(dst + q, nodes[n * R2 + q]);  // level q0 is in place
+    if (smoother && tid < R2) {  // N's nodes
+      int o = 0;
+      for (int q = q0; (nf >> q) > 0; ++q) {
+        const int cnt = (int)(nf >> q);
+        if (cnt & 1) own[(LOG_TILE + q) * R2 + tid] = nodes[(o + cnt - 1) * R2 + tid];
+        o += cnt;
+      }
+    }
+  }
+  __syncthreads();
+  if (smoother && tid < 64) {
+    const bool ok = tail_chain<T, NX>(lev, lane, scratch, N, top_bit(N), [&](int p) { return own + p * R2; }, tail);
+    if (!ok && info) atomicOr(info, SRTM_INFO_COMBINE_SINGULAR);
+  }
+}
+
+// K5: reverse tile-level scan of the time-varying smoother in one workgroup of KS threads. Thread r holds the aggregate of
+// its chunk of 2^lchunk consecutive tiles, counted from the end (thread 0 holds the last tiles),
+// folded under eq. op-smoother (earlier (x) later), and merges it with all later runs (lane
+// shuffles inside a wave, then the later waves' aggregates). Every run reaching the
+// last window has E = 0, i.e. is the smoothed state at its first window; thread r then walks
+// its chunk backwards from the state after it, writing per tile the smoothed state of the
+// first window after the tile (zero after the last tile).
+template <typename T, int NX>
+SRTM_DEV void ld_selem_global(const T* __restrict__ src, SElem<T, NX>& x) {
+  constexpr int NN = NX * NX;
+#pragma unroll
+  for (int i = 0; i < NX; ++i) {
+    x.g[i] = gld(src + NN + i);
+#pragma unroll
+    for (int c = 0; c < NX; ++c) {
+      x.E[i][c] = gld(src + i * NX + c);
+      x.S[i][c] = gld(src + NN + NX + i * NX + c);
+    }
+  }
+}
+
+template <typename T, int NX>
+SRTM_DEV void selem_identity(SElem<T, NX>& x) {
+#pragma unroll
+  for (int i = 0; i < NX; ++i) {
+    x.g[i] = T(0);
+#pragma unroll
+    for (int c = 0; c < NX; ++c) {
+      x.E[i][c] = (i == c) ? T(1) : T(0);
+      x.S[i][c] = T(0);
+    }
+  }
+}
+
+template <typename T, int NX, int NY>
+SRTM_DEV void bwd_tiles_body(const T* __restrict__ tagg, int64_t nt, int lchunk, int steps, T* __restrict__ tstate) {
+  constexpr int NN = NX * NX, SE = 2 * NN + NX, ST = NX + NN;
+  extern __shared__ char smraw[];
+  const Slots<T> S{reinterpret_cast<T*>(smraw), KS};
+  const int tid = threadIdx.x;
+  const int64_t c = int64_t(1) << lchunk;
+  const int64_t thi = nt - 1 - tid * c;  // the chunk is tiles thi - c + 1 .. thi (those >= 0)
+  SElem<T, NX> x, xhi;  // xhi: the aggregate of tile thi itself (c = 2), reused by the walk
+  if (thi >= 0 && c == 2) {  // both loads in flight together
+    SElem<T, NX> a;
+    ld_selem_global(tagg + thi * SE, xhi);
+    if (thi - 1 >= 0) {
+      ld_selem_global(tagg + (thi - 1) * SE, a);
+      selem_combine(a, xhi, x);
+    } else {
+      x = xhi;
+    }
+  } else if (thi >= 0) {
+    ld_selem_global(tagg + thi * SE, x);
+#pragma unroll 1
+    for (int64_t t = thi - 1; t > thi - c && t >= 0; --t) {
+      SElem<T, NX> a;
+      ld_selem_global(tagg + t * SE, a);
+      selem_combine(a, x, x);
+    }
+  } else {
+    selem_identity(x);
+  }
+  // Thread r ends with its run merged with every later run (threads r - 1 .. 0): within each
+  // wave by lane shuffles (distances below 64), then each wave with the aggregates of the waves
+  // before it (later tiles; lane 63 holds its wave's), through LDS.
+  {
+    const int lane = tid & 63, wv = tid >> 6;
+    const int lim = steps < 6 ? steps : 6;
+#pragma unroll 1
+    for (int q = 0; q < lim; ++q) selem_merge_lane<false>(x, 1 << q, lane >= (1 << q));
+    if (steps > 6) {
+      if (lane == 63) st_selem(S, wv, x);
+      __syncthreads();
+#pragma unroll 1
+      for (int v = wv - 1; v >= 0; --v) {  // x (x) A_{wv-1} (x) ... (x) A_0, left to right
+        SElem<T, NX> a;
+        ld_selem(S, v, a);
+        selem_combine(x, a, x);
+      }
+      __syncthreads();  // the aggregates are read before the slots take the results
+    }
+  }
+  st_selem(S, tid, x);
+  __syncthreads();
+  if (thi >= 0) {
+    T m[NX], P[NX][NX];
+    if (tid > 0) {
+      SElem<T, NX> nxt;
+      ld_selem(S, tid - 1, nxt);
+#pragma unroll
+      for (int i = 0; i < NX; ++i) {
+        m[i] = nxt.g[i];
+#pragma unroll
+        for (int cc = 0; cc < NX; ++cc) P[i][cc] = nxt.S[i][cc];
+      }
+    } else {
+#pragma unroll
+      for (int i = 0; i < NX; ++i) {
+        m[i] = T(0);
+#pragma unroll
+        for (int cc = 0; cc < NX; ++cc) P[i][cc] = T(0);
+      }
+    }
+#pragma unroll 1
+    for (int64_t t = thi; t > thi - c && t >= 0; --t) {
+#pragma unroll
+      for (int i = 0; i < NX; ++i) tstate[t * ST + i] = m[i];
+#pragma unroll
+      for (int i = 0; i < NX; ++i)
+#pragma unroll
+        for (int cc = 0; cc < NX; ++cc) tstate[t * ST + NX + i * NX + cc] = P[i][cc];
+      if (t - 1 > thi - c && t - 1 >= 0) {
+        if (c == 2) {
+          sstate_combine(xhi, m, P);
+        } else {
+          SElem<T, NX> a;
+          ld_selem_global(tagg + t * SE, a);
+          sstate_combine(a, m, P);
+        }
+      }
+    }
+  }
+}
+
+// Output staging. Each lane computes one window's blocks; records are written to LDS
+// and copied out by the whole wave so that consecutive lanes store consecutive 16-byte
+// chunks. Covariance records (nx^2 scalars) are flushed every fast step; means are
+// gathered over G consecutive fast steps so that a record fills whole cache lines.
+template <int CH> struct Chunk;
+template <> struct Chunk<16> { using type = u32x4; };
+template <> struct Chunk<8> { using type = u32x2; };
+template <> struct Chunk<4> { using type = unsigned int; };
+
+// Store of one output chunk. Outputs are written once and never read back by the library;
+// when a flush writes whole 128-byte lines they are stored non-temporally (streamed past the
+// L2), otherwise normally, so that partial lines can merge in the L2 first.
+template <bool NT, typename V>
+SRTM_DEV void put_chunk(char* p, const V& v) {
+  using G = __attribute__((address_space(1))) V*;  // outputs are device memory: global stores
+  if constexpr (NT)
+    __builtin_nontemporal_store(v, (G)p);
+  else
+    *(G)p = v;
+}
+
+
+// Copies records w = 0..nvalid-1 (nvalid <= 64) of RB bytes (stride SB bytes in LDS) to
+// dst + w * gstride bytes in chunks of CH bytes. A record is PER = RB / CH chunks; one store
+// instruction moves WPI = 64 / PER whole records (lane l: chunk l mod PER of record
+// l / PER + r WPI; the last 64 mod PER lanes idle), so every store address is a wave-uniform base
+// plus one loop-invariant 32-bit lane offset.
+template <int RB, int SB, int CH, bool NT>
+SRTM_DEV void flush_chunks(int lane, int nvalid, const char* __restrict__ lds, char* __restrict__ dst,
+                           int64_t gstride) {
+  constexpr int PER = RB / CH;
+  static_assert(RB % CH == 0 && SB % CH == 0 && PER <= 64, "whole chunks, at most one per lane");
+  constexpr int WPI = 64 / PER;
+  constexpr int NIT = (64 + WPI - 1) / WPI;
+  using V = typename Chunk<CH>::type;
+  const int wl = lane / PER, pl = lane - wl * PER;
+  const unsigned int lo = (unsigned int)(wl * gstride) + (unsigned int)(pl * CH);
+  const char* lsrc = lds + wl * SB + pl * CH;
+  if constexpr (64 % PER == 0) {  // every lane busy: all LDS reads first, then the stores back to back
+    V v[NIT];
+#pragma unroll
+    for (int r = 0; r < NIT; ++r) v[r] = *reinterpret_cast<const V*>(lsrc + r * WPI * SB);
+    if (nvalid == 64) {
+#pragma unroll
+      for (int r = 0; r < NIT; ++r) put_chunk<NT>(dst + (int64_t)r * WPI * gstride + lo, v[r]);
+    } else {
+#pragma unroll
+      for (int r = 0; r < NIT; ++r)
+        if (wl + r * WPI < nvalid) put_chunk<NT>(dst + (int64_t)r * WPI * gstride + lo, v[r]);
+    }
+  } else {  // groups of four instructions (reads, then stores), to bound the registers held
+    constexpr int G = 4;
+    const bool act = wl < WPI;
+#pragma unroll 1
+    for (int r0 = 0; r0 < NIT; r0 += G) {
+      V v[G];
+#pragma unroll
+      for (int j = 0; j < G; ++j)
+        if (r0 + j < NIT && act && wl + (r0 + j) * WPI < 64)
+          v[j] = *reinterpret_cast<const V*>(lsrc + (r0 + j) * WPI * SB);
+#pragma unroll
+      for (int j = 0; j < G; ++j)
+        if (r0 + j < NIT && act && wl + (r0 + j) * WPI < nvalid)
+          put_chunk<NT>(dst + (int64_t)(r0 + j) * WPI * gstride + lo, v[j]);
+    }
+  }
+}
+
+// Chunks of 16 bytes when the record length and LDS stride allow them and the destination and
+// record stride are 16-byte aligned, 8 bytes for records that are 8- but not 16-byte multiples,
+// 4-byte words otherwise. Without GENERAL only records that divide the wave (64 mod PER = 0) go
+// in chunks. GENERAL (4-byte element types) also chunks the others, e.g. the 144-byte records of
+// a 6 x 6 float covariance; the float64 recovery of the mixed-pair kernels, which spills heavily,
+// returned wrong results for unchanged cases with it, so float64 keeps 4-byte words for them.
+template <int RB, int SB, bool NT = false, bool GENERAL = false>
+SRTM_DEV void flush_records(int lane, int nvalid, const char* __restrict__ lds, char* __restrict__ dst,
+                            int64_t gstride) {
+  const uintptr_t al = reinterpret_cast<uintptr_t>(dst) | (uintptr_t)gstride;
+  if constexpr (RB % 16 == 0 && SB % 16 == 0 && RB / 16 <= 64 && (GENERAL || 64 % (RB / 16) == 0)) {
+    if (al % 16 == 0) {
+      flush_chunks<RB, SB, 16, NT>(lane, nvalid, lds, dst, gstride);
+      return;
+    }
+  }
+  if constexpr (RB % 16 != 0 && RB % 8 == 0 && SB % 8 == 0 && RB / 8 <= 64 && (GENERAL || 64 % (RB / 8) == 0)) {
+    if (al % 8 == 0) {
+      flush_chunks<RB, SB, 8, NT>(lane, nvalid, lds, dst, gstride);
+      return;
+    }
+  }
+  if constexpr (RB % 8 != 0 && 64 % (RB / 4) == 0) {  // whole records of 4-byte words per lane
+    flush_chunks<RB, SB, 4, NT>(lane, nvalid, lds, dst, gstride);
+    return;
+  }
+  for (int c = lane; c < nvalid * (RB / 4); c += 64) {  // 4-byte words
+    const int w = c / (RB / 4), e = c - w * (RB / 4);
+    put_global(reinterpret_cast<unsigned int*>(dst + w * gstride) + e,
+               reinterpret_cast<const unsigned int*>(lds + w * SB)[e]);
+  }
+}
+
+// Element-wise variant for a run-time record length (the last, partial group of means).
+template <typename T>
+SRTM_DEV void flush_records_rt(int lane, int nvalid, const char* __restrict__ lds, int SB, T* __restrict__ dst,
+                               int64_t gstride_elems, int nel) {
+  for (int c = lane; c < nvalid * nel; c += 64) {
+    const int w = c / nel, e = c - w * nel;
+    put_global(dst + w * gstride_elems + e, reinterpret_cast<const T*>(lds + w * SB)[e]);
+  }
+}
+
+// Fast steps gathered into one output record: the largest power of two (at most 8) for
+// which the record still fits in one 128-byte line.
+constexpr int line_group(int bytes) {
+  int g = 1;
+  while (g < 8 && 2 * g * bytes <= 128) g *= 2;
+  return g;
+}
+
+template <typename T, int NX>
+struct OutStage {
+  static constexpr int NN = NX * NX;
+  static constexpr int GM = line_group(NX * (int)sizeof(T));   // means per record
+  static constexpr int GP = line_group(NN * (int)sizeof(T));   // covariances per record
+  static constexpr int RBM = GM * NX * (int)sizeof(T), RBP = GP * NN * (int)sizeof(T);
+  static constexpr int SBP = ((RBP + 15) / 16) * 16 + 16;   // LDS bytes per lane (padded)
+  static constexpr int SBM = ((RBM + 15) / 16) * 16 + 16;
+  static constexpr int BYTES = 64 * (SBP + SBM);             // per wave
+  char* pbuf;
+  char* mbuf;
+  SRTM_DEV OutStage(char* base) : pbuf(base), mbuf(base + 64 * SBP) {}
+  // blocks of fast step i (1-based)
+  SRTM_DEV void put(int lane, int i, const T (&m)[NX], const T (&P)[NX][NX]) const {
+    T* pp = reinterpret_cast<T*>(pbuf + lane * SBP) + ((i - 1) % GP) * NN;
+#pragma unroll
+    for (int r = 0; r < NX; ++r)
+#pragma unroll
+      for (int c = 0; c < NX; ++c) pp[r * NX + c] = P[r][c];
+    T* mp = reinterpret_cast<T*>(mbuf + lane * SBM) + ((i - 1) % GM) * NX;
+#pragma unroll
+    for (int r = 0; r < NX; ++r) mp[r] = m[r];
+  }
+  // After put(i): flush the covariance and mean groups that step i completes. The record of
+  // window w0 + w for fast steps i0 .. i0+g-1 starts at out[((w0 + w) L + i0 - 1) * size].
+  SRTM_DEV void flush(int lane, int nvalid, T* m_out, T* P_out, int64_t w0, int L, int i, int ilim) const {
+    const int sp = (i - 1) % GP, sm = (i - 1) % GM;
+    if (P_out && (sp == GP - 1 || i == ilim)) {
+      T* dst = P_out + (w0 * L + (i - sp - 1)) * NN;
+      if (sp == GP - 1)
+        flush_records<RBP, SBP, RBP % 128 == 0, sizeof(T) == 4>(lane, nvalid, pbuf, reinterpret_cast<char*>(dst),
+                                                (int64_t)L * NN * sizeof(T));
+      else
+        flush_records_rt<T>(lane, nvalid, pbuf, SBP, dst, (int64_t)L * NN, (sp + 1) * NN);
+    }
+    if (m_out && (sm == GM - 1 || i == ilim)) {
+      T* dst = m_out + (w0 * L + (i - sm - 1)) * NX;
+      if (sm == GM - 1)
+        flush_records<RBM, SBM, RBM % 128 == 0, sizeof(T) == 4>(lane, nvalid, mbuf, reinterpret_cast<char*>(dst),
+                                                (int64_t)L * NX * sizeof(T));
+      else
+        flush_records_rt<T>(lane, nvalid, mbuf, SBM, dst, (int64_t)L * NX, (sm + 1) * NX);
+    }
+  }
+  // slow-rate output: the blocks of fast step 1 (call right after put(1)), contiguous windows
+  SRTM_DEV void flush_slow(int lane, int nvalid, T* m_out, T* P_out, int64_t w0) const {
+    if (m_out)
+      flush_records<NX * (int)sizeof(T), SBM, false, sizeof(T) == 4>(lane, nvalid, mbuf, reinterpret_cast<char*>(m_out + w0 * NX),
+                                              (int64_t)NX * sizeof(T));
+    if (P_out)
+      flush_records<NN * (int)sizeof(T), SBP, false, sizeof(T) == 4>(lane, nvalid, pbuf, reinterpret_cast<char*>(P_out + w0 * NN),
+                                              (int64_t)NN * sizeof(T));
+  }
+};
+
+template <typename T, int NX>
+SRTM_DEV bool finite_state(const T (&m)[NX], const T (&P)[NX][NX]) {
+  bool ok = true;
+#pragma unroll
+  for (int r = 0; r < NX; ++r) {
+    ok = ok && isfinite(m[r]);
+#pragma unroll
+    for (int c = r; c < NX; ++c) ok = ok && isfinite(P[r][c]);
+  }
+  return ok;
+}
+
+// Window k's filtered slow state (m^f_{k,l}, P^f_{k,l}) from its window quantities (window_setup
+// on the exclusive state): the recovery's blocks at fast step l, m = A^l m' + c_l S^{-1} e (+ z_{k,l}
+// with inputs) and P = A^l Y1 + Q_ll - c_l Y2 (upper triangle, mirrored). Equal to the inclusive
+// combine X_{k-1} (x) a_k in exact arithmetic, at a fraction of its cost.
+template <bool INP, typename T, int NX, int NY>
+SRTM_DEV void window_slow_state(const Model<T, NX, NY>& M, int L, const Window<T, NX, NY>& w, const T (&zL)[NX],
+                                T (&m)[NX], T (&P)[NX][NX]) {
+  T AL[NX][NX], cL[NX][NY];
+  M.get(AL, M.AL_off(L));
+  M.get(cL, M.cL_off(L));
+  const int oq = M.per_i_off(L) + M.lay.o_Qii;
+#pragma unroll
+  for (int r = 0; r < NX; ++r) {
+    T t = INP ? zL[r] : T(0);
+#pragma unroll
+    for (int k = 0; k < NX; ++k) t = my_fma(AL[r][k], w.mp[k], t);
+#pragma unroll
+    for (int k = 0; k < NY; ++k) t = my_fma(cL[r][k], w.Se[k], t);
+    m[r] = t;
+  }
+#pragma unroll
+  for (int r = 0; r < NX; ++r)
+#pragma unroll
+    for (int c = r; c < NX; ++c) {
+      T t = M.at(oq + r * NX + c);
+#pragma unroll
+      for (int k = 0; k < NX; ++k) t = my_fma(AL[r][k], w.Y1[k][c], t);
+#pragma unroll
+      for (int k = 0; k < NY; ++k) t = my_fma(-cL[r][k], w.Y2[k][c], t);
+      P[r][c] = t;
+      P[c][r] = t;
+    }
+}
+
+// Writes window k's slow-rate filter outputs when requested; reports a state that is not finite.
+template <typename T, int NX>
+SRTM_DEV int store_slow(int64_t k, const T (&m)[NX], const T (&P)[NX][NX], T* __restrict__ m_slow,
+                        T* __restrict__ P_slow) {
+  constexpr int NN = NX * NX;
+  if (m_slow) {
+#pragma unroll
+    for (int r = 0; r < NX; ++r) put_global(m_slow + k * NX + r, m[r]);
+  }
+  if (P_slow) {
+#pragma unroll
+    for (int r = 0; r < NN; ++r) put_global(P_slow + k * NN + r, P[r / NX][r % NX]);
+  }
+  return finite_state(m, P) ? 0 : SRTM_INFO_NONFINITE;
+}
+
+// Writes the slow-rate carry (m^f_{k,l}, P^f_{k,l}) of window k < N, and its slow-rate outputs.
+template <typename T, int NX>
+SRTM_DEV int store_carry(int64_t k, const T (&m)[NX], const T (&P)[NX][NX], T* __restrict__ carry,
+                         T* __restrict__ m_slow, T* __restrict__ P_slow) {
+  constexpr int NN = NX * NX, ST = NX + NN;
+#pragma unroll
+  for (int r = 0; r < NX; ++r) put_global(carry + k * ST + r, m[r]);
+#pragma unroll
+  for (int r = 0; r < NX; ++r)
+#pragma unroll
+    for (int c = 0; c < NX; ++c) put_global(carry + k * ST + NX + r * NX + c, P[r][c]);
+  return store_slow(k, m, P, m_slow, P_slow);
+}
+
+// Smoother correction of window k (fold section): v = (I + J P)^{-1} (eta - J m), W = -(I + J P)^{-1} J, from its
+// inclusive filter state (m, P) = (m^f_{k,l}, P^f_{k,l}) and its information record (column `col` of a tile
+// of nw windows; zero after the last window, which gives v = 0 and W = 0). Returns false when I + J P is numerically singular.
+template <bool INP, typename T, int NX, int NY, typename S>
+SRTM_DEV bool info_correction(const Model<T, NX, NY>& M, int L, const Window<T, NX, NY>& w, const T (&zL)[NX],
+                              const S* __restrict__ col, int nw, T (&v)[NX], T (&W)[NX][NX]) {
+  T m[NX], P[NX][NX], eta[NX], J[NX][NX], A[NX][NX], Ai[NX][NX];
+  record_load(eta, J, col, nw);
+  window_slow_state<INP>(M, L, w, zL, m, P);
+  mm(J, P, A);
+#pragma unroll
+  for (int r = 0; r < NX; ++r) {
+    A[r][r] += T(1);
+#pragma unroll
+    for (int k = 0; k < NX; ++k) eta[r] = my_fma(-J[r][k], m[k], eta[r]);
+  }
+  const bool ok = inv_small(A, Ai);
+  mv(Ai, eta, v);
+#pragma unroll
+  for (int r = 0; r < NX; ++r)
+#pragma unroll
+    for (int c = r; c < NX; ++c) {
+      T t = T(0);
+#pragma unroll
+      for (int k = 0; k < NX; ++k) t = my_fma(-Ai[r][k], J[k][c], t);
+      W[r][c] = W[c][r] = t;
+    }
+  return ok;
+}
+
+// K3: the fold of one tile. Every window's exclusive filter state (m^f_{k-1,l}, P^f_{k-1,l}), its prior and
+// the slow filter output of the window before, and (SMOOTH) the information of the windows after it, from the dyadic tree: the
+// tile's own bits and the window's bits 4 .. 7 on the matrix cores, four 16-window groups per wave
+// (the tile's bits are the same for all of them), the low four bits one lane per window.
+// `want_last`: also the filter state after the last window when no lane stands for window N (N a multiple of
+// TILE).
+template <bool SMOOTH, bool INP, typename T, int NX, int NY>
+SRTM_DEV void fold_body(const T* __restrict__ y, int64_t N, int L, int nlev, const T* __restrict__ cst, InputView<T> in,
+                        const T* __restrict__ m0, const T* __restrict__ P0, const T* __restrict__ tagg,
+                        const T* __restrict__ ttree, const T* __restrict__ utree, const double* __restrict__ tail_g,
+                        T* __restrict__ prior, T* __restrict__ m_slow, T* __restrict__ P_slow, T* __restrict__ rec,
+                        int32_t* info, int64_t tile, bool want_last) {
+  constexpr int NN = NX * NX, R2 = 2 * NX, IS = info_stride(NX), NZ = FoldLds<T, NX>::NZ, LB = lane_levels<NX>();
+  constexpr bool B4 = blocks4<NX>();
+  extern __shared__ char smraw[];
+  const int tid = threadIdx.x, wv = tid >> 6, lane_id = tid & 63;
+  const int64_t k = tile * TILE + tid;
+  const int64_t nf = N >> LOG_TILE;            // whole tiles
+  const int rem = (int)(N & (TILE - 1));       // windows of the partial last tile
+  const bool ragged = tile == nf, single = N <= TILE;
+  if (single) nlev = LOG_TILE;
+  const int hb = ragged ? -1 : top_bit(tile ^ nf);
+  const FoldLds<T, NX> lo(nlev);
+  T* leaf = reinterpret_cast<T*>(smraw + lo.leaf);
+  T* tree = reinterpret_cast<T*>(smraw + lo.tree);
+  T* lane = reinterpret_cast<T*>(smraw + lo.lane);
+  double* lev = reinterpret_cast<double*>(smraw + lo.lev);
+  T* node = reinterpret_cast<T*>(smraw + lo.node);
+  double* tail = reinterpret_cast<double*>(smraw + lo.tail) + (single ? wv * NZ * IS : 0);
+  double* scratch = reinterpret_cast<double*>(smraw + lo.scratch) + wv * 64;
+  const Model<T, NX, NY> M{cst, make_const_layout(NX, NY, L), in};
+  int flag = 0;
+
+  // ---- everything the fold reads, in one round of loads: all of them are issued before the first
+  // is stored to LDS (one memory round trip instead of one per table)
+  constexpr int NCH = tree_off(LOG_TILE) * R2 * (int)sizeof(T) / 16, PCH = (NCH + TILE - 1) / TILE;
+  constexpr int PLV = B4 ? (MAXLEV * 48 + TILE - 1) / TILE : 1;
+  u32x4 tv[PCH];
+  const char* tsrc = reinterpret_cast<const char*>(utree + tile * (R2 * TILE));
+#pragma unroll
+  for (int i = 0; i < PCH; ++i) {
+    const int q = i * TILE + tid;
+    if (q < NCH) tv[i] = gld(reinterpret_cast<const u32x4*>(tsrc) + q);
+  }
+  T yt[NY], zL[NX];
+  window_meas<INP>(M, y, k, N, yt, zL);
+  const int p0 = SMOOTH && single ? 0 : LB, nlv = B4 ? (nlev - p0) * 48 : 0;
+  T lvv[PLV];
+  if constexpr (B4) {
+#pragma unroll
+    for (int i = 0; i < PLV; ++i) {
+      const int q = i * TILE + tid;
+      lvv[i] = q < nlv ? block_entry<T, NX>(cst, M.lay, p0, q) : T(0);
+    }
+  }
+  T ndv = T(0);
+  double tlv = 0.0;
+  if (tid < FoldLds<T, NX>::MAXT * R2) {  // the tile's own nodes
+    const int q = tid / R2, e = tid % R2;
+    if (((tile >> q) & 1) || (SMOOTH && q < hb)) {
+      const int64_t i = (tile >> q) ^ 1;
+      ndv = q == 0 ? gld(tagg + i * R2 + e) : gld(ttree + (tile_level_off(nf, q) + i) * R2 + e);
+    }
+  }
+  const int tl0 = ragged ? 0 : LOG_TILE, tln = !SMOOTH || single ? 0 : ragged ? LOG_TILE * IS : IS;
+  if constexpr (SMOOTH) {  // the entries this tile can ask for
+    if (tid < tln) tlv = gld(tail_g + (ragged ? 0 : (LOG_TILE + hb) * IS) + tid);
+  }
+  stage_lane_tables<T, NX>(cst, M.lay, B4 ? LB : nlev, lane, tid, TILE);
+  {
+    T d[NX], e[NX];
+    fwd_element<INP>(M, yt, zL, d, e);
+#pragma unroll
+    for (int r = 0; r < NX; ++r) {
+      leaf[tid * R2 + r] = d[r];
+      leaf[tid * R2 + NX + r] = e[r];
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < PCH; ++i) {
+    const int q = i * TILE + tid;
+    if (q < NCH) reinterpret_cast<u32x4*>(tree)[q] = tv[i];
+  }
+  if constexpr (B4) {
+#pragma unroll
+    for (int i = 0; i < PLV; ++i) {
+      const int q = i * TILE + tid;
+      if (q < nlv) lev[p0 * 48 + q] = (double)lvv[i];
+    }
+  }
+  if (tid < FoldLds<T, NX>::MAXT * R2) node[tid] = ndv;
+  if (tid < tln) tail[tl0 * IS + tid] = tlv;
+  __syncthreads();
+  if constexpr (SMOOTH) {
+    if (single) {  // each wave its own copy
+      const bool ok = tail_chain<T, NX>(lev, lane, scratch, N, top_bit(N), [&](int p) {
+        return p == 0 ? leaf + (rem ^ 1) * R2 : tree + (tree_off(p) + ((rem >> p) ^ 1)) * R2;
+      }, tail);
+      if (!ok) flag |= SRTM_INFO_COMBINE_SINGULAR;
+      wave_sync();
+    }
+  }
+
+  // ---- upper bits
+  Belief<T, NX> fs, bs;  // filter state at the window's start; information after the window
+  int bl = ragged ? 0 : LB;  // the window's bits below bl take backward combines
+  const int tq = top_bit(tile) > hb - 1 ? top_bit(tile) : hb - 1;  // top bit of the tile that is used
+  if constexpr (B4) {
+    const Block4 B(scratch);
+    const bool in4 = B.r < NX && B.c < NX;
+    const int g = wv * 4 + B.b, gr = rem >> 4;
+    double fu = B.r < NX ? (double)gld(m0 + B.r) : 0.0;
+    double fP = in4 ? 0.5 * ((double)gld(P0 + B.r * NX + B.c) + (double)gld(P0 + B.c * NX + B.r)) : 0.0;
+    double bu = 0.0, bP = 0.0;
+    int bw = LOG_TILE;  // the group's bits below bw take backward combines
+    if (ragged) bw = g < gr ? LB + top_bit(g ^ gr) : 0;
+    if constexpr (SMOOTH) {
+      if (in4 && bw > 0) {
+        const int a = B.r < B.c ? B.r : B.c, e = B.r < B.c ? B.c : B.r;
+        bu = tail[bw * IS + B.r];
+        bP = tail[bw * IS + NX + a * NX - a * (a - 1) / 2 + e - a];
+      }
+    }
+    // The steps, highest bit first: the tile's bits that ask for a combine, then the group's four. The
+    // operands of a step are read while the step before it runs.
+    struct Step {
+      double Tt, Dp, Jp, vd, ve;
+      bool f, act;
+    };
+    auto fetch = [&](int p) {
+      Step st;
+      const T* nd;
+      if (p >= LOG_TILE) {
+        st.f = (tile >> (p - LOG_TILE)) & 1;
+        st.act = true;
+        nd = node + (p - LOG_TILE) * R2;
+      } else {
+        const int i = g >> (p - LB);
+        st.f = i & 1;
+        st.act = st.f || (SMOOTH && p < bw);
+        nd = tree + (tree_off(p) + (i ^ 1)) * R2;
+      }
+      const double* lv = lev + p * 48;
+      st.Tt = lv[st.f ? 4 * B.c + B.r : 4 * B.r + B.c];
+      st.Dp = lv[(st.f ? 16 : 32) + 4 * B.r + B.c];
+      st.Jp = lv[(st.f ? 32 : 16) + 4 * B.r + B.c];
+      const double d = B.r < NX ? (double)nd[B.r] : 0.0, e = B.r < NX ? (double)nd[NX + B.r] : 0.0;
+      st.vd = st.f ? d : e;
+      st.ve = st.f ? e : -d;
+      return st;
+    };
+    uint32_t todo = (uint32_t)tile << LOG_TILE | 0xF0u;
+    if (SMOOTH && hb > 0) todo |= ((1u << hb) - 1u) << LOG_TILE;
+    int p = 31 - __builtin_clz(todo);
+    Step cur = fetch(p);
+#pragma unroll 1
+    while (true) {
+      todo &= ~(1u << p);
+      p = todo ? 31 - __builtin_clz(todo) : LB;
+      const Step next = fetch(p);
+      double u = cur.f ? fu : bu, P = cur.f ? fP : bP;
+      const bool ok = combine4(B, u, P, cur.Tt, cur.Dp, cur.Jp, cur.vd, cur.ve);
+      if (cur.act) {
+        if (!ok) flag |= SRTM_INFO_COMBINE_SINGULAR;
+        fu = cur.f ? u : fu;
+        fP = cur.f ? P : fP;
+        bu = cur.f ? bu : u;
+        bP = cur.f ? bP : P;
+      }
+      if (!todo) break;
+      cur = next;
+    }
+    // each group's states to its 16 lanes
+    double* grp = reinterpret_cast<double*>(smraw + lo.group) + wv * 160;
+    grp[B.b * 40 + 4 * B.r + B.c] = fP;
+    if (B.c == 0) grp[B.b * 40 + 16 + B.r] = fu;
+    if constexpr (SMOOTH) {
+      grp[B.b * 40 + 20 + 4 * B.r + B.c] = bP;
+      if (B.c == 0) grp[B.b * 40 + 36 + B.r] = bu;
+    }
+    wave_sync();
+    const double* mine = grp + (lane_id >> 4) * 40;
+#pragma unroll
+    for (int r = 0; r < NX; ++r) {
+      fs.u[r] = (T)mine[16 + r];
+      bs.u[r] = SMOOTH ? (T)mine[36 + r] : T(0);
+#pragma unroll
+      for (int c = r; c < NX; ++c) {
+        fs.P[r][c] = fs.P[c][r] = (T)mine[4 * r + c];
+        bs.P[r][c] = bs.P[c][r] = SMOOTH ? (T)mine[20 + 4 * r + c] : T(0);
+      }
+    }
+    if (ragged) {
+      bl = (tid >> 4) < gr ? LB : 0;
+      if (SMOOTH && (tid >> 4) == gr && tid < rem) {
+        bl = top_bit(tid ^ rem);
+        belief_load(bs, tail + bl * IS);
+      }
+    }
+  } else {
+    gloadv(fs.u, m0);
+    gload(fs.P, P0);
+    symmetrize(fs.P);
+    belief_zero(bs);
+    if constexpr (SMOOTH) {
+      if (ragged && tid < rem) bl = top_bit(tid ^ rem);
+      if (!ragged || tid < rem) belief_load(bs, tail + bl * IS);
+    }
+#pragma unroll 1
+    for (int q = tq; q >= 0; --q) {
+      const bool f = (tile >> q) & 1;
+      if (!f && !(SMOOTH && q < hb)) continue;
+      Belief<T, NX> x;
+#pragma unroll
+      for (int r = 0; r < NX; ++r) {
+        x.u[r] = f ? fs.u[r] : bs.u[r];
+#pragma unroll
+        for (int c = 0; c < NX; ++c) x.P[r][c] = f ? fs.P[r][c] : bs.P[r][c];
+      }
+      if (!lane_combine(x, lane + (size_t)(LOG_TILE + q) * 6 * NN + (f ? 0 : 3 * NN), node + q * R2, f))
+        flag |= SRTM_INFO_COMBINE_SINGULAR;
+      if (f) fs = x;
+      else bs = x;
+    }
+  }
+
+  // ---- the low bits, one lane per window
+#pragma unroll 1
+  for (int p = LB - 1; p >= 0; --p) {
+    const bool f = (tid >> p) & 1;
+    const bool act = f || (SMOOTH && p < bl);
+    const int i = (tid >> p) ^ 1;
+    const T* nd = p == 0 ? leaf + i * R2 : tree + (tree_off(p) + i) * R2;
+    if (SMOOTH || f) {
+      Belief<T, NX> x;
+#pragma unroll
+      for (int r = 0; r < NX; ++r) {
+        x.u[r] = f ? fs.u[r] : bs.u[r];
+#pragma unroll
+        for (int c = 0; c < NX; ++c) x.P[r][c] = f ? fs.P[r][c] : bs.P[r][c];
+      }
+      const bool ok = lane_combine(x, lane + (size_t)p * 6 * NN + (f ? 0 : 3 * NN), nd, f);
+      if (act && !ok) flag |= SRTM_INFO_COMBINE_SINGULAR;
+#pragma unroll
+      for (int r = 0; r < NX; ++r) {
+        fs.u[r] = f ? x.u[r] : fs.u[r];
+        bs.u[r] = act && !f ? x.u[r] : bs.u[r];
+#pragma unroll
+        for (int c = 0; c < NX; ++c) {
+          fs.P[r][c] = f ? x.P[r][c] : fs.P[r][c];
+          bs.P[r][c] = act && !f ? x.P[r][c] : bs.P[r][c];
+        }
+      }
+    }
+  }
+
+  // ---- outputs: the window's prior and information records; the slow filter output of the window before
+  const int nw = tile_windows(N, tile);
+  if (k >= 1 && k <= N) flag |= store_slow(k - 1, fs.u, fs.P, m_slow, P_slow);
+  if (k < N) record_store(fs.u, fs.P, prior + tile * (TILE * IS) + tid, nw);
+  if constexpr (SMOOTH) {
+    if (k < N) {
+      record_store(bs.u, bs.P, rec + tile * (TILE * IS) + tid, nw);
+      if (k >= 1) {  // the prediction of x_{k,1}: P^- = A P A^T + Q has to be positive definite
+        T A[NX][NX], Qm[NX][NX], Pm[NX][NX], Pi[NX][NX];
+        load(A, M.cst + M.lay.A);
+        load(Qm, M.cst + M.lay.Q);
+        sandwich(A, fs.P, Qm, Pm);
+        if (!spd_inv(Pm, Pi)) flag |= SRTM_INFO_PRED_SINGULAR;
+      }
+    }
+  }
+  if (want_last && k == N - 1 && rem == 0) {
+    if (!lane_combine(fs, lane, leaf + tid * R2, true)) flag |= SRTM_INFO_COMBINE_SINGULAR;
+    flag |= store_slow(k, fs.u, fs.P, m_slow, P_slow);
+  }
+  if (flag && info) atomicOr(info, flag);
+}
+
+// ============================================================================ backward
+// The smoother half of the per-window models' fused forward/backward kernel for window k of tile `tile`,
+// given the window quantities w (window_setup on the exclusive filter state), the inclusive filter state
+// (m, P) and (An, Qn), the model of the step into x_{k+1,1}: its smoother element (eq.
+// parallel-ak-smoothing), the in-tile reverse scan under eq. op-smoother, the tile aggregate
+// a_first (x) ... (x) a_last, and per window the smoother correction of eq. seq-smoothing-all written as terms
+// linear in the smoothed state (m_in, P_in) that enters the tile from the right (the first window after
+// it). With B = (P^-)^{-1} A and the in-tile exclusive suffix (E', g', S') = a_{k+1} (x) ... (x) a_{last of tile}:
+//   v = A^T (P^-)^{-1} (m^s_{k+1,1} - A m^f_{k,l}) = Et m_in + gt,
+//   W = A^T (P^-)^{-1} (P^s_{k+1,1} - P^-) (P^-)^{-1} A = Et P_in Et^T + St,
+//   Et = B^T E',  gt = B^T (g' - A m^f_{k,l}),  St = B^T (S' - P^-) B;
+// all three are zero for the last window, whose smoothed blocks equal the filtered ones. Returns
+// numerical status bits.
+template <bool INP, typename T, int NX, int NY, class MV>
+SRTM_DEV int smoother_part(const MV& M, const Slots<T>& S, int L, int64_t k, int64_t N,
+                           const Window<T, NX, NY>& w, const T (&m)[NX], const T (&P)[NX][NX],
+                           const T (&An)[NX][NX], const T (&Qn)[NX][NX], T* __restrict__ btagg,
+                           T* __restrict__ sfx, int64_t tile) {
+  constexpr int NN = NX * NX, SE = 2 * NN + NX, SF = sfx_stride(NX);
+  const int tid = threadIdx.x;
+  const bool valid = k < N;
+  int flag = 0;
+  SElem<T, NX> x;
+  T B[NX][NX], Bm[NX], BPB[NX][NX];  // B = (P^-)^{-1} A, B^T (predicted mean), B^T P^- B = A^T B
+  {
+    T z1[NX], bnext[NX];  // B u_{k,0} and B u_{k+1,0}
+#pragma unroll
+    for (int r = 0; r < NX; ++r) z1[r] = bnext[r] = T(0);
+    if constexpr (INP) {
+      if (valid) input_drive(M.in, M.in.u + k * L * M.in.nu, z1);
+      if (k + 1 < N) input_drive(M.in, M.in.u + (k + 1) * L * M.in.nu, bnext);
+    }
+    T Pmi[NX][NX], mpred[NX], Pm[NX][NX];
+    const int f = smoother_element<INP>(M, L, w, k == N - 1, m, P, z1, bnext, An, Qn, x, Pmi, mpred, Pm);
+    if (valid) flag |= f;
+    mm(Pmi, An, B);
+    mtv(B, mpred, Bm);
+#pragma unroll
+    for (int r = 0; r < NX; ++r)
+#pragma unroll
+      for (int c = r; c < NX; ++c) {
+        T t = T(0);
+#pragma unroll
+        for (int q = 0; q < NX; ++q) t = my_fma(An[q][r], B[q][c], t);
+        BPB[r][c] = t;
+        BPB[c][r] = t;
+      }
+  }
+  if (!valid) {  // past the last window: a zero element (finite, and absorbed by E_N = 0)
+#pragma unroll
+    for (int r = 0; r < NX; ++r) {
+      x.g[r] = T(0);
+#pragma unroll
+      for (int c = 0; c < NX; ++c) {
+        x.E[r][c] = T(0);
+        x.S[r][c] = T(0);
+      }
+    }
+  }
+  // Lane j ends with a_j (x) a_{j+1} (x) ... (x) a_{TILE-1}. Within each wave first, by lane
+  // shuffles at distances 1 .. 32: lane l then holds its wave's elements l .. 63 merged, and lane
+  // 0 the whole wave's. Then each wave merges with the aggregates of the waves after it, which
+  // pass through LDS (runs of any length merge: eq. op-smoother carries whole matrices).
+  {
+    const int lane = tid & 63, wv = tid >> 6;
+    constexpr int NW = TILE / 64;
+#pragma unroll 1
+    for (int s = 1; s < 64; s *= 2) selem_merge_lane<true>(x, s, lane + s < 64);
+    __syncthreads();  // the slots switch from forward states to smoother elements
+    if (lane == 0) st_selem(S, wv, x);
+    __syncthreads();
+#pragma unroll 1
+    for (int v = wv + 1; v < NW; ++v) {  // x (x) A_{wv+1} (x) ... (x) A_{NW-1}, left to right
+      SElem<T, NX> a;
+      ld_selem(S, v, a);
+      selem_combine(x, a, x);
+    }
+    __syncthreads();  // the aggregates are read before the slots take the suffixes
+  }
+  st_selem(S, tid, x);
+  __syncthreads();
+  if (tid == 0) {
+    T* dst = btagg + tile * SE;
+#pragma unroll
+    for (int r = 0; r < NX; ++r) {
+      dst[NN + r] = x.g[r];
+#pragma unroll
+      for (int c = 0; c < NX; ++c) {
+        dst[r * NX + c] = x.E[r][c];
+        dst[NN + NX + r * NX + c] = x.S[r][c];
+      }
+    }
+  }
+  SElem<T, NX> nxt;  // exclusive suffix; the identity (I, 0, 0) for the tile's last lane
+  if (tid + 1 < TILE) {
+    ld_selem(S, tid + 1, nxt);
+  } else {
+#pragma unroll
+    for (int r = 0; r < NX; ++r) {
+      nxt.g[r] = T(0);
+#pragma unroll
+      for (int c = 0; c < NX; ++c) {
+        nxt.E[r][c] = (r == c) ? T(1) : T(0);
+        nxt.S[r][c] = T(0);
+      }
+    }
+  }
+  if (valid) {
+    T rec[SF];
+    if (k < N - 1) {
+      T SB[NX][NX];
+      mm(nxt.S, B, SB);
+#pragma unroll
+      for (int r = 0; r < NX; ++r) {
+        T t = -Bm[r];
+#pragma unroll
+        for (int q = 0; q < NX; ++q) t = my_fma(B[q][r], nxt.g[q], t);
+        rec[NN + r] = t;
+#pragma unroll
+        for (int c = 0; c < NX; ++c) {
+          T e = T(0);
+#pragma unroll
+          for (int q = 0; q < NX; ++q) e = my_fma(B[q][r], nxt.E[q][c], e);
+          rec[r * NX + c] = e;
+        }
+      }
+      int o = NN + NX;
+#pragma unroll
+      for (int r = 0; r < NX; ++r)
+#pragma unroll
+        for (int c = r; c < NX; ++c) {
+          T t = -BPB[r][c];
+#pragma unroll
+          for (int q = 0; q < NX; ++q) t = my_fma(B[q][r], SB[q][c], t);
+          rec[o++] = t;
+        }
+    } else {
+#pragma unroll
+      for (int r = 0; r < SF; ++r) rec[r] = T(0);
+    }
+    T* dst = sfx + k * SF;
+#pragma unroll
+    for (int r = 0; r < SF; ++r) put_global(dst + r, rec[r]);
+  }
+  return flag;
+}
+
+// ---------------------------------------------------------------- float32 gradient: scan of smoother elements
+// The sums of the gradient nearly vanish near the data's own parameters, so a float32 gradient carries the
+// rounding of the float32 states magnified: on one model of the gradient workload (nx = 4, ny = 1, L = 10,
+// N = 2^14) it is 7e-5 off the float64 gradient here and 6e-6 through the fold. The entry point keeps the values
+// it has had, so float32 gradients still take the states and corrections from this scan (k_fwd_tiles,
+// k_fwd_bwd, k_bwd_tiles); float64 gradients, where both agree to 1e-12, and everything else use the fold.
+template <typename T> constexpr bool grad_by_elements() { return std::is_same_v<T, float>; }
+
+// Vector part of eq. op-filter for two runs of 2^p elements (the level's row table).
+template <typename T, int NX>
+SRTM_DEV void level_vec_combine(const T* __restrict__ lev, const ConstLayout& lay, const T (&di)[NX],
+                                const T (&ei)[NX], T (&dj)[NX], T (&ej)[NX]) {
+  const T* C = lev + lay.o_C;
+  T nd[NX], ne[NX];
+#pragma unroll
+  for (int r = 0; r < NX; ++r) {
+    T s = dj[r], t = ei[r];
+#pragma unroll
+    for (int k = 0; k < NX; ++k) {
+      s = my_fma(C[r * 2 * NX + k], di[k], s);
+      s = my_fma(C[r * 2 * NX + NX + k], ej[k], s);
+      t = my_fma(C[(NX + r) * 2 * NX + k], ej[k], t);
+      t = my_fma(C[(NX + r) * 2 * NX + NX + k], di[k], t);
+    }
+    nd[r] = s;
+    ne[r] = t;
+  }
+#pragma unroll
+  for (int r = 0; r < NX; ++r) {
+    dj[r] = nd[r];
+    ej[r] = ne[r];
+  }
+}
+
+// Tile-level forward scan in one workgroup of KS threads. Thread tau
 // holds the vector parts of its chunk of 2^lchunk tiles (matrices Theta(2^lchunk TILE)); the
 // prior (m0, P0) is folded into thread 0, which makes it a state. At step q, threads in
 // [2^q, 2^{q+1}) combine the state of thread tau - 2^q with their run (one state combine,
@@ -1775,340 +3052,29 @@ SRTM_DEV void fwd_tiles_body(const T* __restrict__ tagg, int64_t nt, int lchunk,
   if (flag && info) atomicOr(info, flag);
 }
 
-// K5: reverse tile-level scan in one workgroup of KS threads. Thread r holds the aggregate of
-// its chunk of 2^lchunk consecutive tiles, counted from the end (thread 0 holds the last tiles),
-// folded under eq. op-smoother (earlier (x) later), and merges it with all later runs (lane
-// shuffles inside a wave, then the later waves' aggregates). Every run reaching the
-// last window has E = 0, i.e. is the smoothed state at its first window; thread r then walks
-// its chunk backwards from the state after it, writing per tile the smoothed state of the
-// first window after the tile (zero after the last tile).
-template <typename T, int NX>
-SRTM_DEV void ld_selem_global(const T* __restrict__ src, SElem<T, NX>& x) {
-  constexpr int NN = NX * NX;
-#pragma unroll
-  for (int i = 0; i < NX; ++i) {
-    x.g[i] = gld(src + NN + i);
-#pragma unroll
-    for (int c = 0; c < NX; ++c) {
-      x.E[i][c] = gld(src + i * NX + c);
-      x.S[i][c] = gld(src + NN + NX + i * NX + c);
-    }
-  }
-}
-
-template <typename T, int NX>
-SRTM_DEV void selem_identity(SElem<T, NX>& x) {
-#pragma unroll
-  for (int i = 0; i < NX; ++i) {
-    x.g[i] = T(0);
-#pragma unroll
-    for (int c = 0; c < NX; ++c) {
-      x.E[i][c] = (i == c) ? T(1) : T(0);
-      x.S[i][c] = T(0);
-    }
-  }
-}
-
-template <typename T, int NX, int NY>
-SRTM_DEV void bwd_tiles_body(const T* __restrict__ tagg, int64_t nt, int lchunk, int steps, T* __restrict__ tstate) {
-  constexpr int NN = NX * NX, SE = 2 * NN + NX, ST = NX + NN;
-  extern __shared__ char smraw[];
-  const Slots<T> S{reinterpret_cast<T*>(smraw), KS};
-  const int tid = threadIdx.x;
-  const int64_t c = int64_t(1) << lchunk;
-  const int64_t thi = nt - 1 - tid * c;  // the chunk is tiles thi - c + 1 .. thi (those >= 0)
-  SElem<T, NX> x, xhi;  // xhi: the aggregate of tile thi itself (c = 2), reused by the walk
-  if (thi >= 0 && c == 2) {  // both loads in flight together
-    SElem<T, NX> a;
-    ld_selem_global(tagg + thi * SE, xhi);
-    if (thi - 1 >= 0) {
-      ld_selem_global(tagg + (thi - 1) * SE, a);
-      selem_combine(a, xhi, x);
-    } else {
-      x = xhi;
-    }
-  } else if (thi >= 0) {
-    ld_selem_global(tagg + thi * SE, x);
-#pragma unroll 1
-    for (int64_t t = thi - 1; t > thi - c && t >= 0; --t) {
-      SElem<T, NX> a;
-      ld_selem_global(tagg + t * SE, a);
-      selem_combine(a, x, x);
-    }
-  } else {
-    selem_identity(x);
-  }
-  // Thread r ends with its run merged with every later run (threads r - 1 .. 0): within each
-  // wave by lane shuffles (distances below 64), then each wave with the aggregates of the waves
-  // before it (later tiles; lane 63 holds its wave's), through LDS.
-  {
-    const int lane = tid & 63, wv = tid >> 6;
-    const int lim = steps < 6 ? steps : 6;
-#pragma unroll 1
-    for (int q = 0; q < lim; ++q) selem_merge_lane<false>(x, 1 << q, lane >= (1 << q));
-    if (steps > 6) {
-      if (lane == 63) st_selem(S, wv, x);
-      __syncthreads();
-#pragma unroll 1
-      for (int v = wv - 1; v >= 0; --v) {  // x (x) A_{wv-1} (x) ... (x) A_0, left to right
-        SElem<T, NX> a;
-        ld_selem(S, v, a);
-        selem_combine(x, a, x);
-      }
-      __syncthreads();  // the aggregates are read before the slots take the results
-    }
-  }
-  st_selem(S, tid, x);
-  __syncthreads();
-  if (thi >= 0) {
-    T m[NX], P[NX][NX];
-    if (tid > 0) {
-      SElem<T, NX> nxt;
-      ld_selem(S, tid - 1, nxt);
-#pragma unroll
-      for (int i = 0; i < NX; ++i) {
-        m[i] = nxt.g[i];
-#pragma unroll
-        for (int cc = 0; cc < NX; ++cc) P[i][cc] = nxt.S[i][cc];
-      }
-    } else {
-#pragma unroll
-      for (int i = 0; i < NX; ++i) {
-        m[i] = T(0);
-#pragma unroll
-        for (int cc = 0; cc < NX; ++cc) P[i][cc] = T(0);
-      }
-    }
-#pragma unroll 1
-    for (int64_t t = thi; t > thi - c && t >= 0; --t) {
-#pragma unroll
-      for (int i = 0; i < NX; ++i) tstate[t * ST + i] = m[i];
-#pragma unroll
-      for (int i = 0; i < NX; ++i)
-#pragma unroll
-        for (int cc = 0; cc < NX; ++cc) tstate[t * ST + NX + i * NX + cc] = P[i][cc];
-      if (t - 1 > thi - c && t - 1 >= 0) {
-        if (c == 2) {
-          sstate_combine(xhi, m, P);
-        } else {
-          SElem<T, NX> a;
-          ld_selem_global(tagg + t * SE, a);
-          sstate_combine(a, m, P);
-        }
-      }
-    }
-  }
-}
-
-// Output staging. Each lane computes one window's blocks; records are written to LDS
-// and copied out by the whole wave so that consecutive lanes store consecutive 16-byte
-// chunks. Covariance records (nx^2 scalars) are flushed every fast step; means are
-// gathered over G consecutive fast steps so that a record fills whole cache lines.
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
-template <int CH> struct Chunk;
-template <> struct Chunk<16> { using type = u32x4; };
-template <> struct Chunk<8> { using type = u32x2; };
-template <> struct Chunk<4> { using type = unsigned int; };
-
-// Store of one output chunk. Outputs are written once and never read back by the library;
-// when a flush writes whole 128-byte lines they are stored non-temporally (streamed past the
-// L2), otherwise normally, so that partial lines can merge in the L2 first.
-template <bool NT, typename V>
-SRTM_DEV void put_chunk(char* p, const V& v) {
-  using G = __attribute__((address_space(1))) V*;  // outputs are device memory: global stores
-  if constexpr (NT)
-    __builtin_nontemporal_store(v, (G)p);
-  else
-    *(G)p = v;
-}
-
-
-// Copies records w = 0..nvalid-1 (nvalid <= 64) of RB bytes (stride SB bytes in LDS) to
-// dst + w * gstride bytes in chunks of CH bytes. A record is PER = RB / CH chunks; one store
-// instruction moves WPI = 64 / PER whole records (lane l: chunk l mod PER of record
-// l / PER + r WPI; the last 64 mod PER lanes idle), so every store address is a wave-uniform base
-// plus one loop-invariant 32-bit lane offset.
-template <int RB, int SB, int CH, bool NT>
-SRTM_DEV void flush_chunks(int lane, int nvalid, const char* __restrict__ lds, char* __restrict__ dst,
-                           int64_t gstride) {
-  constexpr int PER = RB / CH;
-  static_assert(RB % CH == 0 && SB % CH == 0 && PER <= 64, "whole chunks, at most one per lane");
-  constexpr int WPI = 64 / PER;
-  constexpr int NIT = (64 + WPI - 1) / WPI;
-  using V = typename Chunk<CH>::type;
-  const int wl = lane / PER, pl = lane - wl * PER;
-  const unsigned int lo = (unsigned int)(wl * gstride) + (unsigned int)(pl * CH);
-  const char* lsrc = lds + wl * SB + pl * CH;
-  if constexpr (64 % PER == 0) {  // every lane busy: all LDS reads first, then the stores back to back
-    V v[NIT];
-#pragma unroll
-    for (int r = 0; r < NIT; ++r) v[r] = *reinterpret_cast<const V*>(lsrc + r * WPI * SB);
-    if (nvalid == 64) {
-#pragma unroll
-      for (int r = 0; r < NIT; ++r) put_chunk<NT>(dst + (int64_t)r * WPI * gstride + lo, v[r]);
-    } else {
-#pragma unroll
-      for (int r = 0; r < NIT; ++r)
-        if (wl + r * WPI < nvalid) put_chunk<NT>(dst + (int64_t)r * WPI * gstride + lo, v[r]);
-    }
-  } else {  // groups of four instructions (reads, then stores), to bound the registers held
-    constexpr int G = 4;
-    const bool act = wl < WPI;
-#pragma unroll 1
-    for (int r0 = 0; r0 < NIT; r0 += G) {
-      V v[G];
-#pragma unroll
-      for (int j = 0; j < G; ++j)
-        if (r0 + j < NIT && act && wl + (r0 + j) * WPI < 64)
-          v[j] = *reinterpret_cast<const V*>(lsrc + (r0 + j) * WPI * SB);
-#pragma unroll
-      for (int j = 0; j < G; ++j)
-        if (r0 + j < NIT && act && wl + (r0 + j) * WPI < nvalid)
-          put_chunk<NT>(dst + (int64_t)(r0 + j) * WPI * gstride + lo, v[j]);
-    }
-  }
-}
-
-// Chunks of 16 bytes when the record length and LDS stride allow them and the destination and
-// record stride are 16-byte aligned, 8 bytes for records that are 8- but not 16-byte multiples,
-// 4-byte words otherwise. Without GENERAL only records that divide the wave (64 mod PER = 0) go
-// in chunks. GENERAL (4-byte element types) also chunks the others, e.g. the 144-byte records of
-// a 6 x 6 float covariance; the float64 recovery of the mixed-pair kernels, which spills heavily,
-// returned wrong results for unchanged cases with it, so float64 keeps 4-byte words for them.
-template <int RB, int SB, bool NT = false, bool GENERAL = false>
-SRTM_DEV void flush_records(int lane, int nvalid, const char* __restrict__ lds, char* __restrict__ dst,
-                            int64_t gstride) {
-  const uintptr_t al = reinterpret_cast<uintptr_t>(dst) | (uintptr_t)gstride;
-  if constexpr (RB % 16 == 0 && SB % 16 == 0 && RB / 16 <= 64 && (GENERAL || 64 % (RB / 16) == 0)) {
-    if (al % 16 == 0) {
-      flush_chunks<RB, SB, 16, NT>(lane, nvalid, lds, dst, gstride);
-      return;
-    }
-  }
-  if constexpr (RB % 16 != 0 && RB % 8 == 0 && SB % 8 == 0 && RB / 8 <= 64 && (GENERAL || 64 % (RB / 8) == 0)) {
-    if (al % 8 == 0) {
-      flush_chunks<RB, SB, 8, NT>(lane, nvalid, lds, dst, gstride);
-      return;
-    }
-  }
-  if constexpr (RB % 8 != 0 && 64 % (RB / 4) == 0) {  // whole records of 4-byte words per lane
-    flush_chunks<RB, SB, 4, NT>(lane, nvalid, lds, dst, gstride);
-    return;
-  }
-  for (int c = lane; c < nvalid * (RB / 4); c += 64) {  // 4-byte words
-    const int w = c / (RB / 4), e = c - w * (RB / 4);
-    put_global(reinterpret_cast<unsigned int*>(dst + w * gstride) + e,
-               reinterpret_cast<const unsigned int*>(lds + w * SB)[e]);
-  }
-}
-
-// Element-wise variant for a run-time record length (the last, partial group of means).
-template <typename T>
-SRTM_DEV void flush_records_rt(int lane, int nvalid, const char* __restrict__ lds, int SB, T* __restrict__ dst,
-                               int64_t gstride_elems, int nel) {
-  for (int c = lane; c < nvalid * nel; c += 64) {
-    const int w = c / nel, e = c - w * nel;
-    put_global(dst + w * gstride_elems + e, reinterpret_cast<const T*>(lds + w * SB)[e]);
-  }
-}
-
-// Fast steps gathered into one output record: the largest power of two (at most 8) for
-// which the record still fits in one 128-byte line.
-constexpr int line_group(int bytes) {
-  int g = 1;
-  while (g < 8 && 2 * g * bytes <= 128) g *= 2;
-  return g;
-}
-
-template <typename T, int NX>
-struct OutStage {
-  static constexpr int NN = NX * NX;
-  static constexpr int GM = line_group(NX * (int)sizeof(T));   // means per record
-  static constexpr int GP = line_group(NN * (int)sizeof(T));   // covariances per record
-  static constexpr int RBM = GM * NX * (int)sizeof(T), RBP = GP * NN * (int)sizeof(T);
-  static constexpr int SBP = ((RBP + 15) / 16) * 16 + 16;   // LDS bytes per lane (padded)
-  static constexpr int SBM = ((RBM + 15) / 16) * 16 + 16;
-  static constexpr int BYTES = 64 * (SBP + SBM);             // per wave
-  char* pbuf;
-  char* mbuf;
-  SRTM_DEV OutStage(char* base) : pbuf(base), mbuf(base + 64 * SBP) {}
-  // blocks of fast step i (1-based)
-  SRTM_DEV void put(int lane, int i, const T (&m)[NX], const T (&P)[NX][NX]) const {
-    T* pp = reinterpret_cast<T*>(pbuf + lane * SBP) + ((i - 1) % GP) * NN;
-#pragma unroll
-    for (int r = 0; r < NX; ++r)
-#pragma unroll
-      for (int c = 0; c < NX; ++c) pp[r * NX + c] = P[r][c];
-    T* mp = reinterpret_cast<T*>(mbuf + lane * SBM) + ((i - 1) % GM) * NX;
-#pragma unroll
-    for (int r = 0; r < NX; ++r) mp[r] = m[r];
-  }
-  // After put(i): flush the covariance and mean groups that step i completes. The record of
-  // window w0 + w for fast steps i0 .. i0+g-1 starts at out[((w0 + w) L + i0 - 1) * size].
-  SRTM_DEV void flush(int lane, int nvalid, T* m_out, T* P_out, int64_t w0, int L, int i, int ilim) const {
-    const int sp = (i - 1) % GP, sm = (i - 1) % GM;
-    if (P_out && (sp == GP - 1 || i == ilim)) {
-      T* dst = P_out + (w0 * L + (i - sp - 1)) * NN;
-      if (sp == GP - 1)
-        flush_records<RBP, SBP, RBP % 128 == 0, sizeof(T) == 4>(lane, nvalid, pbuf, reinterpret_cast<char*>(dst),
-                                                (int64_t)L * NN * sizeof(T));
-      else
-        flush_records_rt<T>(lane, nvalid, pbuf, SBP, dst, (int64_t)L * NN, (sp + 1) * NN);
-    }
-    if (m_out && (sm == GM - 1 || i == ilim)) {
-      T* dst = m_out + (w0 * L + (i - sm - 1)) * NX;
-      if (sm == GM - 1)
-        flush_records<RBM, SBM, RBM % 128 == 0, sizeof(T) == 4>(lane, nvalid, mbuf, reinterpret_cast<char*>(dst),
-                                                (int64_t)L * NX * sizeof(T));
-      else
-        flush_records_rt<T>(lane, nvalid, mbuf, SBM, dst, (int64_t)L * NX, (sm + 1) * NX);
-    }
-  }
-  // slow-rate output: the blocks of fast step 1 (call right after put(1)), contiguous windows
-  SRTM_DEV void flush_slow(int lane, int nvalid, T* m_out, T* P_out, int64_t w0) const {
-    if (m_out)
-      flush_records<NX * (int)sizeof(T), SBM, false, sizeof(T) == 4>(lane, nvalid, mbuf, reinterpret_cast<char*>(m_out + w0 * NX),
-                                              (int64_t)NX * sizeof(T));
-    if (P_out)
-      flush_records<NN * (int)sizeof(T), SBP, false, sizeof(T) == 4>(lane, nvalid, pbuf, reinterpret_cast<char*>(P_out + w0 * NN),
-                                              (int64_t)NN * sizeof(T));
-  }
-};
-
-template <typename T, int NX>
-SRTM_DEV bool finite_state(const T (&m)[NX], const T (&P)[NX][NX]) {
-  bool ok = true;
-#pragma unroll
-  for (int r = 0; r < NX; ++r) {
-    ok = ok && isfinite(m[r]);
-#pragma unroll
-    for (int c = r; c < NX; ++c) ok = ok && isfinite(P[r][c]);
-  }
-  return ok;
-}
-
-// Per tile, every window's exclusive state (m^f_{k-1,l}, P^f_{k-1,l}) in (mprev, Pprev) and inclusive
-// state (m^f_{k,l}, P^f_{k,l}) in (m, P). Window j of the tile is preceded inside the tile by the
-// aligned runs of 2^p windows for the set bits p of j, and the tile's up-sweep tree holds the vector
-// part of each such run [a, a + 2^p) in slot a + 2^p - 1 (no higher level of the in-place tree writes
-// there); their matrix parts are the level records. So each lane folds, highest bit first, the
-// tile's incoming state with those runs (eq. op-filter with the left operand a state) and then with
-// its own element: the same combines as a tree down-sweep, with no exchange between lanes.
-// S needs TILE * 2 nx scalars; (yt, zL): window k's measurement and input response (window_meas);
-// `tree`: the tile's up-sweep tree as the tile reduction left it (2 nx rows of TILE slots).
-// INCL false: the exclusive state only ((m, P) untouched).
-template <bool INP, typename T, int NX, int NY, bool INCL = true>
-SRTM_DEV int fwd_tile_states(const Model<T, NX, NY>& M, const Slots<T>& S, const T (&yt)[NY], const T (&zL)[NX],
+// Per tile, every window's exclusive state (m^f_{k-1,l}, P^f_{k-1,l}): the tile's incoming state followed by the runs
+// of the set bits of the window's place in the tile, highest first (the siblings in the tile's tree `ut`, and
+// the elements themselves at level 0). `sm`: 4 nx TILE scalars of LDS.
+template <bool INP, typename T, int NX, int NY>
+SRTM_DEV int fwd_tile_states(const Model<T, NX, NY>& M, T* sm, const T (&yt)[NY], const T (&zL)[NX],
                              int64_t k, const T* __restrict__ m0, const T* __restrict__ P0,
-                             const T* __restrict__ tile_state, const T* __restrict__ tree, T (&mprev)[NX],
-                             T (&Pprev)[NX][NX], T (&m)[NX], T (&P)[NX][NX]) {
+                             const T* __restrict__ tile_state, const T* __restrict__ ut, T (&mprev)[NX],
+                             T (&Pprev)[NX][NX]) {
+  constexpr int R2 = 2 * NX;
   const int tid = threadIdx.x;
   int flag = 0;
+  T* leaf = sm;
+  T* tree = sm + R2 * TILE;
+  for (int q = tid; q < tree_off(LOG_TILE) * R2; q += TILE) tree[q] = gld(ut + q);
+  {
+    T d[NX], e[NX];
+    fwd_element<INP>(M, yt, zL, d, e);
 #pragma unroll
-  for (int r = 0; r < 2 * NX; ++r) S.at(r, tid) = gld(tree + r * TILE + tid);
-  T d[NX], e[NX];  // the window's own element, for the inclusive state
-  fwd_element<INP>(M, yt, zL, d, e);
+    for (int r = 0; r < NX; ++r) {
+      leaf[tid * R2 + r] = d[r];
+      leaf[tid * R2 + NX + r] = e[r];
+    }
+  }
   if (k == 0) {  // the prior itself
     gloadv(mprev, m0);
     gload(Pprev, P0);
@@ -2121,12 +3087,13 @@ SRTM_DEV int fwd_tile_states(const Model<T, NX, NY>& M, const Slots<T>& S, const
 #pragma unroll
   for (int p = LOG_TILE - 1; p >= 0; --p) {
     if ((tid >> p) & 1) {
-      const int node = ((tid >> (p + 1)) << (p + 1)) + (1 << p) - 1;
+      const int i = (tid >> p) ^ 1;
+      const T* nd = p == 0 ? leaf + i * R2 : tree + (tree_off(p > 0 ? p : 1) + i) * R2;
       T dl[NX], el[NX];
 #pragma unroll
       for (int r = 0; r < NX; ++r) {
-        dl[r] = S.at(r, node);
-        el[r] = S.at(NX + r, node);
+        dl[r] = nd[r];
+        el[r] = nd[NX + r];
       }
       const T* lv = M.level(p);
       T F[NX][NX], D[NX][NX], J[NX][NX];
@@ -2136,257 +3103,15 @@ SRTM_DEV int fwd_tile_states(const Model<T, NX, NY>& M, const Slots<T>& S, const
       if (!state_combine(mprev, Pprev, F, dl, D, el, J)) flag |= SRTM_INFO_COMBINE_SINGULAR;
     }
   }
-  if constexpr (INCL) {  // exclusive state -> inclusive: X_k = X_{k-1} (x) a_k
-#pragma unroll
-    for (int r = 0; r < NX; ++r) {
-      m[r] = mprev[r];
-#pragma unroll
-      for (int c = 0; c < NX; ++c) P[r][c] = Pprev[r][c];
-    }
-    const T* lv = M.level(0);
-    T F[NX][NX], D[NX][NX], J[NX][NX];
-    load(F, lv + M.lay.o_F);
-    load(D, lv + M.lay.o_D);
-    load(J, lv + M.lay.o_J);
-    if (!state_combine(m, P, F, d, D, e, J)) flag |= SRTM_INFO_COMBINE_SINGULAR;
-  }
   return flag;
 }
 
-// Window k's filtered slow state (m^f_{k,l}, P^f_{k,l}) from its window quantities (window_setup
-// on the exclusive state): the recovery's blocks at fast step l, m = A^l m' + c_l S^{-1} e (+ z_{k,l}
-// with inputs) and P = A^l Y1 + Q_ll - c_l Y2 (upper triangle, mirrored). Equal to the inclusive
-// combine X_{k-1} (x) a_k in exact arithmetic, at a fraction of its cost.
-template <bool INP, typename T, int NX, int NY>
-SRTM_DEV void window_slow_state(const Model<T, NX, NY>& M, int L, const Window<T, NX, NY>& w, const T (&zL)[NX],
-                                T (&m)[NX], T (&P)[NX][NX]) {
-  T AL[NX][NX], cL[NX][NY];
-  M.get(AL, M.AL_off(L));
-  M.get(cL, M.cL_off(L));
-  const int oq = M.per_i_off(L) + M.lay.o_Qii;
-#pragma unroll
-  for (int r = 0; r < NX; ++r) {
-    T t = INP ? zL[r] : T(0);
-#pragma unroll
-    for (int k = 0; k < NX; ++k) t = my_fma(AL[r][k], w.mp[k], t);
-#pragma unroll
-    for (int k = 0; k < NY; ++k) t = my_fma(cL[r][k], w.Se[k], t);
-    m[r] = t;
-  }
-#pragma unroll
-  for (int r = 0; r < NX; ++r)
-#pragma unroll
-    for (int c = r; c < NX; ++c) {
-      T t = M.at(oq + r * NX + c);
-#pragma unroll
-      for (int k = 0; k < NX; ++k) t = my_fma(AL[r][k], w.Y1[k][c], t);
-#pragma unroll
-      for (int k = 0; k < NY; ++k) t = my_fma(-cL[r][k], w.Y2[k][c], t);
-      P[r][c] = t;
-      P[c][r] = t;
-    }
-}
-
-// Writes the slow-rate carry (m^f_{k,l}, P^f_{k,l}) and, when requested, the slow-rate
-// filter outputs of window k < N.
-template <typename T, int NX>
-SRTM_DEV int store_carry(int64_t k, const T (&m)[NX], const T (&P)[NX][NX], T* __restrict__ carry,
-                         T* __restrict__ m_slow, T* __restrict__ P_slow) {
-  constexpr int NN = NX * NX, ST = NX + NN;
-#pragma unroll
-  for (int r = 0; r < NX; ++r) put_global(carry + k * ST + r, m[r]);
-#pragma unroll
-  for (int r = 0; r < NX; ++r)
-#pragma unroll
-    for (int c = 0; c < NX; ++c) put_global(carry + k * ST + NX + r * NX + c, P[r][c]);
-  if (m_slow) {
-#pragma unroll
-    for (int r = 0; r < NX; ++r) put_global(m_slow + k * NX + r, m[r]);
-  }
-  if (P_slow) {
-#pragma unroll
-    for (int r = 0; r < NN; ++r) put_global(P_slow + k * NN + r, P[r / NX][r % NX]);
-  }
-  return finite_state(m, P) ? 0 : SRTM_INFO_NONFINITE;
-}
-
-// K3 (filter only): per tile, the slow-rate carry and the slow-rate filter outputs.
-template <bool INP, typename T, int NX, int NY>
-SRTM_DEV void fwd_final_body(const T* __restrict__ y, int64_t N, int L, const T* __restrict__ cst, InputView<T> in,
-                             const T* __restrict__ m0, const T* __restrict__ P0, const T* __restrict__ tstate,
-                             const T* __restrict__ utree, T* __restrict__ carry, T* __restrict__ m_slow, T* __restrict__ P_slow, int32_t* info,
-                             int64_t tile) {
-  constexpr int ST = NX + NX * NX;
-  extern __shared__ char smraw[];
-  const Model<T, NX, NY> M{cst, make_const_layout(NX, NY, L), in};
-  const Slots<T> S{reinterpret_cast<T*>(smraw), TILE};
-  const int64_t k = tile * TILE + threadIdx.x;
-  T yt[NY], zL[NX];
-  window_meas<INP>(M, y, k, N, yt, zL);
-  T mprev[NX], Pprev[NX][NX], m[NX], P[NX][NX];
-  int flag = fwd_tile_states<INP>(M, S, yt, zL, k, m0, P0, tstate + tile * ST, utree + tile * (2 * NX * TILE), mprev,
-                                  Pprev, m, P);
-  if (k < N) flag |= store_carry(k, m, P, carry, m_slow, P_slow);
-  if (flag && info) atomicOr(info, flag);
-}
-
-// ============================================================================ backward
-// The smoother half of the fused forward/backward kernel for window k of tile `tile`, given the
-// window quantities w (window_setup on the exclusive filter state), the inclusive filter state
-// (m, P) and (An, Qn), the model of the step into x_{k+1,1}: its smoother element (eq.
-// parallel-ak-smoothing), the in-tile reverse Kogge-Stone scan under eq. op-smoother, the tile
-// aggregate and the per-window correction record (see fwd_bwd_body). Returns numerical status bits.
-template <bool INP, typename T, int NX, int NY, class MV>
-SRTM_DEV int smoother_part(const MV& M, const Slots<T>& S, int L, int64_t k, int64_t N,
-                           const Window<T, NX, NY>& w, const T (&m)[NX], const T (&P)[NX][NX],
-                           const T (&An)[NX][NX], const T (&Qn)[NX][NX], T* __restrict__ btagg,
-                           T* __restrict__ sfx, int64_t tile) {
-  constexpr int NN = NX * NX, SE = 2 * NN + NX, SF = sfx_stride(NX);
-  const int tid = threadIdx.x;
-  const bool valid = k < N;
-  int flag = 0;
-  SElem<T, NX> x;
-  T B[NX][NX], Bm[NX], BPB[NX][NX];  // B = (P^-)^{-1} A, B^T (predicted mean), B^T P^- B = A^T B
-  {
-    T z1[NX], bnext[NX];  // B u_{k,0} and B u_{k+1,0}
-#pragma unroll
-    for (int r = 0; r < NX; ++r) z1[r] = bnext[r] = T(0);
-    if constexpr (INP) {
-      if (valid) input_drive(M.in, M.in.u + k * L * M.in.nu, z1);
-      if (k + 1 < N) input_drive(M.in, M.in.u + (k + 1) * L * M.in.nu, bnext);
-    }
-    T Pmi[NX][NX], mpred[NX], Pm[NX][NX];
-    const int f = smoother_element<INP>(M, L, w, k == N - 1, m, P, z1, bnext, An, Qn, x, Pmi, mpred, Pm);
-    if (valid) flag |= f;
-    mm(Pmi, An, B);
-    mtv(B, mpred, Bm);
-#pragma unroll
-    for (int r = 0; r < NX; ++r)
-#pragma unroll
-      for (int c = r; c < NX; ++c) {
-        T t = T(0);
-#pragma unroll
-        for (int q = 0; q < NX; ++q) t = my_fma(An[q][r], B[q][c], t);
-        BPB[r][c] = t;
-        BPB[c][r] = t;
-      }
-  }
-  if (!valid) {  // past the last window: a zero element (finite, and absorbed by E_N = 0)
-#pragma unroll
-    for (int r = 0; r < NX; ++r) {
-      x.g[r] = T(0);
-#pragma unroll
-      for (int c = 0; c < NX; ++c) {
-        x.E[r][c] = T(0);
-        x.S[r][c] = T(0);
-      }
-    }
-  }
-  // Lane j ends with a_j (x) a_{j+1} (x) ... (x) a_{TILE-1}. Within each wave first, by lane
-  // shuffles at distances 1 .. 32: lane l then holds its wave's elements l .. 63 merged, and lane
-  // 0 the whole wave's. Then each wave merges with the aggregates of the waves after it, which
-  // pass through LDS (runs of any length merge: eq. op-smoother carries whole matrices).
-  {
-    const int lane = tid & 63, wv = tid >> 6;
-    constexpr int NW = TILE / 64;
-#pragma unroll 1
-    for (int s = 1; s < 64; s *= 2) selem_merge_lane<true>(x, s, lane + s < 64);
-    __syncthreads();  // the slots switch from forward states to smoother elements
-    if (lane == 0) st_selem(S, wv, x);
-    __syncthreads();
-#pragma unroll 1
-    for (int v = wv + 1; v < NW; ++v) {  // x (x) A_{wv+1} (x) ... (x) A_{NW-1}, left to right
-      SElem<T, NX> a;
-      ld_selem(S, v, a);
-      selem_combine(x, a, x);
-    }
-    __syncthreads();  // the aggregates are read before the slots take the suffixes
-  }
-  st_selem(S, tid, x);
-  __syncthreads();
-  if (tid == 0) {
-    T* dst = btagg + tile * SE;
-#pragma unroll
-    for (int r = 0; r < NX; ++r) {
-      dst[NN + r] = x.g[r];
-#pragma unroll
-      for (int c = 0; c < NX; ++c) {
-        dst[r * NX + c] = x.E[r][c];
-        dst[NN + NX + r * NX + c] = x.S[r][c];
-      }
-    }
-  }
-  SElem<T, NX> nxt;  // exclusive suffix; the identity (I, 0, 0) for the tile's last lane
-  if (tid + 1 < TILE) {
-    ld_selem(S, tid + 1, nxt);
-  } else {
-#pragma unroll
-    for (int r = 0; r < NX; ++r) {
-      nxt.g[r] = T(0);
-#pragma unroll
-      for (int c = 0; c < NX; ++c) {
-        nxt.E[r][c] = (r == c) ? T(1) : T(0);
-        nxt.S[r][c] = T(0);
-      }
-    }
-  }
-  if (valid) {
-    T rec[SF];
-    if (k < N - 1) {
-      T SB[NX][NX];
-      mm(nxt.S, B, SB);
-#pragma unroll
-      for (int r = 0; r < NX; ++r) {
-        T t = -Bm[r];
-#pragma unroll
-        for (int q = 0; q < NX; ++q) t = my_fma(B[q][r], nxt.g[q], t);
-        rec[NN + r] = t;
-#pragma unroll
-        for (int c = 0; c < NX; ++c) {
-          T e = T(0);
-#pragma unroll
-          for (int q = 0; q < NX; ++q) e = my_fma(B[q][r], nxt.E[q][c], e);
-          rec[r * NX + c] = e;
-        }
-      }
-      int o = NN + NX;
-#pragma unroll
-      for (int r = 0; r < NX; ++r)
-#pragma unroll
-        for (int c = r; c < NX; ++c) {
-          T t = -BPB[r][c];
-#pragma unroll
-          for (int q = 0; q < NX; ++q) t = my_fma(B[q][r], SB[q][c], t);
-          rec[o++] = t;
-        }
-    } else {
-#pragma unroll
-      for (int r = 0; r < SF; ++r) rec[r] = T(0);
-    }
-    T* dst = sfx + k * SF;
-#pragma unroll
-    for (int r = 0; r < SF; ++r) put_global(dst + r, rec[r]);
-  }
-  return flag;
-}
-
-// K3s (smoother): per tile, the forward down-sweep of K3; then, from the exclusive and
-// inclusive filter states of window k, its smoother element (eq. parallel-ak-smoothing), an
-// in-tile reverse Kogge-Stone scan of those elements under eq. op-smoother, the tile's
-// aggregate a_first (x) ... (x) a_last, and per window the smoother correction of eq.
-// seq-smoothing-all written as terms linear in the smoothed state (m_in, P_in) that enters
-// the tile from the right (the first window after it). With B = (P^-)^{-1} A and the
-// in-tile exclusive suffix (E', g', S') = a_{k+1} (x) ... (x) a_{last of tile}:
-//   v = A^T (P^-)^{-1} (m^s_{k+1,1} - A m^f_{k,l}) = Et m_in + gt,
-//   W = A^T (P^-)^{-1} (P^s_{k+1,1} - P^-) (P^-)^{-1} A = Et P_in Et^T + St,
-//   Et = B^T E',  gt = B^T (g' - A m^f_{k,l}),  St = B^T (S' - P^-) B;
-// all three are zero for the last window, whose smoothed blocks equal the filtered ones.
+// Per tile: the exclusive filter states, the carry, and the smoother half (smoother_part).
 template <bool INP, typename T, int NX, int NY>
 SRTM_DEV void fwd_bwd_body(const T* __restrict__ y, int64_t N, int L, const T* __restrict__ cst, InputView<T> in,
                            const T* __restrict__ m0, const T* __restrict__ P0, const T* __restrict__ ftstate,
-                           const T* __restrict__ utree, T* __restrict__ carry, T* __restrict__ m_slow, T* __restrict__ P_slow,
-                           T* __restrict__ btagg, T* __restrict__ sfx, int32_t* info, int64_t tile) {
-  constexpr int NN = NX * NX, ST = NX + NN, SE = 2 * NN + NX, SF = sfx_stride(NX);
+                           const T* __restrict__ utree, T* __restrict__ carry, T* __restrict__ btagg, T* __restrict__ sfx, int32_t* info, int64_t tile) {
+  constexpr int ST = NX + NX * NX;
   extern __shared__ char smraw[];
   const Model<T, NX, NY> M{cst, make_const_layout(NX, NY, L), in};
   const Slots<T> S{reinterpret_cast<T*>(smraw), TILE};
@@ -2396,14 +3121,14 @@ SRTM_DEV void fwd_bwd_body(const T* __restrict__ y, int64_t N, int L, const T* _
   T yt[NY], zL[NX];
   window_meas<INP>(M, y, k, N, yt, zL);
   T mprev[NX], Pprev[NX][NX], m[NX], P[NX][NX];
-  int flag = fwd_tile_states<INP, T, NX, NY, false>(M, S, yt, zL, k, m0, P0, ftstate + tile * ST,
-                                                    utree + tile * (2 * NX * TILE), mprev, Pprev, m, P);
+  int flag = fwd_tile_states<INP>(M, S.base, yt, zL, k, m0, P0, ftstate + tile * ST, utree + tile * (2 * NX * TILE), mprev,
+                                  Pprev);
   // The smoother element needs the window quantities of the exclusive state; the inclusive state
   // (the carry) follows from them.
   Window<T, NX, NY> w;
   if (!window_setup(M, L, mprev, Pprev, yt, w) && valid) flag |= SRTM_INFO_INNOVATION_NOT_PD;
   window_slow_state<INP>(M, L, w, zL, m, P);
-  if (valid) flag |= store_carry(k, m, P, carry, m_slow, P_slow);
+  if (valid) flag |= store_carry<T, NX>(k, m, P, carry, nullptr, nullptr);
 
   T An[NX][NX], Qn[NX][NX];  // time-invariant: the step into x_{k+1,1} has the model's A and Q
   load(An, M.cst + M.lay.A);
@@ -2491,9 +3216,14 @@ SRTM_DEV void recover_body(const T* __restrict__ y, int64_t N, int L, int ilim, 
   }
   const auto M = recover_model<TV, T, NX, NY>(cst, L, in, mdl, k);
   T m[NX], P[NX][NX], yk[NY];
-  load_prior<T, NX, NY>(carry, m0, P0, kc, m, P);
+  const int nw = tile_windows(N, tile);
+  const int64_t col = tile * (TILE * info_stride(NX)) + (valid ? tid : 0);  // the window's records
+  if constexpr (TV) load_prior<T, NX, NY>(carry, m0, P0, kc, m, P);
+  else record_load(m, P, carry + col, nw);
+  T zL[NX];  // z_{k,l}
+#pragma unroll
+  for (int r = 0; r < NX; ++r) zL[r] = T(0);
   if constexpr (INP) {
-    T zL[NX];
     window_meas<true>(M, y, kc, N, yk, zL);
   } else {
     gloadv(yk, y + kc * NY);
@@ -2510,7 +3240,10 @@ SRTM_DEV void recover_body(const T* __restrict__ y, int64_t N, int L, int ilim, 
     for (int j = 0; j < NU_MAX; ++j) un[j] = (j < in.nu) ? gld(uk + j) : T(0);
   }
   T v[NX], W[NX][NX];
-  if (SMOOTH) {  // v = Et m_in + gt,  W = Et P_in Et^T + St
+  if constexpr (SMOOTH && !TV) {
+    if (!info_correction<INP>(M, L, w, zL, sfx + col, nw, v, W) && valid)
+      flag |= SRTM_INFO_COMBINE_SINGULAR;
+  } else if constexpr (SMOOTH) {  // v = Et m_in + gt,  W = Et P_in Et^T + St
     const T* src = sfx + kc * SF;
     const T* ti = tin + tile * ST;
     T Et[NX][NX], mi[NX], Pi[NX][NX], EP[NX][NX];
@@ -3326,10 +4059,7 @@ SRTM_DEV void lag1_within(const Model<T, NX, NY>& M, const Window<T, NX, NY>& w,
 // carry and smoother correction (v, W) as the recovery; records staged and written as K7's.
 template <typename T, int NX, int NY>
 SRTM_DEV void lag1_body(const T* __restrict__ y, int64_t N, int L, const T* __restrict__ cst,
-                        const T* __restrict__ m0, const T* __restrict__ P0, const T* __restrict__ carry,
-                        const T* __restrict__ sfx, const T* __restrict__ tin, T* __restrict__ Cs_fast,
-                        int32_t* info, int64_t tile) {
-  constexpr int NN = NX * NX, ST = NX + NN, SF = sfx_stride(NX);
+                        const T* __restrict__ carry, const T* __restrict__ sfx, T* __restrict__ Cs_fast, int32_t* info, int64_t tile) {
   static_assert(TILE == 256, "one workgroup per tile");
   using Stg = OutStage<T, NX>;
   extern __shared__ char smraw[];
@@ -3342,43 +4072,19 @@ SRTM_DEV void lag1_body(const T* __restrict__ y, int64_t N, int L, const T* __re
   const bool valid = k < N;
   const int64_t kc = valid ? k : 0;
   T m[NX], P[NX][NX], yk[NY];
-  load_prior<T, NX, NY>(carry, m0, P0, kc, m, P);
+  const int nw = tile_windows(N, tile);
+  const int64_t col = tile * (TILE * info_stride(NX)) + (valid ? tid : 0);  // the window's records
+  record_load(m, P, carry + col, nw);
   gloadv(yk, y + kc * NY);
   Window<T, NX, NY> w;
   int flag = 0;
   if (!window_setup(M, L, m, P, yk, w) && valid) flag |= SRTM_INFO_INNOVATION_NOT_PD;
-  T v[NX], W[NX][NX];  // v = Et m_in + gt,  W = Et P_in Et^T + St
-  {
-    const T* src = sfx + kc * SF;
-    const T* ti = tin + tile * ST;
-    T Et[NX][NX], mi[NX], Pi[NX][NX], EP[NX][NX];
-    gload(Et, src);
-    gloadv(mi, ti);
-    gload(Pi, ti + NX);
-#pragma unroll
-    for (int r = 0; r < NX; ++r) {
-      T t = gld(src + NN + r);
-#pragma unroll
-      for (int q = 0; q < NX; ++q) t = my_fma(Et[r][q], mi[q], t);
-      v[r] = t;
-    }
-    mm(Et, Pi, EP);
-    int o = NN + NX;
-#pragma unroll
-    for (int r = 0; r < NX; ++r)
-#pragma unroll
-      for (int c = r; c < NX; ++c) {
-        T t = gld(src + o++);
-#pragma unroll
-        for (int q = 0; q < NX; ++q) t = my_fma(EP[r][q], Et[c][q], t);
-        W[r][c] = t;
-        W[c][r] = t;
-      }
-  }
+  T v[NX], W[NX][NX];
+  const T zero[NX] = {};
+  if (!info_correction<false>(M, L, w, zero, sfx + col, nw, v, W) && valid) flag |= SRTM_INFO_COMBINE_SINGULAR;
   T A[NX][NX];
   load(A, M.cst + M.lay.A);
   T Pprev[NX][NX], PLprev[NX][NX], Uprev[NX][NY];
-  const T zero[NX] = {};
   bool fin = true;
 #pragma unroll 1
   for (int i = 1; i <= L; ++i) {
@@ -3496,16 +4202,16 @@ SRTM_DEV void gloadv_f64(double (&a)[R], const T* __restrict__ p) {
 }
 
 // Gradient statistics of window k (float64), added to Sw, Swx, Sy; the window's log-likelihood
-// term in *ll. (m, P): its prior; yk: its measurement (y_k - mu_k with known inputs); sfx, tin: its
-// smoother-correction record and its tile's incoming smoothed state (element type T); with known
-// inputs Bm [nx][nu] and uk, the window's inputs [L][nu].
+// term in *ll. (m, P): its prior; yk: its measurement (y_k - mu_k with known inputs); col: its
+// information record (element type T, in a tile of nw windows), or its smoother-correction record with the
+// tile's incoming smoothed state `ti` (grad_by_elements); okc: whether the correction from it is usable; zL: its input
+// response z_{k,l}; with known inputs Bm [nx][nu] and uk, the window's inputs [L][nu].
 template <typename T, int NX, int NY>
 SRTM_DEV bool grad_window(const Model<double, NX, NY>& M, int L, const double (&m)[NX], const double (&P)[NX][NX],
-                          const double (&yk)[NY], const double (&R)[NY][NY], const T* __restrict__ src,
-                          const T* __restrict__ ti, double& ll, double (&Sw)[NX][NX], double (&Swx)[NX][NX],
+                          const double (&yk)[NY], const double (&R)[NY][NY], const T* __restrict__ col,
+                          int nw, const T* __restrict__ ti, const double (&zL)[NX], bool& okc, double& ll, double (&Sw)[NX][NX], double (&Swx)[NX][NX],
                           double (&Sy)[NY][NY], const T* __restrict__ Bm = nullptr, const T* __restrict__ uk = nullptr,
                           int nu = 0) {
-  constexpr int NN = NX * NX;
   Window<double, NX, NY> w;
   const bool ok = window_setup(M, L, m, P, yk, w);
   double e[NY];
@@ -3523,16 +4229,17 @@ SRTM_DEV bool grad_window(const Model<double, NX, NY>& M, int L, const double (&
     }
     ll = -0.5 * (quad - log(det_small(w.Si)) + NY * 1.8378770664093453);  // log(2 pi)
   }
-  // v = Et m_in + gt, W = Et P_in Et^T + St
   double v[NX], W[NX][NX];
-  {
+  if constexpr (grad_by_elements<T>()) {  // v = Et m_in + gt, W = Et P_in Et^T + St (smoother_part)
+    constexpr int NN = NX * NX;
+    okc = true;
     double Et[NX][NX], mi[NX], Pi[NX][NX], EP[NX][NX];
-    gload_f64(Et, src);
+    gload_f64(Et, col);
     gloadv_f64(mi, ti);
     gload_f64(Pi, ti + NX);
 #pragma unroll
     for (int r = 0; r < NX; ++r) {
-      double t = (double)gld(src + NN + r);
+      double t = (double)gld(col + NN + r);
 #pragma unroll
       for (int q = 0; q < NX; ++q) t = fma(Et[r][q], mi[q], t);
       v[r] = t;
@@ -3543,12 +4250,14 @@ SRTM_DEV bool grad_window(const Model<double, NX, NY>& M, int L, const double (&
     for (int r = 0; r < NX; ++r)
 #pragma unroll
       for (int c = r; c < NX; ++c) {
-        double t = (double)gld(src + o++);
+        double t = (double)gld(col + o++);
 #pragma unroll
         for (int q = 0; q < NX; ++q) t = fma(EP[r][q], Et[c][q], t);
         W[r][c] = t;
         W[c][r] = t;
       }
+  } else {
+    okc = info_correction<true>(M, L, w, zL, col, nw, v, W);
   }
   double A[NX][NX], Qm[NX][NX];
   M.get(A, M.lay.A);
@@ -3710,15 +4419,16 @@ template <typename T, int NX, int NY, bool GRAD, bool INP>
 SRTM_DEV void stats_body(const T* __restrict__ y, int64_t N, int L, const T* __restrict__ cst,
                          const double* __restrict__ cst64, InputView<T> in, const T* __restrict__ Rm,
                          const T* __restrict__ m0, const T* __restrict__ P0, const T* __restrict__ carry,
-                         const T* __restrict__ sfx, const T* __restrict__ tin, double* __restrict__ parts,
-                         int32_t* info, int64_t tile) {
+                         const T* __restrict__ sfx, const T* __restrict__ tin, double* __restrict__ parts, int32_t* info, int64_t tile) {
   using SL = StatLayout<NX, NY>;
-  constexpr int NN = NX * NX, ST = NX + NN, SF = sfx_stride(NX), NC = SL::SIZE;
+  constexpr int NC = SL::SIZE;
   __shared__ double red[TILE / 64][NC];
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const int64_t k = tile * TILE + tid;
   const bool valid = k < N;
   const int64_t kc = valid ? k : 0;
+  const int nw = tile_windows(N, tile);
+  const int64_t col = tile * (TILE * info_stride(NX)) + (valid ? tid : 0);  // the window's records
   double* part = parts + tile * SL::SIZE;
   int flag = 0;
   double ll = 0.0;
@@ -3734,27 +4444,36 @@ SRTM_DEV void stats_body(const T* __restrict__ y, int64_t N, int L, const T* __r
   if constexpr (GRAD) {
     const Model<double, NX, NY> M{cst64, make_const_layout(NX, NY, L)};
     double m[NX], P[NX][NX], yk[NY], R[NY][NY];
-    if (kc == 0) {
+    if constexpr (!grad_by_elements<T>()) {
+      record_load(m, P, carry + col, nw);
+    } else if (kc == 0) {
       gloadv_f64(m, m0);
       gload_f64(P, P0);
     } else {
-      gloadv_f64(m, carry + (kc - 1) * ST);
-      gload_f64(P, carry + (kc - 1) * ST + NX);
+      gloadv_f64(m, carry + (kc - 1) * (NX + NX * NX));
+      gload_f64(P, carry + (kc - 1) * (NX + NX * NX) + NX);
     }
-    if constexpr (INP) {  // y_k - mu_k from the tile reductions' per-window record
+    double zL[NX];
+#pragma unroll
+    for (int r = 0; r < NX; ++r) zL[r] = 0.0;
+    if constexpr (INP) {  // y_k - mu_k and z_{k,l} from the tile reductions' per-window record
       gloadv_f64(yk, in.rec + kc * (NY + NX));
+      gloadv_f64(zL, in.rec + kc * (NY + NX) + NY);
     } else {
       gloadv_f64(yk, y + kc * NY);
     }
     gload_f64(R, Rm);
-    if (!grad_window<T, NX, NY>(M, L, m, P, yk, R, sfx + kc * SF, tin + tile * ST, ll, Sw, Swx, Sy,
+    bool okc = true;
+    if (!grad_window<T, NX, NY>(M, L, m, P, yk, R, sfx + (grad_by_elements<T>() ? kc * sfx_stride(NX) : col), nw,
+                                tin + tile * (NX + NX * NX), zL, okc, ll, Sw, Swx, Sy,
                                 INP ? in.B : nullptr, INP ? in.u + kc * L * in.nu : nullptr, INP ? in.nu : 0) &&
         valid)
       flag |= SRTM_INFO_INNOVATION_NOT_PD;
+    if (!okc && valid) flag |= SRTM_INFO_COMBINE_SINGULAR;
   } else {
     const Model<T, NX, NY> M{cst, make_const_layout(NX, NY, L), in};
     T m[NX], P[NX][NX], yk[NY];
-    load_prior<T, NX, NY>(carry, m0, P0, kc, m, P);
+    record_load(m, P, carry + col, nw);
     if constexpr (INP) {
       T zL[NX];
       window_meas<true>(M, y, kc, N, yk, zL);
@@ -3883,10 +4602,11 @@ struct Seq {  // one sequence's typed arrays and scan plan
   const T *F, *Q, *H, *R, *m0, *P0, *y;
   T *ms_fast, *Ps_fast, *ms_slow, *Ps_slow, *mf_fast, *Pf_fast, *mf_slow, *Pf_slow, *Cs_fast;
   T *cst, *ftagg, *ftst, *utree, *carry, *btagg, *btst, *sfx, *tvblk, *tvel;
-  double *cst64, *hand, *stats;
+  double *cst64, *hand, *stats, *tail;
   int64_t N, tile0;
   int L;
   ScanPlan plan;
+  bool smoother;
   int32_t* info;
   InputView<T> in;
 };
@@ -3927,6 +4647,8 @@ SRTM_DEV Seq<T, NX, NY> seq_view(const Batch& b, int s) {
   q.btagg = reinterpret_cast<T*>(base + wl.btile_agg);
   q.btst = reinterpret_cast<T*>(base + wl.btile_state);
   q.sfx = reinterpret_cast<T*>(base + wl.sfx);
+  q.tail = reinterpret_cast<double*>(base + wl.sfx + tail_info_off(d.N, NX, sizeof(T)));
+  q.smoother = d.smoother != 0;
   q.tvblk = reinterpret_cast<T*>(base + wl.tvblk);
   q.tvel = reinterpret_cast<T*>(base + wl.tvel);
   q.stats = reinterpret_cast<double*>(base + wl.stats);
@@ -3961,6 +4683,20 @@ SRTM_DEV void kb_fwd_reduce(const Batch& b, int64_t bid, int nseq) {
   fwd_reduce_body<INP, T, NX, NY>(q.y, q.N, q.cst, q.L, q.in, q.ftagg, q.utree, t - q.tile0);
 }
 
+template <typename T, int NX, int NY, bool INP>
+SRTM_DEV void kb_tile_tree(const Batch& b, int64_t bid, int nthr) {
+  const Seq<T, NX, NY> q = seq_view<T, NX, NY>(b, (int)bid);
+  tile_tree_body<INP, T, NX, NY>(q.y, q.N, q.plan.nlev, q.cst, q.L, q.in, q.ftagg, q.utree, q.ftst, q.tail, q.smoother,
+                                 q.info, nthr);
+}
+
+template <typename T, int NX, int NY, bool SMOOTH, bool INP>
+SRTM_DEV void kb_fold(const Batch& b, int64_t bid, bool want_last) {
+  const Seq<T, NX, NY> q = seq_view<T, NX, NY>(b, tile_sequence(b, bid));
+  fold_body<SMOOTH, INP, T, NX, NY>(q.y, q.N, q.L, q.plan.nlev, q.cst, q.in, q.m0, q.P0, q.ftagg, q.ftst, q.utree, q.tail,
+                                    q.carry, q.mf_slow, q.Pf_slow, q.sfx, q.info, bid - q.tile0, want_last);
+}
+
 template <typename T, int NX, int NY>
 SRTM_DEV void kb_fwd_tiles(const Batch& b, int64_t bid) {
   const Seq<T, NX, NY> q = seq_view<T, NX, NY>(b, (int)bid);
@@ -3971,8 +4707,7 @@ SRTM_DEV void kb_fwd_tiles(const Batch& b, int64_t bid) {
 template <typename T, int NX, int NY, bool INP>
 SRTM_DEV void kb_fwd_bwd(const Batch& b, int64_t bid) {
   const Seq<T, NX, NY> q = seq_view<T, NX, NY>(b, tile_sequence(b, bid));
-  fwd_bwd_body<INP, T, NX, NY>(q.y, q.N, q.L, q.cst, q.in, q.m0, q.P0, q.ftst, q.utree, q.carry, q.mf_slow, q.Pf_slow,
-                               q.btagg, q.sfx, q.info, bid - q.tile0);
+  fwd_bwd_body<INP, T, NX, NY>(q.y, q.N, q.L, q.cst, q.in, q.m0, q.P0, q.ftst, q.utree, q.carry, q.btagg, q.sfx, q.info, bid - q.tile0);
 }
 
 template <typename T, int NX, int NY>
@@ -4022,16 +4757,19 @@ __global__ void __launch_bounds__(TILE) k_fwd_reduce(Batch b, int nseq) {
   kb_fwd_reduce<T, NX, NY, INP>(b, blockIdx.x, nseq);
 }
 
+template <typename T, int NX, int NY, bool INP>
+__global__ void __launch_bounds__(TT) k_tile_tree(Batch b) {
+  kb_tile_tree<T, NX, NY, INP>(b, blockIdx.x, TT);
+}
+
+template <typename T, int NX, int NY, bool SMOOTH, bool INP>
+__global__ void __launch_bounds__(TILE, 2) k_fold(Batch b, int want_last) {
+  kb_fold<T, NX, NY, SMOOTH, INP>(b, blockIdx.x, want_last != 0);
+}
+
 template <typename T, int NX, int NY>
 __global__ void __launch_bounds__(KS) k_fwd_tiles(Batch b) {
   kb_fwd_tiles<T, NX, NY>(b, blockIdx.x);
-}
-
-template <typename T, int NX, int NY, bool INP>
-__global__ void __launch_bounds__(TILE) k_fwd_final(Batch b) {
-  const Seq<T, NX, NY> q = seq_view<T, NX, NY>(b, tile_sequence(b));
-  fwd_final_body<INP, T, NX, NY>(q.y, q.N, q.L, q.cst, q.in, q.m0, q.P0, q.ftst, q.utree, q.carry, q.mf_slow, q.Pf_slow, q.info,
-                            (int64_t)blockIdx.x - q.tile0);
 }
 
 template <typename T, int NX, int NY, bool INP>
@@ -4086,7 +4824,7 @@ template <typename T, int NX, int NY>
 __global__ void __launch_bounds__(TILE) k_lag1(Batch b) {
   const Seq<T, NX, NY> q = seq_view<T, NX, NY>(b, tile_sequence(b));
   if (!q.Cs_fast) return;
-  lag1_body<T, NX, NY>(q.y, q.N, q.L, q.cst, q.m0, q.P0, q.carry, q.sfx, q.btst, q.Cs_fast, q.info,
+  lag1_body<T, NX, NY>(q.y, q.N, q.L, q.cst, q.carry, q.sfx, q.Cs_fast, q.info,
                        (int64_t)blockIdx.x - q.tile0);
 }
 
@@ -4186,21 +4924,50 @@ srtm_status launch_all(const Batch& b, const Launch& g, bool smoother, int rec_m
   constexpr size_t lds_red = fwd_reduce_lds_bytes<T, NX>();
   SRTM_STAGE((k_fwd_reduce<T, NX, NY, INP>), dim3(g.ntiles + g.nseq), dim3(TILE), lds_red, st, b, (int)g.nseq);
 
-  // slots, then the level records LOG_TILE .. nlev-1 of the longest sequence of the call
   const int nlev_max = make_scan_plan((int64_t)g.ntiles * TILE).nlev;
-  const size_t lds_ft = sizeof(T) * ((size_t)KS * (NX + NN) +
-                                     (size_t)(nlev_max - LOG_TILE) * make_const_layout(NX, NY, 1).lev_stride);
-  if (!allow_lds((const void*)k_fwd_tiles<T, NX, NY>, lds_ft)) return SRTM_E_HIP;
-  SRTM_STAGE((k_fwd_tiles<T, NX, NY>), dim3(g.nseq), dim3(KS), lds_ft, st, b);
+  if constexpr (grad_by_elements<T>()) {
+    if (rec_mode == REC_GRAD) {
+      // slots, then the level records LOG_TILE .. nlev-1 of the longest sequence of the call
+      const size_t lds_ft = sizeof(T) * ((size_t)KS * (NX + NN) +
+                                         (size_t)(nlev_max - LOG_TILE) * make_const_layout(NX, NY, 1).lev_stride);
+      const size_t lds_fb = sizeof(T) * (size_t)TILE * (2 * NN + NX > 4 * NX ? 2 * NN + NX : 4 * NX);
+      const size_t lds_bk = sizeof(T) * (size_t)KS * (2 * NN + NX);
+      if (!allow_lds((const void*)k_fwd_tiles<T, NX, NY>, lds_ft) ||
+          !allow_lds((const void*)k_fwd_bwd<T, NX, NY, INP>, lds_fb) ||
+          !allow_lds((const void*)k_bwd_tiles<T, NX, NY>, lds_bk))
+        return SRTM_E_HIP;
+      SRTM_STAGE((k_fwd_tiles<T, NX, NY>), dim3(g.nseq), dim3(KS), lds_ft, st, b);
+      SRTM_STAGE((k_fwd_bwd<T, NX, NY, INP>), dim3(g.ntiles), dim3(TILE), lds_fb, st, b);
+      hipLaunchKernelGGL((k_bwd_tiles<T, NX, NY>), dim3(g.nseq), dim3(KS), lds_bk, st, b);
+      SRTM_CHECK_LAUNCH();
+      hipLaunchKernelGGL((k_stats<T, NX, NY, true, INP>), dim3(g.ntiles), dim3(TILE), 0, st, b);
+      SRTM_CHECK_LAUNCH();
+      hipLaunchKernelGGL((k_stats_final<T, NX, NY, true>), dim3(g.nseq), dim3(256), 0, st, b, lo.ll, lo.dF, lo.dQ,
+                         lo.dR);
+      SRTM_CHECK_LAUNCH();
+      return SRTM_OK;
+    }
+  }
+  // A call whose sequences are all of one tile has no tree above the tiles.
+  if (g.ntiles > g.nseq) {
+    const size_t lds_tt = tile_tree_lds_bytes<T, NX>(nlev_max);
+    if (!allow_lds((const void*)k_tile_tree<T, NX, NY, INP>, lds_tt)) return SRTM_E_HIP;
+    SRTM_STAGE((k_tile_tree<T, NX, NY, INP>), dim3(g.nseq), dim3(TT), lds_tt, st, b);
+  } else {
+    SRTM_EV(ev.pre(st));
+    SRTM_EV(ev.post(st));
+  }
+  const size_t lds_fold = FoldLds<T, NX>(nlev_max).total;
+  // the last carry is an output of its own, or the only place where a last window's failure shows
+  const int want_last = b.one.mf_slow || b.one.Pf_slow || rec_mode == REC_LL || rec_mode == REC_GRAD ? 1 : 0;
 
   // output staging, then the per-step tables of up to RSTEPS fast steps
   const size_t ptab = sizeof(T) * (size_t)(g.max_L < RSTEPS ? g.max_L : RSTEPS) *
                       make_const_layout(NX, NY, g.max_L).per_i_stride;
   const size_t lds_rec = (size_t)4 * OutStage<T, NX>::BYTES * ((rec_mode == 3) ? 2 : 1) + ptab;
   if (!smoother) {
-    const size_t lds_ff = sizeof(T) * (size_t)TILE * ((2 * NX > NX + NN) ? 2 * NX : NX + NN);
-    if (!allow_lds((const void*)k_fwd_final<T, NX, NY, INP>, lds_ff)) return SRTM_E_HIP;
-    SRTM_STAGE((k_fwd_final<T, NX, NY, INP>), dim3(g.ntiles), dim3(TILE), lds_ff, st, b);
+    if (!allow_lds((const void*)k_fold<T, NX, NY, false, INP>, lds_fold)) return SRTM_E_HIP;
+    SRTM_STAGE((k_fold<T, NX, NY, false, INP>), dim3(g.ntiles), dim3(TILE), lds_fold, st, b, want_last);
     if (rec_mode == 1) {
       if (!allow_lds((const void*)k_recover<T, NX, NY, 1, INP>, lds_rec)) return SRTM_E_HIP;
       SRTM_STAGE((k_recover<T, NX, NY, 1, INP>), dim3(g.ntiles), dim3(TILE), lds_rec, st, b);
@@ -4218,13 +4985,8 @@ srtm_status launch_all(const Batch& b, const Launch& g, bool smoother, int rec_m
     return SRTM_OK;
   }
 
-  const size_t lds_fb = sizeof(T) * (size_t)TILE * ((2 * NN + NX > NX + NN) ? 2 * NN + NX : NX + NN);
-  if (!allow_lds((const void*)k_fwd_bwd<T, NX, NY, INP>, lds_fb)) return SRTM_E_HIP;
-  SRTM_STAGE((k_fwd_bwd<T, NX, NY, INP>), dim3(g.ntiles), dim3(TILE), lds_fb, st, b);
-
-  const size_t lds_bk = sizeof(T) * (size_t)KS * (2 * NN + NX);
-  if (!allow_lds((const void*)k_bwd_tiles<T, NX, NY>, lds_bk)) return SRTM_E_HIP;
-  SRTM_STAGE((k_bwd_tiles<T, NX, NY>), dim3(g.nseq), dim3(KS), lds_bk, st, b);
+  if (!allow_lds((const void*)k_fold<T, NX, NY, true, INP>, lds_fold)) return SRTM_E_HIP;
+  SRTM_STAGE((k_fold<T, NX, NY, true, INP>), dim3(g.ntiles), dim3(TILE), lds_fold, st, b, want_last);
 
   if (rec_mode == 2) {
     if (!allow_lds((const void*)k_recover<T, NX, NY, 2, INP>, lds_rec)) return SRTM_E_HIP;
@@ -4426,14 +5188,16 @@ __global__ void __launch_bounds__(TILE) km_reduce(Batch b, int nseq) {
 }
 
 template <typename T>
-__global__ void __launch_bounds__(KS) km_fwd_tiles(Batch b) {
+__global__ void __launch_bounds__(KS) km_tiles(Batch b) {
   const SeqDesc& d = b.table[blockIdx.x];
 #define SRTM_MX(a, c)                                      \
   if (d.nx == a && d.ny == c) {                            \
     if (d.tv) {                                            \
       if constexpr (a <= TV_NX_MAX) kb_tv_tiles<T, a, c>(b, blockIdx.x); \
+    } else if (d.B) {                                      \
+      kb_tile_tree<T, a, c, true>(b, blockIdx.x, KS);      \
     } else {                                               \
-      kb_fwd_tiles<T, a, c>(b, blockIdx.x);                \
+      kb_tile_tree<T, a, c, false>(b, blockIdx.x, KS);     \
     }                                                      \
     return;                                                \
   }
@@ -4442,16 +5206,16 @@ __global__ void __launch_bounds__(KS) km_fwd_tiles(Batch b) {
 }
 
 template <typename T>
-__global__ void __launch_bounds__(TILE) km_fwd_bwd(Batch b) {
+__global__ void __launch_bounds__(TILE) km_fold(Batch b) {
   const SeqDesc& d = b.table[tile_sequence(b)];
 #define SRTM_MX(a, c)                                                    \
   if (d.nx == a && d.ny == c) {                                          \
     if (d.tv) {                                                          \
       if constexpr (a <= TV_NX_MAX) kb_tv_fwd<T, a, c, true>(b, blockIdx.x); \
     } else if (d.B) {                                                    \
-      kb_fwd_bwd<T, a, c, true>(b, blockIdx.x);                          \
+      kb_fold<T, a, c, true, true>(b, blockIdx.x, false);                \
     } else {                                                             \
-      kb_fwd_bwd<T, a, c, false>(b, blockIdx.x);                         \
+      kb_fold<T, a, c, true, false>(b, blockIdx.x, false);               \
     }                                                                    \
     return;                                                              \
   }
@@ -4459,12 +5223,14 @@ __global__ void __launch_bounds__(TILE) km_fwd_bwd(Batch b) {
 #undef SRTM_MX
 }
 
+// Per-window models only: the tile-level reverse scan.
 template <typename T>
 __global__ void __launch_bounds__(KS) km_bwd_tiles(Batch b) {
   const SeqDesc& d = b.table[blockIdx.x];
+  if (!d.tv) return;
 #define SRTM_MX(a, c)                          \
   if (d.nx == a && d.ny == c) {                \
-    kb_bwd_tiles<T, a, c>(b, blockIdx.x);      \
+    if constexpr (a <= TV_NX_MAX) kb_bwd_tiles<T, a, c>(b, blockIdx.x); \
     return;                                    \
   }
   SRTM_PAIRS(SRTM_MX)
@@ -4498,8 +5264,8 @@ void stage_lds(bool tv, int max_L, int nlev_max, size_t (&o)[6]) {
   if (!tv) {
     up(0, constants_lds_bytes(NX, NY, max_L));
     up(1, fwd_reduce_lds_bytes<T, NX>());
-    up(2, sizeof(T) * ((size_t)KS * (NX + NN) + (size_t)(nlev_max - LOG_TILE) * make_const_layout(NX, NY, 1).lev_stride));
-    up(3, sizeof(T) * (size_t)TILE * ((2 * NN + NX > NX + NN) ? 2 * NN + NX : NX + NN));
+    up(2, tile_tree_lds_bytes<T, NX>(nlev_max));
+    up(3, FoldLds<T, NX>(nlev_max).total);
     up(5, (size_t)4 * OutStage<T, NX>::BYTES +
               sizeof(T) * (size_t)(max_L < RSTEPS ? max_L : RSTEPS) * make_const_layout(NX, NY, max_L).per_i_stride);
   } else {
@@ -4508,10 +5274,10 @@ void stage_lds(bool tv, int max_L, int nlev_max, size_t (&o)[6]) {
       up(1, sizeof(T) * (size_t)TILE * FA);
       up(2, sizeof(T) * (size_t)KS * FA);
       up(3, sizeof(T) * (size_t)TILE * FA);
+      up(4, sizeof(T) * (size_t)KS * (2 * NN + NX));
       up(5, (size_t)4 * OutStage<T, NX>::BYTES + tv_model_lds_bytes<T, NX, NY>());
     }
   }
-  up(4, sizeof(T) * (size_t)KS * (2 * NN + NX));
 }
 
 template <typename T>
@@ -4530,8 +5296,8 @@ srtm_status run_mixed(const SeqDesc* host, const void* table_dev, int nseq, int6
     SRTM_PAIRS(SRTM_MX)
 #undef SRTM_MX
   }
-  const void* fn[6] = {(const void*)km_constants<T>, (const void*)km_reduce<T>, (const void*)km_fwd_tiles<T>,
-                       (const void*)km_fwd_bwd<T>, (const void*)km_bwd_tiles<T>, (const void*)km_recover<T>};
+  const void* fn[6] = {(const void*)km_constants<T>, (const void*)km_reduce<T>, (const void*)km_tiles<T>,
+                       (const void*)km_fold<T>,      (const void*)km_bwd_tiles<T>, (const void*)km_recover<T>};
   for (int j = 0; j < 6; ++j)
     if (!allow_lds(fn[j], lds[j])) return SRTM_E_HIP;
   const unsigned ns = (unsigned)nseq, nt = (unsigned)ntiles;
@@ -4539,12 +5305,14 @@ srtm_status run_mixed(const SeqDesc* host, const void* table_dev, int nseq, int6
   SRTM_CHECK_LAUNCH();
   hipLaunchKernelGGL((km_reduce<T>), dim3(nt + ns), dim3(TILE), lds[1], st, b, nseq);
   SRTM_CHECK_LAUNCH();
-  hipLaunchKernelGGL((km_fwd_tiles<T>), dim3(ns), dim3(KS), lds[2], st, b);
+  hipLaunchKernelGGL((km_tiles<T>), dim3(ns), dim3(KS), lds[2], st, b);
   SRTM_CHECK_LAUNCH();
-  hipLaunchKernelGGL((km_fwd_bwd<T>), dim3(nt), dim3(TILE), lds[3], st, b);
+  hipLaunchKernelGGL((km_fold<T>), dim3(nt), dim3(TILE), lds[3], st, b);
   SRTM_CHECK_LAUNCH();
-  hipLaunchKernelGGL((km_bwd_tiles<T>), dim3(ns), dim3(KS), lds[4], st, b);
-  SRTM_CHECK_LAUNCH();
+  if (lds[4]) {  // per-window models among them
+    hipLaunchKernelGGL((km_bwd_tiles<T>), dim3(ns), dim3(KS), lds[4], st, b);
+    SRTM_CHECK_LAUNCH();
+  }
   hipLaunchKernelGGL((km_recover<T>), dim3(nt), dim3(TILE), lds[5], st, b);
   SRTM_CHECK_LAUNCH();
   return SRTM_OK;

@@ -11,11 +11,7 @@ constexpr int LOG_TILE = 8;
 constexpr int KS = 256;         // threads of the Kogge-Stone tile-level scans
 constexpr int LOG_KS = 8;
 
-inline __host__ __device__ int ceil_log2(int64_t x) {
-  int l = 0;
-  while ((int64_t(1) << l) < x) ++l;
-  return l;
-}
+inline __host__ __device__ int ceil_log2(int64_t x) { return x > 1 ? 64 - __builtin_clzll((unsigned long long)(x - 1)) : 0; }
 
 // Tile-level forward scan plan: each of the KS threads folds `chunk` (a power of two)
 // tiles, `active` threads take part in ceil_log2(active) Kogge-Stone steps, and the
@@ -44,8 +40,8 @@ struct ConstLayout {
   int A, Q, Cbar, Rx, K, Heta;   // model and slow-rate constants
   int per_i, per_i_stride;       // per fast step i = 1..L: A^i, Q_ii, Q_iL, c_i
   int o_Ai, o_Qii, o_QiL, o_ci;
-  int lev, lev_stride;           // per level p: F, D, J of 2^p merged windows and
-  int o_F, o_D, o_J, o_G1, o_G2, o_G3, o_G4;  // the vector-combine coefficients
+  int lev, lev_stride;           // per level p: the row table of the vector combine (2 nx rows of 2 nx
+  int o_C, o_F, o_D, o_J;        // coefficients), then F, D, J of 2^p merged windows
   int total;
 };
 
@@ -64,19 +60,24 @@ inline __host__ __device__ ConstLayout make_const_layout(int nx, int ny, int L, 
   c.o_Ai = 0; c.o_Qii = nn; c.o_QiL = 2 * nn; c.o_ci = 3 * nn;
   c.per_i_stride = (3 * nn + nxy + 7) & ~7;
   c.per_i = o; o += L * c.per_i_stride;
-  c.o_F = 0; c.o_D = nn; c.o_J = 2 * nn;
-  c.o_G1 = 3 * nn; c.o_G2 = 4 * nn; c.o_G3 = 5 * nn; c.o_G4 = 6 * nn;
+  c.o_C = 0; c.o_F = 4 * nn; c.o_D = 5 * nn; c.o_J = 6 * nn;
   c.lev_stride = (7 * nn + 7) & ~7;
   c.lev = o; o += nlev * c.lev_stride;
   c.total = o;
   return c;
 }
 
+// LDS doubles of a level chain: its F, D, J and 64 of exchange scratch (nx <= 4, matrix cores), or two
+// level records and five matrices.
+inline __host__ __device__ constexpr int chain_doubles(int nx) {
+  return 19 * nx * nx > 3 * nx * nx + 64 ? 19 * nx * nx : 3 * nx * nx + 64;
+}
+
 // Dynamic LDS of the constants kernel (float64 per-step tables and level-chain scratch).
 inline __host__ __device__ size_t constants_lds_bytes(int nx, int ny, int L) {
   const int nn = nx * nx, nxy = nx * ny;
   const int w2s = nn > 2 * nxy ? nn : 2 * nxy;
-  return sizeof(double) * (size_t)(2 * nn + nxy + ny * ny + (L + 1) * (3 * nn + w2s + nxy) + 19 * nn);
+  return sizeof(double) * (size_t)(2 * nn + nxy + ny * ny + (L + 1) * (3 * nn + w2s + nxy) + chain_doubles(nx));
 }
 
 // Workspace regions, byte offsets (256-byte aligned).
