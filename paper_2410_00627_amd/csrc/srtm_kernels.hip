@@ -144,7 +144,8 @@ struct Block4 {
 // Level chain over levels p0 .. p1-1, run by wave 0 of a workgroup.
 // `chain` is chain_doubles(nx) doubles of LDS whose first 3 nx^2 hold F, D, J of Theta(2^p0). Writes the
 // level records p0 .. p1-1 and, when p1 < nlev, F, D, J of Theta(2^p1) in float64 to `hand`
-// (3 nx^2 doubles), where a continuation of the chain in a later launch picks them up.
+// (3 nx^2 doubles), where a continuation of the chain in a later launch picks them up. `lev64` (may be null)
+// receives F, D, J of each level in float64 (lev64_off).
 //   Theta(2^{p+1}) = Theta(2^p) (x) Theta(2^p) under eq. op-filter, W = (I + D J)^{-1}, and the
 // coefficients that combine the vector parts of two runs of 2^p elements:
 //   d_ij = G1 d_i + G2 eta_j + d_j,   eta_ij = G3 eta_j - G4 d_i + eta_i,
@@ -153,7 +154,7 @@ struct Block4 {
 // per matrix entry with the operands in LDS.
 template <typename T, int NX>
 SRTM_DEV int level_chain4(double* chain, T* __restrict__ cst, const ConstLayout& lay, int p0, int p1, int nlev,
-                          double* __restrict__ hand) {
+                          double* __restrict__ hand, double* __restrict__ lev64) {
   constexpr int NN = NX * NX;
   static_assert(NX <= 4, "4 x 4 blocks");
   const Block4 B(chain + 3 * NN);
@@ -177,7 +178,9 @@ SRTM_DEV int level_chain4(double* chain, T* __restrict__ cst, const ConstLayout&
       T* dst = cst + lay.lev + p * lay.lev_stride;
       const double a = B.b == 0 ? G1 : B.b == 1 ? G2 : B.b == 2 ? G3 : -G4;
       dst[lay.o_C + ((B.b >> 1) * NX + B.r) * 2 * NX + (B.b & 1) * NX + B.c] = (T)a;
-      if (B.b < 3) dst[lay.o_F + B.b * NN + rc] = (T)(B.b == 0 ? F : B.b == 1 ? D : J);
+      const double x = B.b == 0 ? F : B.b == 1 ? D : J;
+      if (B.b < 3) dst[lay.o_F + B.b * NN + rc] = (T)x;
+      if (lev64 && B.b < 3) put_global(lev64 + p * 3 * NN + B.b * NN + rc, x);
     }
     const double nF = mm4(Ft, WF, 0.0), nFt = mm4(WF, Ft, 0.0);
     D = Block4::mm_sym(Ft, XDF) + D;  // F W D F^T + D
@@ -191,9 +194,9 @@ SRTM_DEV int level_chain4(double* chain, T* __restrict__ cst, const ConstLayout&
 
 template <typename T, int NX>
 SRTM_DEV int level_chain(double* chain, T* __restrict__ cst, const ConstLayout& lay, int p0, int p1, int nlev,
-                         double* __restrict__ hand) {
+                         double* __restrict__ hand, double* __restrict__ lev64) {
   if constexpr (NX <= 4) {
-    return level_chain4<T, NX>(chain, cst, lay, p0, p1, nlev, hand);
+    return level_chain4<T, NX>(chain, cst, lay, p0, p1, nlev, hand, lev64);
   } else {
   constexpr int NN = NX * NX;
   double* rec = chain;
@@ -309,8 +312,8 @@ constexpr size_t fwd_reduce_lds_bytes() {
 // The rest of the level chain (levels CHAIN_SPLIT .. nlev-1), continued from the handed-over
 // Theta(2^CHAIN_SPLIT). The wave runs at raised priority: it shares its SIMD with reductions.
 template <typename T, int NX, int NY>
-SRTM_DEV void chain_tail_body(T* __restrict__ cst, const double* __restrict__ hand, int L, int nlev,
-                              int32_t* info) {
+SRTM_DEV void chain_tail_body(T* __restrict__ cst, const double* __restrict__ hand, double* __restrict__ lev64, int L,
+                              int nlev, int32_t* info) {
   constexpr int NN = NX * NX;
   extern __shared__ char smraw[];
   double* chain = reinterpret_cast<double*>(smraw);  // chain_doubles(nx)
@@ -320,7 +323,7 @@ SRTM_DEV void chain_tail_body(T* __restrict__ cst, const double* __restrict__ ha
   for (int q = tid; q < 3 * NN; q += 64) chain[q] = gld(hand + q);
   wave_sync();
   const ConstLayout lay = make_const_layout(NX, NY, L, nlev);
-  const int f = level_chain<T, NX>(chain, cst, lay, CHAIN_SPLIT, nlev, nlev, nullptr);
+  const int f = level_chain<T, NX>(chain, cst, lay, CHAIN_SPLIT, nlev, nlev, nullptr, lev64);
   if (f && info) atomicOr(info, f);
 }
 
@@ -335,7 +338,8 @@ SRTM_DEV void chain_tail_body(T* __restrict__ cst, const double* __restrict__ ha
 template <typename T, int NX, int NY>
 SRTM_DEV void constants_body(const T* __restrict__ Fm, const T* __restrict__ Qm, const T* __restrict__ Hm,
                              const T* __restrict__ Rm, int L, int nlev, T* __restrict__ cst,
-                             double* __restrict__ cst64, double* __restrict__ hand, int32_t* info) {
+                             double* __restrict__ cst64, double* __restrict__ hand, double* __restrict__ lev64,
+                             int32_t* info) {
   constexpr int NN = NX * NX, NXY = NX * NY;
   constexpr int W2S = (NN > 2 * NXY ? NN : 2 * NXY);
   extern __shared__ double sm[];
@@ -575,7 +579,7 @@ SRTM_DEV void constants_body(const T* __restrict__ Fm, const T* __restrict__ Qm,
   wave_sync();
   // Levels below CHAIN_SPLIT; the others continue in the tile-reduction launch.
   const int p1 = nlev < CHAIN_SPLIT ? nlev : CHAIN_SPLIT;
-  lflag |= level_chain<T, NX>(chain, cst, lay, 0, p1, nlev, hand);
+  lflag |= level_chain<T, NX>(chain, cst, lay, 0, p1, nlev, hand, lev64);
   if (lflag && info) atomicOr(info, lflag);
 }
 
@@ -1694,7 +1698,7 @@ struct FoldLds {
   static constexpr int NN = NX * NX, R2 = 2 * NX, IS = info_stride(NX);
   static constexpr int MAXT = 20;                                          // tile-level bits (N <= 2^26: 18)
   static constexpr int NZ = LOG_TILE + 1;
-  size_t leaf, tree, lane, lev, node, tail, scratch, group, total;
+  size_t leaf, tree, lane, lev, node, tail, scratch, group, gain, total;
   __host__ __device__ FoldLds(int nlev) {
     const int laneL = blocks4<NX>() ? lane_levels<NX>() : nlev;
     size_t o = 0;
@@ -1707,6 +1711,7 @@ struct FoldLds {
     tail = take(sizeof(double) * NZ * IS * 4);                             // information of N's low bits
     scratch = take(blocks4<NX>() ? sizeof(double) * 64 * 4 : 0);
     group = take(blocks4<NX>() ? sizeof(double) * 4 * 4 * 40 : 0);         // states of each wave's four groups
+    gain = take(blocks4<NX>() ? sizeof(T) * LOG_TILE * 2 * 2 * NN : 0);    // a settled tile's gains per level
     total = o;
   }
 };
@@ -1714,17 +1719,53 @@ struct FoldLds {
 // Levels a sequence can have (N <= 2^26).
 constexpr int MAXLEV = 26;
 
-// Entry q of the level tables of the fold from level p0 on: F, D, J as 4 x 4 blocks, 48 entries a level.
+// Float32 sequences of several tiles keep F, D, J of every level in float64 too, behind the prior records
+// (a region sized for the larger per-window records of the per-window models; nx = 1 leaves no room
+// there): the fold's float64 steps then work with one consistent model, so that a state that has settled
+// is seen as settled to float64 rounding.
 template <typename T, int NX>
-SRTM_DEV T block_entry(const T* __restrict__ cst, const ConstLayout& lay, int p0, int q) {
-  const int p = p0 + q / 48, e = q % 48, r = (e % 16) / 4, c = e % 4;
-  if constexpr (NX == 4) return gld(cst + lay.lev + p * lay.lev_stride + lay.o_F + e);
-  return (r < NX && c < NX) ? gld(cst + lay.lev + p * lay.lev_stride + lay.o_F + (e / 16) * NX * NX + r * NX + c) : T(0);
+SRTM_DEV bool has_lev64(int64_t N) { return std::is_same_v<T, float> && NX >= 2 && NX <= 4 && N > TILE; }
+inline __host__ __device__ size_t lev64_off(int64_t N, int nx, size_t esz) {
+  return ((size_t)N * info_stride(nx) * esz + 7) & ~size_t(7);
+}
+
+// Entry q of the fold's level tables: F, D, J as 4 x 4 blocks, 48 entries a level.
+template <typename T, int NX>
+SRTM_DEV double block_entry(const T* __restrict__ cst, const double* __restrict__ lev64, const ConstLayout& lay, int q) {
+  const int p = q / 48, e = q % 48, r = (e % 16) / 4, c = e % 4;
+  if (r >= NX || c >= NX) return 0.0;
+  const int o = (e / 16) * NX * NX + r * NX + c;
+  if (std::is_same_v<T, float> && lev64) return gld(lev64 + p * 3 * NX * NX + o);
+  return (double)gld(cst + lay.lev + p * lay.lev_stride + lay.o_F + o);
 }
 template <typename T, int NX>
-SRTM_DEV void stage_blocks(const T* __restrict__ cst, const ConstLayout& lay, int nlev, double* lev, int tid, int nthr) {
-  staged_copy<4, T>(nlev * 48, tid, nthr, [&](int q) { return block_entry<T, NX>(cst, lay, 0, q); },
-                    [&](int q, T v) { lev[q] = (double)v; });
+SRTM_DEV void stage_blocks(const T* __restrict__ cst, const double* __restrict__ lev64, const ConstLayout& lay, int nlev,
+                           double* lev, int tid, int nthr) {
+  staged_copy<4, double>(nlev * 48, tid, nthr, [&](int q) { return block_entry<T, NX>(cst, lev64, lay, q); },
+                         [&](int q, double v) { lev[q] = v; });
+}
+
+// ---------------------------------------------------------------- settled tiles
+// Under a time-invariant model the covariances of a filter and smoother that forget settle: after some
+// hundred windows every window has the same P^f and J, and only vectors differ. The fold tests this per
+// whole tile, in float64, on the state (P) at the tile's start and the information (J) after its end: one
+// window's map and the whole tile's map have to leave each of them where it is, entry by entry within
+// settled_tol of the standard deviations. What changes by less over the tile's 256 windows is the same matrix
+// for all of them to the rounding of the element type. In a settled tile the fold combines vectors only (a 4 x 4
+// gain pair per level, formed once per tile, instead of a matrix inverse per window and level), and the
+// recovery forms the covariances of a fast step once per tile and streams them to every window.
+// Tiles near either end, models that do not settle, and anything not finite take the general way.
+// Float64: 2^-47, some rounding errors of one combine. Float32: 2^-26, a quarter of its rounding.
+template <typename T>
+SRTM_DEV constexpr double settled_tol() { return sizeof(T) == 8 ? 0x1p-47 : 0x1p-26; }
+// Whether a tile is settled is kept in the last slot of its tree (levels 1 .. 7 leave two slots free).
+template <typename T, int NX>
+SRTM_DEV T* settled_flag(T* utree, int64_t tile) { return utree + tile * (2 * NX * TILE) + (TILE - 1) * 2 * NX; }
+template <typename T, int NX>
+SRTM_DEV bool tile_settled(const T* utree, int64_t tile) {
+  if constexpr (NX > 4) return false;
+  const int f = gld(settled_flag<T, NX>(const_cast<T*>(utree), tile)) != T(0);
+  return __builtin_amdgcn_readfirstlane(f) != 0;
 }
 
 // One lane's state / information: vector and symmetric matrix.
@@ -1754,25 +1795,28 @@ SRTM_DEV void belief_load(Belief<T, NX>& b, const S* p) {
   }
 }
 
-// One window's record (vector and symmetric matrix) from its column `col` with W windows per field.
+// One window's record: the vector from its column `col`, the symmetric matrix from column `mcol` (the same,
+// or the tile's first window's in a settled tile), W windows per field.
 template <typename T, int NX, typename S>
-SRTM_DEV void record_load(T (&u)[NX], T (&P)[NX][NX], const S* __restrict__ col, int W) {
+SRTM_DEV void record_load(T (&u)[NX], T (&P)[NX][NX], const S* __restrict__ col, const S* __restrict__ mcol, int W) {
   int o = NX;
 #pragma unroll
   for (int r = 0; r < NX; ++r) {
     u[r] = (T)gld(col + (int64_t)r * W);
 #pragma unroll
-    for (int c = r; c < NX; ++c) P[r][c] = P[c][r] = (T)gld(col + (int64_t)(o++) * W);
+    for (int c = r; c < NX; ++c) P[r][c] = P[c][r] = (T)gld(mcol + (int64_t)(o++) * W);
   }
 }
 template <typename T, int NX>
-SRTM_DEV void record_store(const T (&u)[NX], const T (&P)[NX][NX], T* __restrict__ col, int W) {
-  int o = NX;
+SRTM_DEV void record_store(const T (&u)[NX], const T (&P)[NX][NX], T* __restrict__ col, int W, bool matrix) {
 #pragma unroll
-  for (int r = 0; r < NX; ++r) {
-    put_global(col + (int64_t)r * W, u[r]);
+  for (int r = 0; r < NX; ++r) put_global(col + (int64_t)r * W, u[r]);
+  if (matrix) {
+    int o = NX;
 #pragma unroll
-    for (int c = r; c < NX; ++c) put_global(col + (int64_t)(o++) * W, P[r][c]);
+    for (int r = 0; r < NX; ++r)
+#pragma unroll
+      for (int c = r; c < NX; ++c) put_global(col + (int64_t)(o++) * W, P[r][c]);
   }
 }
 
@@ -1885,7 +1929,8 @@ inline size_t tile_tree_lds_bytes(int nlev) {
 // N's set bits below each bit. A sequence of one tile has no level above it and its fold finds
 // the information of N's bits by itself.
 template <bool INP, typename T, int NX, int NY>
-SRTM_DEV void tile_tree_body(const T* __restrict__ y, int64_t N, int nlev, const T* __restrict__ cst, int L,
+SRTM_DEV void tile_tree_body(const T* __restrict__ y, int64_t N, int nlev, const T* __restrict__ cst,
+                             const double* __restrict__ lev64, int L,
                              InputView<T> in, const T* __restrict__ tagg, const T* __restrict__ utree,
                              T* __restrict__ ttree, double* __restrict__ tail, bool smoother, int32_t* info, int nthr) {
   constexpr int NN = NX * NX, R2 = 2 * NX, RS2 = row_slots<NX>(), TT_NODES = tt_nodes<NX>();
@@ -1905,7 +1950,7 @@ SRTM_DEV void tile_tree_body(const T* __restrict__ y, int64_t N, int nlev, const
                     [&](int q) { return row_coefficient<T, NX>(M.level(LOG_TILE), M.lay, q); },
                     [&](int q, T v) { sC[q] = v; });
   if (smoother) {
-    if constexpr (blocks4<NX>()) stage_blocks<T, NX>(cst, M.lay, nlev, lev, tid, nthr);
+    if constexpr (blocks4<NX>()) stage_blocks<T, NX>(cst, lev64, M.lay, nlev, lev, tid, nthr);
     else stage_lane_tables<T, NX>(cst, M.lay, nlev, lane, tid, nthr);
     // N's nodes within the last tile (its bits 1 .. 7), and bit 0's window
     const T* ut = utree + (N >> LOG_TILE) * (R2 * TILE);
@@ -2272,6 +2317,46 @@ struct OutStage {
   }
 };
 
+// A wave's place in the output [64 windows][L steps][RB bytes] of one element size when every window has the
+// same records: the records of fast steps i0 .. i0 + ns - 1 lie in LDS one after the other (`tab`), and the
+// wave writes them to all 64 windows front to back, 64 chunks (CH bytes each) per store instruction, so
+// that its stores run through consecutive addresses. PER = RB / CH instructions are ns-th parts of it.
+template <int RB>
+struct Stream {
+  static constexpr int CH = RB % 16 == 0 ? 16 : RB % 8 == 0 ? 8 : 4, PER = RB / CH;
+  int r, n, dr;          // chunk within a window's ns records, their number, its advance per instruction
+  unsigned off, dn, dw;  // byte offset, its advance and the extra when the window changes
+  SRTM_DEV Stream(int lane, int ns, int L) {
+    n = ns * PER;
+    const int dq = 64 / n;
+    dr = 64 - dq * n;
+    const int w = lane / n;
+    r = lane - w * n;
+    const unsigned win = (unsigned)L * RB;
+    off = w * win + r * CH;
+    dn = dq * win + dr * CH;
+    dw = win - (unsigned)n * CH;
+  }
+  SRTM_DEV void put(const char* tab, char* dst) {
+    using V = typename Chunk<CH>::type;
+    V v[PER];
+    unsigned o[PER];
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+      v[q] = *reinterpret_cast<const V*>(tab + r * CH);
+      o[q] = off;
+      r += dr;
+      off += dn;
+      if (r >= n) {
+        r -= n;
+        off += dw;
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < PER; ++q) put_chunk<true>(dst + o[q], v[q]);
+  }
+};
+
 template <typename T, int NX>
 SRTM_DEV bool finite_state(const T (&m)[NX], const T (&P)[NX][NX]) {
   bool ok = true;
@@ -2349,13 +2434,13 @@ SRTM_DEV int store_carry(int64_t k, const T (&m)[NX], const T (&P)[NX][NX], T* _
 }
 
 // Smoother correction of window k (fold section): v = (I + J P)^{-1} (eta - J m), W = -(I + J P)^{-1} J, from its
-// inclusive filter state (m, P) = (m^f_{k,l}, P^f_{k,l}) and its information record (column `col` of a tile
-// of nw windows; zero after the last window, which gives v = 0 and W = 0). Returns false when I + J P is numerically singular.
+// inclusive filter state (m, P) = (m^f_{k,l}, P^f_{k,l}) and its information record (columns `col` and
+// `mcol` of a tile of nw windows, record_load; zero after the last window, which gives v = 0 and W = 0). Returns false when I + J P is numerically singular.
 template <bool INP, typename T, int NX, int NY, typename S>
 SRTM_DEV bool info_correction(const Model<T, NX, NY>& M, int L, const Window<T, NX, NY>& w, const T (&zL)[NX],
-                              const S* __restrict__ col, int nw, T (&v)[NX], T (&W)[NX][NX]) {
+                              const S* __restrict__ col, const S* __restrict__ mcol, int nw, T (&v)[NX], T (&W)[NX][NX]) {
   T m[NX], P[NX][NX], eta[NX], J[NX][NX], A[NX][NX], Ai[NX][NX];
-  record_load(eta, J, col, nw);
+  record_load(eta, J, col, mcol, nw);
   window_slow_state<INP>(M, L, w, zL, m, P);
   mm(J, P, A);
 #pragma unroll
@@ -2385,9 +2470,10 @@ SRTM_DEV bool info_correction(const Model<T, NX, NY>& M, int L, const Window<T, 
 // `want_last`: also the filter state after the last window when no lane stands for window N (N a multiple of
 // TILE).
 template <bool SMOOTH, bool INP, typename T, int NX, int NY>
-SRTM_DEV void fold_body(const T* __restrict__ y, int64_t N, int L, int nlev, const T* __restrict__ cst, InputView<T> in,
+SRTM_DEV void fold_body(const T* __restrict__ y, int64_t N, int L, int nlev, const T* __restrict__ cst,
+                        const double* __restrict__ lev64, InputView<T> in,
                         const T* __restrict__ m0, const T* __restrict__ P0, const T* __restrict__ tagg,
-                        const T* __restrict__ ttree, const T* __restrict__ utree, const double* __restrict__ tail_g,
+                        const T* __restrict__ ttree, T* __restrict__ utree, const double* __restrict__ tail_g,
                         T* __restrict__ prior, T* __restrict__ m_slow, T* __restrict__ P_slow, T* __restrict__ rec,
                         int32_t* info, int64_t tile, bool want_last) {
   constexpr int NN = NX * NX, R2 = 2 * NX, IS = info_stride(NX), NZ = FoldLds<T, NX>::NZ, LB = lane_levels<NX>();
@@ -2424,13 +2510,13 @@ SRTM_DEV void fold_body(const T* __restrict__ y, int64_t N, int L, int nlev, con
   }
   T yt[NY], zL[NX];
   window_meas<INP>(M, y, k, N, yt, zL);
-  const int p0 = SMOOTH && single ? 0 : LB, nlv = B4 ? (nlev - p0) * 48 : 0;
-  T lvv[PLV];
+  const int nlv = B4 ? nlev * 48 : 0;
+  double lvv[PLV];
   if constexpr (B4) {
 #pragma unroll
     for (int i = 0; i < PLV; ++i) {
       const int q = i * TILE + tid;
-      lvv[i] = q < nlv ? block_entry<T, NX>(cst, M.lay, p0, q) : T(0);
+      lvv[i] = q < nlv ? block_entry<T, NX>(cst, lev64, M.lay, q) : 0.0;
     }
   }
   T ndv = T(0);
@@ -2465,7 +2551,7 @@ SRTM_DEV void fold_body(const T* __restrict__ y, int64_t N, int L, int nlev, con
 #pragma unroll
     for (int i = 0; i < PLV; ++i) {
       const int q = i * TILE + tid;
-      if (q < nlv) lev[p0 * 48 + q] = (double)lvv[i];
+      if (q < nlv) lev[q] = lvv[i];
     }
   }
   if (tid < FoldLds<T, NX>::MAXT * R2) node[tid] = ndv;
@@ -2483,6 +2569,7 @@ SRTM_DEV void fold_body(const T* __restrict__ y, int64_t N, int L, int nlev, con
 
   // ---- upper bits
   Belief<T, NX> fs, bs;  // filter state at the window's start; information after the window
+  bool settled = false;  // the tile's covariances are the same for all of its windows
   int bl = ragged ? 0 : LB;  // the window's bits below bl take backward combines
   const int tq = top_bit(tile) > hb - 1 ? top_bit(tile) : hb - 1;  // top bit of the tile that is used
   if constexpr (B4) {
@@ -2529,27 +2616,116 @@ SRTM_DEV void fold_body(const T* __restrict__ y, int64_t N, int L, int nlev, con
       st.ve = st.f ? e : -d;
       return st;
     };
-    uint32_t todo = (uint32_t)tile << LOG_TILE | 0xF0u;
+    uint32_t todo = (uint32_t)tile << LOG_TILE;
     if (SMOOTH && hb > 0) todo |= ((1u << hb) - 1u) << LOG_TILE;
-    int p = 31 - __builtin_clz(todo);
-    Step cur = fetch(p);
+    auto run = [&](uint32_t bits) {
+      int p = 31 - __builtin_clz(bits);
+      Step cur = fetch(p);
 #pragma unroll 1
-    while (true) {
-      todo &= ~(1u << p);
-      p = todo ? 31 - __builtin_clz(todo) : LB;
-      const Step next = fetch(p);
-      double u = cur.f ? fu : bu, P = cur.f ? fP : bP;
-      const bool ok = combine4(B, u, P, cur.Tt, cur.Dp, cur.Jp, cur.vd, cur.ve);
-      if (cur.act) {
-        if (!ok) flag |= SRTM_INFO_COMBINE_SINGULAR;
-        fu = cur.f ? u : fu;
-        fP = cur.f ? P : fP;
-        bu = cur.f ? bu : u;
-        bP = cur.f ? bP : P;
+      while (true) {
+        bits &= ~(1u << p);
+        p = bits ? 31 - __builtin_clz(bits) : LB;
+        const Step next = fetch(p);
+        double u = cur.f ? fu : bu, P = cur.f ? fP : bP;
+        const bool ok = combine4(B, u, P, cur.Tt, cur.Dp, cur.Jp, cur.vd, cur.ve);
+        if (cur.act) {
+          if (!ok) flag |= SRTM_INFO_COMBINE_SINGULAR;
+          fu = cur.f ? u : fu;
+          fP = cur.f ? P : fP;
+          bu = cur.f ? bu : u;
+          bP = cur.f ? bP : P;
+        }
+        if (!bits) break;
+        cur = next;
       }
-      if (!todo) break;
-      cur = next;
+    };
+    if (todo) run(todo);
+    if (!ragged && !single) {  // settled? (every wave finds the same)
+      // blocks 0, 1: P over one window and over a tile; blocks 2, 3: J
+      const bool f = B.b < 2;
+      const double* lv = lev + ((B.b & 1) ? LOG_TILE : 0) * 48;
+      const double P = f ? fP : bP;
+      double u = 0.0, P1 = P;
+      const bool ok = combine4(B, u, P1, lv[f ? 4 * B.c + B.r : 4 * B.r + B.c], lv[(f ? 16 : 32) + 4 * B.r + B.c],
+                               lv[(f ? 32 : 16) + 4 * B.r + B.c], 0.0, 0.0);
+      *B.own = P;
+      wave_sync();
+      const double dev = P1 - P, tol = settled_tol<T>();
+      const bool same = ok && dev * dev <= tol * tol * (sld(B.base + 5 * B.r) * sld(B.base + 5 * B.c));
+      wave_sync();
+      settled = __all(same || (!SMOOTH && !f));
     }
+    if (settled) {
+      // Vectors only. Level p's forward gains (G, G P), G = F W with W = (I + P J)^{-1}, and backward ones: wave wv
+      // forms those of levels 2 wv and 2 wv + 1, one per block.
+      const int lvl = 2 * wv + (B.b >> 1);
+      const bool f = (B.b & 1) == 0;
+      const double* lv = lev + lvl * 48;
+      const double P = f ? fP : bP;
+      bool ok = true;
+      const double Tt = lv[f ? 4 * B.c + B.r : 4 * B.r + B.c];
+      const double Wt = B.inv_t(mm4(P, lv[(f ? 32 : 16) + 4 * B.r + B.c], B.eye), ok);
+      const double G = mm4(Tt, mm4(Wt, B.eye, 0.0), 0.0);
+      const double GP = mm4(Tt, Block4::mm_sym(Wt, P), 0.0);
+      T* gain = reinterpret_cast<T*>(smraw + lo.gain);
+      if (in4) {
+        T* row = gain + ((lvl * 2 + (f ? 0 : 1)) * NX + B.r) * R2;
+        row[B.c] = (T)G;
+        row[NX + B.c] = (T)GP;
+      }
+      if (!ok && (SMOOTH || f)) flag |= SRTM_INFO_COMBINE_SINGULAR;
+      double* grp = reinterpret_cast<double*>(smraw + lo.group) + wv * 160;
+      if (B.b == 0) {
+        grp[4 * B.r + B.c] = fP;
+        grp[20 + 4 * B.r + B.c] = bP;
+        if (B.c == 0) {
+          grp[16 + B.r] = fu;
+          grp[36 + B.r] = bu;
+        }
+      }
+      __syncthreads();
+#pragma unroll
+      for (int r = 0; r < NX; ++r) {
+        fs.u[r] = (T)grp[16 + r];
+        bs.u[r] = (T)grp[36 + r];
+#pragma unroll
+        for (int c = r; c < NX; ++c) {
+          fs.P[r][c] = fs.P[c][r] = (T)grp[4 * r + c];
+          bs.P[r][c] = bs.P[c][r] = (T)grp[20 + 4 * r + c];
+        }
+      }
+#pragma unroll 1
+      for (int p = LOG_TILE - 1; p >= 0; --p) {
+        const bool fw = (tid >> p) & 1;
+        if (SMOOTH || fw) {
+          const int i = (tid >> p) ^ 1;
+          const T* nd = p == 0 ? leaf + i * R2 : tree + (tree_off(p) + i) * R2;
+          const T* g = gain + (p * 2 + (fw ? 0 : 1)) * 2 * NN;
+          T x[NX], ve[NX], nu[NX];
+#pragma unroll
+          for (int r = 0; r < NX; ++r) {
+            const T d = nd[r], e = nd[NX + r];
+            x[r] = fw ? fs.u[r] : bs.u[r];
+            ve[r] = fw ? e : -d;
+            nu[r] = fw ? d : e;
+          }
+#pragma unroll
+          for (int r = 0; r < NX; ++r) {
+#pragma unroll
+            for (int c = 0; c < NX; ++c) {
+              nu[r] = my_fma(g[r * R2 + c], x[c], nu[r]);
+              nu[r] = my_fma(g[r * R2 + NX + c], ve[c], nu[r]);
+            }
+          }
+#pragma unroll
+          for (int r = 0; r < NX; ++r) {
+            fs.u[r] = fw ? nu[r] : fs.u[r];
+            bs.u[r] = fw ? bs.u[r] : nu[r];
+          }
+        }
+      }
+    } else {
+      run(0xF0u);
     // each group's states to its 16 lanes
     double* grp = reinterpret_cast<double*>(smraw + lo.group) + wv * 160;
     grp[B.b * 40 + 4 * B.r + B.c] = fP;
@@ -2576,6 +2752,7 @@ SRTM_DEV void fold_body(const T* __restrict__ y, int64_t N, int L, int nlev, con
         bl = top_bit(tid ^ rem);
         belief_load(bs, tail + bl * IS);
       }
+    }
     }
   } else {
     gloadv(fs.u, m0);
@@ -2606,7 +2783,7 @@ SRTM_DEV void fold_body(const T* __restrict__ y, int64_t N, int L, int nlev, con
 
   // ---- the low bits, one lane per window
 #pragma unroll 1
-  for (int p = LB - 1; p >= 0; --p) {
+  for (int p = settled ? -1 : LB - 1; p >= 0; --p) {
     const bool f = (tid >> p) & 1;
     const bool act = f || (SMOOTH && p < bl);
     const int i = (tid >> p) ^ 1;
@@ -2634,19 +2811,24 @@ SRTM_DEV void fold_body(const T* __restrict__ y, int64_t N, int L, int nlev, con
     }
   }
 
-  // ---- outputs: the window's prior and information records; the slow filter output of the window before
+  // ---- outputs: the window's prior and information records; the slow filter output of the window
+  // before. The windows of a settled tile share the first window's matrices.
   const int nw = tile_windows(N, tile);
+  T* prec = prior + tile * (TILE * IS) + tid;
+  if (tid == 0) put_global(settled_flag<T, NX>(utree, tile), settled ? T(1) : T(0));
   if (k >= 1 && k <= N) flag |= store_slow(k - 1, fs.u, fs.P, m_slow, P_slow);
-  if (k < N) record_store(fs.u, fs.P, prior + tile * (TILE * IS) + tid, nw);
+  const bool whole = !settled || tid == 0;
+  if (k < N) record_store(fs.u, fs.P, prec, nw, whole);
   if constexpr (SMOOTH) {
     if (k < N) {
-      record_store(bs.u, bs.P, rec + tile * (TILE * IS) + tid, nw);
-      if (k >= 1) {  // the prediction of x_{k,1}: P^- = A P A^T + Q has to be positive definite
+      record_store(bs.u, bs.P, rec + tile * (TILE * IS) + tid, nw, whole);
+      // the prediction of x_{k,1}: P^- = A P A^T + Q has to be positive definite
+      if (settled ? wv == 0 : k >= 1) {
         T A[NX][NX], Qm[NX][NX], Pm[NX][NX], Pi[NX][NX];
         load(A, M.cst + M.lay.A);
         load(Qm, M.cst + M.lay.Q);
         sandwich(A, fs.P, Qm, Pm);
-        if (!spd_inv(Pm, Pi)) flag |= SRTM_INFO_PRED_SINGULAR;
+        if (!spd_inv(Pm, Pi) && k >= 1) flag |= SRTM_INFO_PRED_SINGULAR;
       }
     }
   }
@@ -3183,16 +3365,19 @@ constexpr int RSTEPS = 32;
 // MODE bit 1: filter blocks p(x_{k,i} | y_{1:k}); bit 2: smoothed blocks p(x_{k,i} | y_{1:N})
 // (and the smoother's slow state, block i = 1) from the correction (v, W) that K3s left as
 // terms linear in the smoothed state entering the tile; a workgroup covers exactly one tile.
-// `ilim` is L when fast-rate outputs are requested and 1 when only the slow smoothed state is.
+// `ilim` is L when fast-rate outputs are requested and 1 when only the slow smoothed state is. Part `part` of
+// `nparts` takes its share of the fast steps (kb_recover).
 // TV: per-window model; `cst` then holds the per-window constants blocks (stored by tv_column)
 // and Fa, Qa (with in.H) the per-window F, Q and H.
 template <typename T, int NX, int NY, int MODE, bool INP, bool TV = false>
 SRTM_DEV void recover_body(const T* __restrict__ y, int64_t N, int L, int ilim, const T* __restrict__ cst,
                            InputView<T> in, const T* __restrict__ Fa, const T* __restrict__ Qa,
                            const T* __restrict__ m0, const T* __restrict__ P0, const T* __restrict__ carry,
-                           const T* __restrict__ sfx, const T* __restrict__ tin, T* __restrict__ mf_fast,
+                           const T* __restrict__ sfx, const T* __restrict__ tin, const T* __restrict__ utree,
+                           T* __restrict__ mf_fast,
                            T* __restrict__ Pf_fast, T* __restrict__ ms_fast, T* __restrict__ Ps_fast,
-                           T* __restrict__ ms_slow, T* __restrict__ Ps_slow, int32_t* info, int64_t tile) {
+                           T* __restrict__ ms_slow, T* __restrict__ Ps_slow, int32_t* info, int64_t tile, int part,
+                           int nparts) {
   constexpr int NN = NX * NX, ST = NX + NN, SF = sfx_stride(NX);
   static_assert(TILE == 256, "one recovery workgroup per tile");
   constexpr bool FILT = (MODE & 1) != 0, SMOOTH = (MODE & 2) != 0;
@@ -3217,9 +3402,23 @@ SRTM_DEV void recover_body(const T* __restrict__ y, int64_t N, int L, int ilim, 
   const auto M = recover_model<TV, T, NX, NY>(cst, L, in, mdl, k);
   T m[NX], P[NX][NX], yk[NY];
   const int nw = tile_windows(N, tile);
+  bool settled = false;  // the tile's windows share their covariances
+  if constexpr (!TV) settled = tile_settled<T, NX>(utree, tile);
+  int ibeg = 1;  // this workgroup's fast steps are ibeg .. ilim
+  if (!TV && nparts > 1) {
+    if (settled) {
+      if (part > 0) return;
+    } else {  // whole groups of means per part
+      const int per = ((ilim + nparts - 1) / nparts + Stg::GM - 1) / Stg::GM * Stg::GM;
+      ibeg = part * per + 1;
+      if (ibeg > ilim) return;
+      ilim = ilim < ibeg + per - 1 ? ilim : ibeg + per - 1;
+    }
+  }
   const int64_t col = tile * (TILE * info_stride(NX)) + (valid ? tid : 0);  // the window's records
+  const int64_t mcol = settled ? tile * (TILE * info_stride(NX)) : col;
   if constexpr (TV) load_prior<T, NX, NY>(carry, m0, P0, kc, m, P);
-  else record_load(m, P, carry + col, nw);
+  else record_load(m, P, carry + col, carry + mcol, nw);
   T zL[NX];  // z_{k,l}
 #pragma unroll
   for (int r = 0; r < NX; ++r) zL[r] = T(0);
@@ -3241,7 +3440,7 @@ SRTM_DEV void recover_body(const T* __restrict__ y, int64_t N, int L, int ilim, 
   }
   T v[NX], W[NX][NX];
   if constexpr (SMOOTH && !TV) {
-    if (!info_correction<INP>(M, L, w, zL, sfx + col, nw, v, W) && valid)
+    if (!info_correction<INP>(M, L, w, zL, sfx + col, sfx + mcol, nw, v, W) && valid)
       flag |= SRTM_INFO_COMBINE_SINGULAR;
   } else if constexpr (SMOOTH) {  // v = Et m_in + gt,  W = Et P_in Et^T + St
     const T* src = sfx + kc * SF;
@@ -3271,34 +3470,9 @@ SRTM_DEV void recover_body(const T* __restrict__ y, int64_t N, int L, int ilim, 
       }
   }
   bool fin = true;
-  std::conditional_t<TV, TvSteps<T, NX, NY>, NoSteps> steps;
-#pragma unroll 1
-  for (int i = 1; i <= ilim; ++i) {
-    T mf[NX], Pii[NX][NX], PiL[NX][NX];
-    if constexpr (!TV) {
-      // The per-step tables go to LDS, RSTEPS steps at a time: read per step as wave-uniform
-      // scalar loads they outgrow the scalar registers (spilled to vector-register lanes and
-      // read back every step).
-      if ((i - 1) % RSTEPS == 0) {
-        const int n = (ilim - i + 1 < RSTEPS ? ilim - i + 1 : RSTEPS) * M.lay.per_i_stride;
-        const T* src = M.per_i(i);
-        __syncthreads();  // every wave is done with the previous steps' tables
-        staged_copy<8, T>(n, tid, TILE, [&](int q) { return gld(src + q); }, [&](int q, T v) { mdl[q] = v; });
-        __syncthreads();
-      }
-    }
-    if constexpr (TV) {
-      steps.template next<SMOOTH, true>(M, L, w, mf, Pii, PiL);
-    } else {  // step i's A^i, c_i, Q_ii and Q_il from the LDS copy
-      const T* ps = mdl + ((i - 1) % RSTEPS) * M.lay.per_i_stride;
-      T Ai[NX][NX], ci[NX][NY];
-      load(Ai, ps + M.lay.o_Ai);
-      load(ci, ps + M.lay.o_ci);
-      step_blocks<SMOOTH>(
-          w, Ai, ci, [&](int r, int c) { return ps[M.lay.o_Qii + r * NX + c]; },
-          [&](int r, int c) { return ps[M.lay.o_QiL + r * NX + c]; }, mf, Pii, PiL);
-    }
-    if constexpr (INP) {  // z_i = A z_{i-1} + B u_{k,i-1}, the loads of step i+1 issued first
+  // z_i = A z_{i-1} + B u_{k,i-1}, the loads of step i+1 issued first
+  auto input_advance = [&](int i) {
+    if constexpr (INP) {
       T uc[NU_MAX];
 #pragma unroll
       for (int j = 0; j < NU_MAX; ++j) {
@@ -3318,10 +3492,261 @@ SRTM_DEV void recover_body(const T* __restrict__ y, int64_t N, int L, int ilim, 
         nz[r] = t;
       }
 #pragma unroll
-      for (int r = 0; r < NX; ++r) {
-        z[r] = nz[r];
-        mf[r] += z[r];
+      for (int r = 0; r < NX; ++r) z[r] = nz[r];
+    }
+  };
+  // The per-step tables of fast steps i .. go to LDS, RSTEPS steps at a time: read per step as
+  // wave-uniform scalar loads they outgrow the scalar registers (spilled to vector-register lanes and
+  // read back every step).
+  auto stage_steps = [&](int i) {
+    if constexpr (!TV) {
+      const int n = (ilim - i + 1 < RSTEPS ? ilim - i + 1 : RSTEPS) * M.lay.per_i_stride;
+      const T* src = M.per_i(i);
+      __syncthreads();  // every wave is done with the previous steps' tables
+      staged_copy<8, T>(n, tid, TILE, [&](int q) { return gld(src + q); }, [&](int q, T v) { mdl[q] = v; });
+      __syncthreads();
+    }
+  };
+  if constexpr (!TV && blocks4<NX>()) {
+    if (settled) {
+      // Every window has the same covariances: four threads form those of a fast step once for the tile, and
+      // each wave writes them to its 64 windows front to back (Stream). The means of a step are one small
+      // matrix product for all windows, m^s_i = [A^i c_i P^f_{i,l}] (m'; S^{-1}e; v), four windows to a block of
+      // the matrix cores (Block4's layout; float64 for both types). With one lane per window the same product
+      // read its 40 coefficients from LDS in every lane, 1800 cycles a step against 300.
+      constexpr int SC = 24;  // fast steps at a time
+      constexpr int KF = NX + NY, KS2 = KF + NX, KBF = (KF + 3) / 4, KBS = SMOOTH ? (KS2 + 3) / 4 : KBF;
+      constexpr int RB = NN * (int)sizeof(T);
+      static_assert(SC * RB <= 64 * Stg::SBP && SC * KBS * 128 <= 64 * Stg::SBP && KBS * 4 * 512 <= 4 * 64 * Stg::SBP,
+                    "each table fits one wave's covariance staging");
+      char* tab_s = smraw;                                                   // P^s of the steps
+      double* row_s = reinterpret_cast<double*>(smraw + (size_t)Stg::BYTES);   // rows of the smoothed means
+      char* tab_f = smraw + (size_t)2 * Stg::BYTES;                          // P^f
+      double* row_f = reinterpret_cast<double*>(smraw + (size_t)3 * Stg::BYTES);
+      const int bk = lane >> 4, bw = lane & 15, bc = lane & 3;  // row, window of 16, column of the block layout
+      double x[4][KBS];  // (m'; S^{-1}e; v) of window 16 n + bw, entry 4 kb + bk
+      {
+        double* sx = reinterpret_cast<double*>(fst.pbuf);  // [entry][window], KBS * 4 entries at most
+        constexpr int KA = SMOOTH ? KS2 : KF;
+        constexpr int KP = 64 * Stg::SBP / 512 < KA ? 64 * Stg::SBP / 512 : KA;  // entries at a time
+#pragma unroll
+        for (int k0 = 0; k0 < KA; k0 += KP) {
+#pragma unroll
+          for (int e = k0; e < k0 + KP && e < KA; ++e)
+            sx[(e - k0) * 64 + lane] = e < NX ? (double)w.mp[e] : e < KF ? (double)w.Se[e < KF && e >= NX ? e - NX : 0]
+                                                                  : SMOOTH ? (double)v[e >= KF ? e - KF : 0] : 0.0;
+          wave_sync();
+#pragma unroll
+          for (int n = 0; n < 4; ++n)
+#pragma unroll
+            for (int kb = 0; kb < KBS; ++kb) {
+              const int e = 4 * kb + bk;
+              if (e >= k0 && e < k0 + KP && e < KA) x[n][kb] = sx[(e - k0) * 64 + 16 * n + bw];
+              else if (k0 == 0) x[n][kb] = 0.0;
+            }
+          wave_sync();
+        }
       }
+      // input response of the same windows, entry bk: z_i = A z_{i-1} + B u_{k,i-1}
+      double zr[4] = {0.0, 0.0, 0.0, 0.0}, Aop = 0.0, Bop = 0.0, un4[4] = {0.0, 0.0, 0.0, 0.0};
+      auto load_u = [&](int i) {  // inputs of the step into x_{k,i}
+#pragma unroll
+        for (int n = 0; n < 4; ++n)
+          un4[n] = bk < M.in.nu && i <= ilim ? (double)gld(M.in.u + ((w0 + 16 * n + bw) * L + (i - 1)) * M.in.nu + bk) : 0.0;
+      };
+      if constexpr (INP) {
+        Aop = bc < NX && bk < NX ? (double)gld(M.cst + M.lay.A + bc * NX + bk) : 0.0;
+        Bop = bc < NX && bk < M.in.nu ? (double)gld(M.in.B + bc * M.in.nu + bk) : 0.0;
+        load_u(1);
+      }
+      auto base_of = [&](T* out, int i) { return reinterpret_cast<char*>(out) + (w0 * L + (i - 1)) * RB; };
+#pragma unroll 1
+      for (int i0 = 1; i0 <= ilim; i0 += SC) {
+        const int ns = ilim - i0 + 1 < SC ? ilim - i0 + 1 : SC;
+        stage_steps(i0);  // its first barrier also ends the reads of the previous tables
+        // one thread per step and row: row r of step_blocks' matrices and of P^s
+        const int sq = tid >> 2, r = tid & 3;
+        if (sq < ns && r < NX) {
+          const T* ps = mdl + sq * M.lay.per_i_stride;
+          const T* Ai = ps + M.lay.o_Ai;
+          const T* ci = ps + M.lay.o_ci;
+          T Ar[NX], cr[NY], AP[NX], US[NY], Pr[NX], Lr[NX], TW[NX];
+          loadv(Ar, Ai + r * NX);
+          loadv(cr, ci + r * NY);
+          auto u_row = [&](const T (&ar)[NX], const T (&cc)[NY], T (&u)[NY]) {  // U_i = A^i V + c_i, one row
+#pragma unroll
+            for (int q = 0; q < NY; ++q) {
+              T t = ar[0] * w.V[0][q];
+#pragma unroll
+              for (int k2 = 1; k2 < NX; ++k2) t = my_fma(ar[k2], w.V[k2][q], t);
+              u[q] = t + cc[q];
+            }
+          };
+          {
+            T u[NY];
+            u_row(Ar, cr, u);
+#pragma unroll
+            for (int q = 0; q < NY; ++q) {
+              T t = T(0);
+#pragma unroll
+              for (int k2 = 0; k2 < NY; ++k2) t = my_fma(u[k2], symget(w.Si, k2, q), t);
+              US[q] = t;
+            }
+          }
+#pragma unroll
+          for (int c = 0; c < NX; ++c) {
+            T t = T(0);
+#pragma unroll
+            for (int k2 = 0; k2 < NX; ++k2) t = my_fma(Ar[k2], symget(w.P, k2, c), t);
+            AP[c] = t;
+          }
+#pragma unroll
+          for (int c = 0; c < NX; ++c) {  // row r of P^f_{i,i} (the entries right of the diagonal are used)
+            T ac[NX], cc[NY], u[NY];
+            loadv(ac, Ai + c * NX);
+            loadv(cc, ci + c * NY);
+            u_row(ac, cc, u);
+            T t = ps[M.lay.o_Qii + r * NX + c];
+#pragma unroll
+            for (int k2 = 0; k2 < NX; ++k2) t = my_fma(AP[k2], ac[k2], t);
+#pragma unroll
+            for (int k2 = 0; k2 < NY; ++k2) t = my_fma(-US[k2], u[k2], t);
+            Pr[c] = t;
+          }
+          auto rows = [&](double* o, int kn, int kb_n) {  // column r of each entry; idle rows stay zero
+#pragma unroll
+            for (int e = 0; e < 4 * KBS; ++e)
+              if (e < 4 * kb_n) {
+                const double t = e >= kn ? 0.0 : e < NX ? (double)Ar[e < NX ? e : 0]
+                                 : e < KF ? (double)cr[e >= NX && e < KF ? e - NX : 0]
+                                          : (double)Lr[e >= KF && e < KS2 ? e - KF : 0];
+                o[e * 4 + r] = t;
+                if (r == 0) {
+#pragma unroll
+                  for (int z0 = NX; z0 < 4; ++z0) o[e * 4 + z0] = 0.0;
+                }
+              }
+          };
+          if constexpr (FILT) {
+            T* o = reinterpret_cast<T*>(tab_f + sq * RB);
+#pragma unroll
+            for (int c = 0; c < NX; ++c)
+              if (c >= r) {
+                o[r * NX + c] = o[c * NX + r] = Pr[c];
+                fin = fin && isfinite(Pr[c]);
+              }
+            rows(row_f + sq * KBF * 16, KF, KBF);
+          }
+          if constexpr (SMOOTH) {
+#pragma unroll
+            for (int c = 0; c < NX; ++c) {  // row r of P^f_{i,l} = A^i Y1 + Q_il - c_i Y2
+              T t = ps[M.lay.o_QiL + r * NX + c];
+#pragma unroll
+              for (int k2 = 0; k2 < NX; ++k2) t = my_fma(Ar[k2], w.Y1[k2][c], t);
+#pragma unroll
+              for (int k2 = 0; k2 < NY; ++k2) t = my_fma(-cr[k2], w.Y2[k2][c], t);
+              Lr[c] = t;
+            }
+#pragma unroll
+            for (int c = 0; c < NX; ++c) {
+              T t = T(0);
+#pragma unroll
+              for (int k2 = 0; k2 < NX; ++k2) t = my_fma(Lr[k2], symget(W, k2, c), t);
+              TW[c] = t;
+            }
+            double* ro = row_s + sq * KBS * 16;
+            rows(ro, KS2, KBS);
+            wave_sync();  // the four rows of a step belong to one wave
+            T* o = reinterpret_cast<T*>(tab_s + sq * RB);
+#pragma unroll
+            for (int c = 0; c < NX; ++c) {
+              T t = Pr[c];
+#pragma unroll
+              for (int k2 = 0; k2 < NX; ++k2) t = my_fma(TW[k2], (T)ro[(KF + k2) * 4 + c], t);
+              if (c >= r) {
+                o[r * NX + c] = o[c * NX + r] = t;
+                fin = fin && isfinite(t);
+              }
+            }
+          }
+        }
+        __syncthreads();
+        Stream<RB> sf(lane, ns, L), ss(lane, ns, L);
+#pragma unroll 1
+        for (int j = 0; j < ns; ++j) {
+          const int i = i0 + j;
+          if constexpr (INP) {
+#pragma unroll
+            for (int n = 0; n < 4; ++n) zr[n] = mm4(Aop, zr[n], mm4(Bop, un4[n], 0.0));
+            load_u(i + 1);
+          }
+          auto means = [&](const double* row, int kb_n, const Stg& st) {
+            double a[KBS];
+#pragma unroll
+            for (int kb = 0; kb < KBS; ++kb)
+              if (kb < kb_n) a[kb] = row[(j * kb_n + kb) * 16 + 4 * bk + bc];
+            T* mp = reinterpret_cast<T*>(st.mbuf + bw * Stg::SBM) + ((i - 1) % Stg::GM) * NX + bk;
+#pragma unroll
+            for (int n = 0; n < 4; ++n) {
+              double acc = zr[n];
+#pragma unroll
+              for (int kb = 0; kb < KBS; ++kb)
+                if (kb < kb_n) acc = mm4(a[kb], x[n][kb], acc);
+              if (bk < NX) {
+                *reinterpret_cast<T*>(reinterpret_cast<char*>(mp) + n * 16 * Stg::SBM) = (T)acc;
+                fin = fin && isfinite((T)acc);
+              }
+            }
+          };
+          if constexpr (FILT) means(row_f, KBF, fst);
+          if constexpr (SMOOTH) means(row_s, KBS, sst);
+          if (FILT && Pf_fast) sf.put(tab_f, base_of(Pf_fast, i0));
+          if (SMOOTH && Ps_fast) ss.put(tab_s, base_of(Ps_fast, i0));
+          wave_sync();
+          if (FILT) fst.flush(lane, 64, mf_fast, nullptr, w0, L, i, ilim);
+          if (SMOOTH) {
+            if (i == 1) {
+              sst.flush_slow(lane, 64, ms_slow, nullptr, w0);
+              if (Ps_slow) {
+                Stream<RB> one(lane, 1, 1);
+                one.put(tab_s, reinterpret_cast<char*>(Ps_slow + w0 * NN));
+              }
+            }
+            sst.flush(lane, 64, ms_fast, nullptr, w0, L, i, ilim);
+          }
+          wave_sync();
+        }
+      }
+      if (!fin) flag |= SRTM_INFO_NONFINITE;
+      if (flag && info) atomicOr(info, flag);
+      return;
+    }
+  }
+  if constexpr (INP) {
+    for (int i = 1; i < ibeg; ++i) input_advance(i);
+  }
+  std::conditional_t<TV, TvSteps<T, NX, NY>, NoSteps> steps;
+#pragma unroll 1
+  for (int i = ibeg; i <= ilim; ++i) {
+    T mf[NX], Pii[NX][NX], PiL[NX][NX];
+    if constexpr (!TV) {
+      if ((i - ibeg) % RSTEPS == 0) stage_steps(i);
+    }
+    if constexpr (TV) {
+      steps.template next<SMOOTH, true>(M, L, w, mf, Pii, PiL);
+    } else {  // step i's A^i, c_i, Q_ii and Q_il from the LDS copy
+      const T* ps = mdl + ((i - ibeg) % RSTEPS) * M.lay.per_i_stride;
+      T Ai[NX][NX], ci[NX][NY];
+      load(Ai, ps + M.lay.o_Ai);
+      load(ci, ps + M.lay.o_ci);
+      step_blocks<SMOOTH>(
+          w, Ai, ci, [&](int r, int c) { return ps[M.lay.o_Qii + r * NX + c]; },
+          [&](int r, int c) { return ps[M.lay.o_QiL + r * NX + c]; }, mf, Pii, PiL);
+    }
+    if constexpr (INP) {
+      input_advance(i);
+#pragma unroll
+      for (int r = 0; r < NX; ++r) mf[r] += z[r];
     }
     if (FILT) {
       fin = fin && finite_state(mf, Pii);
@@ -4059,7 +4484,8 @@ SRTM_DEV void lag1_within(const Model<T, NX, NY>& M, const Window<T, NX, NY>& w,
 // carry and smoother correction (v, W) as the recovery; records staged and written as K7's.
 template <typename T, int NX, int NY>
 SRTM_DEV void lag1_body(const T* __restrict__ y, int64_t N, int L, const T* __restrict__ cst,
-                        const T* __restrict__ carry, const T* __restrict__ sfx, T* __restrict__ Cs_fast, int32_t* info, int64_t tile) {
+                        const T* __restrict__ carry, const T* __restrict__ sfx, const T* __restrict__ utree,
+                        T* __restrict__ Cs_fast, int32_t* info, int64_t tile) {
   static_assert(TILE == 256, "one workgroup per tile");
   using Stg = OutStage<T, NX>;
   extern __shared__ char smraw[];
@@ -4073,15 +4499,17 @@ SRTM_DEV void lag1_body(const T* __restrict__ y, int64_t N, int L, const T* __re
   const int64_t kc = valid ? k : 0;
   T m[NX], P[NX][NX], yk[NY];
   const int nw = tile_windows(N, tile);
+  const bool settled = tile_settled<T, NX>(utree, tile);
   const int64_t col = tile * (TILE * info_stride(NX)) + (valid ? tid : 0);  // the window's records
-  record_load(m, P, carry + col, nw);
+  const int64_t mcol = settled ? tile * (TILE * info_stride(NX)) : col;
+  record_load(m, P, carry + col, carry + mcol, nw);
   gloadv(yk, y + kc * NY);
   Window<T, NX, NY> w;
   int flag = 0;
   if (!window_setup(M, L, m, P, yk, w) && valid) flag |= SRTM_INFO_INNOVATION_NOT_PD;
   T v[NX], W[NX][NX];
   const T zero[NX] = {};
-  if (!info_correction<false>(M, L, w, zero, sfx + col, nw, v, W) && valid) flag |= SRTM_INFO_COMBINE_SINGULAR;
+  if (!info_correction<false>(M, L, w, zero, sfx + col, sfx + mcol, nw, v, W) && valid) flag |= SRTM_INFO_COMBINE_SINGULAR;
   T A[NX][NX];
   load(A, M.cst + M.lay.A);
   T Pprev[NX][NX], PLprev[NX][NX], Uprev[NX][NY];
@@ -4203,13 +4631,13 @@ SRTM_DEV void gloadv_f64(double (&a)[R], const T* __restrict__ p) {
 
 // Gradient statistics of window k (float64), added to Sw, Swx, Sy; the window's log-likelihood
 // term in *ll. (m, P): its prior; yk: its measurement (y_k - mu_k with known inputs); col: its
-// information record (element type T, in a tile of nw windows), or its smoother-correction record with the
+// information record (columns col and mcol, element type T, in a tile of nw windows), or its smoother-correction record with the
 // tile's incoming smoothed state `ti` (grad_by_elements); okc: whether the correction from it is usable; zL: its input
 // response z_{k,l}; with known inputs Bm [nx][nu] and uk, the window's inputs [L][nu].
 template <typename T, int NX, int NY>
 SRTM_DEV bool grad_window(const Model<double, NX, NY>& M, int L, const double (&m)[NX], const double (&P)[NX][NX],
                           const double (&yk)[NY], const double (&R)[NY][NY], const T* __restrict__ col,
-                          int nw, const T* __restrict__ ti, const double (&zL)[NX], bool& okc, double& ll, double (&Sw)[NX][NX], double (&Swx)[NX][NX],
+                          const T* __restrict__ mcol, int nw, const T* __restrict__ ti, const double (&zL)[NX], bool& okc, double& ll, double (&Sw)[NX][NX], double (&Swx)[NX][NX],
                           double (&Sy)[NY][NY], const T* __restrict__ Bm = nullptr, const T* __restrict__ uk = nullptr,
                           int nu = 0) {
   Window<double, NX, NY> w;
@@ -4257,7 +4685,7 @@ SRTM_DEV bool grad_window(const Model<double, NX, NY>& M, int L, const double (&
         W[c][r] = t;
       }
   } else {
-    okc = info_correction<true>(M, L, w, zL, col, nw, v, W);
+    okc = info_correction<true>(M, L, w, zL, col, mcol, nw, v, W);
   }
   double A[NX][NX], Qm[NX][NX];
   M.get(A, M.lay.A);
@@ -4419,7 +4847,8 @@ template <typename T, int NX, int NY, bool GRAD, bool INP>
 SRTM_DEV void stats_body(const T* __restrict__ y, int64_t N, int L, const T* __restrict__ cst,
                          const double* __restrict__ cst64, InputView<T> in, const T* __restrict__ Rm,
                          const T* __restrict__ m0, const T* __restrict__ P0, const T* __restrict__ carry,
-                         const T* __restrict__ sfx, const T* __restrict__ tin, double* __restrict__ parts, int32_t* info, int64_t tile) {
+                         const T* __restrict__ sfx, const T* __restrict__ tin, const T* __restrict__ utree,
+                         double* __restrict__ parts, int32_t* info, int64_t tile) {
   using SL = StatLayout<NX, NY>;
   constexpr int NC = SL::SIZE;
   __shared__ double red[TILE / 64][NC];
@@ -4429,6 +4858,8 @@ SRTM_DEV void stats_body(const T* __restrict__ y, int64_t N, int L, const T* __r
   const int64_t kc = valid ? k : 0;
   const int nw = tile_windows(N, tile);
   const int64_t col = tile * (TILE * info_stride(NX)) + (valid ? tid : 0);  // the window's records
+  const int64_t mcol = !(GRAD && grad_by_elements<T>()) && tile_settled<T, NX>(utree, tile)
+                           ? tile * (TILE * info_stride(NX)) : col;
   double* part = parts + tile * SL::SIZE;
   int flag = 0;
   double ll = 0.0;
@@ -4445,7 +4876,7 @@ SRTM_DEV void stats_body(const T* __restrict__ y, int64_t N, int L, const T* __r
     const Model<double, NX, NY> M{cst64, make_const_layout(NX, NY, L)};
     double m[NX], P[NX][NX], yk[NY], R[NY][NY];
     if constexpr (!grad_by_elements<T>()) {
-      record_load(m, P, carry + col, nw);
+      record_load(m, P, carry + col, carry + mcol, nw);
     } else if (kc == 0) {
       gloadv_f64(m, m0);
       gload_f64(P, P0);
@@ -4464,7 +4895,7 @@ SRTM_DEV void stats_body(const T* __restrict__ y, int64_t N, int L, const T* __r
     }
     gload_f64(R, Rm);
     bool okc = true;
-    if (!grad_window<T, NX, NY>(M, L, m, P, yk, R, sfx + (grad_by_elements<T>() ? kc * sfx_stride(NX) : col), nw,
+    if (!grad_window<T, NX, NY>(M, L, m, P, yk, R, sfx + (grad_by_elements<T>() ? kc * sfx_stride(NX) : col), sfx + mcol, nw,
                                 tin + tile * (NX + NX * NX), zL, okc, ll, Sw, Swx, Sy,
                                 INP ? in.B : nullptr, INP ? in.u + kc * L * in.nu : nullptr, INP ? in.nu : 0) &&
         valid)
@@ -4473,7 +4904,7 @@ SRTM_DEV void stats_body(const T* __restrict__ y, int64_t N, int L, const T* __r
   } else {
     const Model<T, NX, NY> M{cst, make_const_layout(NX, NY, L), in};
     T m[NX], P[NX][NX], yk[NY];
-    record_load(m, P, carry + col, nw);
+    record_load(m, P, carry + col, carry + mcol, nw);
     if constexpr (INP) {
       T zL[NX];
       window_meas<true>(M, y, kc, N, yk, zL);
@@ -4602,7 +5033,7 @@ struct Seq {  // one sequence's typed arrays and scan plan
   const T *F, *Q, *H, *R, *m0, *P0, *y;
   T *ms_fast, *Ps_fast, *ms_slow, *Ps_slow, *mf_fast, *Pf_fast, *mf_slow, *Pf_slow, *Cs_fast;
   T *cst, *ftagg, *ftst, *utree, *carry, *btagg, *btst, *sfx, *tvblk, *tvel;
-  double *cst64, *hand, *stats, *tail;
+  double *cst64, *hand, *stats, *tail, *lev64;
   int64_t N, tile0;
   int L;
   ScanPlan plan;
@@ -4649,6 +5080,7 @@ SRTM_DEV Seq<T, NX, NY> seq_view(const Batch& b, int s) {
   q.sfx = reinterpret_cast<T*>(base + wl.sfx);
   q.tail = reinterpret_cast<double*>(base + wl.sfx + tail_info_off(d.N, NX, sizeof(T)));
   q.smoother = d.smoother != 0;
+  q.lev64 = has_lev64<T, NX>(d.N) ? reinterpret_cast<double*>(base + wl.carry + lev64_off(d.N, NX, sizeof(T))) : nullptr;
   q.tvblk = reinterpret_cast<T*>(base + wl.tvblk);
   q.tvel = reinterpret_cast<T*>(base + wl.tvel);
   q.stats = reinterpret_cast<double*>(base + wl.stats);
@@ -4660,13 +5092,24 @@ SRTM_DEV Seq<T, NX, NY> seq_view(const Batch& b, int s) {
 
 SRTM_DEV int tile_sequence(const Batch& b, int64_t bid) { return b.tile_seq ? b.tile_seq[bid] : 0; }
 SRTM_DEV int tile_sequence(const Batch& b) { return tile_sequence(b, blockIdx.x); }
+// Tile of a sequence of nt tiles for its i-th workgroup, both ends first (0, nt - 1, 1, nt - 2, ...): the
+// tiles that are not settled, next to the ends, take several times as long as the others and would
+// otherwise be the launch's tail.
+SRTM_DEV int64_t ends_first(int64_t i, int64_t nt) { return (i & 1) ? nt - 1 - (i >> 1) : i >> 1; }
+
+// In the recovery the tiles at either end of a sequence, which have not settled, are the slow ones: one of
+// them alone takes its workgroup about 40 us (float64, nx = 4, L = 20), and with fewer tiles than compute units that
+// is the launch. So the first END_TILES tiles (ends_first) are split by fast steps over END_PARTS workgroups; a
+// settled tile, or one that needs fewer parts, lets the extra ones return. The extra workgroups come first
+// in the grid; a batch of more than END_SEQS sequences fills the device without them.
+constexpr int END_TILES = 8, END_PARTS = 4, END_EXTRA = END_TILES * (END_PARTS - 1), END_SEQS = 16;
 
 // Stage bodies of the smoothing launches, for workgroup `bid` of the launch; the kernels below
 // wrap them for one (nx, ny) pair, the mixed-pair kernels dispatch to them per workgroup.
 template <typename T, int NX, int NY>
 SRTM_DEV void kb_constants(const Batch& b, int64_t bid) {
   const Seq<T, NX, NY> q = seq_view<T, NX, NY>(b, (int)bid);
-  constants_body<T, NX, NY>(q.F, q.Q, q.H, q.R, q.L, q.plan.nlev, q.cst, q.cst64, q.hand, q.info);
+  constants_body<T, NX, NY>(q.F, q.Q, q.H, q.R, q.L, q.plan.nlev, q.cst, q.cst64, q.hand, q.lev64, q.info);
 }
 
 // Workgroups 0 .. nseq-1 continue the level chains of the sequences; the others reduce tile
@@ -4675,7 +5118,7 @@ template <typename T, int NX, int NY, bool INP>
 SRTM_DEV void kb_fwd_reduce(const Batch& b, int64_t bid, int nseq) {
   if (bid < nseq) {
     const Seq<T, NX, NY> q = seq_view<T, NX, NY>(b, (int)bid);
-    chain_tail_body<T, NX, NY>(q.cst, q.hand, q.L, q.plan.nlev, q.info);
+    chain_tail_body<T, NX, NY>(q.cst, q.hand, q.lev64, q.L, q.plan.nlev, q.info);
     return;
   }
   const int64_t t = bid - nseq;
@@ -4686,14 +5129,14 @@ SRTM_DEV void kb_fwd_reduce(const Batch& b, int64_t bid, int nseq) {
 template <typename T, int NX, int NY, bool INP>
 SRTM_DEV void kb_tile_tree(const Batch& b, int64_t bid, int nthr) {
   const Seq<T, NX, NY> q = seq_view<T, NX, NY>(b, (int)bid);
-  tile_tree_body<INP, T, NX, NY>(q.y, q.N, q.plan.nlev, q.cst, q.L, q.in, q.ftagg, q.utree, q.ftst, q.tail, q.smoother,
+  tile_tree_body<INP, T, NX, NY>(q.y, q.N, q.plan.nlev, q.cst, q.lev64, q.L, q.in, q.ftagg, q.utree, q.ftst, q.tail, q.smoother,
                                  q.info, nthr);
 }
 
 template <typename T, int NX, int NY, bool SMOOTH, bool INP>
 SRTM_DEV void kb_fold(const Batch& b, int64_t bid, bool want_last) {
   const Seq<T, NX, NY> q = seq_view<T, NX, NY>(b, tile_sequence(b, bid));
-  fold_body<SMOOTH, INP, T, NX, NY>(q.y, q.N, q.L, q.plan.nlev, q.cst, q.in, q.m0, q.P0, q.ftagg, q.ftst, q.utree, q.tail,
+  fold_body<SMOOTH, INP, T, NX, NY>(q.y, q.N, q.L, q.plan.nlev, q.cst, q.lev64, q.in, q.m0, q.P0, q.ftagg, q.ftst, q.utree, q.tail,
                                     q.carry, q.mf_slow, q.Pf_slow, q.sfx, q.info, bid - q.tile0, want_last);
 }
 
@@ -4738,13 +5181,26 @@ SRTM_DEV void kb_tv_fwd(const Batch& b, int64_t bid) {
 // MODE 1: filter outputs only; 2: smoother outputs; 3: both. Fast-rate outputs take all L
 // steps; with only the slow smoothed state requested, step 1 suffices.
 template <typename T, int NX, int NY, int MODE, bool INP, bool TV = false>
-SRTM_DEV void kb_recover(const Batch& b, int64_t bid) {
-  const Seq<T, NX, NY> q = seq_view<T, NX, NY>(b, tile_sequence(b, bid));
+SRTM_DEV void kb_recover(const Batch& b, int64_t bid, int nextra) {
+  int64_t i = bid - nextra;  // the workgroup's number among its sequence's tiles
+  int part = 0, s;
+  if (bid < nextra) {
+    s = (int)(bid / END_EXTRA);
+    const int e = (int)(bid % END_EXTRA);
+    i = e / (END_PARTS - 1);
+    part = 1 + e % (END_PARTS - 1);
+  } else {
+    s = tile_sequence(b, i);
+  }
+  const Seq<T, NX, NY> q = seq_view<T, NX, NY>(b, s);
+  if (bid >= nextra) i -= q.tile0;
+  if (i >= q.plan.nt) return;
+  const int nparts = nextra > 0 && i < END_TILES ? END_PARTS : 1;
   const bool fast = (MODE & 1) || q.ms_fast || q.Ps_fast;
   if (!fast && !q.ms_slow && !q.Ps_slow) return;
   recover_body<T, NX, NY, MODE, INP, TV>(q.y, q.N, q.L, fast ? q.L : 1, TV ? q.tvblk : q.cst, q.in, q.F, q.Q, q.m0,
-                                         q.P0, q.carry, q.sfx, q.btst, q.mf_fast, q.Pf_fast, q.ms_fast, q.Ps_fast,
-                                         q.ms_slow, q.Ps_slow, q.info, bid - q.tile0);
+                                         q.P0, q.carry, q.sfx, q.btst, q.utree, q.mf_fast, q.Pf_fast, q.ms_fast, q.Ps_fast,
+                                         q.ms_slow, q.Ps_slow, q.info, TV ? i : ends_first(i, q.plan.nt), part, nparts);
 }
 
 template <typename T, int NX, int NY>
@@ -4800,8 +5256,8 @@ __global__ void __launch_bounds__(TILE) k_tv_fwd(Batch b) {
 }
 
 template <typename T, int NX, int NY, int MODE, bool INP, bool TV = false>
-__global__ void __launch_bounds__(TILE) k_recover(Batch b) {
-  kb_recover<T, NX, NY, MODE, INP, TV>(b, blockIdx.x);
+__global__ void __launch_bounds__(TILE, sizeof(T) == 4 && NX <= 4 && !TV ? 2 : 1) k_recover(Batch b, int nextra) {
+  kb_recover<T, NX, NY, MODE, INP, TV>(b, blockIdx.x, nextra);
 }
 
 // The constants block without the scan levels (the sequential comparator needs no scan), and the
@@ -4809,7 +5265,7 @@ __global__ void __launch_bounds__(TILE) k_recover(Batch b) {
 template <typename T, int NX, int NY>
 __global__ void __launch_bounds__(256) k_constants_seq(Batch b) {
   const Seq<T, NX, NY> q = seq_view<T, NX, NY>(b, blockIdx.x);
-  constants_body<T, NX, NY>(q.F, q.Q, q.H, q.R, q.L, 0, q.cst, q.cst64, q.hand, q.info);
+  constants_body<T, NX, NY>(q.F, q.Q, q.H, q.R, q.L, 0, q.cst, q.cst64, q.hand, nullptr, q.info);
 }
 
 template <typename T, int NX, int NY>
@@ -4824,14 +5280,14 @@ template <typename T, int NX, int NY>
 __global__ void __launch_bounds__(TILE) k_lag1(Batch b) {
   const Seq<T, NX, NY> q = seq_view<T, NX, NY>(b, tile_sequence(b));
   if (!q.Cs_fast) return;
-  lag1_body<T, NX, NY>(q.y, q.N, q.L, q.cst, q.carry, q.sfx, q.Cs_fast, q.info,
+  lag1_body<T, NX, NY>(q.y, q.N, q.L, q.cst, q.carry, q.sfx, q.utree, q.Cs_fast, q.info,
                        (int64_t)blockIdx.x - q.tile0);
 }
 
 template <typename T, int NX, int NY, bool GRAD, bool INP>
 __global__ void __launch_bounds__(TILE) k_stats(Batch b) {
   const Seq<T, NX, NY> q = seq_view<T, NX, NY>(b, tile_sequence(b));
-  stats_body<T, NX, NY, GRAD, INP>(q.y, q.N, q.L, q.cst, q.cst64, q.in, q.R, q.m0, q.P0, q.carry, q.sfx, q.btst,
+  stats_body<T, NX, NY, GRAD, INP>(q.y, q.N, q.L, q.cst, q.cst64, q.in, q.R, q.m0, q.P0, q.carry, q.sfx, q.btst, q.utree,
                                    q.stats, q.info, (int64_t)blockIdx.x - q.tile0);
 }
 
@@ -4958,6 +5414,7 @@ srtm_status launch_all(const Batch& b, const Launch& g, bool smoother, int rec_m
     SRTM_EV(ev.post(st));
   }
   const size_t lds_fold = FoldLds<T, NX>(nlev_max).total;
+  const int nextra = (int)(g.nseq <= END_SEQS ? g.nseq * END_EXTRA : 0);
   // the last carry is an output of its own, or the only place where a last window's failure shows
   const int want_last = b.one.mf_slow || b.one.Pf_slow || rec_mode == REC_LL || rec_mode == REC_GRAD ? 1 : 0;
 
@@ -4970,7 +5427,7 @@ srtm_status launch_all(const Batch& b, const Launch& g, bool smoother, int rec_m
     SRTM_STAGE((k_fold<T, NX, NY, false, INP>), dim3(g.ntiles), dim3(TILE), lds_fold, st, b, want_last);
     if (rec_mode == 1) {
       if (!allow_lds((const void*)k_recover<T, NX, NY, 1, INP>, lds_rec)) return SRTM_E_HIP;
-      SRTM_STAGE((k_recover<T, NX, NY, 1, INP>), dim3(g.ntiles), dim3(TILE), lds_rec, st, b);
+      SRTM_STAGE((k_recover<T, NX, NY, 1, INP>), dim3(g.ntiles + nextra), dim3(TILE), lds_rec, st, b, nextra);
     } else {
       SRTM_EV(ev.pre(st));
       if (rec_mode == REC_LL) {
@@ -4990,10 +5447,10 @@ srtm_status launch_all(const Batch& b, const Launch& g, bool smoother, int rec_m
 
   if (rec_mode == 2) {
     if (!allow_lds((const void*)k_recover<T, NX, NY, 2, INP>, lds_rec)) return SRTM_E_HIP;
-    SRTM_STAGE((k_recover<T, NX, NY, 2, INP>), dim3(g.ntiles), dim3(TILE), lds_rec, st, b);
+    SRTM_STAGE((k_recover<T, NX, NY, 2, INP>), dim3(g.ntiles + nextra), dim3(TILE), lds_rec, st, b, nextra);
   } else if (rec_mode == 3 && lds_rec <= kMaxLdsBytes) {
     if (!allow_lds((const void*)k_recover<T, NX, NY, 3, INP>, lds_rec)) return SRTM_E_HIP;
-    SRTM_STAGE((k_recover<T, NX, NY, 3, INP>), dim3(g.ntiles), dim3(TILE), lds_rec, st, b);
+    SRTM_STAGE((k_recover<T, NX, NY, 3, INP>), dim3(g.ntiles + nextra), dim3(TILE), lds_rec, st, b, nextra);
   } else {
     SRTM_EV(ev.pre(st));
     if (rec_mode == REC_GRAD) {
@@ -5006,9 +5463,9 @@ srtm_status launch_all(const Batch& b, const Launch& g, bool smoother, int rec_m
       const size_t lds1 = (size_t)4 * OutStage<T, NX>::BYTES + ptab;
       if (!allow_lds((const void*)k_recover<T, NX, NY, 1, INP>, lds1)) return SRTM_E_HIP;
       if (!allow_lds((const void*)k_recover<T, NX, NY, 2, INP>, lds1)) return SRTM_E_HIP;
-      hipLaunchKernelGGL((k_recover<T, NX, NY, 1, INP>), dim3(g.ntiles), dim3(TILE), lds1, st, b);
+      hipLaunchKernelGGL((k_recover<T, NX, NY, 1, INP>), dim3(g.ntiles + nextra), dim3(TILE), lds1, st, b, nextra);
       SRTM_CHECK_LAUNCH();
-      hipLaunchKernelGGL((k_recover<T, NX, NY, 2, INP>), dim3(g.ntiles), dim3(TILE), lds1, st, b);
+      hipLaunchKernelGGL((k_recover<T, NX, NY, 2, INP>), dim3(g.ntiles + nextra), dim3(TILE), lds1, st, b, nextra);
       SRTM_CHECK_LAUNCH();
     }
     SRTM_EV(ev.post(st));
@@ -5051,7 +5508,7 @@ srtm_status launch_tv(const Batch& b, const Launch& g, bool smoother, int rec_mo
       SRTM_CHECK_LAUNCH();
       if (rec_mode == 1) {
         if (!allow_lds((const void*)k_recover<T, NX, NY, 1, false, true>, lds_rec)) return SRTM_E_HIP;
-        hipLaunchKernelGGL((k_recover<T, NX, NY, 1, false, true>), dim3(g.ntiles), dim3(TILE), lds_rec, st, b);
+        hipLaunchKernelGGL((k_recover<T, NX, NY, 1, false, true>), dim3(g.ntiles), dim3(TILE), lds_rec, st, b, 0);
         SRTM_CHECK_LAUNCH();
       }
       return SRTM_OK;
@@ -5066,11 +5523,11 @@ srtm_status launch_tv(const Batch& b, const Launch& g, bool smoother, int rec_mo
     if (rec_mode == 2 || rec_mode == 3) {  // filter and smoother outputs: two recovery passes
       if (rec_mode == 3) {
         if (!allow_lds((const void*)k_recover<T, NX, NY, 1, false, true>, lds_rec)) return SRTM_E_HIP;
-        hipLaunchKernelGGL((k_recover<T, NX, NY, 1, false, true>), dim3(g.ntiles), dim3(TILE), lds_rec, st, b);
+        hipLaunchKernelGGL((k_recover<T, NX, NY, 1, false, true>), dim3(g.ntiles), dim3(TILE), lds_rec, st, b, 0);
         SRTM_CHECK_LAUNCH();
       }
       if (!allow_lds((const void*)k_recover<T, NX, NY, 2, false, true>, lds_rec)) return SRTM_E_HIP;
-      hipLaunchKernelGGL((k_recover<T, NX, NY, 2, false, true>), dim3(g.ntiles), dim3(TILE), lds_rec, st, b);
+      hipLaunchKernelGGL((k_recover<T, NX, NY, 2, false, true>), dim3(g.ntiles), dim3(TILE), lds_rec, st, b, 0);
       SRTM_CHECK_LAUNCH();
     }
     return SRTM_OK;
@@ -5243,11 +5700,11 @@ __global__ void __launch_bounds__(TILE) km_recover(Batch b) {
 #define SRTM_MX(a, c)                                                           \
   if (d.nx == a && d.ny == c) {                                                 \
     if (d.tv) {                                                                 \
-      if constexpr (a <= TV_NX_MAX) kb_recover<T, a, c, 2, false, true>(b, blockIdx.x); \
+      if constexpr (a <= TV_NX_MAX) kb_recover<T, a, c, 2, false, true>(b, blockIdx.x, 0); \
     } else if (d.B) {                                                           \
-      kb_recover<T, a, c, 2, true>(b, blockIdx.x);                              \
+      kb_recover<T, a, c, 2, true>(b, blockIdx.x, 0);                           \
     } else {                                                                    \
-      kb_recover<T, a, c, 2, false>(b, blockIdx.x);                             \
+      kb_recover<T, a, c, 2, false>(b, blockIdx.x, 0);                          \
     }                                                                           \
     return;                                                                     \
   }
