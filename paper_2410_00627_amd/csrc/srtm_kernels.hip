@@ -1711,7 +1711,7 @@ struct FoldLds {
     tail = take(sizeof(double) * NZ * IS * 4);                             // information of N's low bits
     scratch = take(blocks4<NX>() ? sizeof(double) * 64 * 4 : 0);
     group = take(blocks4<NX>() ? sizeof(double) * 4 * 4 * 40 : 0);         // states of each wave's four groups
-    gain = take(blocks4<NX>() ? sizeof(T) * LOG_TILE * 2 * 2 * NN : 0);    // a settled tile's gains per level
+    gain = take(blocks4<NX>() ? sizeof(double) * LOG_TILE * 2 * 2 * NN : 0);    // a settled tile's gains per level
     total = o;
   }
 };
@@ -2446,8 +2446,10 @@ SRTM_DEV bool info_correction(const Model<T, NX, NY>& M, int L, const Window<T, 
 #pragma unroll
   for (int r = 0; r < NX; ++r) {
     A[r][r] += T(1);
+    double t = (double)eta[r];  // eta and J m nearly cancel
 #pragma unroll
-    for (int k = 0; k < NX; ++k) eta[r] = my_fma(-J[r][k], m[k], eta[r]);
+    for (int k = 0; k < NX; ++k) t = fma(-(double)J[r][k], (double)m[k], t);
+    eta[r] = (T)t;
   }
   const bool ok = inv_small(A, Ai);
   mv(Ai, eta, v);
@@ -2667,11 +2669,11 @@ SRTM_DEV void fold_body(const T* __restrict__ y, int64_t N, int L, int nlev, con
       const double Wt = B.inv_t(mm4(P, lv[(f ? 32 : 16) + 4 * B.r + B.c], B.eye), ok);
       const double G = mm4(Tt, mm4(Wt, B.eye, 0.0), 0.0);
       const double GP = mm4(Tt, Block4::mm_sym(Wt, P), 0.0);
-      T* gain = reinterpret_cast<T*>(smraw + lo.gain);
+      double* gain = reinterpret_cast<double*>(smraw + lo.gain);
       if (in4) {
-        T* row = gain + ((lvl * 2 + (f ? 0 : 1)) * NX + B.r) * R2;
-        row[B.c] = (T)G;
-        row[NX + B.c] = (T)GP;
+        double* row = gain + ((lvl * 2 + (f ? 0 : 1)) * NX + B.r) * R2;
+        row[B.c] = G;
+        row[NX + B.c] = GP;
       }
       if (!ok && (SMOOTH || f)) flag |= SRTM_INFO_COMBINE_SINGULAR;
       double* grp = reinterpret_cast<double*>(smraw + lo.group) + wv * 160;
@@ -2684,10 +2686,11 @@ SRTM_DEV void fold_body(const T* __restrict__ y, int64_t N, int L, int nlev, con
         }
       }
       __syncthreads();
+      double fv[NX], bv[NX];  // float64 for both types: as many instructions, one rounding at the end
 #pragma unroll
       for (int r = 0; r < NX; ++r) {
-        fs.u[r] = (T)grp[16 + r];
-        bs.u[r] = (T)grp[36 + r];
+        fv[r] = grp[16 + r];
+        bv[r] = grp[36 + r];
 #pragma unroll
         for (int c = r; c < NX; ++c) {
           fs.P[r][c] = fs.P[c][r] = (T)grp[4 * r + c];
@@ -2700,12 +2703,12 @@ SRTM_DEV void fold_body(const T* __restrict__ y, int64_t N, int L, int nlev, con
         if (SMOOTH || fw) {
           const int i = (tid >> p) ^ 1;
           const T* nd = p == 0 ? leaf + i * R2 : tree + (tree_off(p) + i) * R2;
-          const T* g = gain + (p * 2 + (fw ? 0 : 1)) * 2 * NN;
-          T x[NX], ve[NX], nu[NX];
+          const double* g = gain + (p * 2 + (fw ? 0 : 1)) * 2 * NN;
+          double x[NX], ve[NX], nu[NX];
 #pragma unroll
           for (int r = 0; r < NX; ++r) {
-            const T d = nd[r], e = nd[NX + r];
-            x[r] = fw ? fs.u[r] : bs.u[r];
+            const double d = (double)nd[r], e = (double)nd[NX + r];
+            x[r] = fw ? fv[r] : bv[r];
             ve[r] = fw ? e : -d;
             nu[r] = fw ? d : e;
           }
@@ -2719,10 +2722,15 @@ SRTM_DEV void fold_body(const T* __restrict__ y, int64_t N, int L, int nlev, con
           }
 #pragma unroll
           for (int r = 0; r < NX; ++r) {
-            fs.u[r] = fw ? nu[r] : fs.u[r];
-            bs.u[r] = fw ? bs.u[r] : nu[r];
+            fv[r] = fw ? nu[r] : fv[r];
+            bv[r] = fw ? bv[r] : nu[r];
           }
         }
+      }
+#pragma unroll
+      for (int r = 0; r < NX; ++r) {
+        fs.u[r] = (T)fv[r];
+        bs.u[r] = (T)bv[r];
       }
     } else {
       run(0xF0u);
@@ -4485,8 +4493,9 @@ SRTM_DEV void lag1_within(const Model<T, NX, NY>& M, const Window<T, NX, NY>& w,
 template <typename T, int NX, int NY>
 SRTM_DEV void lag1_body(const T* __restrict__ y, int64_t N, int L, const T* __restrict__ cst,
                         const T* __restrict__ carry, const T* __restrict__ sfx, const T* __restrict__ utree,
-                        T* __restrict__ Cs_fast, int32_t* info, int64_t tile) {
+                        T* __restrict__ Cs_fast, int32_t* info, int64_t tile, int part, int nparts) {
   static_assert(TILE == 256, "one workgroup per tile");
+  constexpr int NN = NX * NX;
   using Stg = OutStage<T, NX>;
   extern __shared__ char smraw[];
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
@@ -4500,6 +4509,17 @@ SRTM_DEV void lag1_body(const T* __restrict__ y, int64_t N, int L, const T* __re
   T m[NX], P[NX][NX], yk[NY];
   const int nw = tile_windows(N, tile);
   const bool settled = tile_settled<T, NX>(utree, tile);
+  int ibeg = 1, iend = L;  // this workgroup's fast steps
+  if (nparts > 1) {
+    if (settled) {
+      if (part > 0) return;
+    } else {
+      const int per = ((L + nparts - 1) / nparts + Stg::GM - 1) / Stg::GM * Stg::GM;
+      ibeg = part * per + 1;
+      if (ibeg > L) return;
+      iend = L < ibeg + per - 1 ? L : ibeg + per - 1;
+    }
+  }
   const int64_t col = tile * (TILE * info_stride(NX)) + (valid ? tid : 0);  // the window's records
   const int64_t mcol = settled ? tile * (TILE * info_stride(NX)) : col;
   record_load(m, P, carry + col, carry + mcol, nw);
@@ -4514,9 +4534,13 @@ SRTM_DEV void lag1_body(const T* __restrict__ y, int64_t N, int L, const T* __re
   load(A, M.cst + M.lay.A);
   T Pprev[NX][NX], PLprev[NX][NX], Uprev[NX][NY];
   bool fin = true;
-#pragma unroll 1
-  for (int i = 1; i <= L; ++i) {
-    T mf[NX], Pii[NX][NX], PiL[NX][NX], PLW[NX][NX], C[NX][NX];
+  auto seed = [&](int i) {  // what step i + 1 needs of step i
+    T mf[NX];
+    window_step<T, NX, NY, true>(M, w, i, mf, Pprev, PLprev);
+    window_U(M, w, i, Uprev);
+  };
+  auto cross = [&](int i, T (&C)[NX][NX]) {  // step i's cross-covariance, from the state that seed or cross left
+    T mf[NX], Pii[NX][NX], PiL[NX][NX], PLW[NX][NX];
     window_step<T, NX, NY, true>(M, w, i, mf, Pii, PiL);
     mm(PiL, W, PLW);
     if (i == 1) {  // across the window boundary, from the smoothed block of x_{k,1}
@@ -4553,9 +4577,41 @@ SRTM_DEV void lag1_body(const T* __restrict__ y, int64_t N, int L, const T* __re
         Pprev[r][c] = Pii[r][c];
         PLprev[r][c] = PiL[r][c];
       }
+  };
+  if (settled) {  // a thread per fast step, then every wave writes the records to its 64 windows (Stream)
+    constexpr int SC = 24, RB = NN * (int)sizeof(T);
+    static_assert(SC * RB <= 64 * Stg::SBP, "the records fit one wave's staging");
+#pragma unroll 1
+    for (int i0 = 1; i0 <= L; i0 += SC) {
+      const int ns = L - i0 + 1 < SC ? L - i0 + 1 : SC;
+      __syncthreads();  // the previous records are written
+      if (tid < ns) {
+        T C[NX][NX];
+        if (i0 + tid > 1) seed(i0 + tid - 1);
+        cross(i0 + tid, C);
+        T* o = reinterpret_cast<T*>(smraw + tid * RB);
+#pragma unroll
+        for (int r = 0; r < NX; ++r)
+#pragma unroll
+          for (int c = 0; c < NX; ++c) o[r * NX + c] = C[r][c];
+      }
+      __syncthreads();
+      Stream<RB> st(lane, ns, L);
+#pragma unroll 1
+      for (int j = 0; j < ns; ++j) st.put(smraw, reinterpret_cast<char*>(Cs_fast) + (w0 * L + (i0 - 1)) * RB);
+    }
+    if (!fin) flag |= SRTM_INFO_NONFINITE;
+    if (flag && info) atomicOr(info, flag);
+    return;
+  }
+  if (ibeg > 1) seed(ibeg - 1);
+#pragma unroll 1
+  for (int i = ibeg; i <= iend; ++i) {
+    T C[NX][NX];
+    cross(i, C);
     stg.put(lane, i, zero, C);
     wave_sync();
-    stg.flush(lane, nvalid, nullptr, Cs_fast, w0, L, i, L);
+    stg.flush(lane, nvalid, nullptr, Cs_fast, w0, L, i, iend);
     wave_sync();
   }
   if (!fin && valid) flag |= SRTM_INFO_NONFINITE;
@@ -4949,6 +5005,8 @@ SRTM_DEV void stats_body(const T* __restrict__ y, int64_t N, int L, const T* __r
   if (flag && info) atomicOr(info, flag);
 }
 
+constexpr int SF_THREADS = 512;
+
 // One workgroup per sequence: sums the tile records in a fixed order and forms the outputs
 // dF = Q^{-1} Swx, dQ = 1/2 Q^{-1} Sw Q^{-1}, dR = 1/2 R^{-1} Sy R^{-1}.
 template <typename T, int NX, int NY, bool GRAD>
@@ -4956,34 +5014,41 @@ SRTM_DEV void stats_final_body(int64_t nt, const T* __restrict__ Qm, const T* __
                                const double* __restrict__ parts, T* __restrict__ ll_out, T* __restrict__ dF,
                                T* __restrict__ dQ, T* __restrict__ dR, int32_t* info) {
   using SL = StatLayout<NX, NY>;
-  constexpr int NR = SL::SIZE, G = 16;
-  __shared__ double red[256][G];
+  constexpr int NR = SL::SIZE, NW = SF_THREADS / 64;
+  __shared__ double red[NW][NR];
   __shared__ double tot[NR];
-  const int tid = threadIdx.x;
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const int ncomp = GRAD ? NR : 1;
-  for (int c0 = 0; c0 < ncomp; c0 += G) {
-    double acc[G];
+  // The log-likelihood alone: a thread per tile. With the gradient, lane c of a wave sums component c (and
+  // c + 64 ..) of tiles wv, wv + NW, ... in order, eight records in flight. The waves' sums are added in
+  // order. With a tile per thread and a tree over 256 threads for 16 components at a time the kernel took
+  // 17 us for 64 tiles, almost all of it barriers and empty lanes.
+  if constexpr (!GRAD) {
+    double s = 0.0;
+    for (int64_t t = tid; t < nt; t += SF_THREADS) s += gld(parts + t * SL::SIZE + SL::LL);
+    s = wave_sum(s);
+    if (lane == 0) red[wv][SL::LL] = s;
+  } else {
+    for (int c = lane; c < ncomp; c += 64) {
+      double s = 0.0;
+      for (int64_t t0 = wv; t0 < nt; t0 += 8 * NW) {
+        double x[8];
 #pragma unroll
-    for (int j = 0; j < G; ++j) acc[j] = 0.0;
-    for (int64_t t = tid; t < nt; t += 256) {  // lane tid: tiles tid, tid + 256, ... in order
-      const double* p = parts + t * SL::SIZE + c0;
+        for (int j = 0; j < 8; ++j) x[j] = t0 + j * NW < nt ? gld(parts + (t0 + j * NW) * SL::SIZE + c) : 0.0;
 #pragma unroll
-      for (int j = 0; j < G; ++j)
-        if (c0 + j < ncomp) acc[j] += p[j];
-    }
-#pragma unroll
-    for (int j = 0; j < G; ++j) red[tid][j] = acc[j];
-    __syncthreads();
-    for (int s = 128; s >= 1; s >>= 1) {
-      if (tid < s) {
-#pragma unroll
-        for (int j = 0; j < G; ++j) red[tid][j] += red[tid + s][j];
+        for (int j = 0; j < 8; ++j) s += x[j];
       }
-      __syncthreads();
+      red[wv][c] = s;
     }
-    if (tid < G && c0 + tid < ncomp) tot[c0 + tid] = red[0][tid];
-    __syncthreads();
   }
+  __syncthreads();
+  for (int c = tid; c < ncomp; c += SF_THREADS) {
+    double s = red[0][c];
+#pragma unroll
+    for (int q = 1; q < NW; ++q) s += red[q][c];
+    tot[c] = s;
+  }
+  __syncthreads();
   if (tid != 0) return;
   if (ll_out) ll_out[0] = (T)tot[SL::LL];
   if constexpr (GRAD) {
@@ -5278,10 +5343,17 @@ __global__ void __launch_bounds__(64) k_seq(Batch b, int nseq) {
 
 template <typename T, int NX, int NY>
 __global__ void __launch_bounds__(TILE) k_lag1(Batch b) {
-  const Seq<T, NX, NY> q = seq_view<T, NX, NY>(b, tile_sequence(b));
+  const Seq<T, NX, NY> q = seq_view<T, NX, NY>(b, 0);  // one sequence; the parts of its end tiles first (kb_recover)
   if (!q.Cs_fast) return;
-  lag1_body<T, NX, NY>(q.y, q.N, q.L, q.cst, q.carry, q.sfx, q.utree, q.Cs_fast, q.info,
-                       (int64_t)blockIdx.x - q.tile0);
+  int64_t i = (int64_t)blockIdx.x - END_EXTRA;
+  int part = 0;
+  if (i < 0) {
+    i = blockIdx.x / (END_PARTS - 1);
+    part = 1 + blockIdx.x % (END_PARTS - 1);
+    if (i >= q.plan.nt) return;
+  }
+  lag1_body<T, NX, NY>(q.y, q.N, q.L, q.cst, q.carry, q.sfx, q.utree, q.Cs_fast, q.info, ends_first(i, q.plan.nt), part,
+                       i < END_TILES ? END_PARTS : 1);
 }
 
 template <typename T, int NX, int NY, bool GRAD, bool INP>
@@ -5294,7 +5366,7 @@ __global__ void __launch_bounds__(TILE) k_stats(Batch b) {
 // Outputs: the given arrays (one sequence), or else, per sequence of a batch, its four output
 // slots (ms_fast, Ps_fast, ms_slow, Ps_slow) hold ll, dF, dQ and dR.
 template <typename T, int NX, int NY, bool GRAD>
-__global__ void __launch_bounds__(256) k_stats_final(Batch b, T* ll, T* dF, T* dQ, T* dR) {
+__global__ void __launch_bounds__(SF_THREADS) k_stats_final(Batch b, T* ll, T* dF, T* dQ, T* dR) {
   const Seq<T, NX, NY> q = seq_view<T, NX, NY>(b, blockIdx.x);
   const bool own = ll == nullptr;
   stats_final_body<T, NX, NY, GRAD>(q.plan.nt, q.Q, q.R, q.stats, own ? q.ms_fast : ll,
@@ -5398,7 +5470,7 @@ srtm_status launch_all(const Batch& b, const Launch& g, bool smoother, int rec_m
       SRTM_CHECK_LAUNCH();
       hipLaunchKernelGGL((k_stats<T, NX, NY, true, INP>), dim3(g.ntiles), dim3(TILE), 0, st, b);
       SRTM_CHECK_LAUNCH();
-      hipLaunchKernelGGL((k_stats_final<T, NX, NY, true>), dim3(g.nseq), dim3(256), 0, st, b, lo.ll, lo.dF, lo.dQ,
+      hipLaunchKernelGGL((k_stats_final<T, NX, NY, true>), dim3(g.nseq), dim3(SF_THREADS), 0, st, b, lo.ll, lo.dF, lo.dQ,
                          lo.dR);
       SRTM_CHECK_LAUNCH();
       return SRTM_OK;
@@ -5433,7 +5505,7 @@ srtm_status launch_all(const Batch& b, const Launch& g, bool smoother, int rec_m
       if (rec_mode == REC_LL) {
         hipLaunchKernelGGL((k_stats<T, NX, NY, false, INP>), dim3(g.ntiles), dim3(TILE), 0, st, b);
         SRTM_CHECK_LAUNCH();
-        hipLaunchKernelGGL((k_stats_final<T, NX, NY, false>), dim3(g.nseq), dim3(256), 0, st, b, lo.ll, lo.dF,
+        hipLaunchKernelGGL((k_stats_final<T, NX, NY, false>), dim3(g.nseq), dim3(SF_THREADS), 0, st, b, lo.ll, lo.dF,
                            lo.dQ, lo.dR);
         SRTM_CHECK_LAUNCH();
       }
@@ -5456,7 +5528,7 @@ srtm_status launch_all(const Batch& b, const Launch& g, bool smoother, int rec_m
     if (rec_mode == REC_GRAD) {
       hipLaunchKernelGGL((k_stats<T, NX, NY, true, INP>), dim3(g.ntiles), dim3(TILE), 0, st, b);
       SRTM_CHECK_LAUNCH();
-      hipLaunchKernelGGL((k_stats_final<T, NX, NY, true>), dim3(g.nseq), dim3(256), 0, st, b, lo.ll, lo.dF, lo.dQ,
+      hipLaunchKernelGGL((k_stats_final<T, NX, NY, true>), dim3(g.nseq), dim3(SF_THREADS), 0, st, b, lo.ll, lo.dF, lo.dQ,
                          lo.dR);
       SRTM_CHECK_LAUNCH();
     } else if (rec_mode == 3) {  // filter and smoother staging do not fit together: two passes
@@ -5580,7 +5652,7 @@ srtm_status run(const srtm_shape& sh, const Ptrs& p, bool smoother, hipStream_t 
   if (s != SRTM_OK) return s;
   const size_t lds = (size_t)4 * OutStage<T, NX>::BYTES;
   if (!allow_lds((const void*)k_lag1<T, NX, NY>, lds)) return SRTM_E_HIP;
-  hipLaunchKernelGGL((k_lag1<T, NX, NY>), dim3(g.ntiles), dim3(TILE), lds, st, b);
+  hipLaunchKernelGGL((k_lag1<T, NX, NY>), dim3(g.ntiles + END_EXTRA), dim3(TILE), lds, st, b);
   SRTM_CHECK_LAUNCH();
   return SRTM_OK;
 }
