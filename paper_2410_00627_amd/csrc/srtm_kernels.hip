@@ -79,6 +79,13 @@ SRTM_DEV void staged_copy(int n, int tid, int nthr, LD ld, ST st) {
   }
 }
 
+// Wave-wide sum (fixed butterfly order, identical on every lane).
+SRTM_DEV double wave_sum(double v) {
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
+  return v;
+}
+
 // ============================================================================ constants
 // ---------------------------------------------------------------- 4 x 4 blocks on the matrix cores
 // Up to four NX x NX problems (NX <= 4, padded with zeros to 4 x 4) per wave, one matrix entry per
@@ -327,6 +334,73 @@ SRTM_DEV void chain_tail_body(T* __restrict__ cst, const double* __restrict__ ha
   if (f && info) atomicOr(info, f);
 }
 
+// Per-step tables of the constants kernel for NX <= 4, on the matrix cores: A^i, Q_ii, Sig_i = sum_{u=0..i} A^u and
+// al_i = sum_{j=1..i-1} A^{i-j} Q_jj for i = 0 .. L by doubling. With everything known up to s, for j = 1 .. s
+//   A^{s+j} = A^j A^s,   Q_{s+j} = Q_j + A^j Q_s A^{jT},   Sig_{s+j} = Sig_{j-1} + A^j Sig_s,
+//   al_{s+j} = al_j + A^j (al_s + Q_s Sig_{j-1}^T),
+// one block of lanes per j, then in one pass Q_il = Q_ii (A^{l-i})^T and c_i = (1/l) (al_i + Q_ii Sig_{l-i}^T) C^T.
+// Log2(l) stages of about 400 cycles; sums over the steps with one entry per thread took 14000 cycles for
+// l = 20 (each an LDS round trip per term). All 256 threads; LDS arrays as in constants_body. Every entry also
+// goes, unrounded, to the float64 copy.
+template <typename T, int NX, int NY>
+SRTM_DEV void step_tables4(int L, const ConstLayout& lay, T* __restrict__ cst, double* __restrict__ cst64,
+                           const double* sC, double* Apow, double* Qii, double* Sig, double* al, double* ci) {
+  constexpr int NN = NX * NX, NXY = NX * NY;
+  const int lane = threadIdx.x & 63, slot = (threadIdx.x >> 6) * 4 + ((lane >> 2) & 3);  // block among the 16
+  const int r = lane >> 4, c = lane & 3;
+  const bool in = r < NX && c < NX;
+  const int rc = in ? r * NX + c : 0, cr = in ? c * NX + r : 0;
+  auto get = [&](const double* a, int i, int o) { return in ? a[i * NN + o] : 0.0; };
+  for (int s = 1; s < L; s *= 2) {
+    const double As = get(Apow, s, rc), Qs = get(Qii, s, rc), Ss = get(Sig, s, rc), as = get(al, s, rc);
+    const int n = 2 * s < L ? s : L - s;  // j = 1 .. n
+    for (int j0 = 0; j0 < n; j0 += 16) {
+      const int j = j0 + slot + 1;
+      const bool act = j <= n;
+      const int jj = act ? j : 1;
+      const double AjT = get(Apow, jj, cr), Qj = get(Qii, jj, rc), Sj = get(Sig, jj - 1, rc), SjT = get(Sig, jj - 1, cr),
+                   aj = get(al, jj, rc);
+      const double nA = mm4(AjT, As, 0.0);
+      const double nQ = Block4::mm_sym(AjT, mm4(Qs, AjT, 0.0)) + Qj;
+      const double nS = mm4(AjT, Ss, Sj);
+      const double na = mm4(AjT, mm4(Qs, SjT, as), aj);
+      if (act && in) {
+        Apow[(s + j) * NN + rc] = nA;
+        Qii[(s + j) * NN + rc] = nQ;
+        Sig[(s + j) * NN + rc] = nS;
+        al[(s + j) * NN + rc] = na;
+      }
+    }
+    __syncthreads();
+  }
+  const double CT = r < NX && c < NY ? sC[c * NX + r] : 0.0, il = 1.0 / (double)L;
+  auto put = [&](int off, double v) {
+    cst[off] = (T)v;
+    cst64[off] = v;
+  };
+  for (int i0 = 0; i0 < L; i0 += 16) {
+    const int i = i0 + slot + 1;
+    const bool act = i <= L;
+    const int ii = act ? i : L;
+    const double Q = get(Qii, ii, rc);
+    const double QL = mm4(Q, get(Apow, L - ii, cr), 0.0);
+    const double tT = mm4(get(Sig, L - ii, cr), Q, get(al, ii, cr));  // (al_i + Q_ii Sig_{l-i}^T)^T
+    const double cv = mm4(tT, CT, 0.0) * il;
+    if (act && r < NX) {
+      const int base = lay.per_i + (i - 1) * lay.per_i_stride;
+      if (c < NX) {
+        put(base + lay.o_Ai + rc, Apow[i * NN + rc]);
+        put(base + lay.o_Qii + rc, Q);
+        put(base + lay.o_QiL + rc, QL);
+      }
+      if (c < NY) {
+        put(base + lay.o_ci + r * NY + c, cv);
+        ci[i * NXY + r * NY + c] = cv;
+      }
+    }
+  }
+}
+
 // One workgroup, float64 throughout. Per-step tables are built in LDS by parallel
 // loops; the slow-rate constants and the level tables by the lanes of wave 0.
 //
@@ -364,146 +438,156 @@ SRTM_DEV void constants_body(const T* __restrict__ Fm, const T* __restrict__ Qm,
   }
   for (int e = tid; e < NXY; e += nthr) sC[e] = (double)Hm[e];
   for (int e = tid; e < NY * NY; e += nthr) sR[e] = (double)Rm[e];
-  __syncthreads();
-
-  // A^i by doubling: A^i = A^s A^{i-s} for i in (s, 2s].
-  for (int s = 1; s < L; s *= 2) {
-    const int hi = (2 * s < L) ? 2 * s : L;
-    for (int e = tid; e < (hi - s) * NN; e += nthr) {
-      const int i = s + 1 + e / NN, rc = e % NN, r = rc / NX, c = rc % NX;
-      double acc = 0.0;
-      for (int k = 0; k < NX; ++k) acc += Apow[s * NN + r * NX + k] * Apow[(i - s) * NN + k * NX + c];
-      Apow[i * NN + rc] = acc;
-    }
-    __syncthreads();
-  }
-  // W2[t] = A^t Q A^tT, t = 0..L-1: one entry of the upper triangle per item, mirrored, so that
-  // every sum of these blocks is exactly symmetric.
-  for (int e = tid; e < L * NN; e += nthr) {
-    const int t = e / NN, rc = e % NN, r = rc / NX, c = rc % NX;
-    if (c < r) continue;
-    const double* At = Apow + t * NN;
-    double acc = 0.0;
-    for (int k = 0; k < NX; ++k) {
-      double aq = 0.0;
-      for (int j = 0; j < NX; ++j) aq += At[r * NX + j] * sQ[j * NX + k];
-      acc += aq * At[c * NX + k];
-    }
-    W2[t * NN + r * NX + c] = acc;
-    W2[t * NN + c * NX + r] = acc;
-  }
-  __syncthreads();
-  // Q_ii = sum_{t<i} W2[t] (Qii[0] = 0) and W1[s] = Sig_s = sum_{u=0}^{s} A^u. Item (i, rc) forms
-  // entry rc of Q_{i+1,i+1} (i < l) and of Sig_i, each as four independent partial sums (a
-  // running sum would chain one LDS round trip per term).
-  auto sum_blocks = [&](const double* src, int n, int rc) {
-    double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0;
-    int t = 0;
-    for (; t + 4 <= n; t += 4) {
-      a0 += src[t * NN + rc];
-      a1 += src[(t + 1) * NN + rc];
-      a2 += src[(t + 2) * NN + rc];
-      a3 += src[(t + 3) * NN + rc];
-    }
-    for (; t < n; ++t) a0 += src[t * NN + rc];
-    return (a0 + a1) + (a2 + a3);
-  };
-  for (int e = tid; e < (L + 1) * NN; e += nthr) {
-    const int i = e / NN, rc = e % NN;
-    if (i < L) Qii[(i + 1) * NN + rc] = sum_blocks(W2, i + 1, rc);
-    if (i == 0) Qii[rc] = 0.0;
-    W1[i * NN + rc] = sum_blocks(Apow, i + 1, rc);
-  }
-  __syncthreads();
-  // CS[s] = C Sig_s (NY x NX) in W2[0 ..], QC[j] = Q_jj C^T (NX x NY) in W2[(L+1) NXY ..]; beside
-  // them the per-step tables go to the constants block: A^i, Q_ii, Q_il = Q_ii (A^{l-i})^T, and
-  // A, Q. Every entry of the model part (below the level tables) also goes, unrounded, to the
-  // float64 copy.
-  double* CS = W2;
-  double* QC = W2 + (L + 1) * NXY;
   auto put = [&](int off, double v) {
     cst[off] = (T)v;
     cst64[off] = v;
   };
-  for (int e = tid; e < (L + 1) * NXY + (L + 1) * NN; e += nthr) {
-    if (e < (L + 1) * NXY) {
-      const int s = e / NXY, rc = e % NXY;
-      {
-        const int r = rc / NX, c = rc % NX;  // CS: NY x NX
-        double acc = 0.0;
-        for (int k = 0; k < NX; ++k) acc += sC[r * NX + k] * W1[s * NN + k * NX + c];
-        CS[s * NXY + rc] = acc;
-      }
-      {
-        const int r = rc / NY, c = rc % NY;  // QC: NX x NY
-        double acc = 0.0;
-        for (int k = 0; k < NX; ++k) acc += Qii[s * NN + r * NX + k] * sC[c * NX + k];
-        QC[s * NXY + rc] = acc;
-      }
-    } else if (e < (L + 1) * NXY + L * NN) {
-      const int e2 = e - (L + 1) * NXY;
-      const int i = 1 + e2 / NN, rc = e2 % NN, r = rc / NX, c = rc % NX;
-      const int base = lay.per_i + (i - 1) * lay.per_i_stride;
-      put(base + lay.o_Ai + rc, Apow[i * NN + rc]);
-      put(base + lay.o_Qii + rc, Qii[i * NN + rc]);
-      double acc = 0.0;
-      for (int k = 0; k < NX; ++k) acc += Qii[i * NN + r * NX + k] * Apow[(L - i) * NN + c * NX + k];
-      put(base + lay.o_QiL + rc, acc);
-    } else {
-      const int q = e - (L + 1) * NXY - L * NN;
-      put(lay.A + q, sA[q]);
-      put(lay.Q + q, sQ[q]);
+  if constexpr (NX <= 4) {
+    for (int e = tid; e < NN; e += nthr) {
+      const double eye = e / NX == e % NX ? 1.0 : 0.0, a = (double)Fm[e];
+      // the symmetric part of Q, as its sums use it (upper triangle mirrored)
+      const int r = e / NX, c = e % NX;
+      Qii[e] = W2[e] = W2[NN + e] = 0.0;  // Q_0, al_0, al_1
+      Qii[NN + e] = (double)Qm[r <= c ? e : c * NX + r];
+      W1[e] = eye;
+      W1[NN + e] = eye + a;
+      put(lay.A + e, a);
+      put(lay.Q + e, (double)Qm[e]);
     }
-  }
-  __syncthreads();
-  // c_i = (1/l) [ sum_{j<i} A^{i-j} Q_jj C^T + Q_ii (C Sig_{l-i})^T ], the sum over j as four
-  // independent partial sums.
-  for (int e = tid; e < L * NXY; e += nthr) {
-    const int i = 1 + e / NXY, rc = e % NXY, r = rc / NY, c = rc % NY;
-    double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0;
-    for (int k = 0; k < NX; ++k) a0 += Qii[i * NN + r * NX + k] * CS[(L - i) * NXY + c * NX + k];
-    int j = 1;
-    for (; j + 4 <= i; j += 4)
-      for (int k = 0; k < NX; ++k) {
-        a0 += Apow[(i - j) * NN + r * NX + k] * QC[j * NXY + k * NY + c];
-        a1 += Apow[(i - j - 1) * NN + r * NX + k] * QC[(j + 1) * NXY + k * NY + c];
-        a2 += Apow[(i - j - 2) * NN + r * NX + k] * QC[(j + 2) * NXY + k * NY + c];
-        a3 += Apow[(i - j - 3) * NN + r * NX + k] * QC[(j + 3) * NXY + k * NY + c];
+    __syncthreads();
+    step_tables4<T, NX, NY>(L, lay, cst, cst64, sC, Apow, Qii, W1, W2, ci);
+    __syncthreads();
+  } else {
+    __syncthreads();
+    // A^i by doubling: A^i = A^s A^{i-s} for i in (s, 2s].
+    for (int s = 1; s < L; s *= 2) {
+      const int hi = (2 * s < L) ? 2 * s : L;
+      for (int e = tid; e < (hi - s) * NN; e += nthr) {
+        const int i = s + 1 + e / NN, rc = e % NN, r = rc / NX, c = rc % NX;
+        double acc = 0.0;
+        for (int k = 0; k < NX; ++k) acc += Apow[s * NN + r * NX + k] * Apow[(i - s) * NN + k * NX + c];
+        Apow[i * NN + rc] = acc;
       }
-    for (; j < i; ++j)
-      for (int k = 0; k < NX; ++k) a0 += Apow[(i - j) * NN + r * NX + k] * QC[j * NXY + k * NY + c];
-    ci[i * NXY + rc] = ((a0 + a1) + (a2 + a3)) / (double)L;
+      __syncthreads();
+    }
+    // W2[t] = A^t Q A^tT, t = 0..L-1: one entry of the upper triangle per item, mirrored, so that
+    // every sum of these blocks is exactly symmetric.
+    for (int e = tid; e < L * NN; e += nthr) {
+      const int t = e / NN, rc = e % NN, r = rc / NX, c = rc % NX;
+      if (c < r) continue;
+      const double* At = Apow + t * NN;
+      double acc = 0.0;
+      for (int k = 0; k < NX; ++k) {
+        double aq = 0.0;
+        for (int j = 0; j < NX; ++j) aq += At[r * NX + j] * sQ[j * NX + k];
+        acc += aq * At[c * NX + k];
+      }
+      W2[t * NN + r * NX + c] = acc;
+      W2[t * NN + c * NX + r] = acc;
+    }
+    __syncthreads();
+    // Q_ii = sum_{t<i} W2[t] (Qii[0] = 0) and W1[s] = Sig_s = sum_{u=0}^{s} A^u. Item (i, rc) forms
+    // entry rc of Q_{i+1,i+1} (i < l) and of Sig_i, each as four independent partial sums (a
+    // running sum would chain one LDS round trip per term).
+    auto sum_blocks = [&](const double* src, int n, int rc) {
+      double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0;
+      int t = 0;
+      for (; t + 4 <= n; t += 4) {
+        a0 += src[t * NN + rc];
+        a1 += src[(t + 1) * NN + rc];
+        a2 += src[(t + 2) * NN + rc];
+        a3 += src[(t + 3) * NN + rc];
+      }
+      for (; t < n; ++t) a0 += src[t * NN + rc];
+      return (a0 + a1) + (a2 + a3);
+    };
+    for (int e = tid; e < (L + 1) * NN; e += nthr) {
+      const int i = e / NN, rc = e % NN;
+      if (i < L) Qii[(i + 1) * NN + rc] = sum_blocks(W2, i + 1, rc);
+      if (i == 0) Qii[rc] = 0.0;
+      W1[i * NN + rc] = sum_blocks(Apow, i + 1, rc);
+    }
+    __syncthreads();
+    // CS[s] = C Sig_s (NY x NX) in W2[0 ..], QC[j] = Q_jj C^T (NX x NY) in W2[(L+1) NXY ..]; beside
+    // them the per-step tables go to the constants block: A^i, Q_ii, Q_il = Q_ii (A^{l-i})^T, and
+    // A, Q. Every entry of the model part (below the level tables) also goes, unrounded, to the
+    // float64 copy.
+    double* CS = W2;
+    double* QC = W2 + (L + 1) * NXY;
+    for (int e = tid; e < (L + 1) * NXY + (L + 1) * NN; e += nthr) {
+      if (e < (L + 1) * NXY) {
+        const int s = e / NXY, rc = e % NXY;
+        {
+          const int r = rc / NX, c = rc % NX;  // CS: NY x NX
+          double acc = 0.0;
+          for (int k = 0; k < NX; ++k) acc += sC[r * NX + k] * W1[s * NN + k * NX + c];
+          CS[s * NXY + rc] = acc;
+        }
+        {
+          const int r = rc / NY, c = rc % NY;  // QC: NX x NY
+          double acc = 0.0;
+          for (int k = 0; k < NX; ++k) acc += Qii[s * NN + r * NX + k] * sC[c * NX + k];
+          QC[s * NXY + rc] = acc;
+        }
+      } else if (e < (L + 1) * NXY + L * NN) {
+        const int e2 = e - (L + 1) * NXY;
+        const int i = 1 + e2 / NN, rc = e2 % NN, r = rc / NX, c = rc % NX;
+        const int base = lay.per_i + (i - 1) * lay.per_i_stride;
+        put(base + lay.o_Ai + rc, Apow[i * NN + rc]);
+        put(base + lay.o_Qii + rc, Qii[i * NN + rc]);
+        double acc = 0.0;
+        for (int k = 0; k < NX; ++k) acc += Qii[i * NN + r * NX + k] * Apow[(L - i) * NN + c * NX + k];
+        put(base + lay.o_QiL + rc, acc);
+      } else {
+        const int q = e - (L + 1) * NXY - L * NN;
+        put(lay.A + q, sA[q]);
+        put(lay.Q + q, sQ[q]);
+      }
+    }
+    __syncthreads();
+    // c_i = (1/l) [ sum_{j<i} A^{i-j} Q_jj C^T + Q_ii (C Sig_{l-i})^T ], the sum over j as four
+    // independent partial sums.
+    for (int e = tid; e < L * NXY; e += nthr) {
+      const int i = 1 + e / NXY, rc = e % NXY, r = rc / NY, c = rc % NY;
+      double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0;
+      for (int k = 0; k < NX; ++k) a0 += Qii[i * NN + r * NX + k] * CS[(L - i) * NXY + c * NX + k];
+      int j = 1;
+      for (; j + 4 <= i; j += 4)
+        for (int k = 0; k < NX; ++k) {
+          a0 += Apow[(i - j) * NN + r * NX + k] * QC[j * NXY + k * NY + c];
+          a1 += Apow[(i - j - 1) * NN + r * NX + k] * QC[(j + 1) * NXY + k * NY + c];
+          a2 += Apow[(i - j - 2) * NN + r * NX + k] * QC[(j + 2) * NXY + k * NY + c];
+          a3 += Apow[(i - j - 3) * NN + r * NX + k] * QC[(j + 3) * NXY + k * NY + c];
+        }
+      for (; j < i; ++j)
+        for (int k = 0; k < NX; ++k) a0 += Apow[(i - j) * NN + r * NX + k] * QC[j * NXY + k * NY + c];
+      ci[i * NXY + rc] = ((a0 + a1) + (a2 + a3)) / (double)L;
+    }
+    __syncthreads();
   }
-  __syncthreads();
 
-  // c_i to the constants block; C_bar = (C/l)(Sig_l - I) and R_x = (1/l) sum_i C c_i + R into LDS
-  // (W2 is free again).
+  // c_i to the constants block (nx > 4); C_bar = (C/l)(Sig_l - I) and R_x = (1/l) sum_i C c_i + R into LDS (W2 is
+  // free again), an entry of R_x per wave with its sum over (i, k) spread over the lanes.
   double* sCbar = W2;
   double* sRx = W2 + NXY;
-  for (int e = tid; e < L * NXY + NXY + NY * NY; e += nthr) {
-    if (e < L * NXY) {
+  const int nci = NX <= 4 ? 0 : L * NXY;
+  for (int e = tid; e < nci + NXY; e += nthr) {
+    if (e < nci) {
       const int i = 1 + e / NXY, rc = e % NXY;
       put(lay.per_i + (i - 1) * lay.per_i_stride + lay.o_ci + rc, ci[i * NXY + rc]);
-    } else if (e < L * NXY + NXY) {
-      const int q = e - L * NXY, r = q / NX, c = q % NX;
+    } else {
+      const int q = e - nci, r = q / NX, c = q % NX;
       double acc = 0.0;
       for (int k = 0; k < NX; ++k) acc += sC[r * NX + k] * (W1[L * NN + k * NX + c] - (k == c ? 1.0 : 0.0));
       sCbar[q] = acc / (double)L;
-    } else {
-      const int q = e - L * NXY - NXY, r = q / NY, c = q % NY;
-      double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0;
-      int i = 1;
-      for (; i + 4 <= L + 1; i += 4)
-        for (int k = 0; k < NX; ++k) {
-          a0 += sC[r * NX + k] * ci[i * NXY + k * NY + c];
-          a1 += sC[r * NX + k] * ci[(i + 1) * NXY + k * NY + c];
-          a2 += sC[r * NX + k] * ci[(i + 2) * NXY + k * NY + c];
-          a3 += sC[r * NX + k] * ci[(i + 3) * NXY + k * NY + c];
-        }
-      for (; i <= L; ++i)
-        for (int k = 0; k < NX; ++k) a0 += sC[r * NX + k] * ci[i * NXY + k * NY + c];
-      sRx[q] = ((a0 + a1) + (a2 + a3)) / (double)L + sR[r * NY + c];
     }
+  }
+  for (int q = tid >> 6; q < NY * NY; q += nthr >> 6) {
+    const int r = q / NY, c = q % NY;
+    double acc = 0.0;
+    for (int t = tid & 63; t < L * NX; t += 64) acc += sC[r * NX + t % NX] * ci[NXY + t * NY + c];
+    acc = wave_sum(acc);
+    if ((tid & 63) == 0) sRx[q] = acc / (double)L + sR[q];
   }
   __syncthreads();
   if (tid >= 64) return;  // the rest is done by wave 0
@@ -4663,13 +4747,6 @@ SRTM_DEV T det_small(const T (&a)[N][N]) {
     return a[0][0];
   else
     return a[0][0] * a[1][1] - a[0][1] * a[1][0];
-}
-
-// Wave-wide sum (fixed butterfly order, identical on every lane).
-SRTM_DEV double wave_sum(double v) {
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
-  return v;
 }
 
 template <typename T, int R, int C>
