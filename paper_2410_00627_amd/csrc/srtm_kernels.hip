@@ -1595,7 +1595,7 @@ SRTM_DEV int smoother_element(const MV& M, int L, const Window<T, NX, NY>& w, bo
 // own set bits below it (fold section). The run that bit p of k asks for is always the sibling of the
 // node that holds k at that level, (k >> p) ^ 1.
 // Levels 1 .. 7 lie within a tile (TILE windows) and are kept per tile in `utree`, node i of level p in
-// slot tree_off(p) + i, 2 nx scalars (d, eta) per slot; level-0 nodes are the window's own elements and are
+// slot tree_off(p) + i of 2 nx rows (d, eta) of TILE slots; level-0 nodes are the window's own elements and are
 // formed again from y where they are needed. Level 8 (whole tiles) is `ftagg`, and the levels above it
 // follow each other in `ttree` (tile_level_off).
 inline __host__ __device__ constexpr int tree_off(int p) { return TILE - (TILE >> (p - 1)); }
@@ -1611,20 +1611,20 @@ SRTM_DEV int top_bit(int64_t x) { return x > 0 ? 63 - __clzll(x) : -1; }
 // Combination of the vector parts of two neighbouring runs of 2^p elements, one output row per thread
 // (rows 0 .. nx-1: d, nx .. 2nx-1: eta). Row r of a level's coefficient table is 2 nx scalars:
 //   d = d_r + G1 d_l + G2 eta_r  (G1, G2),   eta = eta_l + G3 eta_r - G4 d_l  (G3, -G4).
-// A thread that formed the whole pair instead read all 4 nx^2 coefficients for it, and those reads set the
+// Child row c at [c * stride]. A thread that formed the whole pair instead read all 4 nx^2 coefficients for it, and those reads set the
 // time of a level (about 1 us of a wave in either precision, at nx = 4).
 template <int NX>
 constexpr int row_slots() { return 2 * NX <= 2 ? 2 : 2 * NX <= 4 ? 4 : 2 * NX <= 8 ? 8 : 16; }
 
 template <typename T, int NX>
-SRTM_DEV T row_combine(const T* __restrict__ co, const T* __restrict__ left, const T* __restrict__ right, int r) {
-  T acc = r < NX ? right[r] : left[r];
-  const T* a = r < NX ? left : right + NX;
-  const T* b = r < NX ? right + NX : left;
+SRTM_DEV T row_combine(const T* __restrict__ co, const T* __restrict__ left, const T* __restrict__ right, int r, int stride) {
+  T acc = r < NX ? right[r * stride] : left[r * stride];
+  const T* a = r < NX ? left : right + NX * stride;
+  const T* b = r < NX ? right + NX * stride : left;
 #pragma unroll
   for (int k = 0; k < NX; ++k) {
-    acc = my_fma(co[k], a[k], acc);
-    acc = my_fma(co[NX + k], b[k], acc);
+    acc = my_fma(co[k], a[k * stride], acc);
+    acc = my_fma(co[NX + k], b[k * stride], acc);
   }
   return acc;
 }
@@ -1635,6 +1635,54 @@ template <typename T, int NX>
 SRTM_DEV T row_coefficient(const T* __restrict__ lev, const ConstLayout& lay, int q) {
   constexpr int RT = 4 * NX * NX;
   return gld(lev + (q / RT) * lay.lev_stride + lay.o_C + q % RT);
+}
+
+// The same combination for NX <= 4 on the matrix cores, 16 pairs at a time: lane 16 k + col holds row k of the
+// children of output node col, and the level's four coefficient matrices are A operands held in registers.
+// Rows of LDS slots are read as whole left/right pairs. Read one output row per thread, the children and
+// coefficients conflicted in the LDS banks, about 600 cycles for 32 pairs against 150 for 64.
+template <typename T, int NX>
+struct PairCoef {
+  double g1, g2, g3, g4;  // entries (lane & 3, lane >> 4) of G1, G2, G3, -G4
+  SRTM_DEV void load_lds(const T* rows) {
+    const int lane = threadIdx.x & 63, r = lane & 3, c = lane >> 4;
+    const bool in = r < NX && c < NX;
+    const T* C = rows + (in ? r * 2 * NX + c : 0);
+    g1 = in ? (double)C[0] : 0.0;
+    g2 = in ? (double)C[NX] : 0.0;
+    g3 = in ? (double)C[2 * NX * NX] : 0.0;
+    g4 = in ? (double)C[2 * NX * NX + NX] : 0.0;
+  }
+  SRTM_DEV void load(const T* __restrict__ rows) {
+    const int lane = threadIdx.x & 63, r = lane & 3, c = lane >> 4;
+    const bool in = r < NX && c < NX;
+    const T* C = rows + (in ? r * 2 * NX + c : 0);
+    g1 = in ? (double)gld(C) : 0.0;
+    g2 = in ? (double)gld(C + NX) : 0.0;
+    g3 = in ? (double)gld(C + 2 * NX * NX) : 0.0;
+    g4 = in ? (double)gld(C + 2 * NX * NX + NX) : 0.0;
+  }
+};
+
+// Output nodes 16 g .. 16 g + 15 (those below n) of one level: children at src[row * stride + 2 i (+ 1)],
+// results to dst[row * stride + i].
+template <typename T, int NX>
+SRTM_DEV void pair_combine(const PairCoef<T, NX>& co, const T* src, T* dst, int stride, int g, int n) {
+  typedef T T2 __attribute__((ext_vector_type(2)));
+  const int lane = threadIdx.x & 63, k = lane >> 4, i = 16 * g + (lane & 15);
+  const bool in = k < NX && i < n;
+  T2 d = {T(0), T(0)}, e = {T(0), T(0)};
+  if (in) {
+    d = *reinterpret_cast<const T2*>(src + k * stride + 2 * i);
+    e = *reinterpret_cast<const T2*>(src + (NX + k) * stride + 2 * i);
+  }
+  const double dl = (double)d.x, dr = (double)d.y, el = (double)e.x, er = (double)e.y;
+  const double nd = mm4(co.g2, er, mm4(co.g1, dl, dr));
+  const double ne = mm4(co.g4, dl, mm4(co.g3, er, el));
+  if (in) {
+    dst[k * stride + i] = (T)nd;
+    dst[(NX + k) * stride + i] = (T)ne;
+  }
 }
 
 // Vector part (d, eta) of window k's filter element from its measurement yt (y_k - mu_k with
@@ -1654,27 +1702,34 @@ SRTM_DEV void fwd_element(const Model<T, NX, NY>& M, const T (&yt)[NY], const T 
 }
 
 // K1: the dyadic tree of one tile over the vector parts (d, eta) of its windows' filter elements: levels
-// 1 .. LOG_TILE-1 to `utree`, the tile's own node to `ftagg`. One thread per node and output row
-// (row_combine), so that a level reads 4 nx scalars of coefficients per thread and is a few hundred cycles.
-template <bool INP, typename T, int NX, int NY>
+// 1 .. LOG_TILE-1 to `utree`, the tile's own node to `ftagg`. nx <= 4: pairs on the matrix cores
+// (pair_combine). nx > 4, and the float32 gradient, whose results keep their rounding (ROWS): one thread
+// per node and output row (row_combine).
+template <bool INP, bool ROWS, typename T, int NX, int NY>
 SRTM_DEV void fwd_reduce_body(const T* __restrict__ y, int64_t N, const T* __restrict__ cst, int L,
                               InputView<T> in, T* __restrict__ tagg, T* __restrict__ utree, int64_t tile) {
   constexpr int NN = NX * NX, R2 = 2 * NX, RS2 = row_slots<NX>();
   extern __shared__ char smraw[];
-  T* leaf = reinterpret_cast<T*>(smraw);  // TILE elements, then the tree's TILE slots, then
+  T* leaf = reinterpret_cast<T*>(smraw);  // rows of TILE elements, then of the tree's TILE slots, then (ROWS)
   T* tree = leaf + R2 * TILE;
   T* sC = tree + R2 * TILE;               // the row tables of levels 0 .. LOG_TILE-1
   const Model<T, NX, NY> M{cst, make_const_layout(NX, NY, L), in};
-  const int tid = threadIdx.x;
+  const int tid = threadIdx.x, wv = tid >> 6;
   const int64_t k = tile * TILE + tid;
   // The level records were written by an earlier launch, possibly on another die: one load per
   // coefficient, all in flight together, instead of a dependent round trip per level.
-  constexpr int NC = LOG_TILE * 4 * NN, PC = (NC + TILE - 1) / TILE;
-  T cv[PC], yt[NY], zL[NX], d[NX], e[NX];
+  constexpr int NC = ROWS ? LOG_TILE * 4 * NN : 0, PC = (NC + TILE - 1) / TILE;
+  T cv[PC > 0 ? PC : 1], yt[NY], zL[NX], d[NX], e[NX];
+  PairCoef<T, (NX <= 4 ? NX : 1)> co[LOG_TILE];
+  if constexpr (ROWS) {
 #pragma unroll
-  for (int i = 0; i < PC; ++i) {
-    const int q = i * TILE + tid;
-    cv[i] = q < NC ? row_coefficient<T, NX>(M.level(0), M.lay, q) : T(0);
+    for (int i = 0; i < PC; ++i) {
+      const int q = i * TILE + tid;
+      cv[i] = q < NC ? row_coefficient<T, NX>(M.level(0), M.lay, q) : T(0);
+    }
+  } else {
+#pragma unroll
+    for (int p = 0; p < LOG_TILE; ++p) co[p].load(M.level(p) + M.lay.o_C);
   }
   if constexpr (INP) {  // one pass over the window's inputs; later kernels read the record
     if (k < N) {
@@ -1693,37 +1748,60 @@ SRTM_DEV void fwd_reduce_body(const T* __restrict__ y, int64_t N, const T* __res
   } else {
     window_meas<false>(M, y, k, N, yt, zL);
   }
+  if constexpr (ROWS) {
 #pragma unroll
-  for (int i = 0; i < PC; ++i) {
-    const int q = i * TILE + tid;
-    if (q < NC) sC[q] = cv[i];
+    for (int i = 0; i < PC; ++i) {
+      const int q = i * TILE + tid;
+      if (q < NC) sC[q] = cv[i];
+    }
   }
   fwd_element<INP>(M, yt, zL, d, e);
 #pragma unroll
   for (int r = 0; r < NX; ++r) {
-    leaf[tid * R2 + r] = d[r];
-    leaf[tid * R2 + NX + r] = e[r];
+    leaf[r * TILE + tid] = d[r];
+    leaf[(NX + r) * TILE + tid] = e[r];
   }
   __syncthreads();
-  const int row = tid % RS2;
+  constexpr int NT = tree_off(LOG_TILE);  // slots of levels 1 .. LOG_TILE-1
+  if constexpr (ROWS) {
+    const int row = tid % RS2;
 #pragma unroll 1
-  for (int p = 1; p <= LOG_TILE; ++p) {
-    const T* src = p == 1 ? leaf : tree + tree_off(p - 1) * R2;
-    T* dst = tree + tree_off(p) * R2;
-    const int n = TILE >> p;
-    if (row < R2) {
-      T co[R2];
+    for (int p = 1; p <= LOG_TILE; ++p) {
+      const T* src = p == 1 ? leaf : tree + tree_off(p - 1);
+      T* dst = tree + tree_off(p);
+      const int n = TILE >> p;
+      if (row < R2) {
+        T cr[R2];
 #pragma unroll
-      for (int k2 = 0; k2 < R2; ++k2) co[k2] = sC[((p - 1) * R2 + row) * R2 + k2];
-      for (int i = tid / RS2; i < n; i += TILE / RS2)
-        dst[i * R2 + row] = row_combine<T, NX>(co, src + 2 * i * R2, src + (2 * i + 1) * R2, row);
+        for (int k2 = 0; k2 < R2; ++k2) cr[k2] = sC[((p - 1) * R2 + row) * R2 + k2];
+        for (int i = tid / RS2; i < n; i += TILE / RS2)
+          dst[row * TILE + i] = row_combine<T, NX>(cr, src + 2 * i, src + 2 * i + 1, row, TILE);
+      }
+      __syncthreads();
+    }
+  } else {
+    // levels 1 .. 3 by all waves, the rest by wave 0
+#pragma unroll
+    for (int p = 1; p <= LOG_TILE; ++p) {
+      const T* src = p == 1 ? leaf : tree + tree_off(p > 1 ? p - 1 : 1);
+      const int n = TILE >> p;
+      if (p <= 3) {
+        for (int g = wv; g < n / 16; g += TILE / 64) pair_combine<T, NX>(co[p - 1], src, tree + tree_off(p), TILE, g, n);
+        __syncthreads();
+      } else if (wv == 0) {
+        pair_combine<T, NX>(co[p - 1], src, tree + tree_off(p), TILE, 0, n);
+        wave_sync();
+      }
     }
     __syncthreads();
   }
-  constexpr int NT = tree_off(LOG_TILE);  // slots of levels 1 .. LOG_TILE-1
   T* ut = utree + tile * (R2 * TILE);
-  for (int q = tid; q < NT * R2; q += TILE) put_global(ut + q, tree[q]);
-  if (tid < R2) put_global(tagg + tile * R2 + tid, tree[NT * R2 + tid]);
+  constexpr int NCH = R2 * TILE * (int)sizeof(T) / 16;
+  for (int q = tid; q < NCH; q += TILE) {
+    const u32x4 v = reinterpret_cast<const u32x4*>(tree)[q];
+    put_global(reinterpret_cast<u32x4*>(ut) + q, v);
+  }
+  if (tid < R2) put_global(tagg + tile * R2 + tid, tree[tid * TILE + NT]);
 }
 
 // ---------------------------------------------------------------- fold: states and information
@@ -1842,9 +1920,9 @@ SRTM_DEV void stage_blocks(const T* __restrict__ cst, const double* __restrict__
 // Float64: 2^-47, some rounding errors of one combine. Float32: 2^-26, a quarter of its rounding.
 template <typename T>
 SRTM_DEV constexpr double settled_tol() { return sizeof(T) == 8 ? 0x1p-47 : 0x1p-26; }
-// Whether a tile is settled is kept in the last slot of its tree (levels 1 .. 7 leave two slots free).
+// Whether a tile is settled is kept in the last slot of its tree's first row (levels 1 .. 7 leave two free).
 template <typename T, int NX>
-SRTM_DEV T* settled_flag(T* utree, int64_t tile) { return utree + tile * (2 * NX * TILE) + (TILE - 1) * 2 * NX; }
+SRTM_DEV T* settled_flag(T* utree, int64_t tile) { return utree + tile * (2 * NX * TILE) + TILE - 1; }
 template <typename T, int NX>
 SRTM_DEV bool tile_settled(const T* utree, int64_t tile) {
   if constexpr (NX > 4) return false;
@@ -1904,9 +1982,9 @@ SRTM_DEV void record_store(const T (&u)[NX], const T (&P)[NX][NX], T* __restrict
   }
 }
 
-// One lane's combine with the run (d, e) of level tables `tab` = (F, Dp, Jp) as staged for its direction.
+// One lane's combine with the run (d, e), row r at nd[r * stride], of level tables `tab` = (F, Dp, Jp) as staged for its direction.
 template <typename T, int NX, typename S>
-SRTM_DEV bool lane_combine(Belief<T, NX>& b, const T* __restrict__ tab, const S* __restrict__ nd, bool fwd) {
+SRTM_DEV bool lane_combine(Belief<T, NX>& b, const T* __restrict__ tab, const S* __restrict__ nd, int stride, bool fwd) {
   constexpr int NN = NX * NX;
   T F[NX][NX], D[NX][NX], J[NX][NX], d[NX], e[NX];
   load(F, tab);
@@ -1914,7 +1992,7 @@ SRTM_DEV bool lane_combine(Belief<T, NX>& b, const T* __restrict__ tab, const S*
   load(J, tab + 2 * NN);
 #pragma unroll
   for (int r = 0; r < NX; ++r) {
-    const T nd_d = (T)nd[r], nd_e = (T)nd[NX + r];
+    const T nd_d = (T)nd[r * stride], nd_e = (T)nd[(NX + r) * stride];
     d[r] = fwd ? nd_d : nd_e;
     e[r] = fwd ? nd_e : -nd_d;
   }
@@ -1922,11 +2000,12 @@ SRTM_DEV bool lane_combine(Belief<T, NX>& b, const T* __restrict__ tab, const S*
 }
 
 // Information of N's set bits below each bit (tail), low bits first, for a sequence's last windows.
-// `node(p)` is the (d, eta) of N's node of level p, 2 nx scalars in LDS; entry q of `out` (info_stride scalars
+// `node(p)` is the (d, eta) of N's node of level p, row r at node(p)[r * stride] in LDS; entry q of `out` (info_stride scalars
 // each) receives the information of N's set bits below bit q, q = 0 .. qmax. One wave; every block of
 // lanes (every lane, nx > 4) computes the same chain.
 template <typename T, int NX, class ND>
-SRTM_DEV bool tail_chain(const double* lev, const T* lane, double* scratch, int64_t N, int qmax, ND node, double* out) {
+SRTM_DEV bool tail_chain(const double* lev, const T* lane, double* scratch, int64_t N, int qmax, ND node, int stride,
+                         double* out) {
   constexpr int NN = NX * NX, IS = info_stride(NX);
   bool ok = true;
   if constexpr (blocks4<NX>()) {
@@ -1941,7 +2020,7 @@ SRTM_DEV bool tail_chain(const double* lev, const T* lane, double* scratch, int6
       if (q < qmax && ((N >> q) & 1)) {
         const double* lv = lev + q * 48;
         const auto* nd = node(q);
-        const double d = B.r < NX ? (double)nd[B.r] : 0.0, e = B.r < NX ? (double)nd[NX + B.r] : 0.0;
+        const double d = B.r < NX ? (double)nd[B.r * stride] : 0.0, e = B.r < NX ? (double)nd[(NX + B.r) * stride] : 0.0;
         if (!combine4(B, u, P, lv[4 * B.r + B.c], lv[32 + 4 * B.r + B.c], lv[16 + 4 * B.r + B.c], e, -d)) ok = false;
       }
     }
@@ -1960,7 +2039,7 @@ SRTM_DEV bool tail_chain(const double* lev, const T* lane, double* scratch, int6
         }
       }
       if (q < qmax && ((N >> q) & 1)) {
-        if (!lane_combine(b, lane + (size_t)q * 6 * NN + 3 * NN, node(q), false)) ok = false;
+        if (!lane_combine(b, lane + (size_t)q * 6 * NN + 3 * NN, node(q), stride, false)) ok = false;
       }
     }
   }
@@ -2040,14 +2119,15 @@ SRTM_DEV void tile_tree_body(const T* __restrict__ y, int64_t N, int nlev, const
     const T* ut = utree + (N >> LOG_TILE) * (R2 * TILE);
     for (int q = tid; q < (LOG_TILE - 1) * R2; q += nthr) {
       const int p = 1 + q / R2;
-      if ((N >> p) & 1) own[p * R2 + q % R2] = gld(ut + (tree_off(p) + (((int)(N & (TILE - 1)) >> p) ^ 1)) * R2 + q % R2);
+      if ((N >> p) & 1) own[p * R2 + q % R2] = gld(ut + (q % R2) * TILE + tree_off(p) + (((int)(N & (TILE - 1)) >> p) ^ 1));
     }
     if (tid == nthr - 1 && (N & 1)) last_element<INP>(M, y, N, own);
   }
   // Up-sweep; level LOG_TILE + q has nf >> q nodes. Levels longer than the LDS buffer go through device
-  // memory (each of them waits for its stores); the others stay in LDS and are stored together at the end,
-  // so that no level waits for a store to arrive.
-  const int row = tid % RS2;
+  // memory (each of them waits for its stores); the others stay in LDS, rows of 2 TT_NODES slots, and are
+  // stored together at the end, so that no level waits for a store to arrive.
+  constexpr int ST = 2 * TT_NODES;
+  const int row = tid % RS2, wv = tid >> 6;
   int q0 = 0;              // first level kept in LDS
   while ((nf >> q0) > TT_NODES) ++q0;
   {
@@ -2061,43 +2141,49 @@ SRTM_DEV void tile_tree_body(const T* __restrict__ y, int64_t N, int nlev, const
       if (row < R2)
         for (int64_t i = tid / RS2; i < nn; i += nthr / RS2)
           put_global(dst + i * R2 + row, row_combine<T, NX>(sC + ((q - 1) * R2 + row) * R2, src + 2 * i * R2,
-                                                            src + (2 * i + 1) * R2, row));
+                                                            src + (2 * i + 1) * R2, row, 1));
       src = dst;
       dst += nn * R2;
     }
     if (q0) __syncthreads();
     const int n = (int)(nf >> q0);
-    for (int q = tid; q < n * R2; q += nthr) nodes[q] = gld(src + q);
+    staged_copy<8, T>(n * R2, tid, nthr, [&](int q) { return gld(src + q); },
+                      [&](int q, T v) { nodes[(q % R2) * ST + q / R2] = v; });
     __syncthreads();
     int at = 0;  // the level below
 #pragma unroll 1
     for (int q = q0 + 1; (nf >> q) > 0; ++q) {
       const int below = (int)(nf >> (q - 1)), nn = (int)(nf >> q);
-      const T* lsrc = nodes + at * R2;
-      T* ldst = nodes + (at + below) * R2;
-      if (row < R2) {
+      const int to = (at + below + 1) & ~1;  // pairs are read whole: even slots
+      if constexpr (NX <= 4) {
+        PairCoef<T, NX> co;
+        co.load_lds(sC + (q - 1) * 4 * NN);
+        for (int g = wv; g < (nn + 15) / 16; g += nthr >> 6) pair_combine<T, NX>(co, nodes + at, nodes + to, ST, g, nn);
+      } else if (row < R2) {
         T co[R2];
 #pragma unroll
         for (int k2 = 0; k2 < R2; ++k2) co[k2] = sC[((q - 1) * R2 + row) * R2 + k2];
         for (int i = tid / RS2; i < nn; i += nthr / RS2)
-          ldst[i * R2 + row] = row_combine<T, NX>(co, lsrc + 2 * i * R2, lsrc + (2 * i + 1) * R2, row);
+          nodes[row * ST + to + i] = row_combine<T, NX>(co, nodes + at + 2 * i, nodes + at + 2 * i + 1, row, ST);
       }
-      at += below;
+      at = to;
       __syncthreads();
     }
-    for (int q = tid; q < (at + 1 - n) * R2; q += nthr) put_global(dst + q, nodes[n * R2 + q]);  // level q0 is in place
-    if (smoother && tid < R2) {  // N's nodes
-      int o = 0;
-      for (int q = q0; (nf >> q) > 0; ++q) {
-        const int cnt = (int)(nf >> q);
-        if (cnt & 1) own[(LOG_TILE + q) * R2 + tid] = nodes[(o + cnt - 1) * R2 + tid];
-        o += cnt;
+    // the levels above q0 to device memory, and N's nodes
+    int o = 0;
+    for (int q = q0; (nf >> q) > 0; ++q) {
+      const int cnt = (int)(nf >> q);
+      if (q > q0) {
+        for (int e = tid; e < cnt * R2; e += nthr) put_global(dst + e, nodes[(e % R2) * ST + o + e / R2]);
+        dst += cnt * R2;
       }
+      if (smoother && (cnt & 1) && tid < R2) own[(LOG_TILE + q) * R2 + tid] = nodes[tid * ST + o + cnt - 1];
+      o = (o + cnt + 1) & ~1;
     }
   }
   __syncthreads();
   if (smoother && tid < 64) {
-    const bool ok = tail_chain<T, NX>(lev, lane, scratch, N, top_bit(N), [&](int p) { return own + p * R2; }, tail);
+    const bool ok = tail_chain<T, NX>(lev, lane, scratch, N, top_bit(N), [&](int p) { return own + p * R2; }, 1, tail);
     if (!ok && info) atomicOr(info, SRTM_INFO_COMBINE_SINGULAR);
   }
 }
@@ -2585,7 +2671,7 @@ SRTM_DEV void fold_body(const T* __restrict__ y, int64_t N, int L, int nlev, con
 
   // ---- everything the fold reads, in one round of loads: all of them are issued before the first
   // is stored to LDS (one memory round trip instead of one per table)
-  constexpr int NCH = tree_off(LOG_TILE) * R2 * (int)sizeof(T) / 16, PCH = (NCH + TILE - 1) / TILE;
+  constexpr int NCH = TILE * R2 * (int)sizeof(T) / 16, PCH = (NCH + TILE - 1) / TILE;
   constexpr int PLV = B4 ? (MAXLEV * 48 + TILE - 1) / TILE : 1;
   u32x4 tv[PCH];
   const char* tsrc = reinterpret_cast<const char*>(utree + tile * (R2 * TILE));
@@ -2624,8 +2710,8 @@ SRTM_DEV void fold_body(const T* __restrict__ y, int64_t N, int L, int nlev, con
     fwd_element<INP>(M, yt, zL, d, e);
 #pragma unroll
     for (int r = 0; r < NX; ++r) {
-      leaf[tid * R2 + r] = d[r];
-      leaf[tid * R2 + NX + r] = e[r];
+      leaf[r * TILE + tid] = d[r];
+      leaf[(NX + r) * TILE + tid] = e[r];
     }
   }
 #pragma unroll
@@ -2646,8 +2732,8 @@ SRTM_DEV void fold_body(const T* __restrict__ y, int64_t N, int L, int nlev, con
   if constexpr (SMOOTH) {
     if (single) {  // each wave its own copy
       const bool ok = tail_chain<T, NX>(lev, lane, scratch, N, top_bit(N), [&](int p) {
-        return p == 0 ? leaf + (rem ^ 1) * R2 : tree + (tree_off(p) + ((rem >> p) ^ 1)) * R2;
-      }, tail);
+        return p == 0 ? leaf + (rem ^ 1) : tree + tree_off(p) + ((rem >> p) ^ 1);
+      }, TILE, tail);
       if (!ok) flag |= SRTM_INFO_COMBINE_SINGULAR;
       wave_sync();
     }
@@ -2683,6 +2769,7 @@ SRTM_DEV void fold_body(const T* __restrict__ y, int64_t N, int L, int nlev, con
     auto fetch = [&](int p) {
       Step st;
       const T* nd;
+      int ns = 1;
       if (p >= LOG_TILE) {
         st.f = (tile >> (p - LOG_TILE)) & 1;
         st.act = true;
@@ -2691,13 +2778,14 @@ SRTM_DEV void fold_body(const T* __restrict__ y, int64_t N, int L, int nlev, con
         const int i = g >> (p - LB);
         st.f = i & 1;
         st.act = st.f || (SMOOTH && p < bw);
-        nd = tree + (tree_off(p) + (i ^ 1)) * R2;
+        nd = tree + tree_off(p) + (i ^ 1);
+        ns = TILE;
       }
       const double* lv = lev + p * 48;
       st.Tt = lv[st.f ? 4 * B.c + B.r : 4 * B.r + B.c];
       st.Dp = lv[(st.f ? 16 : 32) + 4 * B.r + B.c];
       st.Jp = lv[(st.f ? 32 : 16) + 4 * B.r + B.c];
-      const double d = B.r < NX ? (double)nd[B.r] : 0.0, e = B.r < NX ? (double)nd[NX + B.r] : 0.0;
+      const double d = B.r < NX ? (double)nd[B.r * ns] : 0.0, e = B.r < NX ? (double)nd[(NX + B.r) * ns] : 0.0;
       st.vd = st.f ? d : e;
       st.ve = st.f ? e : -d;
       return st;
@@ -2786,12 +2874,12 @@ SRTM_DEV void fold_body(const T* __restrict__ y, int64_t N, int L, int nlev, con
         const bool fw = (tid >> p) & 1;
         if (SMOOTH || fw) {
           const int i = (tid >> p) ^ 1;
-          const T* nd = p == 0 ? leaf + i * R2 : tree + (tree_off(p) + i) * R2;
+          const T* nd = p == 0 ? leaf + i : tree + tree_off(p) + i;
           const double* g = gain + (p * 2 + (fw ? 0 : 1)) * 2 * NN;
           double x[NX], ve[NX], nu[NX];
 #pragma unroll
           for (int r = 0; r < NX; ++r) {
-            const double d = (double)nd[r], e = (double)nd[NX + r];
+            const double d = (double)nd[r * TILE], e = (double)nd[(NX + r) * TILE];
             x[r] = fw ? fv[r] : bv[r];
             ve[r] = fw ? e : -d;
             nu[r] = fw ? d : e;
@@ -2866,7 +2954,7 @@ SRTM_DEV void fold_body(const T* __restrict__ y, int64_t N, int L, int nlev, con
 #pragma unroll
         for (int c = 0; c < NX; ++c) x.P[r][c] = f ? fs.P[r][c] : bs.P[r][c];
       }
-      if (!lane_combine(x, lane + (size_t)(LOG_TILE + q) * 6 * NN + (f ? 0 : 3 * NN), node + q * R2, f))
+      if (!lane_combine(x, lane + (size_t)(LOG_TILE + q) * 6 * NN + (f ? 0 : 3 * NN), node + q * R2, 1, f))
         flag |= SRTM_INFO_COMBINE_SINGULAR;
       if (f) fs = x;
       else bs = x;
@@ -2879,7 +2967,7 @@ SRTM_DEV void fold_body(const T* __restrict__ y, int64_t N, int L, int nlev, con
     const bool f = (tid >> p) & 1;
     const bool act = f || (SMOOTH && p < bl);
     const int i = (tid >> p) ^ 1;
-    const T* nd = p == 0 ? leaf + i * R2 : tree + (tree_off(p) + i) * R2;
+    const T* nd = p == 0 ? leaf + i : tree + tree_off(p) + i;
     if (SMOOTH || f) {
       Belief<T, NX> x;
 #pragma unroll
@@ -2888,7 +2976,7 @@ SRTM_DEV void fold_body(const T* __restrict__ y, int64_t N, int L, int nlev, con
 #pragma unroll
         for (int c = 0; c < NX; ++c) x.P[r][c] = f ? fs.P[r][c] : bs.P[r][c];
       }
-      const bool ok = lane_combine(x, lane + (size_t)p * 6 * NN + (f ? 0 : 3 * NN), nd, f);
+      const bool ok = lane_combine(x, lane + (size_t)p * 6 * NN + (f ? 0 : 3 * NN), nd, TILE, f);
       if (act && !ok) flag |= SRTM_INFO_COMBINE_SINGULAR;
 #pragma unroll
       for (int r = 0; r < NX; ++r) {
@@ -2925,7 +3013,7 @@ SRTM_DEV void fold_body(const T* __restrict__ y, int64_t N, int L, int nlev, con
     }
   }
   if (want_last && k == N - 1 && rem == 0) {
-    if (!lane_combine(fs, lane, leaf + tid * R2, true)) flag |= SRTM_INFO_COMBINE_SINGULAR;
+    if (!lane_combine(fs, lane, leaf + tid, TILE, true)) flag |= SRTM_INFO_COMBINE_SINGULAR;
     flag |= store_slow(k, fs.u, fs.P, m_slow, P_slow);
   }
   if (flag && info) atomicOr(info, flag);
@@ -3339,14 +3427,14 @@ SRTM_DEV int fwd_tile_states(const Model<T, NX, NY>& M, T* sm, const T (&yt)[NY]
   int flag = 0;
   T* leaf = sm;
   T* tree = sm + R2 * TILE;
-  for (int q = tid; q < tree_off(LOG_TILE) * R2; q += TILE) tree[q] = gld(ut + q);
+  for (int q = tid; q < TILE * R2; q += TILE) tree[q] = gld(ut + q);
   {
     T d[NX], e[NX];
     fwd_element<INP>(M, yt, zL, d, e);
 #pragma unroll
     for (int r = 0; r < NX; ++r) {
-      leaf[tid * R2 + r] = d[r];
-      leaf[tid * R2 + NX + r] = e[r];
+      leaf[r * TILE + tid] = d[r];
+      leaf[(NX + r) * TILE + tid] = e[r];
     }
   }
   if (k == 0) {  // the prior itself
@@ -3362,12 +3450,12 @@ SRTM_DEV int fwd_tile_states(const Model<T, NX, NY>& M, T* sm, const T (&yt)[NY]
   for (int p = LOG_TILE - 1; p >= 0; --p) {
     if ((tid >> p) & 1) {
       const int i = (tid >> p) ^ 1;
-      const T* nd = p == 0 ? leaf + i * R2 : tree + (tree_off(p > 0 ? p : 1) + i) * R2;
+      const T* nd = p == 0 ? leaf + i : tree + tree_off(p > 0 ? p : 1) + i;
       T dl[NX], el[NX];
 #pragma unroll
       for (int r = 0; r < NX; ++r) {
-        dl[r] = nd[r];
-        el[r] = nd[NX + r];
+        dl[r] = nd[r * TILE];
+        el[r] = nd[(NX + r) * TILE];
       }
       const T* lv = M.level(p);
       T F[NX][NX], D[NX][NX], J[NX][NX];
@@ -5256,7 +5344,7 @@ SRTM_DEV void kb_constants(const Batch& b, int64_t bid) {
 
 // Workgroups 0 .. nseq-1 continue the level chains of the sequences; the others reduce tile
 // bid - nseq of the call.
-template <typename T, int NX, int NY, bool INP>
+template <typename T, int NX, int NY, bool INP, bool ROWS = (NX > 4)>
 SRTM_DEV void kb_fwd_reduce(const Batch& b, int64_t bid, int nseq) {
   if (bid < nseq) {
     const Seq<T, NX, NY> q = seq_view<T, NX, NY>(b, (int)bid);
@@ -5265,7 +5353,7 @@ SRTM_DEV void kb_fwd_reduce(const Batch& b, int64_t bid, int nseq) {
   }
   const int64_t t = bid - nseq;
   const Seq<T, NX, NY> q = seq_view<T, NX, NY>(b, tile_sequence(b, t));
-  fwd_reduce_body<INP, T, NX, NY>(q.y, q.N, q.cst, q.L, q.in, q.ftagg, q.utree, t - q.tile0);
+  fwd_reduce_body<INP, ROWS, T, NX, NY>(q.y, q.N, q.cst, q.L, q.in, q.ftagg, q.utree, t - q.tile0);
 }
 
 template <typename T, int NX, int NY, bool INP>
@@ -5350,9 +5438,9 @@ __global__ void __launch_bounds__(256) k_constants(Batch b) {
   kb_constants<T, NX, NY>(b, blockIdx.x);
 }
 
-template <typename T, int NX, int NY, bool INP>
+template <typename T, int NX, int NY, bool INP, bool ROWS = (NX > 4)>
 __global__ void __launch_bounds__(TILE) k_fwd_reduce(Batch b, int nseq) {
-  kb_fwd_reduce<T, NX, NY, INP>(b, blockIdx.x, nseq);
+  kb_fwd_reduce<T, NX, NY, INP, ROWS>(b, blockIdx.x, nseq);
 }
 
 template <typename T, int NX, int NY, bool INP>
@@ -5527,7 +5615,12 @@ srtm_status launch_all(const Batch& b, const Launch& g, bool smoother, int rec_m
   SRTM_STAGE((k_constants<T, NX, NY>), dim3(g.nseq), dim3(256), lds0, st, b);
 
   constexpr size_t lds_red = fwd_reduce_lds_bytes<T, NX>();
-  SRTM_STAGE((k_fwd_reduce<T, NX, NY, INP>), dim3(g.ntiles + g.nseq), dim3(TILE), lds_red, st, b, (int)g.nseq);
+  if (grad_by_elements<T>() && rec_mode == REC_GRAD) {
+    SRTM_STAGE((k_fwd_reduce<T, NX, NY, INP, NX <= 4 ? grad_by_elements<T>() : true>), dim3(g.ntiles + g.nseq), dim3(TILE),
+               lds_red, st, b, (int)g.nseq);
+  } else {
+    SRTM_STAGE((k_fwd_reduce<T, NX, NY, INP>), dim3(g.ntiles + g.nseq), dim3(TILE), lds_red, st, b, (int)g.nseq);
+  }
 
   const int nlev_max = make_scan_plan((int64_t)g.ntiles * TILE).nlev;
   if constexpr (grad_by_elements<T>()) {
