@@ -2444,21 +2444,22 @@ struct OutStage {
   char* pbuf;
   char* mbuf;
   SRTM_DEV OutStage(char* base) : pbuf(base), mbuf(base + 64 * SBP) {}
-  // blocks of fast step i (1-based)
-  SRTM_DEV void put(int lane, int i, const T (&m)[NX], const T (&P)[NX][NX]) const {
-    T* pp = reinterpret_cast<T*>(pbuf + lane * SBP) + ((i - 1) % GP) * NN;
+  // blocks of the workgroup's fast step ph (0-based)
+  SRTM_DEV void put(int lane, int ph, const T (&m)[NX], const T (&P)[NX][NX]) const {
+    T* pp = reinterpret_cast<T*>(pbuf + lane * SBP) + (ph % GP) * NN;
 #pragma unroll
     for (int r = 0; r < NX; ++r)
 #pragma unroll
       for (int c = 0; c < NX; ++c) pp[r * NX + c] = P[r][c];
-    T* mp = reinterpret_cast<T*>(mbuf + lane * SBM) + ((i - 1) % GM) * NX;
+    T* mp = reinterpret_cast<T*>(mbuf + lane * SBM) + (ph % GM) * NX;
 #pragma unroll
     for (int r = 0; r < NX; ++r) mp[r] = m[r];
   }
-  // After put(i): flush the covariance and mean groups that step i completes. The record of
-  // window w0 + w for fast steps i0 .. i0+g-1 starts at out[((w0 + w) L + i0 - 1) * size].
-  SRTM_DEV void flush(int lane, int nvalid, T* m_out, T* P_out, int64_t w0, int L, int i, int ilim) const {
-    const int sp = (i - 1) % GP, sm = (i - 1) % GM;
+  // After put(ph): flush the covariance and mean groups that it completes; ph is fast step i (1-based) and ilim
+  // the workgroup's last. The record of window w0 + w for fast steps i0 .. i0+g-1 starts at
+  // out[((w0 + w) L + i0 - 1) * size].
+  SRTM_DEV void flush(int lane, int nvalid, T* m_out, T* P_out, int64_t w0, int L, int ph, int i, int ilim) const {
+    const int sp = ph % GP, sm = ph % GM;
     if (P_out && (sp == GP - 1 || i == ilim)) {
       T* dst = P_out + (w0 * L + (i - sp - 1)) * NN;
       if (sp == GP - 1)
@@ -3538,6 +3539,59 @@ SRTM_DEV auto recover_model(const T* __restrict__ cst, int L, const InputView<T>
 
 struct NoSteps {};
 
+// The fast steps of a window do not wait for each other, so a tile's can be split over workgroups, each of
+// which repeats what precedes the steps. A tile that has not settled is slow (nx = 4, L = 20, float64: about
+// 40 us for its workgroup), and with few tiles that is the launch:
+//   - where tiles settle (nx <= 4), the slow ones of the first END_TILES tiles of a sequence (ends_first) take 5
+//     parts, or 3 once there is a tile for every compute unit; a batch of more than END_SEQS sequences fills the
+//     device without them. 32767 windows (128 tiles, with inputs, float64): 37 us in 3 parts, 29 us in 5; 276 tiles of
+//     15 sequences (float32): 27 us in 3 parts, 31 us in 5.
+//   - every tile takes as many parts as let all workgroups run at once; where tiles settle, which leaves a
+//     part little but what it repeats, half as many (128 tiles, 2 parts: 41 us against 32 us whole).
+// Recovery of 16000 windows (63 tiles) at nx = 6 in float32: 95 us whole, 37 us in 4 parts; 6000 windows at
+// nx = 4 in float64: 17.5 us with the end tiles alone split, 14.7 us in 5 parts.
+struct Split {
+  int extra, all, ends;  // extra workgroups, first in the grid, for the end tiles; parts of any tile, of an end tile
+};
+constexpr int CUS = 256, END_TILES = 8, END_SEQS = 16, MAX_PARTS = 8, MIN_STEPS = 4;
+template <int NX>
+inline Split make_split(int64_t ntiles, int64_t nseq) {
+  const int64_t fit = (NX <= 4 ? CUS / 2 : CUS) / ntiles;
+  const int all = (int)(fit < 1 ? 1 : fit > MAX_PARTS ? MAX_PARTS : fit);
+  const int ends = ntiles < CUS ? 5 : 3;
+  if (NX > 4 || nseq > END_SEQS || all >= ends) return Split{0, all, all};
+  return Split{(int)nseq * END_TILES * (ends - 1), all, ends};
+}
+// The tile's number in its sequence (ends_first) and its part for workgroup bid, given the grid's numbering.
+SRTM_DEV void split_place(const Split& sp, int64_t bid, int& seq, int64_t& i, int& part) {
+  if (bid < sp.extra) {
+    const int per = sp.ends - 1, e = (int)bid / per;
+    part = 1 + (int)bid % per;
+    seq = e / END_TILES;
+    i = e % END_TILES;
+  } else {
+    const unsigned w = (unsigned)(bid - sp.extra);
+    seq = -1;
+    i = w / (unsigned)sp.all;  // counted over all sequences
+    part = (int)(w % (unsigned)sp.all);
+  }
+}
+
+// Part `part` of the fast steps 1 .. n, beg .. end (none: beg > n): of nslow parts of a tile that has not
+// settled, of nparts of one that has. MIN_STEPS at least, and for nx <= 4 multiples of it: groups of means stay whole.
+template <int NX>
+struct StepShare {
+  int beg, end;
+  SRTM_DEV StepShare(int n, int part, int nparts, int nslow, bool settled) {
+    const int np = settled ? nparts : nslow;
+    int per = (n + np - 1) / np;
+    if (per < MIN_STEPS) per = MIN_STEPS;
+    if (NX <= 4) per = (per + MIN_STEPS - 1) / MIN_STEPS * MIN_STEPS;
+    beg = part < np ? part * per + 1 : n + 1;
+    end = n < beg + per - 1 ? n : beg + per - 1;
+  }
+};
+
 // Fast steps whose tables the time-invariant recovery holds in LDS at a time.
 constexpr int RSTEPS = 32;
 
@@ -3545,8 +3599,8 @@ constexpr int RSTEPS = 32;
 // MODE bit 1: filter blocks p(x_{k,i} | y_{1:k}); bit 2: smoothed blocks p(x_{k,i} | y_{1:N})
 // (and the smoother's slow state, block i = 1) from the correction (v, W) that K3s left as
 // terms linear in the smoothed state entering the tile; a workgroup covers exactly one tile.
-// `ilim` is L when fast-rate outputs are requested and 1 when only the slow smoothed state is. Part `part` of
-// `nparts` takes its share of the fast steps (kb_recover).
+// `ilim` is L when fast-rate outputs are requested and 1 when only the slow smoothed state is. Part `part`
+// takes its share of the fast steps (StepShare).
 // TV: per-window model; `cst` then holds the per-window constants blocks (stored by tv_column)
 // and Fa, Qa (with in.H) the per-window F, Q and H.
 template <typename T, int NX, int NY, int MODE, bool INP, bool TV = false>
@@ -3557,7 +3611,7 @@ SRTM_DEV void recover_body(const T* __restrict__ y, int64_t N, int L, int ilim, 
                            T* __restrict__ mf_fast,
                            T* __restrict__ Pf_fast, T* __restrict__ ms_fast, T* __restrict__ Ps_fast,
                            T* __restrict__ ms_slow, T* __restrict__ Ps_slow, int32_t* info, int64_t tile, int part,
-                           int nparts) {
+                           int nparts, int nslow) {
   constexpr int NN = NX * NX, ST = NX + NN, SF = sfx_stride(NX);
   static_assert(TILE == 256, "one recovery workgroup per tile");
   constexpr bool FILT = (MODE & 1) != 0, SMOOTH = (MODE & 2) != 0;
@@ -3585,15 +3639,11 @@ SRTM_DEV void recover_body(const T* __restrict__ y, int64_t N, int L, int ilim, 
   bool settled = false;  // the tile's windows share their covariances
   if constexpr (!TV) settled = tile_settled<T, NX>(utree, tile);
   int ibeg = 1;  // this workgroup's fast steps are ibeg .. ilim
-  if (!TV && nparts > 1) {
-    if (settled) {
-      if (part > 0) return;
-    } else {  // whole groups of means per part
-      const int per = ((ilim + nparts - 1) / nparts + Stg::GM - 1) / Stg::GM * Stg::GM;
-      ibeg = part * per + 1;
-      if (ibeg > ilim) return;
-      ilim = ilim < ibeg + per - 1 ? ilim : ibeg + per - 1;
-    }
+  if constexpr (!TV) {
+    const StepShare<NX> share(ilim, part, nparts, nslow, settled);
+    if (share.beg > ilim) return;
+    ibeg = share.beg;
+    ilim = share.end;
   }
   const int64_t col = tile * (TILE * info_stride(NX)) + (valid ? tid : 0);  // the window's records
   const int64_t mcol = settled ? tile * (TILE * info_stride(NX)) : col;
@@ -3699,6 +3749,7 @@ SRTM_DEV void recover_body(const T* __restrict__ y, int64_t N, int L, int ilim, 
       constexpr int RB = NN * (int)sizeof(T);
       static_assert(SC * RB <= 64 * Stg::SBP && SC * KBS * 128 <= 64 * Stg::SBP && KBS * 4 * 512 <= 4 * 64 * Stg::SBP,
                     "each table fits one wave's covariance staging");
+      static_assert(SC % Stg::GM == 0, "a chunk of steps begins a group of means");
       char* tab_s = smraw;                                                   // P^s of the steps
       double* row_s = reinterpret_cast<double*>(smraw + (size_t)Stg::BYTES);   // rows of the smoothed means
       char* tab_f = smraw + (size_t)2 * Stg::BYTES;                          // P^f
@@ -3734,14 +3785,21 @@ SRTM_DEV void recover_body(const T* __restrict__ y, int64_t N, int L, int ilim, 
         for (int n = 0; n < 4; ++n)
           un4[n] = bk < M.in.nu && i <= ilim ? (double)gld(M.in.u + ((w0 + 16 * n + bw) * L + (i - 1)) * M.in.nu + bk) : 0.0;
       };
+      auto advance = [&](int i) {
+#pragma unroll
+        for (int n = 0; n < 4; ++n) zr[n] = mm4(Aop, zr[n], mm4(Bop, un4[n], 0.0));
+        load_u(i + 1);
+      };
       if constexpr (INP) {
         Aop = bc < NX && bk < NX ? (double)gld(M.cst + M.lay.A + bc * NX + bk) : 0.0;
         Bop = bc < NX && bk < M.in.nu ? (double)gld(M.in.B + bc * M.in.nu + bk) : 0.0;
         load_u(1);
+#pragma unroll 1
+        for (int i = 1; i < ibeg; ++i) advance(i);
       }
       auto base_of = [&](T* out, int i) { return reinterpret_cast<char*>(out) + (w0 * L + (i - 1)) * RB; };
 #pragma unroll 1
-      for (int i0 = 1; i0 <= ilim; i0 += SC) {
+      for (int i0 = ibeg; i0 <= ilim; i0 += SC) {
         const int ns = ilim - i0 + 1 < SC ? ilim - i0 + 1 : SC;
         stage_steps(i0);  // its first barrier also ends the reads of the previous tables
         // one thread per step and row: row r of step_blocks' matrices and of P^s
@@ -3855,17 +3913,13 @@ SRTM_DEV void recover_body(const T* __restrict__ y, int64_t N, int L, int ilim, 
 #pragma unroll 1
         for (int j = 0; j < ns; ++j) {
           const int i = i0 + j;
-          if constexpr (INP) {
-#pragma unroll
-            for (int n = 0; n < 4; ++n) zr[n] = mm4(Aop, zr[n], mm4(Bop, un4[n], 0.0));
-            load_u(i + 1);
-          }
+          if constexpr (INP) advance(i);
           auto means = [&](const double* row, int kb_n, const Stg& st) {
             double a[KBS];
 #pragma unroll
             for (int kb = 0; kb < KBS; ++kb)
               if (kb < kb_n) a[kb] = row[(j * kb_n + kb) * 16 + 4 * bk + bc];
-            T* mp = reinterpret_cast<T*>(st.mbuf + bw * Stg::SBM) + ((i - 1) % Stg::GM) * NX + bk;
+            T* mp = reinterpret_cast<T*>(st.mbuf + bw * Stg::SBM) + (j % Stg::GM) * NX + bk;
 #pragma unroll
             for (int n = 0; n < 4; ++n) {
               double acc = zr[n];
@@ -3883,7 +3937,7 @@ SRTM_DEV void recover_body(const T* __restrict__ y, int64_t N, int L, int ilim, 
           if (FILT && Pf_fast) sf.put(tab_f, base_of(Pf_fast, i0));
           if (SMOOTH && Ps_fast) ss.put(tab_s, base_of(Ps_fast, i0));
           wave_sync();
-          if (FILT) fst.flush(lane, 64, mf_fast, nullptr, w0, L, i, ilim);
+          if (FILT) fst.flush(lane, 64, mf_fast, nullptr, w0, L, j, i, ilim);
           if (SMOOTH) {
             if (i == 1) {
               sst.flush_slow(lane, 64, ms_slow, nullptr, w0);
@@ -3892,7 +3946,7 @@ SRTM_DEV void recover_body(const T* __restrict__ y, int64_t N, int L, int ilim, 
                 one.put(tab_s, reinterpret_cast<char*>(Ps_slow + w0 * NN));
               }
             }
-            sst.flush(lane, 64, ms_fast, nullptr, w0, L, i, ilim);
+            sst.flush(lane, 64, ms_fast, nullptr, w0, L, j, i, ilim);
           }
           wave_sync();
         }
@@ -3930,7 +3984,7 @@ SRTM_DEV void recover_body(const T* __restrict__ y, int64_t N, int L, int ilim, 
     }
     if (FILT) {
       fin = fin && finite_state(mf, Pii);
-      fst.put(lane, i, mf, Pii);
+      fst.put(lane, i - ibeg, mf, Pii);
     }
     if (SMOOTH) {
       T ms[NX], Ps[NX][NX];
@@ -3958,13 +4012,13 @@ SRTM_DEV void recover_body(const T* __restrict__ y, int64_t N, int L, int ilim, 
         }
       }
       fin = fin && finite_state(ms, Ps);
-      sst.put(lane, i, ms, Ps);
+      sst.put(lane, i - ibeg, ms, Ps);
     }
     wave_sync();
-    if (FILT) fst.flush(lane, nvalid, mf_fast, Pf_fast, w0, L, i, ilim);
+    if (FILT) fst.flush(lane, nvalid, mf_fast, Pf_fast, w0, L, i - ibeg, i, ilim);
     if (SMOOTH) {
       if (i == 1) sst.flush_slow(lane, nvalid, ms_slow, Ps_slow, w0);
-      sst.flush(lane, nvalid, ms_fast, Ps_fast, w0, L, i, ilim);
+      sst.flush(lane, nvalid, ms_fast, Ps_fast, w0, L, i - ibeg, i, ilim);
     }
     wave_sync();
   }
@@ -4665,7 +4719,8 @@ SRTM_DEV void lag1_within(const Model<T, NX, NY>& M, const Window<T, NX, NY>& w,
 template <typename T, int NX, int NY>
 SRTM_DEV void lag1_body(const T* __restrict__ y, int64_t N, int L, const T* __restrict__ cst,
                         const T* __restrict__ carry, const T* __restrict__ sfx, const T* __restrict__ utree,
-                        T* __restrict__ Cs_fast, int32_t* info, int64_t tile, int part, int nparts) {
+                        T* __restrict__ Cs_fast, int32_t* info, int64_t tile, int part, int nparts,
+                        int nslow) {
   static_assert(TILE == 256, "one workgroup per tile");
   constexpr int NN = NX * NX;
   using Stg = OutStage<T, NX>;
@@ -4682,15 +4737,11 @@ SRTM_DEV void lag1_body(const T* __restrict__ y, int64_t N, int L, const T* __re
   const int nw = tile_windows(N, tile);
   const bool settled = tile_settled<T, NX>(utree, tile);
   int ibeg = 1, iend = L;  // this workgroup's fast steps
-  if (nparts > 1) {
-    if (settled) {
-      if (part > 0) return;
-    } else {
-      const int per = ((L + nparts - 1) / nparts + Stg::GM - 1) / Stg::GM * Stg::GM;
-      ibeg = part * per + 1;
-      if (ibeg > L) return;
-      iend = L < ibeg + per - 1 ? L : ibeg + per - 1;
-    }
+  {
+    const StepShare<NX> share(L, part, nparts, nslow, settled);
+    if (share.beg > L) return;
+    ibeg = share.beg;
+    iend = share.end;
   }
   const int64_t col = tile * (TILE * info_stride(NX)) + (valid ? tid : 0);  // the window's records
   const int64_t mcol = settled ? tile * (TILE * info_stride(NX)) : col;
@@ -4754,8 +4805,8 @@ SRTM_DEV void lag1_body(const T* __restrict__ y, int64_t N, int L, const T* __re
     constexpr int SC = 24, RB = NN * (int)sizeof(T);
     static_assert(SC * RB <= 64 * Stg::SBP, "the records fit one wave's staging");
 #pragma unroll 1
-    for (int i0 = 1; i0 <= L; i0 += SC) {
-      const int ns = L - i0 + 1 < SC ? L - i0 + 1 : SC;
+    for (int i0 = ibeg; i0 <= iend; i0 += SC) {
+      const int ns = iend - i0 + 1 < SC ? iend - i0 + 1 : SC;
       __syncthreads();  // the previous records are written
       if (tid < ns) {
         T C[NX][NX];
@@ -4781,9 +4832,9 @@ SRTM_DEV void lag1_body(const T* __restrict__ y, int64_t N, int L, const T* __re
   for (int i = ibeg; i <= iend; ++i) {
     T C[NX][NX];
     cross(i, C);
-    stg.put(lane, i, zero, C);
+    stg.put(lane, i - ibeg, zero, C);
     wave_sync();
-    stg.flush(lane, nvalid, nullptr, Cs_fast, w0, L, i, iend);
+    stg.flush(lane, nvalid, nullptr, Cs_fast, w0, L, i - ibeg, i, iend);
     wave_sync();
   }
   if (!fin && valid) flag |= SRTM_INFO_NONFINITE;
@@ -5327,13 +5378,6 @@ SRTM_DEV int tile_sequence(const Batch& b) { return tile_sequence(b, blockIdx.x)
 // otherwise be the launch's tail.
 SRTM_DEV int64_t ends_first(int64_t i, int64_t nt) { return (i & 1) ? nt - 1 - (i >> 1) : i >> 1; }
 
-// In the recovery the tiles at either end of a sequence, which have not settled, are the slow ones: one of
-// them alone takes its workgroup about 40 us (float64, nx = 4, L = 20), and with fewer tiles than compute units that
-// is the launch. So the first END_TILES tiles (ends_first) are split by fast steps over END_PARTS workgroups; a
-// settled tile, or one that needs fewer parts, lets the extra ones return. The extra workgroups come first
-// in the grid; a batch of more than END_SEQS sequences fills the device without them.
-constexpr int END_TILES = 8, END_PARTS = 4, END_EXTRA = END_TILES * (END_PARTS - 1), END_SEQS = 16;
-
 // Stage bodies of the smoothing launches, for workgroup `bid` of the launch; the kernels below
 // wrap them for one (nx, ny) pair, the mixed-pair kernels dispatch to them per workgroup.
 template <typename T, int NX, int NY>
@@ -5411,26 +5455,21 @@ SRTM_DEV void kb_tv_fwd(const Batch& b, int64_t bid) {
 // MODE 1: filter outputs only; 2: smoother outputs; 3: both. Fast-rate outputs take all L
 // steps; with only the slow smoothed state requested, step 1 suffices.
 template <typename T, int NX, int NY, int MODE, bool INP, bool TV = false>
-SRTM_DEV void kb_recover(const Batch& b, int64_t bid, int nextra) {
-  int64_t i = bid - nextra;  // the workgroup's number among its sequence's tiles
-  int part = 0, s;
-  if (bid < nextra) {
-    s = (int)(bid / END_EXTRA);
-    const int e = (int)(bid % END_EXTRA);
-    i = e / (END_PARTS - 1);
-    part = 1 + e % (END_PARTS - 1);
-  } else {
-    s = tile_sequence(b, i);
-  }
+SRTM_DEV void kb_recover(const Batch& b, int64_t bid, Split sp) {
+  int64_t i;
+  int part, s;
+  split_place(sp, bid, s, i, part);
+  const bool extra = s >= 0;
+  if (!extra) s = tile_sequence(b, i);
   const Seq<T, NX, NY> q = seq_view<T, NX, NY>(b, s);
-  if (bid >= nextra) i -= q.tile0;
-  if (i >= q.plan.nt) return;
-  const int nparts = nextra > 0 && i < END_TILES ? END_PARTS : 1;
+  if (!extra) i -= q.tile0;
+  const int nparts = i < END_TILES ? sp.ends : sp.all;
+  if (i >= q.plan.nt || (!extra && part > 0 && nparts > sp.all)) return;
   const bool fast = (MODE & 1) || q.ms_fast || q.Ps_fast;
   if (!fast && !q.ms_slow && !q.Ps_slow) return;
   recover_body<T, NX, NY, MODE, INP, TV>(q.y, q.N, q.L, fast ? q.L : 1, TV ? q.tvblk : q.cst, q.in, q.F, q.Q, q.m0,
                                          q.P0, q.carry, q.sfx, q.btst, q.utree, q.mf_fast, q.Pf_fast, q.ms_fast, q.Ps_fast,
-                                         q.ms_slow, q.Ps_slow, q.info, TV ? i : ends_first(i, q.plan.nt), part, nparts);
+                                         q.ms_slow, q.Ps_slow, q.info, TV ? i : ends_first(i, q.plan.nt), part, sp.all, nparts);
 }
 
 template <typename T, int NX, int NY>
@@ -5485,9 +5524,15 @@ __global__ void __launch_bounds__(TILE) k_tv_fwd(Batch b) {
   kb_tv_fwd<T, NX, NY, SMOOTH>(b, blockIdx.x);
 }
 
+// Recovery workgroups a compute unit holds (one wave of each on a SIMD).
+template <typename T, int NX, bool TV>
+constexpr int recover_per_cu() {
+  return sizeof(T) == 4 && NX <= 4 && !TV ? 2 : 1;
+}
+
 template <typename T, int NX, int NY, int MODE, bool INP, bool TV = false>
-__global__ void __launch_bounds__(TILE, sizeof(T) == 4 && NX <= 4 && !TV ? 2 : 1) k_recover(Batch b, int nextra) {
-  kb_recover<T, NX, NY, MODE, INP, TV>(b, blockIdx.x, nextra);
+__global__ void __launch_bounds__(TILE, (recover_per_cu<T, NX, TV>())) k_recover(Batch b, Split sp) {
+  kb_recover<T, NX, NY, MODE, INP, TV>(b, blockIdx.x, sp);
 }
 
 // The constants block without the scan levels (the sequential comparator needs no scan), and the
@@ -5507,18 +5552,15 @@ __global__ void __launch_bounds__(64) k_seq(Batch b, int nseq) {
 }
 
 template <typename T, int NX, int NY>
-__global__ void __launch_bounds__(TILE) k_lag1(Batch b) {
+__global__ void __launch_bounds__(TILE) k_lag1(Batch b, Split sp) {
   const Seq<T, NX, NY> q = seq_view<T, NX, NY>(b, 0);  // one sequence; the parts of its end tiles first (kb_recover)
   if (!q.Cs_fast) return;
-  int64_t i = (int64_t)blockIdx.x - END_EXTRA;
-  int part = 0;
-  if (i < 0) {
-    i = blockIdx.x / (END_PARTS - 1);
-    part = 1 + blockIdx.x % (END_PARTS - 1);
-    if (i >= q.plan.nt) return;
-  }
-  lag1_body<T, NX, NY>(q.y, q.N, q.L, q.cst, q.carry, q.sfx, q.utree, q.Cs_fast, q.info, ends_first(i, q.plan.nt), part,
-                       i < END_TILES ? END_PARTS : 1);
+  int64_t i;
+  int part, s;
+  split_place(sp, blockIdx.x, s, i, part);
+  const int nparts = i < END_TILES ? sp.ends : sp.all;
+  if (i >= q.plan.nt || (s < 0 && part > 0 && nparts > sp.all)) return;
+  lag1_body<T, NX, NY>(q.y, q.N, q.L, q.cst, q.carry, q.sfx, q.utree, q.Cs_fast, q.info, ends_first(i, q.plan.nt), part, sp.all, nparts);
 }
 
 template <typename T, int NX, int NY, bool GRAD, bool INP>
@@ -5656,7 +5698,8 @@ srtm_status launch_all(const Batch& b, const Launch& g, bool smoother, int rec_m
     SRTM_EV(ev.post(st));
   }
   const size_t lds_fold = FoldLds<T, NX>(nlev_max).total;
-  const int nextra = (int)(g.nseq <= END_SEQS ? g.nseq * END_EXTRA : 0);
+  const Split sp = make_split<NX>(g.ntiles, g.nseq);
+  const unsigned nrec = g.ntiles * sp.all + sp.extra;
   // the last carry is an output of its own, or the only place where a last window's failure shows
   const int want_last = b.one.mf_slow || b.one.Pf_slow || rec_mode == REC_LL || rec_mode == REC_GRAD ? 1 : 0;
 
@@ -5669,7 +5712,7 @@ srtm_status launch_all(const Batch& b, const Launch& g, bool smoother, int rec_m
     SRTM_STAGE((k_fold<T, NX, NY, false, INP>), dim3(g.ntiles), dim3(TILE), lds_fold, st, b, want_last);
     if (rec_mode == 1) {
       if (!allow_lds((const void*)k_recover<T, NX, NY, 1, INP>, lds_rec)) return SRTM_E_HIP;
-      SRTM_STAGE((k_recover<T, NX, NY, 1, INP>), dim3(g.ntiles + nextra), dim3(TILE), lds_rec, st, b, nextra);
+      SRTM_STAGE((k_recover<T, NX, NY, 1, INP>), dim3(nrec), dim3(TILE), lds_rec, st, b, sp);
     } else {
       SRTM_EV(ev.pre(st));
       if (rec_mode == REC_LL) {
@@ -5689,10 +5732,10 @@ srtm_status launch_all(const Batch& b, const Launch& g, bool smoother, int rec_m
 
   if (rec_mode == 2) {
     if (!allow_lds((const void*)k_recover<T, NX, NY, 2, INP>, lds_rec)) return SRTM_E_HIP;
-    SRTM_STAGE((k_recover<T, NX, NY, 2, INP>), dim3(g.ntiles + nextra), dim3(TILE), lds_rec, st, b, nextra);
+    SRTM_STAGE((k_recover<T, NX, NY, 2, INP>), dim3(nrec), dim3(TILE), lds_rec, st, b, sp);
   } else if (rec_mode == 3 && lds_rec <= kMaxLdsBytes) {
     if (!allow_lds((const void*)k_recover<T, NX, NY, 3, INP>, lds_rec)) return SRTM_E_HIP;
-    SRTM_STAGE((k_recover<T, NX, NY, 3, INP>), dim3(g.ntiles + nextra), dim3(TILE), lds_rec, st, b, nextra);
+    SRTM_STAGE((k_recover<T, NX, NY, 3, INP>), dim3(nrec), dim3(TILE), lds_rec, st, b, sp);
   } else {
     SRTM_EV(ev.pre(st));
     if (rec_mode == REC_GRAD) {
@@ -5705,9 +5748,9 @@ srtm_status launch_all(const Batch& b, const Launch& g, bool smoother, int rec_m
       const size_t lds1 = (size_t)4 * OutStage<T, NX>::BYTES + ptab;
       if (!allow_lds((const void*)k_recover<T, NX, NY, 1, INP>, lds1)) return SRTM_E_HIP;
       if (!allow_lds((const void*)k_recover<T, NX, NY, 2, INP>, lds1)) return SRTM_E_HIP;
-      hipLaunchKernelGGL((k_recover<T, NX, NY, 1, INP>), dim3(g.ntiles + nextra), dim3(TILE), lds1, st, b, nextra);
+      hipLaunchKernelGGL((k_recover<T, NX, NY, 1, INP>), dim3(nrec), dim3(TILE), lds1, st, b, sp);
       SRTM_CHECK_LAUNCH();
-      hipLaunchKernelGGL((k_recover<T, NX, NY, 2, INP>), dim3(g.ntiles + nextra), dim3(TILE), lds1, st, b, nextra);
+      hipLaunchKernelGGL((k_recover<T, NX, NY, 2, INP>), dim3(nrec), dim3(TILE), lds1, st, b, sp);
       SRTM_CHECK_LAUNCH();
     }
     SRTM_EV(ev.post(st));
@@ -5750,7 +5793,7 @@ srtm_status launch_tv(const Batch& b, const Launch& g, bool smoother, int rec_mo
       SRTM_CHECK_LAUNCH();
       if (rec_mode == 1) {
         if (!allow_lds((const void*)k_recover<T, NX, NY, 1, false, true>, lds_rec)) return SRTM_E_HIP;
-        hipLaunchKernelGGL((k_recover<T, NX, NY, 1, false, true>), dim3(g.ntiles), dim3(TILE), lds_rec, st, b, 0);
+        hipLaunchKernelGGL((k_recover<T, NX, NY, 1, false, true>), dim3(g.ntiles), dim3(TILE), lds_rec, st, b, Split{0, 1, 1});
         SRTM_CHECK_LAUNCH();
       }
       return SRTM_OK;
@@ -5765,11 +5808,11 @@ srtm_status launch_tv(const Batch& b, const Launch& g, bool smoother, int rec_mo
     if (rec_mode == 2 || rec_mode == 3) {  // filter and smoother outputs: two recovery passes
       if (rec_mode == 3) {
         if (!allow_lds((const void*)k_recover<T, NX, NY, 1, false, true>, lds_rec)) return SRTM_E_HIP;
-        hipLaunchKernelGGL((k_recover<T, NX, NY, 1, false, true>), dim3(g.ntiles), dim3(TILE), lds_rec, st, b, 0);
+        hipLaunchKernelGGL((k_recover<T, NX, NY, 1, false, true>), dim3(g.ntiles), dim3(TILE), lds_rec, st, b, Split{0, 1, 1});
         SRTM_CHECK_LAUNCH();
       }
       if (!allow_lds((const void*)k_recover<T, NX, NY, 2, false, true>, lds_rec)) return SRTM_E_HIP;
-      hipLaunchKernelGGL((k_recover<T, NX, NY, 2, false, true>), dim3(g.ntiles), dim3(TILE), lds_rec, st, b, 0);
+      hipLaunchKernelGGL((k_recover<T, NX, NY, 2, false, true>), dim3(g.ntiles), dim3(TILE), lds_rec, st, b, Split{0, 1, 1});
       SRTM_CHECK_LAUNCH();
     }
     return SRTM_OK;
@@ -5822,7 +5865,8 @@ srtm_status run(const srtm_shape& sh, const Ptrs& p, bool smoother, hipStream_t 
   if (s != SRTM_OK) return s;
   const size_t lds = (size_t)4 * OutStage<T, NX>::BYTES;
   if (!allow_lds((const void*)k_lag1<T, NX, NY>, lds)) return SRTM_E_HIP;
-  hipLaunchKernelGGL((k_lag1<T, NX, NY>), dim3(g.ntiles + END_EXTRA), dim3(TILE), lds, st, b);
+  const Split sp = make_split<NX>(g.ntiles, 1);
+  hipLaunchKernelGGL((k_lag1<T, NX, NY>), dim3(g.ntiles * sp.all + sp.extra), dim3(TILE), lds, st, b, sp);
   SRTM_CHECK_LAUNCH();
   return SRTM_OK;
 }
@@ -5937,16 +5981,18 @@ __global__ void __launch_bounds__(KS) km_bwd_tiles(Batch b) {
 }
 
 template <typename T>
-__global__ void __launch_bounds__(TILE) km_recover(Batch b) {
-  const SeqDesc& d = b.table[tile_sequence(b)];
+__global__ void __launch_bounds__(TILE) km_recover(Batch b, Split sp) {
+  const SeqDesc& d = b.table[tile_sequence(b, blockIdx.x / (unsigned)sp.all)];
 #define SRTM_MX(a, c)                                                           \
   if (d.nx == a && d.ny == c) {                                                 \
     if (d.tv) {                                                                 \
-      if constexpr (a <= TV_NX_MAX) kb_recover<T, a, c, 2, false, true>(b, blockIdx.x, 0); \
+      if constexpr (a <= TV_NX_MAX)                                             \
+        if (blockIdx.x % (unsigned)sp.all == 0)                                 \
+          kb_recover<T, a, c, 2, false, true>(b, blockIdx.x / (unsigned)sp.all, Split{0, 1, 1}); \
     } else if (d.B) {                                                           \
-      kb_recover<T, a, c, 2, true>(b, blockIdx.x, 0);                           \
+      kb_recover<T, a, c, 2, true>(b, blockIdx.x, sp);                          \
     } else {                                                                    \
-      kb_recover<T, a, c, 2, false>(b, blockIdx.x, 0);                          \
+      kb_recover<T, a, c, 2, false>(b, blockIdx.x, sp);                         \
     }                                                                           \
     return;                                                                     \
   }
@@ -6012,7 +6058,12 @@ srtm_status run_mixed(const SeqDesc* host, const void* table_dev, int nseq, int6
     hipLaunchKernelGGL((km_bwd_tiles<T>), dim3(ns), dim3(KS), lds[4], st, b);
     SRTM_CHECK_LAUNCH();
   }
-  hipLaunchKernelGGL((km_recover<T>), dim3(nt), dim3(TILE), lds[5], st, b);
+  // The tiles of different pairs differ so much in time (nx = 6: 90 us, nx = 2: 10 us) that parts of all of them
+  // fill the device better (178 tiles of 15 sequences: 94 us whole, 58 us in 4 parts, 62 us with those of nx <= 4
+  // whole); with several tiles per compute unit they do that by themselves.
+  const int parts = nt > 4 * CUS ? 1 : nt > 2 * CUS ? 2 : 4;
+  const Split sp{0, parts, parts};
+  hipLaunchKernelGGL((km_recover<T>), dim3(nt * parts), dim3(TILE), lds[5], st, b, sp);
   SRTM_CHECK_LAUNCH();
   return SRTM_OK;
 }
