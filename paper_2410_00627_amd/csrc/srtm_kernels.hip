@@ -148,6 +148,91 @@ struct Block4 {
   SRTM_DEV static double mm_sym(double Xt, double Y) { return 0.5 * (mm4(Xt, Y, 0.0) + mm4(Y, Xt, 0.0)); }
 };
 
+// ---------------------------------------------------------------- 8 x 8 matrices on the matrix cores
+// One matrix of up to 8 x 8 (padded with zeros) per wave: as 2 x 2 blocks of the block layout, lane 16 r + 4 (2 i + j) + c
+// holding entry (4 i + r, 4 j + c). X^T Y is then the sum over k of two 4 x 4 block products, block (i, j) of
+// term k taking X's block (k, i) and Y's block (k, j): Lhs8 and Rhs8 hold an operand's blocks moved there (whole
+// blocks move inside the row of 16 lanes, by row rotations under a bank mask).
+template <int CTRL, int BANKS>
+SRTM_DEV double move_banks(double old, double x) {
+  const int lo = __builtin_amdgcn_update_dpp(__double2loint(old), __double2loint(x), CTRL, 0xf, BANKS, false);
+  const int hi = __builtin_amdgcn_update_dpp(__double2hiint(old), __double2hiint(x), CTRL, 0xf, BANKS, false);
+  return __hiloint2double(hi, lo);
+}
+constexpr int ROW_ROR = 0x120;  // + n: lane l of a row of 16 takes lane (l - n) mod 16
+struct Lhs8 {
+  double k0, k1;
+  SRTM_DEV explicit Lhs8(double x)  // blocks (0, 0, 1, 1) and (2, 2, 3, 3)
+      : k0(move_banks<ROW_ROR + 8, 0x8>(move_banks<ROW_ROR + 4, 0x6>(x, x), x)),
+        k1(move_banks<ROW_ROR + 12, 0x6>(move_banks<ROW_ROR + 8, 0x1>(x, x), x)) {}
+};
+struct Rhs8 {
+  double k0, k1;
+  SRTM_DEV explicit Rhs8(double y)  // blocks (0, 1, 0, 1) and (2, 3, 2, 3)
+      : k0(move_banks<ROW_ROR + 8, 0xc>(y, y)), k1(move_banks<ROW_ROR + 8, 0x3>(y, y)) {}
+};
+SRTM_DEV double mm8(const Lhs8& x, const Rhs8& y, double c) { return mm4(x.k1, y.k1, mm4(x.k0, y.k0, c)); }
+
+// One wave's view of that layout: this lane's entry and its 64 doubles of LDS scratch (row-major 8 x 8).
+template <int NX>
+struct Block8 {
+  static_assert(NX > 4 && NX <= 8, "two blocks a side");
+  int r, c;
+  double* scratch;
+  SRTM_DEV explicit Block8(double* s) : scratch(s) {
+    const int lane = threadIdx.x & 63, b = (lane >> 2) & 3;
+    r = 4 * (b >> 1) + (lane >> 4);
+    c = 4 * (b & 1) + (lane & 3);
+  }
+  SRTM_DEV bool in() const { return r < NX && c < NX; }
+  // Transposed inverse of the leading NX x NX block of M (zero outside it): Gauss-Jordan elimination with
+  // partial pivoting of [M | I], a column per lane, the pivot column read from its lane. ok &= every pivot is usable.
+  // One lane alone took 7000 cycles for it (nx = 6), its 360 multiply-adds one after the other.
+  SRTM_DEV double inv_t(double M, bool& ok) const {
+    const int lane = threadIdx.x & 63;
+    scratch[8 * r + c] = M;
+    wave_sync();
+    double a[NX];
+#pragma unroll
+    for (int q = 0; q < NX; ++q) {
+      const double v = sld(scratch + 8 * q + (lane < NX ? lane : 0));
+      a[q] = lane < NX ? v : lane - NX == q ? 1.0 : 0.0;
+    }
+    wave_sync();
+#pragma unroll
+    for (int k = 0; k < NX; ++k) {
+      double p[NX];  // column k
+#pragma unroll
+      for (int q = 0; q < NX; ++q)
+        p[q] = __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(a[q]), k),
+                                __builtin_amdgcn_readlane(__double2loint(a[q]), k));
+#pragma unroll
+      for (int q = k + 1; q < NX; ++q)
+        if (fabs(p[q]) > fabs(p[k])) {  // the same on every lane
+          const double t = p[q], u = a[q];
+          p[q] = p[k];
+          a[q] = a[k];
+          p[k] = t;
+          a[k] = u;
+        }
+      const double ip = rcp_nr(p[k]);
+      ok = ok && p[k] != 0.0 && isfinite(ip);
+      a[k] *= ip;
+#pragma unroll
+      for (int q = 0; q < NX; ++q)
+        if (q != k) a[q] = my_fma(-p[q], a[k], a[q]);
+    }
+    if (lane >= NX && lane < 2 * NX) {
+#pragma unroll
+      for (int q = 0; q < NX; ++q) scratch[8 * (lane - NX) + q] = a[q];  // column lane - NX of the inverse as a row
+    }
+    wave_sync();
+    const double v = in() ? sld(scratch + 8 * r + c) : 0.0;
+    wave_sync();
+    return v;
+  }
+};
+
 // Level chain over levels p0 .. p1-1, run by wave 0 of a workgroup.
 // `chain` is chain_doubles(nx) doubles of LDS whose first 3 nx^2 hold F, D, J of Theta(2^p0). Writes the
 // level records p0 .. p1-1 and, when p1 < nlev, F, D, J of Theta(2^p1) in float64 to `hand`
@@ -157,8 +242,7 @@ struct Block4 {
 // coefficients that combine the vector parts of two runs of 2^p elements:
 //   d_ij = G1 d_i + G2 eta_j + d_j,   eta_ij = G3 eta_j - G4 d_i + eta_i,
 //   G1 = F W, G2 = F W D, G3 = (W F)^T, G4 = (W F)^T J.
-// nx <= 4: on the matrix cores, one entry per lane and no exchange but the inverse's. nx > 4: one lane
-// per matrix entry with the operands in LDS.
+// On the matrix cores, one entry per lane and no exchange but the inverse's (level_chain8: nx > 4).
 template <typename T, int NX>
 SRTM_DEV int level_chain4(double* chain, T* __restrict__ cst, const ConstLayout& lay, int p0, int p1, int nlev,
                           double* __restrict__ hand, double* __restrict__ lev64) {
@@ -200,103 +284,65 @@ SRTM_DEV int level_chain4(double* chain, T* __restrict__ cst, const ConstLayout&
 }
 
 template <typename T, int NX>
+SRTM_DEV int level_chain8(double* chain, T* __restrict__ cst, const ConstLayout& lay, int p0, int p1, int nlev,
+                          double* __restrict__ hand, double* __restrict__ lev64) {
+  constexpr int NN = NX * NX;
+  const Block8<NX> B(chain + 3 * NN);
+  const bool in = B.in();
+  const int rc = in ? B.r * NX + B.c : 0, cr = in ? B.c * NX + B.r : 0;
+  double F = in ? chain[rc] : 0.0, Ft = in ? chain[cr] : 0.0;
+  double D = in ? chain[NN + rc] : 0.0, J = in ? chain[2 * NN + rc] : 0.0;
+  const double eye = in && B.r == B.c ? 1.0 : 0.0;
+  const Rhs8 rI(eye);
+  bool ok = true;
+  for (int p = p0; p < p1; ++p) {
+    const Lhs8 lD(D), lJ(J), lF(F), lFt(Ft);
+    const Rhs8 rD(D), rJ(J), rF(F), rFt(Ft);
+    const double Wt = B.inv_t(mm8(lD, rJ, eye), ok);  // W^T
+    const Lhs8 lWt(Wt);
+    const Rhs8 rWt(Wt);
+    const double W = mm8(lWt, rI, 0.0), WF = mm8(lWt, rF, 0.0);
+    const double G3 = mm8(lF, rWt, 0.0);  // (W F)^T
+    const double XD = 0.5 * (mm8(lWt, rD, 0.0) + mm8(lD, rWt, 0.0));  // W D
+    const Lhs8 lXD(XD), lWF(WF);
+    const Rhs8 rXD(XD), rWF(WF);
+    const double G1 = mm8(lFt, Rhs8(W), 0.0), G2 = mm8(lFt, rXD, 0.0), G4 = mm8(lWF, rJ, 0.0);
+    const double XDF = mm8(lXD, rFt, 0.0), JWF = mm8(lJ, rWF, 0.0);
+    if (in) {  // the record: rows (G1, G2) and (G3, -G4), then F, D, J
+      T* dst = cst + lay.lev + p * lay.lev_stride;
+      T* o = dst + lay.o_C + B.r * 2 * NX + B.c;
+      o[0] = (T)G1;
+      o[NX] = (T)G2;
+      o[2 * NN] = (T)G3;
+      o[2 * NN + NX] = (T)-G4;
+      dst[lay.o_F + rc] = (T)F;
+      dst[lay.o_F + NN + rc] = (T)D;
+      dst[lay.o_F + 2 * NN + rc] = (T)J;
+      if (lev64) {
+        put_global(lev64 + p * 3 * NN + rc, F);
+        put_global(lev64 + p * 3 * NN + NN + rc, D);
+        put_global(lev64 + p * 3 * NN + 2 * NN + rc, J);
+      }
+    }
+    // F W D F^T + D and (W F)^T J F + J, exactly symmetric (Block4::mm_sym)
+    D += 0.5 * (mm8(lFt, Rhs8(XDF), 0.0) + mm8(Lhs8(XDF), rFt, 0.0));
+    J += 0.5 * (mm8(lF, Rhs8(JWF), 0.0) + mm8(Lhs8(JWF), rF, 0.0));
+    F = mm8(lFt, rWF, 0.0);
+    Ft = mm8(lWF, rFt, 0.0);
+  }
+  if (p1 < nlev && in) {
+    put_global(hand + rc, F);
+    put_global(hand + NN + rc, D);
+    put_global(hand + 2 * NN + rc, J);
+  }
+  return ok ? 0 : SRTM_INFO_COMBINE_SINGULAR;
+}
+
+template <typename T, int NX>
 SRTM_DEV int level_chain(double* chain, T* __restrict__ cst, const ConstLayout& lay, int p0, int p1, int nlev,
                          double* __restrict__ hand, double* __restrict__ lev64) {
-  if constexpr (NX <= 4) {
-    return level_chain4<T, NX>(chain, cst, lay, p0, p1, nlev, hand, lev64);
-  } else {
-  constexpr int NN = NX * NX;
-  double* rec = chain;
-  double* nrec = chain + 7 * NN;
-  double* sM = chain + 14 * NN;
-  double* sW = sM + NN;
-  double* sWF = sW + NN;
-  double* sXD = sWF + NN;
-  int lflag = 0;
-  const int e = threadIdx.x;
-  for (int p = p0; p < p1; ++p) {
-    const double* F = rec;
-    const double* D = rec + NN;
-    const double* J = rec + 2 * NN;
-    for (int o = e; o < NN; o += 64) {  // M = I + D J
-      const int er = o / NX, ec = o % NX;
-      double acc = (er == ec) ? 1.0 : 0.0;
-      for (int k = 0; k < NX; ++k) acc += D[er * NX + k] * J[k * NX + ec];
-      sM[o] = acc;
-    }
-    wave_sync();
-    // one lane, Gaussian elimination with partial pivoting
-    if (e == 0) {
-      double Mr[NX][NX], Wr[NX][NX];
-      for (int r = 0; r < NX; ++r)
-        for (int c = 0; c < NX; ++c) Mr[r][c] = sM[r * NX + c];
-      if (!inv_small(Mr, Wr)) lflag |= SRTM_INFO_COMBINE_SINGULAR;
-      for (int r = 0; r < NX; ++r)
-        for (int c = 0; c < NX; ++c) sW[r * NX + c] = Wr[r][c];
-    }
-    wave_sync();
-    // The three products of each phase are formed by three groups of lanes with the same
-    // instructions (operands chosen by pointer and stride, no divergent branches):
-    //   WF = W F, G1 = F W, XD = sym(W D);
-    for (int q = e; q < 3 * NN; q += 64) {
-      const int part = q / NN, o = q % NN, er = o / NX, ec = o % NX;
-      const double* X = part == 1 ? F : sW;
-      const double* Y = part == 0 ? F : (part == 1 ? sW : D);
-      double t1 = 0.0, t2 = 0.0;
-      for (int k = 0; k < NX; ++k) {
-        t1 += X[er * NX + k] * Y[k * NX + ec];
-        t2 += X[ec * NX + k] * Y[k * NX + er];
-      }
-      double* dst = part == 0 ? sWF + o : (part == 1 ? rec + 3 * NN + o : sXD + o);
-      *dst = part == 2 ? 0.5 * (t1 + t2) : t1;
-    }
-    wave_sync();
-    //   G2 = F XD, G4 = (WF)^T J, next F = F WF; and G3 = (WF)^T;
-    for (int q = e; q < 3 * NN; q += 64) {
-      const int part = q / NN, o = q % NN, er = o / NX, ec = o % NX;
-      const double* X = part == 1 ? sWF : F;
-      const int xr = part == 1 ? 1 : NX, xk = part == 1 ? NX : 1;
-      const double* Y = part == 0 ? sXD : (part == 1 ? J : sWF);
-      double acc = 0.0;
-      for (int k = 0; k < NX; ++k) acc += X[er * xr + k * xk] * Y[k * NX + ec];
-      double* dst = part == 0 ? rec + 4 * NN + o : (part == 1 ? rec + 6 * NN + o : nrec + o);
-      *dst = acc;
-      if (part == 0) rec[5 * NN + ec * NX + er] = sWF[o];
-    }
-    wave_sync();
-    //   next D = sym(G2 F^T) + D, next J = sym(G4 F) + J.
-    for (int q = e; q < 2 * NN; q += 64) {
-      const int part = q / NN, o = q % NN, er = o / NX, ec = o % NX;
-      const double* X = rec + (part == 0 ? 4 : 6) * NN;
-      const int yk = part == 0 ? 1 : NX, yc = part == 0 ? NX : 1;
-      double t1 = 0.0, t2 = 0.0;
-      for (int k = 0; k < NX; ++k) {
-        t1 += X[er * NX + k] * F[k * yk + ec * yc];
-        t2 += X[ec * NX + k] * F[k * yk + er * yc];
-      }
-      nrec[(1 + part) * NN + o] = 0.5 * (t1 + t2) + rec[(1 + part) * NN + o];
-    }
-    T* dst = cst + lay.lev + p * lay.lev_stride;  // the level record
-    for (int q = e; q < 7 * NN; q += 64) {
-      if (q < 4 * NN) {  // rows (G1, G2), then (G3, -G4)
-        const int r = q / (2 * NX), c = q % (2 * NX);
-        const int g = r < NX ? (c < NX ? 3 : 4) : (c < NX ? 5 : 6);
-        const double v = rec[g * NN + (r % NX) * NX + c % NX];
-        dst[q] = (T)(g == 6 ? -v : v);
-      } else {
-        dst[q] = (T)rec[q - 4 * NN];
-      }
-    }
-    wave_sync();
-    double* t = rec;
-    rec = nrec;
-    nrec = t;
-  }
-  if (p1 < nlev) {
-    for (int q = threadIdx.x; q < 3 * NN; q += 64) put_global(hand + q, rec[q]);
-  }
-  return lflag;
-  }
+  if constexpr (NX <= 4) return level_chain4<T, NX>(chain, cst, lay, p0, p1, nlev, hand, lev64);
+  else return level_chain8<T, NX>(chain, cst, lay, p0, p1, nlev, hand, lev64);
 }
 
 // Levels 0 .. CHAIN_SPLIT-1 come from the constants kernel (the in-tile scans need the levels
@@ -5488,7 +5534,7 @@ __global__ void __launch_bounds__(TT) k_tile_tree(Batch b) {
 }
 
 template <typename T, int NX, int NY, bool SMOOTH, bool INP>
-__global__ void __launch_bounds__(TILE, 2) k_fold(Batch b, int want_last) {
+__global__ void __launch_bounds__(TILE, NX > 4 && sizeof(T) == 8 ? 1 : 2) k_fold(Batch b, int want_last) {
   kb_fold<T, NX, NY, SMOOTH, INP>(b, blockIdx.x, want_last != 0);
 }
 
