@@ -1877,6 +1877,33 @@ SRTM_DEV bool combine4(const Block4& B, double& u, double& P, double Tt, double 
   return ok;
 }
 
+// The same for one problem per wave, nx > 4.
+template <int NX>
+SRTM_DEV bool combine8(const Block8<NX>& B, double& u, double& P, double Tt, double Dp, double Jp, double vd, double ve) {
+  bool ok = true;
+  const Lhs8 lP(P), lT(Tt);
+  const Rhs8 rP(P), rT(Tt);
+  const double w = mm8(lP, Rhs8(ve), u);
+  const double Wt = B.inv_t(mm8(lP, Rhs8(Jp), B.in() && B.r == B.c ? 1.0 : 0.0), ok);
+  const Lhs8 lW(Wt);
+  const double X = 0.5 * (mm8(lW, rP, 0.0) + mm8(lP, Rhs8(Wt), 0.0));
+  u = mm8(lT, Rhs8(mm8(lW, Rhs8(w), 0.0)), vd);
+  const double Y = mm8(Lhs8(X), rT, 0.0);
+  P = 0.5 * (mm8(lT, Rhs8(Y), 0.0) + mm8(Lhs8(Y), rT, 0.0)) + Dp;
+  return ok;
+}
+// combine8 with level tables `tab` ((F, D, J), (F^T, J, D)) and the run (d, eta), row r at nd[r * stride].
+template <int NX, typename T>
+SRTM_DEV bool wave_combine(const Block8<NX>& B, double& u, double& P, const T* tab, const T* nd, int stride, bool fwd) {
+  constexpr int NN = NX * NX;
+  const bool in = B.in();
+  const T* t = tab + (in ? B.r * NX + B.c : 0);
+  const double a = in ? (double)t[0] : 0.0, b = in ? (double)t[NN] : 0.0, c = in ? (double)t[2 * NN] : 0.0,
+               at = in ? (double)t[3 * NN] : 0.0;
+  const double d = B.r < NX ? (double)nd[B.r * stride] : 0.0, e = B.r < NX ? (double)nd[(NX + B.r) * stride] : 0.0;
+  return combine8(B, u, P, fwd ? at : a, fwd ? b : c, fwd ? c : b, fwd ? d : e, fwd ? e : -d);
+}
+
 // Scalars of a window's state or information record: the vector, then the matrix's upper triangle. The
 // records of the time-invariant path lie tile by tile and field by field within a tile, so that the
 // lanes of a wave write and read consecutive addresses: field f of window w of tile t at
@@ -1893,12 +1920,13 @@ inline __host__ __device__ size_t tail_info_off(int64_t N, int nx, size_t esz) {
   return ((size_t)N * info_stride(nx) * esz + 7) & ~size_t(7);
 }
 
-// Highest level handled one lane per window in the fold; the ones above it go four problems per wave
-// on the matrix cores (nx <= 4). A level of one lane per window costs a wave about 700 instructions whatever
-// it holds; the four problems of a wave's 16-window groups cost about 60.
+// Levels handled one lane per window in the fold; the ones above go to the matrix cores, four problems per wave for
+// nx <= 4 (a wave's 16-window groups) and one for larger nx (a wave's 64 windows). A level of one lane per
+// window costs a wave about 700 instructions at nx = 4 whatever it holds, the four problems of a wave's
+// groups about 60; at nx = 6 (float32) 3.7 us against 1.3 us.
 constexpr int LANE_LEVELS = 4;
 template <int NX> constexpr bool blocks4() { return NX <= 4; }
-template <int NX> constexpr int lane_levels() { return blocks4<NX>() ? LANE_LEVELS : LOG_TILE; }
+template <int NX> constexpr int lane_levels() { return blocks4<NX>() ? LANE_LEVELS : LOG_TILE - 2; }
 
 // LDS of the fold, in bytes from its start (level tables of nlev levels).
 template <typename T, int NX>
@@ -1908,7 +1936,7 @@ struct FoldLds {
   static constexpr int NZ = LOG_TILE + 1;
   size_t leaf, tree, lane, lev, node, tail, scratch, group, gain, total;
   __host__ __device__ FoldLds(int nlev) {
-    const int laneL = blocks4<NX>() ? lane_levels<NX>() : nlev;
+    const int laneL = blocks4<NX>() ? lane_levels<NX>() : nlev;  // all levels where the matrix cores take them from here
     size_t o = 0;
     auto take = [&](size_t n) { const size_t at = o; o = (o + n + 15) & ~size_t(15); return at; };
     leaf = take(sizeof(T) * R2 * TILE);
@@ -1917,8 +1945,8 @@ struct FoldLds {
     lev = take(blocks4<NX>() ? sizeof(double) * 48 * (size_t)nlev : 0);    // per level F, D, J as 4 x 4 blocks
     node = take(sizeof(T) * MAXT * R2);                                    // tile-level nodes of this tile
     tail = take(sizeof(double) * NZ * IS * 4);                             // information of N's low bits
-    scratch = take(blocks4<NX>() ? sizeof(double) * 64 * 4 : 0);
-    group = take(blocks4<NX>() ? sizeof(double) * 4 * 4 * 40 : 0);         // states of each wave's four groups
+    scratch = take(sizeof(double) * 64 * 4);
+    group = take(sizeof(double) * 4 * (blocks4<NX>() ? 4 * 40 : 2 * (NN + NX)));  // states of each wave's groups
     gain = take(blocks4<NX>() ? sizeof(double) * LOG_TILE * 2 * 2 * NN : 0);    // a settled tile's gains per level
     total = o;
   }
@@ -2048,7 +2076,7 @@ SRTM_DEV bool lane_combine(Belief<T, NX>& b, const T* __restrict__ tab, const S*
 // Information of N's set bits below each bit (tail), low bits first, for a sequence's last windows.
 // `node(p)` is the (d, eta) of N's node of level p, row r at node(p)[r * stride] in LDS; entry q of `out` (info_stride scalars
 // each) receives the information of N's set bits below bit q, q = 0 .. qmax. One wave; every block of
-// lanes (every lane, nx > 4) computes the same chain.
+// lanes (nx <= 4) computes the same chain.
 template <typename T, int NX, class ND>
 SRTM_DEV bool tail_chain(const double* lev, const T* lane, double* scratch, int64_t N, int qmax, ND node, int stride,
                          double* out) {
@@ -2071,21 +2099,16 @@ SRTM_DEV bool tail_chain(const double* lev, const T* lane, double* scratch, int6
       }
     }
   } else {
-    Belief<T, NX> b;
-    belief_zero(b);
+    const Block8<NX> B(scratch);
+    double u = 0.0, P = 0.0;
 #pragma unroll 1
     for (int q = 0; q <= qmax; ++q) {
-      if ((threadIdx.x & 63) == 0) {
-        int o = NX;
-#pragma unroll
-        for (int r = 0; r < NX; ++r) {
-          out[q * IS + r] = (double)b.u[r];
-#pragma unroll
-          for (int c = r; c < NX; ++c) out[q * IS + o++] = (double)b.P[r][c];
-        }
+      if (B.in()) {
+        if (B.c == 0) out[q * IS + B.r] = u;
+        if (B.c >= B.r) out[q * IS + NX + B.r * NX - B.r * (B.r - 1) / 2 + B.c - B.r] = P;
       }
       if (q < qmax && ((N >> q) & 1)) {
-        if (!lane_combine(b, lane + (size_t)q * 6 * NN + 3 * NN, node(q), stride, false)) ok = false;
+        if (!wave_combine(B, u, P, lane + (size_t)q * 6 * NN, node(q), stride, false)) ok = false;
       }
     }
   }
@@ -2982,29 +3005,62 @@ SRTM_DEV void fold_body(const T* __restrict__ y, int64_t N, int L, int nlev, con
     }
     }
   } else {
-    gloadv(fs.u, m0);
-    gload(fs.P, P0);
-    symmetrize(fs.P);
-    belief_zero(bs);
+    const Block8<NX> B(scratch);
+    const bool in = B.in();
+    const int gr = rem >> LB;
+    double fu = B.r < NX ? (double)gld(m0 + B.r) : 0.0;
+    double fP = in ? 0.5 * ((double)gld(P0 + B.r * NX + B.c) + (double)gld(P0 + B.c * NX + B.r)) : 0.0;
+    double bu = 0.0, bP = 0.0;
+    int bw = LOG_TILE;  // the wave's bits below bw take backward combines
+    if (ragged) bw = wv < gr ? LB + top_bit(wv ^ gr) : 0;
     if constexpr (SMOOTH) {
-      if (ragged && tid < rem) bl = top_bit(tid ^ rem);
-      if (!ragged || tid < rem) belief_load(bs, tail + bl * IS);
+      if (in && bw > 0) {
+        const int a = B.r < B.c ? B.r : B.c, e = B.r < B.c ? B.c : B.r;
+        bP = tail[bw * IS + NX + a * NX - a * (a - 1) / 2 + e - a];
+      }
+      if (bw > 0 && B.r < NX) bu = tail[bw * IS + B.r];  // equal columns, the padding ones too
     }
 #pragma unroll 1
-    for (int q = tq; q >= 0; --q) {
-      const bool f = (tile >> q) & 1;
-      if (!f && !(SMOOTH && q < hb)) continue;
-      Belief<T, NX> x;
-#pragma unroll
-      for (int r = 0; r < NX; ++r) {
-        x.u[r] = f ? fs.u[r] : bs.u[r];
-#pragma unroll
-        for (int c = 0; c < NX; ++c) x.P[r][c] = f ? fs.P[r][c] : bs.P[r][c];
+    for (int p = LOG_TILE + tq; p >= LB; --p) {  // the tile's bits, then the wave's
+      const bool low = p < LOG_TILE;
+      const int64_t i = low ? (int64_t)(wv >> (p - LB)) : tile >> (p - LOG_TILE);
+      const bool f = i & 1;
+      if (!f && !(SMOOTH && p < (low ? bw : LOG_TILE + hb))) continue;
+      double u = f ? fu : bu, P = f ? fP : bP;
+      const T* nd = low ? tree + tree_off(p) + (i ^ 1) : node + (p - LOG_TILE) * R2;
+      if (!wave_combine(B, u, P, lane + (size_t)p * 6 * NN, nd, low ? TILE : 1, f)) flag |= SRTM_INFO_COMBINE_SINGULAR;
+      fu = f ? u : fu;
+      fP = f ? P : fP;
+      bu = f ? bu : u;
+      bP = f ? bP : P;
+    }
+    // the wave's states to its lanes
+    double* grp = reinterpret_cast<double*>(smraw + lo.group) + wv * 2 * (NN + NX);
+    if (in) {
+      grp[B.r * NX + B.c] = fP;
+      grp[NN + NX + B.r * NX + B.c] = bP;
+      if (B.c == 0) {
+        grp[NN + B.r] = fu;
+        grp[2 * NN + NX + B.r] = bu;
       }
-      if (!lane_combine(x, lane + (size_t)(LOG_TILE + q) * 6 * NN + (f ? 0 : 3 * NN), node + q * R2, 1, f))
-        flag |= SRTM_INFO_COMBINE_SINGULAR;
-      if (f) fs = x;
-      else bs = x;
+    }
+    wave_sync();
+#pragma unroll
+    for (int r = 0; r < NX; ++r) {
+      fs.u[r] = (T)grp[NN + r];
+      bs.u[r] = SMOOTH ? (T)grp[2 * NN + NX + r] : T(0);
+#pragma unroll
+      for (int c = r; c < NX; ++c) {
+        fs.P[r][c] = fs.P[c][r] = (T)grp[r * NX + c];
+        bs.P[r][c] = bs.P[c][r] = SMOOTH ? (T)grp[NN + NX + r * NX + c] : T(0);
+      }
+    }
+    if (ragged) {
+      bl = wv < gr ? LB : 0;
+      if (SMOOTH && wv == gr && tid < rem) {
+        bl = top_bit(tid ^ rem);
+        belief_load(bs, tail + bl * IS);
+      }
     }
   }
 
