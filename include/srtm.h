@@ -17,8 +17,9 @@
  * filter p(x_{k,L} | y_{1:k}) (Sec. III-A); srtm_smooth returns p(x_{k,i} | y_{1:N})
  * (Sec. III-C, eq. seq-smoothing-all) and the smoother's slow state p(x_{k,1} | y_{1:N})
  * (eq. seq-smoothing-1). Both are computed with the associative scans of Sec. IV
- * (eq. op-filter forward, eq. op-smoother in reverse) followed by a per-window pass that
- * recovers the fast-rate states (Remarks fast-par-filter and parallel-fast-smoothing).
+ * (eq. op-filter; the reverse pass as the information of the later windows under the same operator,
+ * or eq. op-smoother for per-window models) followed by a per-window pass that recovers the
+ * fast-rate states (Remarks fast-par-filter and parallel-fast-smoothing).
  *
  * Conventions for every entry point:
  *  - All array arguments are DEVICE pointers (hipMalloc'd or equivalent), row-major,
@@ -361,8 +362,8 @@ srtm_status srtm_batch_plan_ex(int32_t dtype, const srtm_seq_ex* seqs, int32_t n
                                size_t table_bytes, size_t* table_size, size_t* workspace_size, int64_t* ntiles,
                                int32_t* max_L);
 
-/* Smooths every sequence of a mixed batch with ONE set of six kernel launches, whatever the mix
- * of (nx, ny) pairs and kinds: each workgroup dispatches on its own sequence's descriptor and
+/* Smooths every sequence of a mixed batch with ONE set of kernel launches (five, six with per-window
+ * models), whatever the mix of (nx, ny) pairs and kinds: each workgroup dispatches on its own sequence's descriptor and
  * runs the same arithmetic on the same tiles as srtm_smooth (srtm_smooth_inputs, srtm_smooth_tv)
  * on that sequence alone. The launches size their registers and LDS for the largest pair
  * present, so a batch of one pair can be faster through srtm_smooth_batch. Arguments, checks

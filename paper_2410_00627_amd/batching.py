@@ -1,6 +1,6 @@
 """Running many independent SRTM smoothing problems on one GPU.
 
-A `BatchRunner` either puts every problem into one mixed batch (`mixed=True`: one set of six
+A `BatchRunner` either puts every problem into one mixed batch (`mixed=True`: one set of
 launches whatever the mix of state/measurement sizes, inputs and per-window models; each
 workgroup dispatches on its sequence) or groups the problems by (nx, ny) with one batched call
 per group (kernels compiled for that pair alone). Either way it can split the work into
@@ -126,7 +126,8 @@ class BatchRunner:
             b.check()
 
     def describe(self) -> dict:
-        """The configuration; `calls` batched library calls, `launches` kernel launches per pass."""
+        """The configuration; `calls` batched library calls, `launches` bounds the kernel launches per
+        pass (five per call, six for a mixed one with per-window models)."""
         return dict(segments=self.segments, multi_stream=self.multi_stream, graph=self.use_graph, mixed=self.mixed,
                     calls=len(self.batches), launches=6 * len(self.batches))
 

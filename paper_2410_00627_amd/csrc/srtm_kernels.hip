@@ -18,9 +18,15 @@
 //    generic element of window 1; this equals the paper's a_1 = (0, m^f_{1,l}, P^f_{1,l}).
 //  * A prefix that contains the prior has F = 0, so every exclusive prefix is a "state"
 //    (m, P) and the down-sweeps combine states with aligned segments.
-//  * The suffix scan is a Kogge-Stone scan towards lower window indices inside a tile and,
-//    at tile level, a Kogge-Stone scan over the tiles counted from the end; a suffix that
-//    reaches the last window has E = 0 and is the smoothed state itself.
+//  * The reverse scan runs over the same tree: (eta, J) of a run of filter elements is the
+//    information that its measurements hold about the state before it, and the information of all
+//    later windows together with the filter state gives the smoothed blocks of eq.
+//    seq-smoothing-all. A window's bits select the runs before it (states) and after it
+//    (information), each run once, so one fold finds both.
+//  * Under such a model the covariances settle after some hundred windows; a tile whose windows
+//    share them takes vectors only (settled tiles).
+//  * Short dependent chains (level chain, upper levels of the fold) hold one matrix entry per lane
+//    and run on the float64 matrix cores.
 //  * Within a window only the blocks the outputs need are formed (Remark
 //    cross-covariances): P^f_{k,i,i}, P^f_{k,i,l} and means, from per-step constants
 //    A^i, Q_ii, Q_il, c_i, instead of the dense (l nx)^2 window covariance.
@@ -187,7 +193,8 @@ struct Block8 {
   SRTM_DEV bool in() const { return r < NX && c < NX; }
   // Transposed inverse of the leading NX x NX block of M (zero outside it): Gauss-Jordan elimination with
   // partial pivoting of [M | I], a column per lane, the pivot column read from its lane. ok &= every pivot is usable.
-  // One lane alone took 7000 cycles for it (nx = 6), its 360 multiply-adds one after the other.
+  // With one lane eliminating alone and the products through LDS, the constants kernel took 46 us (nx = 6, l = 20, 8
+  // levels of the chain) against 26 us.
   SRTM_DEV double inv_t(double M, bool& ok) const {
     const int lane = threadIdx.x & 63;
     scratch[8 * r + c] = M;
@@ -346,10 +353,10 @@ SRTM_DEV int level_chain(double* chain, T* __restrict__ cst, const ConstLayout& 
 }
 
 // Levels 0 .. CHAIN_SPLIT-1 come from the constants kernel (the in-tile scans need the levels
-// below LOG_TILE); the rest, which only the tile-level scan uses, from one workgroup of the
+// below LOG_TILE); the rest, which only the levels above the tiles use, from one workgroup of the
 // tile-reduction launch, so that they are computed while the tiles are reduced (for 2^17 windows
-// nine levels, about 12 us in float64, beside reductions of about 10 us; a level costs about 0.9 us
-// more in the constants kernel, so a higher split does not pay).
+// nine levels, 6 us at nx = 4, beside reductions of 8 us; a level costs 0.45 us more in the constants
+// kernel, so a higher split does not pay).
 constexpr int CHAIN_SPLIT = LOG_TILE;
 static_assert(CHAIN_SPLIT >= LOG_TILE, "the tile reductions read levels below LOG_TILE");
 
@@ -1923,7 +1930,7 @@ inline __host__ __device__ size_t tail_info_off(int64_t N, int nx, size_t esz) {
 // Levels handled one lane per window in the fold; the ones above go to the matrix cores, four problems per wave for
 // nx <= 4 (a wave's 16-window groups) and one for larger nx (a wave's 64 windows). A level of one lane per
 // window costs a wave about 700 instructions at nx = 4 whatever it holds, the four problems of a wave's
-// groups about 60; at nx = 6 (float32) 3.7 us against 1.3 us.
+// groups about 60; at nx = 6 (float32, 63 tiles) the fold took 52 us with all 14 levels in lanes, 42 us so.
 constexpr int LANE_LEVELS = 4;
 template <int NX> constexpr bool blocks4() { return NX <= 4; }
 template <int NX> constexpr int lane_levels() { return blocks4<NX>() ? LANE_LEVELS : LOG_TILE - 2; }
@@ -5872,7 +5879,7 @@ srtm_status launch_seq(const Batch& b, const Launch& g, hipStream_t st) {
   return SRTM_OK;
 }
 
-// Per-window (time-varying) model, one sequence: 6 launches for the smoother (k_tv_reduce,
+// Per-window (time-varying) model, one sequence: 5 launches for the smoother (k_tv_reduce,
 // k_tv_tiles, k_tv_fwd<1>, k_bwd_tiles, k_recover), 4 for the filter.
 template <typename T, int NX, int NY>
 srtm_status launch_tv(const Batch& b, const Launch& g, bool smoother, int rec_mode, hipStream_t st) {
@@ -5991,7 +5998,7 @@ srtm_status run_batch(const void* table, int nseq, int64_t ntiles, int max_L, vo
 
 #if defined(SRTM_MIXED_T)
 // ---------------------------------------------------------------- mixed-pair launches
-// One set of six launches for a batch whose sequences differ in (nx, ny) and kind (time-invariant
+// One set of five launches (six with per-window models) for a batch whose sequences differ in (nx, ny) and kind (time-invariant
 // model, with known inputs, or per-window model): every workgroup reads its sequence's descriptor
 // and runs that pair's and kind's stage body. Each sequence gets exactly the per-pair kernels'
 // arithmetic on the same tiles. This object is compiled once per element type (SRTM_MIXED_T).

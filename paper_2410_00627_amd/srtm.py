@@ -557,7 +557,7 @@ class BatchEx:
     """A planned mixed batch (srtm_batch_plan_ex / srtm_smooth_batch_ex): sequences of any
     supported (nx, ny), each with a time-invariant model, with known inputs (problem tuples
     (F, Q, H, R, L, m0, P0, y, B, u)) or with a per-window model (F, Q, H, R of shape [N, ...]),
-    smoothed by one set of six launches. Same members as Batch."""
+    smoothed by one set of launches (five, six with per-window models). Same members as Batch."""
 
     LAUNCHES = 6
 
@@ -623,7 +623,7 @@ class BatchEx:
         self.ntiles, self.max_L = int(ntiles.value), int(max_L.value)
 
     def launch(self, stream=None):
-        """Enqueue the six launches on `stream` (default: the current stream); no allocation, no sync."""
+        """Enqueue the launches on `stream` (default: the current stream); no allocation, no sync."""
         if stream is None:
             stream = torch.cuda.current_stream(self.device).cuda_stream
         _check(lib().srtm_smooth_batch_ex(_dtype_code(self.dtype), self.nseq, _ptr(self.table_host),
