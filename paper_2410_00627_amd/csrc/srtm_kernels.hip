@@ -5032,12 +5032,14 @@ SRTM_DEV void gloadv_f64(double (&a)[R], const T* __restrict__ p) {
 // term in *ll. (m, P): its prior; yk: its measurement (y_k - mu_k with known inputs); col: its
 // information record (columns col and mcol, element type T, in a tile of nw windows), or its smoother-correction record with the
 // tile's incoming smoothed state `ti` (grad_by_elements); okc: whether the correction from it is usable; zL: its input
-// response z_{k,l}; with known inputs Bm [nx][nu] and uk, the window's inputs [L][nu].
+// response z_{k,l}; with known inputs Bm [nx][nu] and uk, the window's inputs [L][nu]. `tab`: LDS for the tables of
+// up to RSTEPS fast steps, which all threads of the workgroup copy (stats_lds_bytes): as wave-uniform loads the
+// six matrices of a step outgrow the scalar registers.
 template <typename T, int NX, int NY>
 SRTM_DEV bool grad_window(const Model<double, NX, NY>& M, int L, const double (&m)[NX], const double (&P)[NX][NX],
                           const double (&yk)[NY], const double (&R)[NY][NY], const T* __restrict__ col,
                           const T* __restrict__ mcol, int nw, const T* __restrict__ ti, const double (&zL)[NX], bool& okc, double& ll, double (&Sw)[NX][NX], double (&Swx)[NX][NX],
-                          double (&Sy)[NY][NY], const T* __restrict__ Bm = nullptr, const T* __restrict__ uk = nullptr,
+                          double (&Sy)[NY][NY], double* tab, const T* __restrict__ Bm = nullptr, const T* __restrict__ uk = nullptr,
                           int nu = 0) {
   Window<double, NX, NY> w;
   const bool ok = window_setup(M, L, m, P, yk, w);
@@ -5105,8 +5107,24 @@ SRTM_DEV bool grad_window(const Model<double, NX, NY>& M, int L, const double (&
   }
 #pragma unroll 1
   for (int i = 1; i <= L; ++i) {
+    const int st = M.lay.per_i_stride, slot = (i - 1) % RSTEPS;
+    double* tabA = tab + (L < RSTEPS ? L : RSTEPS) * st;  // A^{l-i} of the same steps
+    if (slot == 0) {
+      const int n = L - i + 1 < RSTEPS ? L - i + 1 : RSTEPS;
+      const double* src = M.per_i(i);
+      __syncthreads();  // the previous steps are done
+      staged_copy<4, double>(n * st, threadIdx.x, TILE, [&](int q) { return gld(src + q); }, [&](int q, double x) { tab[q] = x; });
+      staged_copy<4, double>(n * NX * NX, threadIdx.x, TILE,
+                             [&](int q) {
+                               const int back = L - i - q / (NX * NX);
+                               return back > 0 ? gld(M.cst + M.per_i_off(back) + M.lay.o_Ai + q % (NX * NX)) : 0.0;
+                             },
+                             [&](int q, double x) { tabA[q] = x; });
+      __syncthreads();
+    }
+    const double* ps = tab + slot * st;
     double ci[NX][NY], b[NX][NY], Kq[NX][NX];
-    M.get(ci, M.per_i_off(i) + M.lay.o_ci);
+    load(ci, ps + M.lay.o_ci);
 #pragma unroll
     for (int r = 0; r < NX; ++r)
 #pragma unroll
@@ -5119,7 +5137,7 @@ SRTM_DEV bool grad_window(const Model<double, NX, NY>& M, int L, const double (&
     // K_i = Q (A^{l-i})^T - b_i Y2 (Y2 = S^{-1} U_l^T)
     if (i < L) {
       double As[NX][NX];
-      M.get(As, M.per_i_off(L - i) + M.lay.o_Ai);
+      load(As, tabA + slot * NX * NX);
       mm_nt(Qm, As, Kq);
     } else {
 #pragma unroll
@@ -5181,9 +5199,16 @@ SRTM_DEV bool grad_window(const Model<double, NX, NY>& M, int L, const double (&
     // step i's own blocks for the next step; with known inputs the fast-step means also carry the
     // input response z_i = A z_{i-1} + B u_{k,i-1} (z_0 = 0), the noise statistics do not change
     if (i < L) {
-      double Pii[NX][NX];
-      window_step<double, NX, NY, true>(M, w, i, mfp, Pii, PLp);
-      window_U(M, w, i, Up);
+      double Ai[NX][NX], Pii[NX][NX];
+      load(Ai, ps + M.lay.o_Ai);
+      step_blocks<true>(
+          w, Ai, ci, [&](int r, int c) { return ps[M.lay.o_Qii + r * NX + c]; },
+          [&](int r, int c) { return ps[M.lay.o_QiL + r * NX + c]; }, mfp, Pii, PLp);
+      mm(Ai, w.V, Up);
+#pragma unroll
+      for (int r = 0; r < NX; ++r)
+#pragma unroll
+        for (int c = 0; c < NY; ++c) Up[r][c] += ci[r][c];
       if (uk) {
         double nz[NX];
 #pragma unroll
@@ -5242,6 +5267,11 @@ SRTM_DEV bool grad_window(const Model<double, NX, NY>& M, int L, const double (&
   return ok;
 }
 
+// Dynamic LDS of the statistics kernel with the gradient.
+inline size_t stats_lds_bytes(int nx, int ny, int L) {
+  return sizeof(double) * (size_t)(L < RSTEPS ? L : RSTEPS) * (make_const_layout(nx, ny, L).per_i_stride + nx * nx);
+}
+
 template <typename T, int NX, int NY, bool GRAD, bool INP>
 SRTM_DEV void stats_body(const T* __restrict__ y, int64_t N, int L, const T* __restrict__ cst,
                          const double* __restrict__ cst64, InputView<T> in, const T* __restrict__ Rm,
@@ -5251,6 +5281,8 @@ SRTM_DEV void stats_body(const T* __restrict__ y, int64_t N, int L, const T* __r
   using SL = StatLayout<NX, NY>;
   constexpr int NC = SL::SIZE;
   __shared__ double red[TILE / 64][NC];
+  extern __shared__ char smraw[];
+  double* tab = reinterpret_cast<double*>(smraw);
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const int64_t k = tile * TILE + tid;
   const bool valid = k < N;
@@ -5295,7 +5327,7 @@ SRTM_DEV void stats_body(const T* __restrict__ y, int64_t N, int L, const T* __r
     gload_f64(R, Rm);
     bool okc = true;
     if (!grad_window<T, NX, NY>(M, L, m, P, yk, R, sfx + (grad_by_elements<T>() ? kc * sfx_stride(NX) : col), sfx + mcol, nw,
-                                tin + tile * (NX + NX * NX), zL, okc, ll, Sw, Swx, Sy,
+                                tin + tile * (NX + NX * NX), zL, okc, ll, Sw, Swx, Sy, tab,
                                 INP ? in.B : nullptr, INP ? in.u + kc * L * in.nu : nullptr, INP ? in.nu : 0) &&
         valid)
       flag |= SRTM_INFO_INNOVATION_NOT_PD;
@@ -5807,7 +5839,7 @@ srtm_status launch_all(const Batch& b, const Launch& g, bool smoother, int rec_m
       SRTM_STAGE((k_fwd_bwd<T, NX, NY, INP>), dim3(g.ntiles), dim3(TILE), lds_fb, st, b);
       hipLaunchKernelGGL((k_bwd_tiles<T, NX, NY>), dim3(g.nseq), dim3(KS), lds_bk, st, b);
       SRTM_CHECK_LAUNCH();
-      hipLaunchKernelGGL((k_stats<T, NX, NY, true, INP>), dim3(g.ntiles), dim3(TILE), 0, st, b);
+      hipLaunchKernelGGL((k_stats<T, NX, NY, true, INP>), dim3(g.ntiles), dim3(TILE), stats_lds_bytes(NX, NY, g.max_L), st, b);
       SRTM_CHECK_LAUNCH();
       hipLaunchKernelGGL((k_stats_final<T, NX, NY, true>), dim3(g.nseq), dim3(SF_THREADS), 0, st, b, lo.ll, lo.dF, lo.dQ,
                          lo.dR);
@@ -5866,7 +5898,7 @@ srtm_status launch_all(const Batch& b, const Launch& g, bool smoother, int rec_m
   } else {
     SRTM_EV(ev.pre(st));
     if (rec_mode == REC_GRAD) {
-      hipLaunchKernelGGL((k_stats<T, NX, NY, true, INP>), dim3(g.ntiles), dim3(TILE), 0, st, b);
+      hipLaunchKernelGGL((k_stats<T, NX, NY, true, INP>), dim3(g.ntiles), dim3(TILE), stats_lds_bytes(NX, NY, g.max_L), st, b);
       SRTM_CHECK_LAUNCH();
       hipLaunchKernelGGL((k_stats_final<T, NX, NY, true>), dim3(g.nseq), dim3(SF_THREADS), 0, st, b, lo.ll, lo.dF, lo.dQ,
                          lo.dR);
