@@ -1961,9 +1961,12 @@ inline __host__ __device__ size_t tail_info_off(int64_t N, int nx, size_t esz) {
 // nx <= 4 (a wave's 16-window groups) and one for larger nx (a wave's 64 windows). A level of one lane per
 // window costs a wave about 700 instructions at nx = 4 whatever it holds, the four problems of a wave's
 // groups about 60; at nx = 6 (float32, 63 tiles) the fold took 52 us with all 14 levels in lanes, 42 us so.
+// nx = 1 stays in lanes: a combine of scalars is shorter there than a 4 x 4 one on the matrix cores (20000 windows in
+// float32: the filter's fold 4 us in lanes, 10 us in blocks), and its tiles gain too little from being settled.
 constexpr int LANE_LEVELS = 4;
-template <int NX> constexpr bool blocks4() { return NX <= 4; }
-template <int NX> constexpr int lane_levels() { return blocks4<NX>() ? LANE_LEVELS : LOG_TILE - 2; }
+template <int NX> constexpr bool blocks4() { return NX >= 2 && NX <= 4; }
+template <int NX> constexpr bool block8() { return NX > 4; }
+template <int NX> constexpr int lane_levels() { return blocks4<NX>() ? LANE_LEVELS : block8<NX>() ? LOG_TILE - 2 : LOG_TILE; }
 
 // LDS of the fold, in bytes from its start (level tables of nlev levels).
 template <typename T, int NX>
@@ -2036,7 +2039,7 @@ template <typename T, int NX>
 SRTM_DEV T* settled_flag(T* utree, int64_t tile) { return utree + tile * (2 * NX * TILE) + TILE - 1; }
 template <typename T, int NX>
 SRTM_DEV bool tile_settled(const T* utree, int64_t tile) {
-  if constexpr (NX > 4) return false;
+  if constexpr (!blocks4<NX>()) return false;
   const int f = gld(settled_flag<T, NX>(const_cast<T*>(utree), tile)) != T(0);
   return __builtin_amdgcn_readfirstlane(f) != 0;
 }
@@ -2135,7 +2138,7 @@ SRTM_DEV bool tail_chain(const double* lev, const T* lane, double* scratch, int6
         if (!combine4(B, u, P, lv[4 * B.r + B.c], lv[32 + 4 * B.r + B.c], lv[16 + 4 * B.r + B.c], e, -d)) ok = false;
       }
     }
-  } else {
+  } else if constexpr (block8<NX>()) {
     const Block8<NX> B(scratch);
     double u = 0.0, P = 0.0;
 #pragma unroll 1
@@ -2146,6 +2149,24 @@ SRTM_DEV bool tail_chain(const double* lev, const T* lane, double* scratch, int6
       }
       if (q < qmax && ((N >> q) & 1)) {
         if (!wave_combine(B, u, P, lane + (size_t)q * 6 * NN, node(q), stride, false)) ok = false;
+      }
+    }
+  } else {
+    Belief<T, NX> b;
+    belief_zero(b);
+#pragma unroll 1
+    for (int q = 0; q <= qmax; ++q) {
+      if ((threadIdx.x & 63) == 0) {
+        int o = NX;
+#pragma unroll
+        for (int r = 0; r < NX; ++r) {
+          out[q * IS + r] = (double)b.u[r];
+#pragma unroll
+          for (int c = r; c < NX; ++c) out[q * IS + o++] = (double)b.P[r][c];
+        }
+      }
+      if (q < qmax && ((N >> q) & 1)) {
+        if (!lane_combine(b, lane + (size_t)q * 6 * NN + 3 * NN, node(q), stride, false)) ok = false;
       }
     }
   }
@@ -3041,7 +3062,7 @@ SRTM_DEV void fold_body(const T* __restrict__ y, int64_t N, int L, int nlev, con
       }
     }
     }
-  } else {
+  } else if constexpr (block8<NX>()) {
     const Block8<NX> B(scratch);
     const bool in = B.in();
     const int gr = rem >> LB;
@@ -3098,6 +3119,31 @@ SRTM_DEV void fold_body(const T* __restrict__ y, int64_t N, int L, int nlev, con
         bl = top_bit(tid ^ rem);
         belief_load(bs, tail + bl * IS);
       }
+    }
+  } else {
+    gloadv(fs.u, m0);
+    gload(fs.P, P0);
+    symmetrize(fs.P);
+    belief_zero(bs);
+    if constexpr (SMOOTH) {
+      if (ragged && tid < rem) bl = top_bit(tid ^ rem);
+      if (!ragged || tid < rem) belief_load(bs, tail + bl * IS);
+    }
+#pragma unroll 1
+    for (int q = tq; q >= 0; --q) {
+      const bool f = (tile >> q) & 1;
+      if (!f && !(SMOOTH && q < hb)) continue;
+      Belief<T, NX> x;
+#pragma unroll
+      for (int r = 0; r < NX; ++r) {
+        x.u[r] = f ? fs.u[r] : bs.u[r];
+#pragma unroll
+        for (int c = 0; c < NX; ++c) x.P[r][c] = f ? fs.P[r][c] : bs.P[r][c];
+      }
+      if (!lane_combine(x, lane + (size_t)(LOG_TILE + q) * 6 * NN + (f ? 0 : 3 * NN), node + q * R2, 1, f))
+        flag |= SRTM_INFO_COMBINE_SINGULAR;
+      if (f) fs = x;
+      else bs = x;
     }
   }
 
@@ -3681,7 +3727,7 @@ struct NoSteps {};
 // The fast steps of a window do not wait for each other, so a tile's can be split over workgroups, each of
 // which repeats what precedes the steps. A tile that has not settled is slow (nx = 4, L = 20, float64: about
 // 40 us for its workgroup), and with few tiles that is the launch:
-//   - where tiles settle (nx <= 4), the slow ones of the first END_TILES tiles of a sequence (ends_first) take 5
+//   - where tiles settle (nx 2 .. 4), the slow ones of the first END_TILES tiles of a sequence (ends_first) take 5
 //     parts, or 3 once there is a tile for every compute unit; a batch of more than END_SEQS sequences fills the
 //     device without them. 32767 windows (128 tiles, with inputs, float64): 37 us in 3 parts, 29 us in 5; 276 tiles of
 //     15 sequences (float32): 27 us in 3 parts, 31 us in 5.
@@ -3695,10 +3741,10 @@ struct Split {
 constexpr int CUS = 256, END_TILES = 8, END_SEQS = 16, MAX_PARTS = 8, MIN_STEPS = 4;
 template <int NX>
 inline Split make_split(int64_t ntiles, int64_t nseq) {
-  const int64_t fit = (NX <= 4 ? CUS / 2 : CUS) / ntiles;
+  const int64_t fit = (blocks4<NX>() ? CUS / 2 : CUS) / ntiles;
   const int all = (int)(fit < 1 ? 1 : fit > MAX_PARTS ? MAX_PARTS : fit);
   const int ends = ntiles < CUS ? 5 : 3;
-  if (NX > 4 || nseq > END_SEQS || all >= ends) return Split{0, all, all};
+  if (!blocks4<NX>() || nseq > END_SEQS || all >= ends) return Split{0, all, all};
   return Split{(int)nseq * END_TILES * (ends - 1), all, ends};
 }
 // The tile's number in its sequence (ends_first) and its part for workgroup bid, given the grid's numbering.
