@@ -67,8 +67,8 @@ inline __host__ __device__ ConstLayout make_const_layout(int nx, int ny, int L, 
   return c;
 }
 
-// LDS doubles of a level chain: its F, D, J and 64 of exchange scratch (nx <= 4, matrix cores), or two
-// level records and five matrices.
+// LDS doubles set aside for a level chain, which needs its F, D, J and 64 of exchange scratch. The size also
+// sets the largest L that the constants kernel accepts, so it stays what it was for larger nx.
 inline __host__ __device__ constexpr int chain_doubles(int nx) {
   return 19 * nx * nx > 3 * nx * nx + 64 ? 19 * nx * nx : 3 * nx * nx + 64;
 }
