@@ -2749,32 +2749,62 @@ SRTM_DEV int store_carry(int64_t k, const T (&m)[NX], const T (&P)[NX][NX], T* _
 // Smoother correction of window k (fold section): v = (I + J P)^{-1} (eta - J m), W = -(I + J P)^{-1} J, from its
 // inclusive filter state (m, P) = (m^f_{k,l}, P^f_{k,l}) and its information record (columns `col` and
 // `mcol` of a tile of nw windows, record_load; zero after the last window, which gives v = 0 and W = 0). Returns false when I + J P is numerically singular.
+// After a wide prior or with accurate measurements P is many times J^{-1}, and P^f_{i,l} multiplies what W and v lose:
+// in float64 for both types, W exactly symmetric (a mean with its transpose), and for float64, which has no wider
+// type, one step of iterative refinement of both solutions.
 template <bool INP, typename T, int NX, int NY, typename S>
 SRTM_DEV bool info_correction(const Model<T, NX, NY>& M, int L, const Window<T, NX, NY>& w, const T (&zL)[NX],
                               const S* __restrict__ col, const S* __restrict__ mcol, int nw, T (&v)[NX], T (&W)[NX][NX]) {
-  T m[NX], P[NX][NX], eta[NX], J[NX][NX], A[NX][NX], Ai[NX][NX];
-  record_load(eta, J, col, mcol, nw);
-  window_slow_state<INP>(M, L, w, zL, m, P);
+  double P[NX][NX], r[NX], J[NX][NX], A[NX][NX], Ai[NX][NX], x[NX], X[NX][NX];
+  record_load(r, J, col, mcol, nw);
+  {
+    T m[NX], Pt[NX][NX];
+    window_slow_state<INP>(M, L, w, zL, m, Pt);
+#pragma unroll
+    for (int i = 0; i < NX; ++i) {
+#pragma unroll
+      for (int k = 0; k < NX; ++k) {
+        P[i][k] = (double)Pt[i][k];
+        r[i] = fma(-J[i][k], (double)m[k], r[i]);  // eta and J m nearly cancel
+      }
+    }
+  }
   mm(J, P, A);
 #pragma unroll
-  for (int r = 0; r < NX; ++r) {
-    A[r][r] += T(1);
-    double t = (double)eta[r];  // eta and J m nearly cancel
-#pragma unroll
-    for (int k = 0; k < NX; ++k) t = fma(-(double)J[r][k], (double)m[k], t);
-    eta[r] = (T)t;
-  }
+  for (int i = 0; i < NX; ++i) A[i][i] += 1.0;
   const bool ok = inv_small(A, Ai);
-  mv(Ai, eta, v);
+  // (I + J P) y = b from y = Ai b, refined by the residual b - y - J (P y)
+  auto solve = [&](const double (&b)[NX], double (&y)[NX]) {
+    mv(Ai, b, y);
+    if constexpr (sizeof(T) == 8) {
+      double Py[NX], e[NX];
+      mv(P, y, Py);
 #pragma unroll
-  for (int r = 0; r < NX; ++r)
+      for (int i = 0; i < NX; ++i) {
+        double t = b[i] - y[i];
 #pragma unroll
-    for (int c = r; c < NX; ++c) {
-      T t = T(0);
-#pragma unroll
-      for (int k = 0; k < NX; ++k) t = my_fma(-Ai[r][k], J[k][c], t);
-      W[r][c] = W[c][r] = t;
+        for (int k = 0; k < NX; ++k) t = fma(-J[i][k], Py[k], t);
+        e[i] = t;
+      }
+      mv_acc(Ai, e, y);
     }
+  };
+  solve(r, x);
+#pragma unroll
+  for (int c = 0; c < NX; ++c) {
+    double b[NX], y[NX];
+#pragma unroll
+    for (int i = 0; i < NX; ++i) b[i] = -J[i][c];
+    solve(b, y);
+#pragma unroll
+    for (int i = 0; i < NX; ++i) X[i][c] = y[i];
+  }
+#pragma unroll
+  for (int i = 0; i < NX; ++i) {
+    v[i] = (T)x[i];
+#pragma unroll
+    for (int c = i; c < NX; ++c) W[i][c] = W[c][i] = (T)(0.5 * (X[i][c] + X[c][i]));
+  }
   return ok;
 }
 

@@ -1,0 +1,57 @@
+"""Priors much wider than what the measurements leave, and measurements much more accurate than the filter's
+prediction: the later windows' information then shrinks a window's covariance many times over (J P >> 1),
+which the smoother has to do without losing the digits in between. Against the float64 oracle, at the
+repository's tolerances (1e-8 float64, 1e-3 float32 on the rounded inputs).
+"""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2410_00627_amd import workloads as wl
+from test_gpu_lag1 import lag1_error
+from test_gpu_settled import TOL, _errors
+
+pytestmark = pytest.mark.gpu
+
+
+def _model(kind, nx, ny, L, seed, wide, r):
+    m = (wl.random_stable_model if kind == "stable" else wl.random_general_model)(nx, ny, L, seed)
+    m.P0, m.R = wide * m.P0, r * m.R
+    return m
+
+
+def _run(m, N, seed, dtype, **kw):
+    from paper_2410_00627_amd import srtm
+    args = [t.to(dtype) for t in srtm.model_tensors(m, "cuda", torch.float64)]
+    yt = torch.as_tensor(wl.simulate(m, N, seed), device="cuda").to(dtype)
+    out = srtm.smooth(*args[:4], m.L, *args[4:], yt, **kw)
+    a = [t.double().cpu().numpy() for t in (*args, yt)]
+    return out, oracle.srtm_smoother(a[0], a[1], a[2], a[3], m.L, a[4], a[5], a[6], with_filter=True, lag1=True)
+
+
+COVARIANCES = [  # P^s was 2e-8 .. 1e-5 off in float64, 6e-3 in float32, with W in the element type and its upper half mirrored
+    ("stable", 3, 2, 10, 0, 1e4, 1.0, 30, torch.float64), ("stable", 4, 1, 1, 2, 100.0, 1.0, 30, torch.float64),
+    ("stable", 4, 2, 10, 1, 1e4, 1.0, 30, torch.float64), ("stable", 6, 1, 1, 1, 100.0, 1.0, 30, torch.float64),
+    ("general", 4, 2, 4, 5, 1e4, 1e-2, 30, torch.float64), ("stable", 4, 2, 4, 3, 1e4, 1.0, 5 * 256 + 19, torch.float64),
+    ("stable", 6, 1, 4, 3, 1e4, 1.0, 5 * 256 + 19, torch.float64), ("stable", 3, 2, 10, 0, 100.0, 1.0, 30, torch.float32),
+]
+
+
+@pytest.mark.parametrize("kind,nx,ny,L,seed,wide,r,N,dtype", COVARIANCES)
+def test_smoothed_covariances(kind, nx, ny, L, seed, wide, r, N, dtype):
+    out, ref = _run(_model(kind, nx, ny, L, seed, wide, r), N, 60 + seed, dtype)
+    P, Pr = out["Ps_fast"].double().cpu().numpy(), ref["Ps_fast"]
+    assert np.max(np.linalg.norm(P - Pr, axis=(-2, -1)) / np.linalg.norm(Pr, axis=(-2, -1))) <= TOL[dtype]
+    assert torch.equal(out["Ps_fast"], out["Ps_fast"].mT)
+
+
+@pytest.mark.parametrize("r", [1e-3, 1e-4])
+def test_accurate_measurements_float32(r):
+    """J P about 700 in every window, settled tiles and the others. From the second window on: the first one's
+    filter covariance, of which 1/500 is left, is itself 5e-6 off, the rounding of its prior."""
+    out, ref = _run(_model("general", 2, 1, 1, 4, 1.0, r), 6 * 256 + 5, 91, torch.float32, lag1=True)
+    e = _errors(out["ms_fast"][1:], out["Ps_fast"][1:], ref["ms_fast"][1:], ref["Ps_fast"][1:])
+    assert max(e) <= TOL[torch.float32]
+    C = out["Cs_fast"][1:].double().cpu().numpy()
+    assert lag1_error(C, ref["Cs_fast"][1:], ref["Ps_fast"][1:]) <= TOL[torch.float32]
