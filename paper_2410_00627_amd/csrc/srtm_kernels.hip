@@ -4008,6 +4008,11 @@ SRTM_DEV void recover_body(const T* __restrict__ y, int64_t N, int L, int ilim, 
           wave_sync();
         }
       }
+      // The filter's product ends at S^{-1}e: its last block of four has zeros in place of v, which a later measurement
+      // that is not finite makes NaN.
+      double xf[4];
+#pragma unroll
+      for (int n = 0; n < 4; ++n) xf[n] = 4 * (KBF - 1) + bk < KF ? x[n][KBF - 1] : 0.0;
       // input response of the same windows, entry bk: z_i = A z_{i-1} + B u_{k,i-1}
       double zr[4] = {0.0, 0.0, 0.0, 0.0}, Aop = 0.0, Bop = 0.0, un4[4] = {0.0, 0.0, 0.0, 0.0}, uq[4] = {0.0, 0.0, 0.0, 0.0};
       auto load_u = [&](int i) {  // inputs of the step into x_{k,i}, two steps before they are used
@@ -4147,7 +4152,7 @@ SRTM_DEV void recover_body(const T* __restrict__ y, int64_t N, int L, int ilim, 
         for (int j = 0; j < ns; ++j) {
           const int i = i0 + j;
           if constexpr (INP) advance(i);
-          auto means = [&](const double* row, int kb_n, const Stg& st) {
+          auto means = [&](const double* row, int kb_n, const Stg& st, bool filt) {
             double a[KBS];
 #pragma unroll
             for (int kb = 0; kb < KBS; ++kb)
@@ -4158,15 +4163,15 @@ SRTM_DEV void recover_body(const T* __restrict__ y, int64_t N, int L, int ilim, 
               double acc = zr[n];
 #pragma unroll
               for (int kb = 0; kb < KBS; ++kb)
-                if (kb < kb_n) acc = mm4(a[kb], x[n][kb], acc);
+                if (kb < kb_n) acc = mm4(a[kb], filt && kb == KBF - 1 ? xf[n] : x[n][kb], acc);
               if (bk < NX) {
                 *reinterpret_cast<T*>(reinterpret_cast<char*>(mp) + n * 16 * Stg::SBM) = (T)acc;
                 fin = fin && isfinite((T)acc);
               }
             }
           };
-          if constexpr (FILT) means(row_f, KBF, fst);
-          if constexpr (SMOOTH) means(row_s, KBS, sst);
+          if constexpr (FILT) means(row_f, KBF, fst, true);
+          if constexpr (SMOOTH) means(row_s, KBS, sst, false);
           if (FILT && Pf_fast) sf.put(tab_f, base_of(Pf_fast, i0));
           if (SMOOTH && Ps_fast) ss.put(tab_s, base_of(Ps_fast, i0));
           wave_sync();
