@@ -3840,8 +3840,8 @@ SRTM_DEV void recover_body(const T* __restrict__ y, int64_t N, int L, int ilim, 
                            const T* __restrict__ sfx, const T* __restrict__ tin, const T* __restrict__ utree,
                            T* __restrict__ mf_fast,
                            T* __restrict__ Pf_fast, T* __restrict__ ms_fast, T* __restrict__ Ps_fast,
-                           T* __restrict__ ms_slow, T* __restrict__ Ps_slow, int32_t* info, int64_t tile, int part,
-                           int nparts, int nslow) {
+                           T* __restrict__ ms_slow, T* __restrict__ Ps_slow, T* __restrict__ mf_slow,
+                           T* __restrict__ Pf_slow, int32_t* info, int64_t tile, int part, int nparts, int nslow) {
   constexpr int NN = NX * NX, ST = NX + NN, SF = sfx_stride(NX);
   static_assert(TILE == 256, "one recovery workgroup per tile");
   constexpr bool FILT = (MODE & 1) != 0, SMOOTH = (MODE & 2) != 0;
@@ -3897,6 +3897,15 @@ SRTM_DEV void recover_body(const T* __restrict__ y, int64_t N, int L, int ilim, 
   if constexpr (INP) {
 #pragma unroll
     for (int j = 0; j < NU_MAX; ++j) un[j] = (j < in.nu) ? gld(uk + j) : T(0);
+  }
+  // Slow-rate filter outputs beside smoothed ones: a window update keeps the digits of an accurate measurement that
+  // the fold's state of the next window loses (its runs carry y as eta = C_bar^T R_x^{-1} y, rounded).
+  if constexpr (SMOOTH && !TV) {
+    if ((mf_slow || Pf_slow) && part == 0 && valid) {
+      T ml[NX], Pl[NX][NX];
+      window_slow_state<INP>(M, L, w, zL, ml, Pl);
+      flag |= store_slow(k, ml, Pl, mf_slow, Pf_slow);
+    }
   }
   T v[NX], W[NX][NX];
   if constexpr (SMOOTH && !TV) {
@@ -5689,11 +5698,18 @@ SRTM_DEV void kb_tile_tree(const Batch& b, int64_t bid, int nthr) {
                                  q.info, nthr);
 }
 
+// What the fold writes besides its records: the slow-rate filter outputs (where no smoothing recovery writes them), and
+// with them, or where only the state tells of a failure there, the state after the last window.
+struct FoldOut {
+  bool slow, last;
+};
+
 template <typename T, int NX, int NY, bool SMOOTH, bool INP>
-SRTM_DEV void kb_fold(const Batch& b, int64_t bid, bool want_last) {
-  const Seq<T, NX, NY> q = seq_view<T, NX, NY>(b, tile_sequence(b, bid));
+SRTM_DEV void kb_fold(const Batch& b, int64_t bid, FoldOut want) {
+  Seq<T, NX, NY> q = seq_view<T, NX, NY>(b, tile_sequence(b, bid));
+  if (!want.slow) q.mf_slow = q.Pf_slow = nullptr;
   fold_body<SMOOTH, INP, T, NX, NY>(q.y, q.N, q.L, q.plan.nlev, q.cst, q.lev64, q.in, q.m0, q.P0, q.ftagg, q.ftst, q.utree, q.tail,
-                                    q.carry, q.mf_slow, q.Pf_slow, q.sfx, q.info, bid - q.tile0, want_last);
+                                    q.carry, q.mf_slow, q.Pf_slow, q.sfx, q.info, bid - q.tile0, want.last);
 }
 
 template <typename T, int NX, int NY>
@@ -5751,7 +5767,8 @@ SRTM_DEV void kb_recover(const Batch& b, int64_t bid, Split sp) {
   if (!fast && !q.ms_slow && !q.Ps_slow) return;
   recover_body<T, NX, NY, MODE, INP, TV>(q.y, q.N, q.L, fast ? q.L : 1, TV ? q.tvblk : q.cst, q.in, q.F, q.Q, q.m0,
                                          q.P0, q.carry, q.sfx, q.btst, q.utree, q.mf_fast, q.Pf_fast, q.ms_fast, q.Ps_fast,
-                                         q.ms_slow, q.Ps_slow, q.info, TV ? i : ends_first(i, q.plan.nt), part, sp.all, nparts);
+                                         q.ms_slow, q.Ps_slow, q.mf_slow, q.Pf_slow, q.info, TV ? i : ends_first(i, q.plan.nt), part,
+                                         sp.all, nparts);
 }
 
 template <typename T, int NX, int NY>
@@ -5770,8 +5787,8 @@ __global__ void __launch_bounds__(TT) k_tile_tree(Batch b) {
 }
 
 template <typename T, int NX, int NY, bool SMOOTH, bool INP>
-__global__ void __launch_bounds__(TILE, NX > 4 && sizeof(T) == 8 ? 1 : 2) k_fold(Batch b, int want_last) {
-  kb_fold<T, NX, NY, SMOOTH, INP>(b, blockIdx.x, want_last != 0);
+__global__ void __launch_bounds__(TILE, NX > 4 && sizeof(T) == 8 ? 1 : 2) k_fold(Batch b, FoldOut want) {
+  kb_fold<T, NX, NY, SMOOTH, INP>(b, blockIdx.x, want);
 }
 
 template <typename T, int NX, int NY>
@@ -5983,7 +6000,8 @@ srtm_status launch_all(const Batch& b, const Launch& g, bool smoother, int rec_m
   const Split sp = make_split<NX>(g.ntiles, g.nseq);
   const unsigned nrec = g.ntiles * sp.all + sp.extra;
   // the last carry is an output of its own, or the only place where a last window's failure shows
-  const int want_last = b.one.mf_slow || b.one.Pf_slow || rec_mode == REC_LL || rec_mode == REC_GRAD ? 1 : 0;
+  const bool slow = !(smoother && (rec_mode == 2 || rec_mode == 3));
+  const FoldOut want{slow, (slow && (b.one.mf_slow || b.one.Pf_slow)) || rec_mode == REC_LL || rec_mode == REC_GRAD};
 
   // output staging, then the per-step tables of up to RSTEPS fast steps
   const size_t ptab = sizeof(T) * (size_t)(g.max_L < RSTEPS ? g.max_L : RSTEPS) *
@@ -5991,7 +6009,7 @@ srtm_status launch_all(const Batch& b, const Launch& g, bool smoother, int rec_m
   const size_t lds_rec = (size_t)4 * OutStage<T, NX>::BYTES * ((rec_mode == 3) ? 2 : 1) + ptab;
   if (!smoother) {
     if (!allow_lds((const void*)k_fold<T, NX, NY, false, INP>, lds_fold)) return SRTM_E_HIP;
-    SRTM_STAGE((k_fold<T, NX, NY, false, INP>), dim3(g.ntiles), dim3(TILE), lds_fold, st, b, want_last);
+    SRTM_STAGE((k_fold<T, NX, NY, false, INP>), dim3(g.ntiles), dim3(TILE), lds_fold, st, b, want);
     if (rec_mode == 1) {
       if (!allow_lds((const void*)k_recover<T, NX, NY, 1, INP>, lds_rec)) return SRTM_E_HIP;
       SRTM_STAGE((k_recover<T, NX, NY, 1, INP>), dim3(nrec), dim3(TILE), lds_rec, st, b, sp);
@@ -6010,7 +6028,7 @@ srtm_status launch_all(const Batch& b, const Launch& g, bool smoother, int rec_m
   }
 
   if (!allow_lds((const void*)k_fold<T, NX, NY, true, INP>, lds_fold)) return SRTM_E_HIP;
-  SRTM_STAGE((k_fold<T, NX, NY, true, INP>), dim3(g.ntiles), dim3(TILE), lds_fold, st, b, want_last);
+  SRTM_STAGE((k_fold<T, NX, NY, true, INP>), dim3(g.ntiles), dim3(TILE), lds_fold, st, b, want);
 
   if (rec_mode == 2) {
     if (!allow_lds((const void*)k_recover<T, NX, NY, 2, INP>, lds_rec)) return SRTM_E_HIP;
@@ -6238,9 +6256,9 @@ __global__ void __launch_bounds__(TILE) km_fold(Batch b) {
     if (d.tv) {                                                          \
       if constexpr (a <= TV_NX_MAX) kb_tv_fwd<T, a, c, true>(b, blockIdx.x); \
     } else if (d.B) {                                                    \
-      kb_fold<T, a, c, true, true>(b, blockIdx.x, false);                \
+      kb_fold<T, a, c, true, true>(b, blockIdx.x, FoldOut{false, false}); \
     } else {                                                             \
-      kb_fold<T, a, c, true, false>(b, blockIdx.x, false);               \
+      kb_fold<T, a, c, true, false>(b, blockIdx.x, FoldOut{false, false}); \
     }                                                                    \
     return;                                                              \
   }

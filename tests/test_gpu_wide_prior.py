@@ -55,3 +55,19 @@ def test_accurate_measurements_float32(r):
     assert max(e) <= TOL[torch.float32]
     C = out["Cs_fast"][1:].double().cpu().numpy()
     assert lag1_error(C, ref["Cs_fast"][1:], ref["Ps_fast"][1:]) <= TOL[torch.float32]
+
+
+@pytest.mark.parametrize("dtype", [torch.float64, torch.float32], ids=["f64", "f32"])
+@pytest.mark.parametrize("nx,ny,L", [(2, 1, 1), (4, 2, 4), (3, 1, 2)])
+def test_slow_filter_outputs_are_the_last_fast_step(nx, ny, L, dtype):
+    """p(x_{k,L} | y_{1:k}) twice, as the slow-rate output and as the last fast step of the same window update:
+    equal to the rounding of its sums (some 20 terms each, 64 units allowed)."""
+    from paper_2410_00627_amd import srtm
+    m = _model("general", nx, ny, L, 4, 1.0, 1e-4)
+    N = 6 * 256 + 5
+    args = [t.to(dtype) for t in srtm.model_tensors(m, "cuda", torch.float64)]
+    yt = torch.as_tensor(wl.simulate(m, N, 91), device="cuda").to(dtype)
+    out = srtm.smooth(*args[:4], L, *args[4:], yt, with_filter=True)
+    P = out["Pf_fast"][:, -1].double().cpu().numpy()
+    e = _errors(out["mf_slow"], out["Pf_slow"], out["mf_fast"][:, -1].double().cpu().numpy(), P)
+    assert max(e) <= 64 * torch.finfo(dtype).eps
