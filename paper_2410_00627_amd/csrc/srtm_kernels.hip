@@ -1916,15 +1916,28 @@ SRTM_DEV void fwd_reduce_body(const T* __restrict__ y, int64_t N, const T* __res
 // filter states and scanned after them, (eta, J) comes from the same tree as the states, so both are
 // found in one pass and no second tile-level scan follows it.
 
+// A combine solves (I + P J) y = u + P ve and (I + P J) X = P by the explicit inverse; then y' = T y + vd and
+// P' = T X T^T + D. Where P J is large, as after a wide prior, the inverse loses digits that T y and T X T^T show
+// (float64, nx = 2, P0 = 1e4 I: filter means 2e-6 off). A wave with P J beyond REFINE_FROM among its
+// problems therefore refines both solutions by one residual step, b - y - P (J y), and takes the mean of X with its
+// transpose; in all waves that would be 10 % of a call (nx = 4, float64, 3000 windows). Float32 calls need none in
+// float64 steps, and nx = 1 and nx > 4 (elimination with pivoting) lost nothing against the window-by-window form.
+constexpr double REFINE_FROM = 256.0;
+
 // One combine in the block layout (four problems per wave): state (u, P) and run (Tt = F^T or F, Dp, Jp, vd,
 // ve), in place. u is a vector held as equal columns; P, Dp and Jp are symmetric.
-template <int NX>
+template <int NX, bool REFINE>
 SRTM_DEV bool combine4(const Block4& B, double& u, double& P, double Tt, double Dp, double Jp, double vd, double ve) {
   bool ok = true;
-  const double w = mm4(P, ve, u);                           // u + P ve
-  const double Wt = B.template inv_t<NX>(mm4(P, Jp, B.eye), ok);         // W^T, W = (I + P Jp)^{-1}
-  const double X = Block4::mm_sym(Wt, P);                   // W P
-  u = mm4(Tt, mm4(Wt, w, 0.0), vd);
+  const double b = mm4(P, ve, u), A = mm4(P, Jp, B.eye);    // u + P ve, I + P Jp
+  const double Wt = B.template inv_t<NX>(A, ok);            // A^{-T}
+  double X = Block4::mm_sym(Wt, P), y = mm4(Wt, b, 0.0);
+  if (REFINE && __any(fabs(A) > REFINE_FROM)) {
+    const double E = mm4(P, -mm4(Jp, X, 0.0), P - X), e = mm4(P, -mm4(Jp, y, 0.0), b - y);
+    X = 0.5 * (mm4(Wt, E, X) + mm4(E, Wt, X));
+    y = mm4(Wt, e, y);
+  }
+  u = mm4(Tt, y, vd);
   P = Block4::mm_sym(Tt, mm4(X, Tt, 0.0)) + Dp;
   return ok;
 }
@@ -2115,17 +2128,72 @@ SRTM_DEV void record_store(const T (&u)[NX], const T (&P)[NX][NX], T* __restrict
 template <typename T, int NX, typename S>
 SRTM_DEV bool lane_combine(Belief<T, NX>& b, const T* __restrict__ tab, const S* __restrict__ nd, int stride, bool fwd) {
   constexpr int NN = NX * NX;
-  T F[NX][NX], D[NX][NX], J[NX][NX], d[NX], e[NX];
-  load(F, tab);
-  load(D, tab + NN);
+  T J[NX][NX], A[NX][NX], W[NX][NX], X[NX][NX], r[NX], y[NX], vd[NX];
   load(J, tab + 2 * NN);
 #pragma unroll
-  for (int r = 0; r < NX; ++r) {
-    const T nd_d = (T)nd[r * stride], nd_e = (T)nd[(NX + r) * stride];
-    d[r] = fwd ? nd_d : nd_e;
-    e[r] = fwd ? nd_e : -nd_d;
+  for (int i = 0; i < NX; ++i) r[i] = b.u[i];
+#pragma unroll
+  for (int k = 0; k < NX; ++k) {
+    const T d = (T)nd[k * stride], e = (T)nd[(NX + k) * stride], ve = fwd ? e : -d;
+    vd[k] = fwd ? d : e;
+#pragma unroll
+    for (int i = 0; i < NX; ++i) r[i] = my_fma(b.P[i][k], ve, r[i]);
   }
-  return state_combine(b.u, b.P, F, d, D, e, J);
+  mm(b.P, J, A);
+  T big = T(0);
+#pragma unroll
+  for (int i = 0; i < NX; ++i) {
+#pragma unroll
+    for (int k = 0; k < NX; ++k) big = my_fma(A[i][k], A[i][k], big);
+    A[i][i] += T(1);
+  }
+  const bool ok = inv_small(A, W);
+  mv(W, r, y);
+#pragma unroll
+  for (int i = 0; i < NX; ++i)
+#pragma unroll
+    for (int c = i; c < NX; ++c) {
+      T t = T(0);
+#pragma unroll
+      for (int k = 0; k < NX; ++k) t = my_fma(W[i][k], b.P[k][c], t);
+      X[i][c] = X[c][i] = t;
+    }
+  if (blocks4<NX>() && __builtin_expect(__any(big > T(REFINE_FROM * REFINE_FROM)), 0)) {
+    auto residual = [&](const T (&q)[NX], const T (&z)[NX], T (&e)[NX]) {  // q - z - P (J z)
+      T Jz[NX];
+      mv(J, z, Jz);
+#pragma unroll
+      for (int i = 0; i < NX; ++i) {
+        T t = q[i] - z[i];
+#pragma unroll
+        for (int k = 0; k < NX; ++k) t = my_fma(-b.P[i][k], Jz[k], t);
+        e[i] = t;
+      }
+    };
+    T e[NX];
+    residual(r, y, e);
+    mv_acc(W, e, y);
+#pragma unroll
+    for (int c = 0; c < NX; ++c) {
+      T q[NX], z[NX];
+#pragma unroll
+      for (int i = 0; i < NX; ++i) q[i] = b.P[i][c];
+      mv(W, q, z);
+      residual(q, z, e);
+      mv_acc(W, e, z);
+#pragma unroll
+      for (int i = 0; i < NX; ++i) X[i][c] = z[i];
+    }
+    symmetrize(X);
+  }
+  T F[NX][NX], D[NX][NX];
+  load(F, tab);
+  load(D, tab + NN);
+#pragma unroll
+  for (int i = 0; i < NX; ++i) b.u[i] = vd[i];
+  mv_acc(F, y, b.u);
+  sandwich(F, X, D, b.P);
+  return ok;
 }
 
 // Information of N's set bits below each bit (tail), low bits first, for a sequence's last windows.
@@ -2150,7 +2218,7 @@ SRTM_DEV bool tail_chain(const double* lev, const T* lane, double* scratch, int6
         const double* lv = lev + q * 48;
         const auto* nd = node(q);
         const double d = B.r < NX ? (double)nd[B.r * stride] : 0.0, e = B.r < NX ? (double)nd[(NX + B.r) * stride] : 0.0;
-        if (!combine4<NX>(B, u, P, lv[4 * B.r + B.c], lv[32 + 4 * B.r + B.c], lv[16 + 4 * B.r + B.c], e, -d)) ok = false;
+        if (!combine4<NX, sizeof(T) == 8>(B, u, P, lv[4 * B.r + B.c], lv[32 + 4 * B.r + B.c], lv[16 + 4 * B.r + B.c], e, -d)) ok = false;
       }
     }
   } else if constexpr (block8<NX>()) {
@@ -2913,6 +2981,7 @@ SRTM_DEV void fold_body(const T* __restrict__ y, int64_t N, int L, int nlev, con
   }
 
   // ---- upper bits
+  constexpr bool REF = sizeof(T) == 8;
   Belief<T, NX> fs, bs;  // filter state at the window's start; information after the window
   bool settled = false;  // the tile's covariances are the same for all of its windows
   int bl = ragged ? 0 : LB;  // the window's bits below bl take backward combines
@@ -2974,7 +3043,7 @@ SRTM_DEV void fold_body(const T* __restrict__ y, int64_t N, int L, int nlev, con
         p = bits ? 31 - __builtin_clz(bits) : LB;
         const Step next = fetch(p);
         double u = cur.f ? fu : bu, P = cur.f ? fP : bP;
-        const bool ok = combine4<NX>(B, u, P, cur.Tt, cur.Dp, cur.Jp, cur.vd, cur.ve);
+        const bool ok = combine4<NX, REF>(B, u, P, cur.Tt, cur.Dp, cur.Jp, cur.vd, cur.ve);
         if (cur.act) {
           if (!ok) flag |= SRTM_INFO_COMBINE_SINGULAR;
           fu = cur.f ? u : fu;
@@ -2993,7 +3062,7 @@ SRTM_DEV void fold_body(const T* __restrict__ y, int64_t N, int L, int nlev, con
       const double* lv = lev + ((B.b & 1) ? LOG_TILE : 0) * 48;
       const double P = f ? fP : bP;
       double u = 0.0, P1 = P;
-      const bool ok = combine4<NX>(B, u, P1, lv[f ? 4 * B.c + B.r : 4 * B.r + B.c], lv[(f ? 16 : 32) + 4 * B.r + B.c],
+      const bool ok = combine4<NX, REF>(B, u, P1, lv[f ? 4 * B.c + B.r : 4 * B.r + B.c], lv[(f ? 16 : 32) + 4 * B.r + B.c],
                                lv[(f ? 32 : 16) + 4 * B.r + B.c], 0.0, 0.0);
       *B.own = P;
       wave_sync();
@@ -3011,9 +3080,15 @@ SRTM_DEV void fold_body(const T* __restrict__ y, int64_t N, int L, int nlev, con
       const double P = f ? fP : bP;
       bool ok = true;
       const double Tt = lv[f ? 4 * B.c + B.r : 4 * B.r + B.c];
-      const double Wt = B.template inv_t<NX>(mm4(P, lv[(f ? 32 : 16) + 4 * B.r + B.c], B.eye), ok);
-      const double G = mm4(Tt, mm4(Wt, B.eye, 0.0), 0.0);
-      const double GP = mm4(Tt, Block4::mm_sym(Wt, P), 0.0);
+      const double Jp = lv[(f ? 32 : 16) + 4 * B.r + B.c], A = mm4(P, Jp, B.eye);
+      const double Wt = B.template inv_t<NX>(A, ok);
+      double W = mm4(Wt, B.eye, 0.0), X = Block4::mm_sym(Wt, P);
+      if (REF && __any(fabs(A) > REFINE_FROM)) {
+        const double E = mm4(P, -mm4(Jp, X, 0.0), P - X), e = mm4(P, -mm4(Jp, W, 0.0), B.eye - W);
+        X = 0.5 * (mm4(Wt, E, X) + mm4(E, Wt, X));
+        W = mm4(Wt, e, W);
+      }
+      const double G = mm4(Tt, W, 0.0), GP = mm4(Tt, X, 0.0);
       double* gain = reinterpret_cast<double*>(smraw + lo.gain);
       if (in4) {
         double* row = gain + ((lvl * 2 + (f ? 0 : 1)) * NX + B.r) * R2;
@@ -5786,8 +5861,10 @@ __global__ void __launch_bounds__(TT) k_tile_tree(Batch b) {
   kb_tile_tree<T, NX, NY, INP>(b, blockIdx.x, TT);
 }
 
+// Workgroups a compute unit holds: with the rare refinement in its code the float32 fold would take 160 registers, 3 a
+// unit, and 262144 windows at nx = 4 4 us more; its spills at 128 fall into that branch.
 template <typename T, int NX, int NY, bool SMOOTH, bool INP>
-__global__ void __launch_bounds__(TILE, NX > 4 && sizeof(T) == 8 ? 1 : 2) k_fold(Batch b, FoldOut want) {
+__global__ void __launch_bounds__(TILE, NX > 4 && sizeof(T) == 8 ? 1 : NX <= 4 && sizeof(T) == 4 ? 4 : 2) k_fold(Batch b, FoldOut want) {
   kb_fold<T, NX, NY, SMOOTH, INP>(b, blockIdx.x, want);
 }
 

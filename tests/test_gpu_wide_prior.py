@@ -46,6 +46,29 @@ def test_smoothed_covariances(kind, nx, ny, L, seed, wide, r, N, dtype):
     assert torch.equal(out["Ps_fast"], out["Ps_fast"].mT)
 
 
+STATES = [  # the filter's means and covariances were 2e-8 .. 1e-6 off in float64, 2e-3 .. 7e-2 in float32
+    ("general", 2, 1, 4, 4, 1e4, 1.0, torch.float64), ("stable", 2, 1, 10, 1, 1e4, 1.0, torch.float64),
+    ("general", 3, 1, 1, 5, 1e4, 1e-2, torch.float64), ("stable", 4, 2, 1, 1, 1e4, 1.0, torch.float64),
+    ("stable", 4, 1, 10, 0, 1e4, 1.0, torch.float64), ("stable", 4, 1, 1, 1, 100.0, 1.0, torch.float32),
+    ("stable", 4, 2, 1, 1, 100.0, 1.0, torch.float32),
+]
+
+
+@pytest.mark.parametrize("N", [30, 2 * 256 + 17])
+@pytest.mark.parametrize("kind,nx,ny,L,seed,wide,r,dtype", STATES)
+def test_filter_states(kind, nx, ny, L, seed, wide, r, dtype, N):
+    from paper_2410_00627_amd import srtm
+    m = _model(kind, nx, ny, L, seed, wide, r)
+    out, ref = _run(m, N, 60 + seed, dtype, with_filter=True)
+    args = [t.to(dtype) for t in srtm.model_tensors(m, "cuda", torch.float64)]
+    alone = srtm.filter(*args[:4], L, *args[4:], torch.as_tensor(wl.simulate(m, N, 60 + seed), device="cuda").to(dtype))
+    for o, k, rk in ((out, "ms_fast", "ms_fast"), (out, "mf_fast", "m_fast"), (out, "mf_slow", "m_slow"),
+                     (alone, "m_fast", "m_fast"), (alone, "m_slow", "m_slow")):
+        P, Pr = o[k.replace("m", "P", 1)], ref[rk.replace("m", "P", 1)]
+        e = _errors(o[k], P, ref[rk], Pr)
+        assert e[0] <= TOL[dtype] and (k == "ms_fast" or e[1] <= TOL[dtype]), (k, e)
+
+
 @pytest.mark.parametrize("r", [1e-3, 1e-4])
 def test_accurate_measurements_float32(r):
     """J P about 700 in every window, settled tiles and the others. From the second window on: the first one's
