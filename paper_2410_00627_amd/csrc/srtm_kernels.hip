@@ -3916,7 +3916,7 @@ SRTM_DEV void recover_body(const T* __restrict__ y, int64_t N, int L, int ilim, 
                            T* __restrict__ mf_fast,
                            T* __restrict__ Pf_fast, T* __restrict__ ms_fast, T* __restrict__ Ps_fast,
                            T* __restrict__ ms_slow, T* __restrict__ Ps_slow, T* __restrict__ mf_slow,
-                           T* __restrict__ Pf_slow, int32_t* info, int64_t tile, int part, int nparts, int nslow) {
+                           int32_t* info, int64_t tile, int part, int nparts, int nslow) {
   constexpr int NN = NX * NX, ST = NX + NN, SF = sfx_stride(NX);
   static_assert(TILE == 256, "one recovery workgroup per tile");
   constexpr bool FILT = (MODE & 1) != 0, SMOOTH = (MODE & 2) != 0;
@@ -3973,13 +3973,15 @@ SRTM_DEV void recover_body(const T* __restrict__ y, int64_t N, int L, int ilim, 
 #pragma unroll
     for (int j = 0; j < NU_MAX; ++j) un[j] = (j < in.nu) ? gld(uk + j) : T(0);
   }
-  // Slow-rate filter outputs beside smoothed ones: a window update keeps the digits of an accurate measurement that
-  // the fold's state of the next window loses (its runs carry y as eta = C_bar^T R_x^{-1} y, rounded).
+  // The slow-rate filter means beside smoothed outputs: a window update keeps the digits of an accurate measurement
+  // that the fold's state of the next window loses (its runs carry y as eta = C_bar^T R_x^{-1} y, rounded). The
+  // covariances stay the fold's, which loses none where the update subtracts nearly equal matrices.
   if constexpr (SMOOTH && !TV) {
-    if ((mf_slow || Pf_slow) && part == 0 && valid) {
+    if (mf_slow && part == 0 && valid) {
       T ml[NX], Pl[NX][NX];
       window_slow_state<INP>(M, L, w, zL, ml, Pl);
-      flag |= store_slow(k, ml, Pl, mf_slow, Pf_slow);
+#pragma unroll
+      for (int r = 0; r < NX; ++r) put_global(mf_slow + k * NX + r, ml[r]);
     }
   }
   T v[NX], W[NX][NX];
@@ -5773,16 +5775,17 @@ SRTM_DEV void kb_tile_tree(const Batch& b, int64_t bid, int nthr) {
                                  q.info, nthr);
 }
 
-// What the fold writes besides its records: the slow-rate filter outputs (where no smoothing recovery writes them), and
-// with them, or where only the state tells of a failure there, the state after the last window.
+// What the fold writes besides its records and the slow-rate filter covariances: the slow-rate filter means (where no
+// smoothing recovery writes them), and the state after the last window (an output, or the only place where a failure
+// there shows).
 struct FoldOut {
-  bool slow, last;
+  bool means, last;
 };
 
 template <typename T, int NX, int NY, bool SMOOTH, bool INP>
 SRTM_DEV void kb_fold(const Batch& b, int64_t bid, FoldOut want) {
   Seq<T, NX, NY> q = seq_view<T, NX, NY>(b, tile_sequence(b, bid));
-  if (!want.slow) q.mf_slow = q.Pf_slow = nullptr;
+  if (!want.means) q.mf_slow = nullptr;
   fold_body<SMOOTH, INP, T, NX, NY>(q.y, q.N, q.L, q.plan.nlev, q.cst, q.lev64, q.in, q.m0, q.P0, q.ftagg, q.ftst, q.utree, q.tail,
                                     q.carry, q.mf_slow, q.Pf_slow, q.sfx, q.info, bid - q.tile0, want.last);
 }
@@ -5842,8 +5845,7 @@ SRTM_DEV void kb_recover(const Batch& b, int64_t bid, Split sp) {
   if (!fast && !q.ms_slow && !q.Ps_slow) return;
   recover_body<T, NX, NY, MODE, INP, TV>(q.y, q.N, q.L, fast ? q.L : 1, TV ? q.tvblk : q.cst, q.in, q.F, q.Q, q.m0,
                                          q.P0, q.carry, q.sfx, q.btst, q.utree, q.mf_fast, q.Pf_fast, q.ms_fast, q.Ps_fast,
-                                         q.ms_slow, q.Ps_slow, q.mf_slow, q.Pf_slow, q.info, TV ? i : ends_first(i, q.plan.nt), part,
-                                         sp.all, nparts);
+                                         q.ms_slow, q.Ps_slow, q.mf_slow, q.info, TV ? i : ends_first(i, q.plan.nt), part, sp.all, nparts);
 }
 
 template <typename T, int NX, int NY>
@@ -6076,9 +6078,8 @@ srtm_status launch_all(const Batch& b, const Launch& g, bool smoother, int rec_m
   const size_t lds_fold = FoldLds<T, NX>(nlev_max).total;
   const Split sp = make_split<NX>(g.ntiles, g.nseq);
   const unsigned nrec = g.ntiles * sp.all + sp.extra;
-  // the last carry is an output of its own, or the only place where a last window's failure shows
-  const bool slow = !(smoother && (rec_mode == 2 || rec_mode == 3));
-  const FoldOut want{slow, (slow && (b.one.mf_slow || b.one.Pf_slow)) || rec_mode == REC_LL || rec_mode == REC_GRAD};
+  const FoldOut want{!(smoother && (rec_mode == 2 || rec_mode == 3)),
+                     b.one.mf_slow || b.one.Pf_slow || rec_mode == REC_LL || rec_mode == REC_GRAD};
 
   // output staging, then the per-step tables of up to RSTEPS fast steps
   const size_t ptab = sizeof(T) * (size_t)(g.max_L < RSTEPS ? g.max_L : RSTEPS) *

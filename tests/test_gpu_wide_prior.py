@@ -82,9 +82,10 @@ def test_accurate_measurements_float32(r):
 
 @pytest.mark.parametrize("dtype", [torch.float64, torch.float32], ids=["f64", "f32"])
 @pytest.mark.parametrize("nx,ny,L", [(2, 1, 1), (4, 2, 4), (3, 1, 2)])
-def test_slow_filter_outputs_are_the_last_fast_step(nx, ny, L, dtype):
-    """p(x_{k,L} | y_{1:k}) twice, as the slow-rate output and as the last fast step of the same window update:
-    equal to the rounding of its sums (some 20 terms each, 64 units allowed)."""
+def test_slow_filter_means_are_the_last_fast_step(nx, ny, L, dtype):
+    """The mean of x_{k,L} given y_{1:k} twice, as the slow-rate output and as the last fast step of the same window
+    update: equal to the rounding of its sums (some 20 terms each, 64 units allowed). The slow-rate covariance, which
+    is not taken from that update, against the float64 oracle: in float32 it keeps digits that the update's loses."""
     from paper_2410_00627_amd import srtm
     m = _model("general", nx, ny, L, 4, 1.0, 1e-4)
     N = 6 * 256 + 5
@@ -93,4 +94,7 @@ def test_slow_filter_outputs_are_the_last_fast_step(nx, ny, L, dtype):
     out = srtm.smooth(*args[:4], L, *args[4:], yt, with_filter=True)
     P = out["Pf_fast"][:, -1].double().cpu().numpy()
     e = _errors(out["mf_slow"], out["Pf_slow"], out["mf_fast"][:, -1].double().cpu().numpy(), P)
-    assert max(e) <= 64 * torch.finfo(dtype).eps
+    assert e[0] <= 64 * torch.finfo(dtype).eps
+    a = [t.double().cpu().numpy() for t in (*args, yt)]
+    ref = oracle.srtm_smoother(a[0], a[1], a[2], a[3], L, a[4], a[5], a[6], with_filter=True)
+    assert _errors(out["mf_slow"], out["Pf_slow"], ref["m_slow"], ref["P_slow"])[1] <= 1e-2 * TOL[dtype]
