@@ -3847,33 +3847,46 @@ struct NoSteps {};
 // The fast steps of a window do not wait for each other, so a tile's can be split over workgroups, each of
 // which repeats what precedes the steps. A tile that has not settled is slow (nx = 4, L = 20, float64: about
 // 40 us for its workgroup), and with few tiles that is the launch:
-//   - where tiles settle (nx 2 .. 4), the slow ones of the first END_TILES tiles of a sequence (ends_first) take 5
-//     parts, or 3 once there is a tile for every compute unit; a batch of more than END_SEQS sequences fills the
-//     device without them. 32767 windows (128 tiles, with inputs, float64): 37 us in 3 parts, 29 us in 5; 276 tiles of
-//     15 sequences (float32): 27 us in 3 parts, 31 us in 5.
+//   - where tiles settle (nx 2 .. 4), the slow ones of the first END_TILES tiles of each sequence (ends_first) take parts
+//     of their own: 5 while that leaves a compute unit for every workgroup; 3, or else 2, while the device holds all of
+//     them, the parts counted half, since about half of these tiles have settled and their parts leave at once; at
+//     nx = 2, where a slow tile is short, 2 at most. Beyond that the parts only queue before the other tiles. One
+//     sequence (nx = 4, L = 20, float64; tiles: whole, 3, 5 parts): 128 with inputs: 121, 86, 78 us a call; 235: 94,
+//     87, 90. Batches of 3000 windows each (nx = 4, L = 10; whole, 2, 3, 5 parts): 8 sequences, float64: 62, 58, 53, 55;
+//     15, float64: 68, 69, 80, 80; 24, float32: 68, 66, 63, 65; 40 of 1000 windows, float64: 64, 66, 69, 76.
+//     Part p of all sequences' n-th tile follow each other in the grid, so that the first tiles, slow in every
+//     sequence, spread over the dies (a sequence's parts together put them on the same ones: the 24 sequences 78 us in 5).
 //   - every tile takes as many parts as let all workgroups run at once; where tiles settle, which leaves a
 //     part little but what it repeats, half as many (128 tiles, 2 parts: 41 us against 32 us whole).
 // Recovery of 16000 windows (63 tiles) at nx = 6 in float32: 95 us whole, 37 us in 4 parts; 6000 windows at
 // nx = 4 in float64: 17.5 us with the end tiles alone split, 14.7 us in 5 parts.
 struct Split {
   int extra, all, ends;  // extra workgroups, first in the grid, for the end tiles; parts of any tile, of an end tile
+  int nseq;
 };
-constexpr int CUS = 256, END_TILES = 8, END_SEQS = 16, MAX_PARTS = 8, MIN_STEPS = 4;
-template <int NX>
+constexpr int CUS = 256, END_TILES = 8, MAX_PARTS = 8, MIN_STEPS = 4;
+// Recovery workgroups that a compute unit has to hold (one wave of each on a SIMD); float64 at nx <= 3 fits twice as well.
+template <typename T, int NX, bool TV>
+constexpr int recover_per_cu() {
+  return sizeof(T) == 4 && NX <= 4 && !TV ? 2 : 1;
+}
+template <typename T, int NX>
 inline Split make_split(int64_t ntiles, int64_t nseq) {
   const int64_t fit = (blocks4<NX>() ? CUS / 2 : CUS) / ntiles;
   const int all = (int)(fit < 1 ? 1 : fit > MAX_PARTS ? MAX_PARTS : fit);
-  const int ends = ntiles < CUS ? 5 : 3;
-  if (!blocks4<NX>() || nseq > END_SEQS || all >= ends) return Split{0, all, all};
-  return Split{(int)nseq * END_TILES * (ends - 1), all, ends};
+  if (!blocks4<NX>()) return Split{0, all, all, 1};
+  const int64_t slow = nseq * END_TILES, room = CUS * (sizeof(T) == 4 || NX <= 3 ? 2 : 1) - ntiles * all;
+  const int ends = NX > 2 && ntiles * all + 4 * slow <= CUS ? 5 : NX > 2 && slow <= room ? 3 : slow <= 2 * room ? 2 : 1;
+  if (all >= ends) return Split{0, all, all, 1};
+  return Split{(int)slow * (ends - 1), all, ends, (int)nseq};
 }
 // The tile's number in its sequence (ends_first) and its part for workgroup bid, given the grid's numbering.
 SRTM_DEV void split_place(const Split& sp, int64_t bid, int& seq, int64_t& i, int& part) {
   if (bid < sp.extra) {
     const int per = sp.ends - 1, e = (int)bid / per;
     part = 1 + (int)bid % per;
-    seq = e / END_TILES;
-    i = e % END_TILES;
+    seq = e % sp.nseq;
+    i = e / sp.nseq;
   } else {
     const unsigned w = (unsigned)(bid - sp.extra);
     seq = -1;
@@ -5902,12 +5915,6 @@ __global__ void __launch_bounds__(TILE) k_tv_fwd(Batch b) {
   kb_tv_fwd<T, NX, NY, SMOOTH>(b, blockIdx.x);
 }
 
-// Recovery workgroups a compute unit holds (one wave of each on a SIMD).
-template <typename T, int NX, bool TV>
-constexpr int recover_per_cu() {
-  return sizeof(T) == 4 && NX <= 4 && !TV ? 2 : 1;
-}
-
 template <typename T, int NX, int NY, int MODE, bool INP, bool TV = false>
 __global__ void __launch_bounds__(TILE, (recover_per_cu<T, NX, TV>())) k_recover(Batch b, Split sp) {
   kb_recover<T, NX, NY, MODE, INP, TV>(b, blockIdx.x, sp);
@@ -6076,7 +6083,7 @@ srtm_status launch_all(const Batch& b, const Launch& g, bool smoother, int rec_m
     SRTM_EV(ev.post(st));
   }
   const size_t lds_fold = FoldLds<T, NX>(nlev_max).total;
-  const Split sp = make_split<NX>(g.ntiles, g.nseq);
+  const Split sp = make_split<T, NX>(g.ntiles, g.nseq);
   const unsigned nrec = g.ntiles * sp.all + sp.extra;
   const FoldOut want{!(smoother && (rec_mode == 2 || rec_mode == 3)),
                      b.one.mf_slow || b.one.Pf_slow || rec_mode == REC_LL || rec_mode == REC_GRAD};
@@ -6171,7 +6178,7 @@ srtm_status launch_tv(const Batch& b, const Launch& g, bool smoother, int rec_mo
       SRTM_CHECK_LAUNCH();
       if (rec_mode == 1) {
         if (!allow_lds((const void*)k_recover<T, NX, NY, 1, false, true>, lds_rec)) return SRTM_E_HIP;
-        hipLaunchKernelGGL((k_recover<T, NX, NY, 1, false, true>), dim3(g.ntiles), dim3(TILE), lds_rec, st, b, Split{0, 1, 1});
+        hipLaunchKernelGGL((k_recover<T, NX, NY, 1, false, true>), dim3(g.ntiles), dim3(TILE), lds_rec, st, b, Split{0, 1, 1, 1});
         SRTM_CHECK_LAUNCH();
       }
       return SRTM_OK;
@@ -6186,11 +6193,11 @@ srtm_status launch_tv(const Batch& b, const Launch& g, bool smoother, int rec_mo
     if (rec_mode == 2 || rec_mode == 3) {  // filter and smoother outputs: two recovery passes
       if (rec_mode == 3) {
         if (!allow_lds((const void*)k_recover<T, NX, NY, 1, false, true>, lds_rec)) return SRTM_E_HIP;
-        hipLaunchKernelGGL((k_recover<T, NX, NY, 1, false, true>), dim3(g.ntiles), dim3(TILE), lds_rec, st, b, Split{0, 1, 1});
+        hipLaunchKernelGGL((k_recover<T, NX, NY, 1, false, true>), dim3(g.ntiles), dim3(TILE), lds_rec, st, b, Split{0, 1, 1, 1});
         SRTM_CHECK_LAUNCH();
       }
       if (!allow_lds((const void*)k_recover<T, NX, NY, 2, false, true>, lds_rec)) return SRTM_E_HIP;
-      hipLaunchKernelGGL((k_recover<T, NX, NY, 2, false, true>), dim3(g.ntiles), dim3(TILE), lds_rec, st, b, Split{0, 1, 1});
+      hipLaunchKernelGGL((k_recover<T, NX, NY, 2, false, true>), dim3(g.ntiles), dim3(TILE), lds_rec, st, b, Split{0, 1, 1, 1});
       SRTM_CHECK_LAUNCH();
     }
     return SRTM_OK;
@@ -6243,7 +6250,7 @@ srtm_status run(const srtm_shape& sh, const Ptrs& p, bool smoother, hipStream_t 
   if (s != SRTM_OK) return s;
   const size_t lds = (size_t)4 * OutStage<T, NX>::BYTES;
   if (!allow_lds((const void*)k_lag1<T, NX, NY>, lds)) return SRTM_E_HIP;
-  const Split sp = make_split<NX>(g.ntiles, 1);
+  const Split sp = make_split<T, NX>(g.ntiles, 1);
   hipLaunchKernelGGL((k_lag1<T, NX, NY>), dim3(g.ntiles * sp.all + sp.extra), dim3(TILE), lds, st, b, sp);
   SRTM_CHECK_LAUNCH();
   return SRTM_OK;
@@ -6366,7 +6373,7 @@ __global__ void __launch_bounds__(TILE) km_recover(Batch b, Split sp) {
     if (d.tv) {                                                                 \
       if constexpr (a <= TV_NX_MAX)                                             \
         if (blockIdx.x % (unsigned)sp.all == 0)                                 \
-          kb_recover<T, a, c, 2, false, true>(b, blockIdx.x / (unsigned)sp.all, Split{0, 1, 1}); \
+          kb_recover<T, a, c, 2, false, true>(b, blockIdx.x / (unsigned)sp.all, Split{0, 1, 1, 1}); \
     } else if (d.B) {                                                           \
       kb_recover<T, a, c, 2, true>(b, blockIdx.x, sp);                          \
     } else {                                                                    \
@@ -6440,7 +6447,7 @@ srtm_status run_mixed(const SeqDesc* host, const void* table_dev, int nseq, int6
   // fill the device better (178 tiles of 15 sequences: 94 us whole, 58 us in 4 parts, 62 us with those of nx <= 4
   // whole); with several tiles per compute unit they do that by themselves.
   const int parts = nt > 4 * CUS ? 1 : nt > 2 * CUS ? 2 : 4;
-  const Split sp{0, parts, parts};
+  const Split sp{0, parts, parts, 1};
   hipLaunchKernelGGL((km_recover<T>), dim3(nt * parts), dim3(TILE), lds[5], st, b, sp);
   SRTM_CHECK_LAUNCH();
   return SRTM_OK;
