@@ -1713,17 +1713,17 @@ SRTM_DEV int top_bit(int64_t x) { return x > 0 ? 63 - __clzll(x) : -1; }
 template <int NX>
 constexpr int row_slots() { return 2 * NX <= 2 ? 2 : 2 * NX <= 4 ? 4 : 2 * NX <= 8 ? 8 : 16; }
 
-template <typename T, int NX>
+template <typename T, int NX, typename ACC = T>
 SRTM_DEV T row_combine(const T* __restrict__ co, const T* __restrict__ left, const T* __restrict__ right, int r, int stride) {
-  T acc = r < NX ? right[r * stride] : left[r * stride];
+  ACC acc = (ACC)(r < NX ? right[r * stride] : left[r * stride]);
   const T* a = r < NX ? left : right + NX * stride;
   const T* b = r < NX ? right + NX * stride : left;
 #pragma unroll
   for (int k = 0; k < NX; ++k) {
-    acc = my_fma(co[k], a[k * stride], acc);
-    acc = my_fma(co[NX + k], b[k * stride], acc);
+    acc = my_fma((ACC)co[k], (ACC)a[k * stride], acc);
+    acc = my_fma((ACC)co[NX + k], (ACC)b[k * stride], acc);
   }
-  return acc;
+  return (T)acc;
 }
 
 // Entry q of the row tables of consecutive levels (4 nx^2 scalars a level), from the level records at
@@ -1798,14 +1798,23 @@ SRTM_DEV void fwd_element(const Model<T, NX, NY>& M, const T (&yt)[NY], const T 
   }
 }
 
+// How a tile's tree is formed: pairs on the matrix cores (pair_combine), or one thread per node and output row
+// (row_combine), its sums in the element type or in float64.
+enum TreeForm { TREE_MFMA, TREE_ROWS, TREE_ROWS64 };
+// The matrix cores take nx = 3 and 4. A pair of shorter vectors is less than their 4 x 4 blocks carry: 2048 tiles of
+// 64 sequences at nx = 2 (float32) take 16 us there, 9 us in rows; 12 tiles at nx = 1 (float64) 5.8 and 4.0.
+template <typename T, int NX>
+constexpr TreeForm tree_form() { return NX > 4 || (NX <= 2 && sizeof(T) == 8) ? TREE_ROWS : NX <= 2 ? TREE_ROWS64 : TREE_MFMA; }
+
 // K1: the dyadic tree of one tile over the vector parts (d, eta) of its windows' filter elements: levels
-// 1 .. LOG_TILE-1 to `utree`, the tile's own node to `ftagg`. nx <= 4: pairs on the matrix cores
-// (pair_combine). nx > 4, and the float32 gradient, whose results keep their rounding (ROWS): one thread
-// per node and output row (row_combine).
-template <bool INP, bool ROWS, typename T, int NX, int NY>
+// 1 .. LOG_TILE-1 to `utree`, the tile's own node to `ftagg`. The float32 gradient, whose results keep their rounding,
+// takes TREE_ROWS for every nx.
+template <bool INP, TreeForm FORM, typename T, int NX, int NY>
 SRTM_DEV void fwd_reduce_body(const T* __restrict__ y, int64_t N, const T* __restrict__ cst, int L,
                               InputView<T> in, T* __restrict__ tagg, T* __restrict__ utree, int64_t tile) {
   constexpr int NN = NX * NX, R2 = 2 * NX, RS2 = row_slots<NX>();
+  constexpr bool ROWS = FORM != TREE_MFMA;
+  using ACC = std::conditional_t<FORM == TREE_ROWS64, double, T>;
   extern __shared__ char smraw[];
   T* leaf = reinterpret_cast<T*>(smraw);  // rows of TILE elements, then of the tree's TILE slots, then (ROWS)
   T* tree = leaf + R2 * TILE;
@@ -1872,7 +1881,7 @@ SRTM_DEV void fwd_reduce_body(const T* __restrict__ y, int64_t N, const T* __res
 #pragma unroll
         for (int k2 = 0; k2 < R2; ++k2) cr[k2] = sC[((p - 1) * R2 + row) * R2 + k2];
         for (int i = tid / RS2; i < n; i += TILE / RS2)
-          dst[row * TILE + i] = row_combine<T, NX>(cr, src + 2 * i, src + 2 * i + 1, row, TILE);
+          dst[row * TILE + i] = row_combine<T, NX, ACC>(cr, src + 2 * i, src + 2 * i + 1, row, TILE);
       }
       __syncthreads();
     }
@@ -5769,7 +5778,7 @@ SRTM_DEV void kb_constants(const Batch& b, int64_t bid) {
 
 // Workgroups 0 .. nseq-1 continue the level chains of the sequences; the others reduce tile
 // bid - nseq of the call.
-template <typename T, int NX, int NY, bool INP, bool ROWS = (NX > 4)>
+template <typename T, int NX, int NY, bool INP, TreeForm FORM = tree_form<T, NX>()>
 SRTM_DEV void kb_fwd_reduce(const Batch& b, int64_t bid, int nseq) {
   if (bid < nseq) {
     const Seq<T, NX, NY> q = seq_view<T, NX, NY>(b, (int)bid);
@@ -5778,7 +5787,7 @@ SRTM_DEV void kb_fwd_reduce(const Batch& b, int64_t bid, int nseq) {
   }
   const int64_t t = bid - nseq;
   const Seq<T, NX, NY> q = seq_view<T, NX, NY>(b, tile_sequence(b, t));
-  fwd_reduce_body<INP, ROWS, T, NX, NY>(q.y, q.N, q.cst, q.L, q.in, q.ftagg, q.utree, t - q.tile0);
+  fwd_reduce_body<INP, FORM, T, NX, NY>(q.y, q.N, q.cst, q.L, q.in, q.ftagg, q.utree, t - q.tile0);
 }
 
 template <typename T, int NX, int NY, bool INP>
@@ -5866,9 +5875,9 @@ __global__ void __launch_bounds__(256) k_constants(Batch b) {
   kb_constants<T, NX, NY>(b, blockIdx.x);
 }
 
-template <typename T, int NX, int NY, bool INP, bool ROWS = (NX > 4)>
+template <typename T, int NX, int NY, bool INP, TreeForm FORM = tree_form<T, NX>()>
 __global__ void __launch_bounds__(TILE) k_fwd_reduce(Batch b, int nseq) {
-  kb_fwd_reduce<T, NX, NY, INP, ROWS>(b, blockIdx.x, nseq);
+  kb_fwd_reduce<T, NX, NY, INP, FORM>(b, blockIdx.x, nseq);
 }
 
 template <typename T, int NX, int NY, bool INP>
@@ -6043,7 +6052,7 @@ srtm_status launch_all(const Batch& b, const Launch& g, bool smoother, int rec_m
 
   constexpr size_t lds_red = fwd_reduce_lds_bytes<T, NX>();
   if (grad_by_elements<T>() && rec_mode == REC_GRAD) {
-    SRTM_STAGE((k_fwd_reduce<T, NX, NY, INP, NX <= 4 ? grad_by_elements<T>() : true>), dim3(g.ntiles + g.nseq), dim3(TILE),
+    SRTM_STAGE((k_fwd_reduce<T, NX, NY, INP, TREE_ROWS>), dim3(g.ntiles + g.nseq), dim3(TILE),
                lds_red, st, b, (int)g.nseq);
   } else {
     SRTM_STAGE((k_fwd_reduce<T, NX, NY, INP>), dim3(g.ntiles + g.nseq), dim3(TILE), lds_red, st, b, (int)g.nseq);
