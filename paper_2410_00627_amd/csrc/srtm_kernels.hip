@@ -2828,7 +2828,8 @@ SRTM_DEV int store_carry(int64_t k, const T (&m)[NX], const T (&P)[NX][NX], T* _
 // `mcol` of a tile of nw windows, record_load; zero after the last window, which gives v = 0 and W = 0). Returns false when I + J P is numerically singular.
 // After a wide prior or with accurate measurements P is many times J^{-1}, and P^f_{i,l} multiplies what W and v lose:
 // in float64 for both types, W exactly symmetric (a mean with its transpose), and for float64, which has no wider
-// type, one step of iterative refinement of both solutions.
+// type, one step of iterative refinement of both solutions in waves with J P beyond REFINE_FROM (in all of them the
+// recovery of 3000 windows at nx = 4 took 1 us more).
 template <bool INP, typename T, int NX, int NY, typename S>
 SRTM_DEV bool info_correction(const Model<T, NX, NY>& M, int L, const Window<T, NX, NY>& w, const T (&zL)[NX],
                               const S* __restrict__ col, const S* __restrict__ mcol, int nw, T (&v)[NX], T (&W)[NX][NX]) {
@@ -2847,13 +2848,26 @@ SRTM_DEV bool info_correction(const Model<T, NX, NY>& M, int L, const Window<T, 
     }
   }
   mm(J, P, A);
+  double big = 0.0;
 #pragma unroll
-  for (int i = 0; i < NX; ++i) A[i][i] += 1.0;
+  for (int i = 0; i < NX; ++i) {
+#pragma unroll
+    for (int k = 0; k < NX; ++k) big = fma(A[i][k], A[i][k], big);
+    A[i][i] += 1.0;
+  }
   const bool ok = inv_small(A, Ai);
-  // (I + J P) y = b from y = Ai b, refined by the residual b - y - J (P y)
-  auto solve = [&](const double (&b)[NX], double (&y)[NX]) {
-    mv(Ai, b, y);
-    if constexpr (sizeof(T) == 8) {
+  mv(Ai, r, x);
+#pragma unroll
+  for (int i = 0; i < NX; ++i)
+#pragma unroll
+    for (int c = 0; c < NX; ++c) {
+      double t = 0.0;
+#pragma unroll
+      for (int k = 0; k < NX; ++k) t = fma(-Ai[i][k], J[k][c], t);
+      X[i][c] = t;
+    }
+  if (sizeof(T) == 8 && __builtin_expect(__any(big > REFINE_FROM * REFINE_FROM), 0)) {
+    auto refine = [&](const double (&b)[NX], double (&y)[NX]) {  // by the residual b - y - J (P y)
       double Py[NX], e[NX];
       mv(P, y, Py);
 #pragma unroll
@@ -2864,17 +2878,20 @@ SRTM_DEV bool info_correction(const Model<T, NX, NY>& M, int L, const Window<T, 
         e[i] = t;
       }
       mv_acc(Ai, e, y);
+    };
+    refine(r, x);
+#pragma unroll
+    for (int c = 0; c < NX; ++c) {
+      double b[NX], y[NX];
+#pragma unroll
+      for (int i = 0; i < NX; ++i) {
+        b[i] = -J[i][c];
+        y[i] = X[i][c];
+      }
+      refine(b, y);
+#pragma unroll
+      for (int i = 0; i < NX; ++i) X[i][c] = y[i];
     }
-  };
-  solve(r, x);
-#pragma unroll
-  for (int c = 0; c < NX; ++c) {
-    double b[NX], y[NX];
-#pragma unroll
-    for (int i = 0; i < NX; ++i) b[i] = -J[i][c];
-    solve(b, y);
-#pragma unroll
-    for (int i = 0; i < NX; ++i) X[i][c] = y[i];
   }
 #pragma unroll
   for (int i = 0; i < NX; ++i) {
