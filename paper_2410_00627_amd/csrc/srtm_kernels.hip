@@ -2346,6 +2346,7 @@ SRTM_DEV void tile_tree_body(const T* __restrict__ y, int64_t N, int nlev, const
   // memory (each of them waits for its stores); the others stay in LDS, rows of 2 TT_NODES slots, and are
   // stored together at the end, so that no level waits for a store to arrive.
   constexpr int ST = 2 * TT_NODES;
+  using ACC = std::conditional_t<tree_form<T, NX>() == TREE_ROWS64, double, T>;
   const int row = tid % RS2, wv = tid >> 6;
   int q0 = 0;              // first level kept in LDS
   while ((nf >> q0) > TT_NODES) ++q0;
@@ -2374,7 +2375,7 @@ SRTM_DEV void tile_tree_body(const T* __restrict__ y, int64_t N, int nlev, const
     for (int q = q0 + 1; (nf >> q) > 0; ++q) {
       const int below = (int)(nf >> (q - 1)), nn = (int)(nf >> q);
       const int to = (at + below + 1) & ~1;  // pairs are read whole: even slots
-      if constexpr (NX <= 4) {
+      if constexpr (tree_form<T, NX>() == TREE_MFMA) {
         PairCoef<T, NX> co;
         co.load_lds(sC + (q - 1) * 4 * NN);
         for (int g = wv; g < (nn + 15) / 16; g += nthr >> 6) pair_combine<T, NX>(co, nodes + at, nodes + to, ST, g, nn);
@@ -2383,7 +2384,7 @@ SRTM_DEV void tile_tree_body(const T* __restrict__ y, int64_t N, int nlev, const
 #pragma unroll
         for (int k2 = 0; k2 < R2; ++k2) co[k2] = sC[((q - 1) * R2 + row) * R2 + k2];
         for (int i = tid / RS2; i < nn; i += nthr / RS2)
-          nodes[row * ST + to + i] = row_combine<T, NX>(co, nodes + at + 2 * i, nodes + at + 2 * i + 1, row, ST);
+          nodes[row * ST + to + i] = row_combine<T, NX, ACC>(co, nodes + at + 2 * i, nodes + at + 2 * i + 1, row, ST);
       }
       at = to;
       __syncthreads();
