@@ -2826,19 +2826,25 @@ SRTM_DEV int store_carry(int64_t k, const T (&m)[NX], const T (&P)[NX][NX], T* _
 
 // Smoother correction of window k (fold section): v = (I + J P)^{-1} (eta - J m), W = -(I + J P)^{-1} J, from its
 // inclusive filter state (m, P) = (m^f_{k,l}, P^f_{k,l}) and its information record (columns `col` and
-// `mcol` of a tile of nw windows, record_load; zero after the last window, which gives v = 0 and W = 0). Returns false when I + J P is numerically singular.
+// `mcol` of a tile of nw windows, record_load; zero after the last window, which gives v = 0 and W = 0). `mean` (may be
+// null) receives m. Returns false when I + J P is numerically singular.
 // After a wide prior or with accurate measurements P is many times J^{-1}, and P^f_{i,l} multiplies what W and v lose:
 // in float64 for both types, W exactly symmetric (a mean with its transpose), and for float64, which has no wider
 // type, one step of iterative refinement of both solutions in waves with J P beyond REFINE_FROM (in all of them the
 // recovery of 3000 windows at nx = 4 took 1 us more).
 template <bool INP, typename T, int NX, int NY, typename S>
 SRTM_DEV bool info_correction(const Model<T, NX, NY>& M, int L, const Window<T, NX, NY>& w, const T (&zL)[NX],
-                              const S* __restrict__ col, const S* __restrict__ mcol, int nw, T (&v)[NX], T (&W)[NX][NX]) {
+                              const S* __restrict__ col, const S* __restrict__ mcol, int nw, T (&v)[NX], T (&W)[NX][NX],
+                              T* __restrict__ mean = nullptr) {
   double P[NX][NX], r[NX], J[NX][NX], A[NX][NX], Ai[NX][NX], x[NX], X[NX][NX];
   record_load(r, J, col, mcol, nw);
   {
     T m[NX], Pt[NX][NX];
     window_slow_state<INP>(M, L, w, zL, m, Pt);
+    if (mean) {
+#pragma unroll
+      for (int i = 0; i < NX; ++i) put_global(mean + i, m[i]);
+    }
 #pragma unroll
     for (int i = 0; i < NX; ++i) {
 #pragma unroll
@@ -4013,20 +4019,13 @@ SRTM_DEV void recover_body(const T* __restrict__ y, int64_t N, int L, int ilim, 
 #pragma unroll
     for (int j = 0; j < NU_MAX; ++j) un[j] = (j < in.nu) ? gld(uk + j) : T(0);
   }
-  // The slow-rate filter means beside smoothed outputs: a window update keeps the digits of an accurate measurement
-  // that the fold's state of the next window loses (its runs carry y as eta = C_bar^T R_x^{-1} y, rounded). The
-  // covariances stay the fold's, which loses none where the update subtracts nearly equal matrices.
-  if constexpr (SMOOTH && !TV) {
-    if (mf_slow && part == 0 && valid) {
-      T ml[NX], Pl[NX][NX];
-      window_slow_state<INP>(M, L, w, zL, ml, Pl);
-#pragma unroll
-      for (int r = 0; r < NX; ++r) put_global(mf_slow + k * NX + r, ml[r]);
-    }
-  }
   T v[NX], W[NX][NX];
   if constexpr (SMOOTH && !TV) {
-    if (!info_correction<INP>(M, L, w, zL, sfx + col, sfx + mcol, nw, v, W) && valid)
+    // The slow-rate filter means beside smoothed outputs: a window update keeps the digits of an accurate measurement
+    // that the fold's state of the next window loses (its runs carry y as eta = C_bar^T R_x^{-1} y, rounded). The
+    // covariances stay the fold's, which loses none where the update subtracts nearly equal matrices.
+    T* mean = mf_slow && part == 0 && valid ? mf_slow + k * NX : nullptr;
+    if (!info_correction<INP>(M, L, w, zL, sfx + col, sfx + mcol, nw, v, W, mean) && valid)
       flag |= SRTM_INFO_COMBINE_SINGULAR;
   } else if constexpr (SMOOTH) {  // v = Et m_in + gt,  W = Et P_in Et^T + St
     const T* src = sfx + kc * SF;
