@@ -3898,17 +3898,17 @@ struct Split {
   int nseq;
 };
 constexpr int CUS = 256, END_TILES = 8, MAX_PARTS = 8, MIN_STEPS = 4;
-// Recovery workgroups that a compute unit has to hold (one wave of each on a SIMD); float64 at nx <= 3 fits twice as well.
+// Recovery workgroups a compute unit holds (one wave of each on a SIMD).
 template <typename T, int NX, bool TV>
 constexpr int recover_per_cu() {
-  return sizeof(T) == 4 && NX <= 4 && !TV ? 2 : 1;
+  return NX <= (sizeof(T) == 4 ? 4 : 3) && !TV ? 2 : 1;
 }
 template <typename T, int NX>
 inline Split make_split(int64_t ntiles, int64_t nseq) {
   const int64_t fit = (blocks4<NX>() ? CUS / 2 : CUS) / ntiles;
   const int all = (int)(fit < 1 ? 1 : fit > MAX_PARTS ? MAX_PARTS : fit);
   if (!blocks4<NX>()) return Split{0, all, all, 1};
-  const int64_t slow = nseq * END_TILES, room = CUS * (sizeof(T) == 4 || NX <= 3 ? 2 : 1) - ntiles * all;
+  const int64_t slow = nseq * END_TILES, room = CUS * recover_per_cu<T, NX, false>() - ntiles * all;
   const int ends = NX > 2 && ntiles * all + 4 * slow <= CUS ? 5 : NX > 2 && slow <= room ? 3 : slow <= 2 * room ? 2 : 1;
   if (all >= ends) return Split{0, all, all, 1};
   return Split{(int)slow * (ends - 1), all, ends, (int)nseq};
