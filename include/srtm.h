@@ -63,7 +63,8 @@ typedef enum {
 
 /* Device-side numerical status bits (OR-ed into *info). */
 #define SRTM_INFO_INNOVATION_NOT_PD 1 /* C_bar P C_bar^T + R_x (eq. m-h-k-l) not positive definite */
-#define SRTM_INFO_COMBINE_SINGULAR 2  /* I + D_i J_j of eq. op-filter numerically singular          */
+#define SRTM_INFO_COMBINE_SINGULAR 2  /* I + D_i J_j of eq. op-filter, or I + P^f_{k,l} J of a window's
+                                         correction by its later windows, numerically singular      */
 #define SRTM_INFO_PRED_SINGULAR 4     /* A P^f_{k,l} A^T + Q of eq. parallel-ak-smoothing singular  */
 #define SRTM_INFO_NONFINITE 8         /* a non-finite value reached an output                       */
 

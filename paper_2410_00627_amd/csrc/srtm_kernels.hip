@@ -94,8 +94,8 @@ SRTM_DEV double wave_sum(double v) {
 
 // Wave-wide sums of N values, each as wave_sum forms it: at every distance a lane passes the half of its values
 // on that it does not keep (N - 1 exchanges or a few more, not 6 N), and ends with the sums start ..
-// start + cnt - 1 in x[0 ..] (start = 0 and cnt = N before). 33 sums of a wave
-// one by one took 6 us of the gradient's statistics kernel.
+// start + cnt - 1 in x[0 ..] (start = 0 and cnt = N before). The 33 or 34 sums of
+// a wave (nx = 4) one by one took 6 us of the gradient's statistics kernel.
 template <int N, int DIST, int SZ>
 SRTM_DEV void wave_sums(double (&x)[SZ], int lane, int& start, int& cnt) {
   if constexpr (DIST >= 1) {
@@ -1999,7 +1999,7 @@ inline __host__ __device__ size_t tail_info_off(int64_t N, int nx, size_t esz) {
 // window costs a wave about 700 instructions at nx = 4 whatever it holds, the four problems of a wave's
 // groups about 60; at nx = 6 (float32, 63 tiles) the fold took 52 us with all 14 levels in lanes, 42 us so.
 // nx = 1 stays in lanes: a combine of scalars is shorter there than a 4 x 4 one on the matrix cores (20000 windows in
-// float32: the filter's fold 4 us in lanes, 10 us in blocks), and its tiles gain too little from being settled.
+// float32: the filter's fold 5 us in lanes, 10 us in blocks), and its tiles gain too little from being settled.
 constexpr int LANE_LEVELS = 4;
 template <int NX> constexpr bool blocks4() { return NX >= 2 && NX <= 4; }
 template <int NX> constexpr bool block8() { return NX > 4; }
@@ -2308,8 +2308,8 @@ inline size_t tile_tree_lds_bytes(int nlev) {
          tab + sizeof(T) * 2 * NX * 32 + sizeof(double) * 64 + 128;
 }
 
-// K2: the levels of the tree above the tiles, over the sequence's whole tiles (one workgroup per sequence,
-// one thread per node and output row as in the tile reductions), and, for the smoother, the information of
+// K2: the levels of the tree above the tiles, over the sequence's whole tiles (one workgroup per sequence;
+// nodes formed as in the tile reductions, tree_form), and, for the smoother, the information of
 // N's set bits below each bit. A sequence of one tile has no level above it and its fold finds
 // the information of N's bits by itself.
 template <bool INP, typename T, int NX, int NY>
@@ -3950,8 +3950,9 @@ constexpr int RSTEPS = 32;
 
 // K7: fast-rate recovery, one window per lane and a loop over the window's fast steps.
 // MODE bit 1: filter blocks p(x_{k,i} | y_{1:k}); bit 2: smoothed blocks p(x_{k,i} | y_{1:N})
-// (and the smoother's slow state, block i = 1) from the correction (v, W) that K3s left as
-// terms linear in the smoothed state entering the tile; a workgroup covers exactly one tile.
+// (and the smoother's slow state, block i = 1) from the correction (v, W), formed of the fold's state and
+// information (info_correction), or, for per-window models, of what the tile's forward pass left as terms
+// linear in the smoothed state entering the tile; a workgroup covers exactly one tile.
 // `ilim` is L when fast-rate outputs are requested and 1 when only the slow smoothed state is. Part `part`
 // takes its share of the fast steps (StepShare).
 // TV: per-window model; `cst` then holds the per-window constants blocks (stored by tv_column)

@@ -17,7 +17,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(HERE, "libsrtm.so")
 
 SRTM_F32, SRTM_F64 = 0, 1
-INFO_BITS = {1: "innovation covariance not positive definite", 2: "I + D_i J_j singular in the filter combine",
+INFO_BITS = {1: "innovation covariance not positive definite", 2: "I + D_i J_j singular in the filter combine, or I + P J in the smoother's correction",
              4: "smoother prediction covariance singular", 8: "non-finite output"}
 
 
