@@ -1695,13 +1695,6 @@ SRTM_DEV int smoother_element(const MV& M, int L, const Window<T, NX, NY>& w, bo
 // slot tree_off(p) + i of 2 nx rows (d, eta) of TILE slots; level-0 nodes are the window's own elements and are
 // formed again from y where they are needed. Level 8 (whole tiles) is `ftagg`, and the levels above it
 // follow each other in `ttree` (tile_level_off).
-inline __host__ __device__ constexpr int tree_off(int p) { return TILE - (TILE >> (p - 1)); }
-// First node of level LOG_TILE + q, q >= 1, among the levels above the tiles, for nf whole tiles.
-inline __host__ __device__ int64_t tile_level_off(int64_t nf, int q) {
-  int64_t o = 0;
-  for (int j = 1; j < q; ++j) o += nf >> j;
-  return o;
-}
 // Highest set bit of x > 0, and -1 for 0.
 SRTM_DEV int top_bit(int64_t x) { return x > 0 ? 63 - __clzll(x) : -1; }
 
@@ -1978,20 +1971,9 @@ SRTM_DEV bool wave_combine(const Block8<NX>& B, double& u, double& P, const T* t
   return combine8(B, u, P, fwd ? at : a, fwd ? b : c, fwd ? c : b, fwd ? d : e, fwd ? e : -d);
 }
 
-// Scalars of a window's state or information record: the vector, then the matrix's upper triangle. The
-// records of the time-invariant path lie tile by tile and field by field within a tile, so that the
-// lanes of a wave write and read consecutive addresses: field f of window w of tile t at
-// base[t * TILE * info_stride + f * W + w], W the number of windows of that tile.
-inline __host__ __device__ constexpr int info_stride(int nx) { return nx + nx * (nx + 1) / 2; }
 SRTM_DEV int tile_windows(int64_t N, int64_t tile) {
   const int64_t w = N - tile * TILE;
   return (int)(w < TILE ? w : TILE);
-}
-// The information of N's own set bits below bit q, q = 0 .. top_bit(N), float64, behind the records of a
-// sequence of more than one tile (the region is sized for the larger per-window records of the
-// time-varying smoother).
-inline __host__ __device__ size_t tail_info_off(int64_t N, int nx, size_t esz) {
-  return ((size_t)N * info_stride(nx) * esz + 7) & ~size_t(7);
 }
 
 // Levels handled one lane per window in the fold; the ones above go to the matrix cores, four problems per wave for
@@ -2033,14 +2015,10 @@ struct FoldLds {
 constexpr int MAXLEV = 26;
 
 // Float32 sequences of several tiles keep F, D, J of every level in float64 too, behind the prior records
-// (a region sized for the larger per-window records of the per-window models; nx = 1 leaves no room
-// there): the fold's float64 steps then work with one consistent model, so that a state that has settled
+// (nx = 1 leaves no room there): the fold's float64 steps then work with one consistent model, so that a state that has settled
 // is seen as settled to float64 rounding.
 template <typename T, int NX>
 SRTM_DEV bool has_lev64(int64_t N) { return std::is_same_v<T, float> && NX >= 2 && NX <= 4 && N > TILE; }
-inline __host__ __device__ size_t lev64_off(int64_t N, int nx, size_t esz) {
-  return ((size_t)N * info_stride(nx) * esz + 7) & ~size_t(7);
-}
 
 // Entry q of the fold's level tables: F, D, J as 4 x 4 blocks, 48 entries a level.
 template <typename T, int NX>

@@ -126,6 +126,35 @@ inline __host__ __device__ constexpr int stat_size(int nx, int ny) { return 1 + 
 // Per-window smoother-correction record: Et (nx^2), gt (nx), St (upper triangle).
 inline __host__ __device__ constexpr int sfx_stride(int nx) { return nx * nx + nx + nx * (nx + 1) / 2; }
 
+// The records behind `carry`, `sfx` and `ftile_state` come in two formats:
+//  * fold records (time-invariant calls other than the float32 gradient): a window's prior state (`carry`) and the
+//    information of its later windows (`sfx`), a vector and the upper triangle of a matrix each, in the element type. They lie
+//    tile by tile and field by field within a tile, so that the lanes of a wave write and read consecutive
+//    addresses: field f of window w of tile t at base[t * TILE * info_stride + f * W + w], W the number of windows of that
+//    tile; a settled tile stores its matrices with its first window only. `ftile_state` holds the levels of the tree above the tiles.
+//  * element records (per-window models and the float32 gradient): a state of nx + nx^2 scalars per window (`carry`) and
+//    per tile (`ftile_state`), and a smoother-correction record of sfx_stride scalars per window (`sfx`), window by window.
+// The regions are sized for element records, which are the larger ones.
+inline __host__ __device__ constexpr int info_stride(int nx) { return nx + nx * (nx + 1) / 2; }
+
+// Behind the fold records of a sequence of more than one tile lie, float64: in `sfx` the information of N's own
+// set bits below bit q, q = 0 .. the highest, info_stride scalars each; in `carry` of float32 sequences F, D, J of
+// every level.
+inline __host__ __device__ size_t tail_info_off(int64_t N, int nx, size_t esz) {
+  return ((size_t)N * info_stride(nx) * esz + 7) & ~size_t(7);
+}
+inline __host__ __device__ size_t lev64_off(int64_t N, int nx, size_t esz) { return tail_info_off(N, nx, esz); }
+
+// First slot of level p = 1 .. LOG_TILE-1 in a tile's tree (`utree`).
+inline __host__ __device__ constexpr int tree_off(int p) { return TILE - (TILE >> (p - 1)); }
+// First node of level LOG_TILE + q, q >= 1, among the levels above the tiles (`ftile_state`, 2 nx scalars a
+// node), for nf whole tiles.
+inline __host__ __device__ int64_t tile_level_off(int64_t nf, int q) {
+  int64_t o = 0;
+  for (int j = 1; j < q; ++j) o += nf >> j;
+  return o;
+}
+
 inline __host__ __device__ size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 
 // `utree` (time-invariant models): the tile reductions' up-sweep trees, per tile 2 nx rows of TILE
