@@ -3927,7 +3927,9 @@ struct StepShare {
 constexpr int RSTEPS = 32;
 
 // K7: fast-rate recovery, one window per lane and a loop over the window's fast steps.
-// MODE bit 1: filter blocks p(x_{k,i} | y_{1:k}); bit 2: smoothed blocks p(x_{k,i} | y_{1:N})
+// MODE bit 1: filter blocks p(x_{k,i} | y_{1:k}); bit 2: smoothed blocks p(x_{k,i} | y_{1:N}); bits 1 and 2 together or
+// bit 4 beside bit 2: also the slow filter means, where asked for (a bit of its own: the unused store took the
+// recovery of 1094 windows with inputs, nx = 3 in float64, from 20.3 to 22.3 us).
 // (and the smoother's slow state, block i = 1) from the correction (v, W), formed of the fold's state and
 // information (info_correction), or, for per-window models, of what the tile's forward pass left as terms
 // linear in the smoothed state entering the tile; a workgroup covers exactly one tile.
@@ -3946,7 +3948,7 @@ SRTM_DEV void recover_body(const T* __restrict__ y, int64_t N, int L, int ilim, 
                            int32_t* info, int64_t tile, int part, int nparts, int nslow) {
   constexpr int NN = NX * NX, ST = NX + NN, SF = sfx_stride(NX);
   static_assert(TILE == 256, "one recovery workgroup per tile");
-  constexpr bool FILT = (MODE & 1) != 0, SMOOTH = (MODE & 2) != 0;
+  constexpr bool FILT = (MODE & 1) != 0, SMOOTH = (MODE & 2) != 0, MEANS = MODE == 3 || (MODE & 4) != 0;
   static_assert(!(TV && FILT && SMOOTH), "per-window models: filter and smoother outputs in two passes "
                                          "(the LDS copy of the model follows one staging buffer per wave)");
   using Stg = OutStage<T, NX>;
@@ -4005,7 +4007,7 @@ SRTM_DEV void recover_body(const T* __restrict__ y, int64_t N, int L, int ilim, 
     // The slow-rate filter means beside smoothed outputs: a window update keeps the digits of an accurate measurement
     // that the fold's state of the next window loses (its runs carry y as eta = C_bar^T R_x^{-1} y, rounded). The
     // covariances stay the fold's, which loses none where the update subtracts nearly equal matrices.
-    T* mean = mf_slow && part == 0 && valid ? mf_slow + k * NX : nullptr;
+    T* mean = MEANS && mf_slow && part == 0 && valid ? mf_slow + k * NX : nullptr;
     if (!info_correction<INP>(M, L, w, zL, sfx + col, sfx + mcol, nw, v, W, mean) && valid)
       flag |= SRTM_INFO_COMBINE_SINGULAR;
   } else if constexpr (SMOOTH) {  // v = Et m_in + gt,  W = Et P_in Et^T + St
@@ -5848,7 +5850,7 @@ SRTM_DEV void kb_tv_fwd(const Batch& b, int64_t bid) {
                                  q.mf_slow, q.Pf_slow, q.btagg, q.sfx, q.info, bid - q.tile0);
 }
 
-// MODE 1: filter outputs only; 2: smoother outputs; 3: both. Fast-rate outputs take all L
+// MODE 1: filter outputs only; 2: smoother outputs; 3: both; 6: smoother outputs and slow filter means. Fast-rate outputs take all L
 // steps; with only the slow smoothed state requested, step 1 suffices.
 template <typename T, int NX, int NY, int MODE, bool INP, bool TV = false>
 SRTM_DEV void kb_recover(const Batch& b, int64_t bid, Split sp) {
@@ -6122,7 +6124,10 @@ srtm_status launch_all(const Batch& b, const Launch& g, bool smoother, int rec_m
   if (!allow_lds((const void*)k_fold<T, NX, NY, true, INP>, lds_fold)) return SRTM_E_HIP;
   SRTM_STAGE((k_fold<T, NX, NY, true, INP>), dim3(g.ntiles), dim3(TILE), lds_fold, st, b, want);
 
-  if (rec_mode == 2) {
+  if (rec_mode == 2 && b.one.mf_slow) {
+    if (!allow_lds((const void*)k_recover<T, NX, NY, 6, INP>, lds_rec)) return SRTM_E_HIP;
+    SRTM_STAGE((k_recover<T, NX, NY, 6, INP>), dim3(nrec), dim3(TILE), lds_rec, st, b, sp);
+  } else if (rec_mode == 2) {
     if (!allow_lds((const void*)k_recover<T, NX, NY, 2, INP>, lds_rec)) return SRTM_E_HIP;
     SRTM_STAGE((k_recover<T, NX, NY, 2, INP>), dim3(nrec), dim3(TILE), lds_rec, st, b, sp);
   } else if (rec_mode == 3 && lds_rec <= kMaxLdsBytes) {
@@ -6139,10 +6144,10 @@ srtm_status launch_all(const Batch& b, const Launch& g, bool smoother, int rec_m
     } else if (rec_mode == 3) {  // filter and smoother staging do not fit together: two passes
       const size_t lds1 = (size_t)4 * OutStage<T, NX>::BYTES + ptab;
       if (!allow_lds((const void*)k_recover<T, NX, NY, 1, INP>, lds1)) return SRTM_E_HIP;
-      if (!allow_lds((const void*)k_recover<T, NX, NY, 2, INP>, lds1)) return SRTM_E_HIP;
+      if (!allow_lds((const void*)k_recover<T, NX, NY, 6, INP>, lds1)) return SRTM_E_HIP;
       hipLaunchKernelGGL((k_recover<T, NX, NY, 1, INP>), dim3(nrec), dim3(TILE), lds1, st, b, sp);
       SRTM_CHECK_LAUNCH();
-      hipLaunchKernelGGL((k_recover<T, NX, NY, 2, INP>), dim3(nrec), dim3(TILE), lds1, st, b, sp);
+      hipLaunchKernelGGL((k_recover<T, NX, NY, 6, INP>), dim3(nrec), dim3(TILE), lds1, st, b, sp);
       SRTM_CHECK_LAUNCH();
     }
     SRTM_EV(ev.post(st));

@@ -98,3 +98,22 @@ def test_slow_filter_means_are_the_last_fast_step(nx, ny, L, dtype):
     a = [t.double().cpu().numpy() for t in (*args, yt)]
     ref = oracle.srtm_smoother(a[0], a[1], a[2], a[3], L, a[4], a[5], a[6], with_filter=True)
     assert _errors(out["mf_slow"], out["Pf_slow"], ref["m_slow"], ref["P_slow"])[1] <= 1e-2 * TOL[dtype]
+
+
+@pytest.mark.parametrize("dtype", [torch.float64, torch.float32], ids=["f64", "f32"])
+@pytest.mark.parametrize("nx,ny,L,nu", [(2, 1, 1, 0), (4, 2, 4, 0), (3, 1, 20, 3), (6, 1, 40, 0)])
+def test_slow_filter_outputs_beside_smoothed_ones(nx, ny, L, nu, dtype):
+    """Without the fast filter outputs the slow ones come from another kernel (or, at nx = 6 with long windows, from a
+    second pass): the same numbers as with them, to the rounding of their sums (64 units allowed)."""
+    from paper_2410_00627_amd import srtm
+    m, N = wl.random_stable_model(nx, ny, L, 4), 2 * 256 + 9
+    args = [t.to(dtype) for t in srtm.model_tensors(m, "cuda", torch.float64)]
+    B, u = wl.random_inputs(nx, nu, L, N, 32) if nu else (None, None)
+    yt = torch.as_tensor(wl.simulate(m, N, 91, B=B, u=u), device="cuda").to(dtype)
+    kw = dict(B=torch.as_tensor(B, device="cuda").to(dtype), u=torch.as_tensor(u, device="cuda").to(dtype)) if nu else {}
+    all_ = srtm.smooth(*args[:4], L, *args[4:], yt, with_filter=True, **kw)
+    out = {k: torch.empty_like(all_[k]) for k in ("ms_fast", "Ps_fast", "ms_slow", "Ps_slow", "mf_slow", "Pf_slow")}
+    srtm.smooth(*args[:4], L, *args[4:], yt, out=out, **kw)
+    for mk, pk in (("mf_slow", "Pf_slow"), ("ms_slow", "Ps_slow"), ("ms_fast", "Ps_fast")):
+        e = _errors(out[mk], out[pk], all_[mk].double().cpu().numpy(), all_[pk].double().cpu().numpy())
+        assert max(e) <= 64 * torch.finfo(dtype).eps, (mk, e)
