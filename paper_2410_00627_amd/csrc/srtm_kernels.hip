@@ -2046,11 +2046,9 @@ SRTM_DEV void stage_blocks(const T* __restrict__ cst, const double* __restrict__
 // gain pair per level, formed once per tile, instead of a matrix inverse per window and level), and the
 // recovery forms the covariances of a fast step once per tile and streams them to every window.
 // Tiles near either end, models that do not settle, and anything not finite take the general way.
-// Float64: 2^-49, some rounding errors of one combine: at 2^-47 sequences that settle slowly shared matrices a little
-// early (nx = 2, A = 0.999 U: P^f 3.5e-15 off, 1.5e-15 so), at 2^-50 two of the ten settling models tried no longer
-// settle. Float32: 2^-26, a quarter of its rounding.
+// Float64: 2^-47, some rounding errors of one combine. Float32: 2^-26, a quarter of its rounding.
 template <typename T>
-SRTM_DEV constexpr double settled_tol() { return sizeof(T) == 8 ? 0x1p-49 : 0x1p-26; }
+SRTM_DEV constexpr double settled_tol() { return sizeof(T) == 8 ? 0x1p-47 : 0x1p-26; }
 // Whether a tile is settled is kept in the last slot of its tree's first row (levels 1 .. 7 leave two free).
 template <typename T, int NX>
 SRTM_DEV T* settled_flag(T* utree, int64_t tile) { return utree + tile * (2 * NX * TILE) + TILE - 1; }
