@@ -2046,7 +2046,9 @@ SRTM_DEV void stage_blocks(const T* __restrict__ cst, const double* __restrict__
 // gain pair per level, formed once per tile, instead of a matrix inverse per window and level), and the
 // recovery forms the covariances of a fast step once per tile and streams them to every window.
 // Tiles near either end, models that do not settle, and anything not finite take the general way.
-// Float64: 2^-47, some rounding errors of one combine. Float32: 2^-26, a quarter of its rounding.
+// Float64: 2^-47, some rounding errors of one combine. 2^-49 is at the rounding itself: 4 of 36 random models (nx = 4) then
+// never settle, and a call of 32767 windows with inputs takes 123 us instead of 79; the worst P^f of 30 models that
+// settle slowly would be 3.3e-15 off instead of 7.4e-15. Float32: 2^-26, a quarter of its rounding.
 template <typename T>
 SRTM_DEV constexpr double settled_tol() { return sizeof(T) == 8 ? 0x1p-47 : 0x1p-26; }
 // Whether a tile is settled is kept in the last slot of its tree's first row (levels 1 .. 7 leave two free).
